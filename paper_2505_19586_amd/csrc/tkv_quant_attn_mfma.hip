@@ -64,7 +64,7 @@ struct MfmaParams {
   TkvSeqLens chunks;  // split-K chunks of every sequence, in proportion to its length: blockIdx.x runs over all of them
   // The step's new tokens, when the call also appends them (Eq. 2): the last n_add[b] tokens of
   // sequence b, rows k_new / v_new [B][n_stride][Hkv][D], are copied into the fp16 ring by the
-  // workgroups that own the head's tail before they read it.  k_new == nullptr: none.
+  // workgroups that own the head's tail, which read them from here themselves.  k_new == nullptr: none.
   const __half* k_new;
   const __half* v_new;
   int32_t n_stride;
@@ -163,13 +163,12 @@ constexpr int kHeadroomLog2 = 4;  // lazy rescale: weights may reach 2^kHeadroom
 constexpr int kRefBelowMax = 3;   // a rescale puts the reference this far under the largest logit (< headroom)
 constexpr int kBkStride = 80;     // words per head row of the query-side operand in LDS
 constexpr int kMaxGpc = 512;      // groups per chunk that the zero-point table holds
-constexpr int kTailWaves = 4;     // waves of the last chunk that share the fp16 tail
+constexpr int kTailBlocks = 3;    // blocks that a 32-token piece of the fp16 tail counts as in the split (2 to 5: no difference)
+// Sequences of up to this many blocks (tail pieces counted as above) per wave are one workgroup's:
+// no partials to write, no arrival, no merge.  2 bit, 8 KV heads, batch 1: 600 tokens (29 blocks)
+// 12.6 us in one workgroup, 13.7 in two; 1000 tokens (42 blocks) 14.1 against 12.9.
+constexpr int kOneChunkRounds = 3;
 
-struct TailEntry {
-  float m[4];
-  float l[4];
-  float o[4][TKV_D];
-};
 // Results of one wave for the merge inside the workgroup; it takes the place of the start of
 // the wave's own load ring once the wave has left the group loop.
 struct MergeWave {
@@ -186,8 +185,7 @@ struct MergeWave {
 //          slot + 4*l (fp16 rows), i.e. a slot is a copy of the group's packed block.  After
 //          the main loop the start of a wave's ring holds its results for the workgroup merge.
 //   cz     zero-point term of every group of the chunk, [group][4 heads] float
-//   tail   partial results of the waves that share the fp16 tail
-//   q      the 4 query rows as fp16, for the tail
+// (a wave that has pieces of the fp16 tail uses its bk area as scratch before its first group)
 // GS = quantization group / 32: the K scalers of a slot are those of the block's key group,
 // the V scalers and zero-points [128 / (32 GS)][32 tokens] fp16 each.
 template <int BITS, int GS, int W>
@@ -209,95 +207,138 @@ struct Cfg {
   static constexpr int kBkWave = 2 * 4 * kBkStride * 4;
   static constexpr int oRing = W * kBkWave;
   static constexpr int oCz = oRing + W * kWaveRing;
-  static constexpr int oTail = oCz + kMaxGpc * 16;
-  static constexpr int oQ = oTail + kTailWaves * (int)sizeof(TailEntry);
-  static constexpr int kLdsBytes = oQ + 4 * TKV_D * 2;
+  static constexpr int kLdsBytes = oCz + kMaxGpc * 16;
+  static_assert(4 * TKV_D * 4 <= kBkWave, "the tail's scratch fits in a wave's operand area");
   static_assert(sizeof(MergeWave) <= (size_t)kWaveRing, "a wave's results fit in its own ring");
   static_assert((3 * 4 * TKV_MAX_CHUNKS + 4 * 4 * TKV_D + 4) * 4 <= (size_t)W * kWaveRing, "merge scratch must fit in the ring");
   static_assert(kLdsBytes + 64 <= 160 * 1024, "LDS budget of one compute unit");
 };
 
-// fp16 tail (ring of unquantized tokens): wave w of the last chunk takes the 32-token
-// sub-blocks w, w + kTailWaves, ... with plain float math and an online softmax, and leaves
-// its partial result in `te`.  Lane = (token, channel half) for the logits, lane = channel
-// pair for the weighted sum.
-__device__ inline void tail_wave(const MfmaParams& p, TailEntry& te, const uint32_t* q_h, size_t bh, int nq, int n,
-                                 int ring, int wave, int lane) {
-  const int r_total = n - nq;
-  const int t = lane / 2, half = lane % 2;
-  float M[4], Ls[4], acc[4][2];
+// fp16 tail (the unquantized tokens): wave w of the last chunk takes the 32-token pieces w,
+// w + W, ... and leaves its result as the state its block loop starts from: reference m_run =
+// largest logit, accumulators in the layout and units of the block loop (acc_o: channel rows of
+// the column group that owns them, codes' 2^-24 and weights' 2^kEP included; acc_z: denominator).
+//
+// Everything runs on the matrix cores: the logits as K rows (A operand, straight from memory)
+// against the exact fp16 query (the set-up's B operand), in the token order of a block's tiles;
+// P.V in float32 on v_mfma_f32_4x4x1 (16 independent 4 heads x 4 channels products of one token
+// each): its B operand is one channel of one token per lane, so a lane's 16-byte piece of a V row
+// feeds eight of them with no transpose, and the weights keep all their bits.  A wave is bound by
+// the latency of its loads (16 in flight per lane) and then by some 300 instructions: 3.8 us from the
+// set-up barrier at 2000 tokens, all pieces in parallel.  Plain float math with one token per lane
+// pair and the weights broadcast lane by lane, on 4 waves, took 9 to 12.5 us, longer than
+// everything else a workgroup had to do at up to 32768 tokens (2 bit, one sequence: 2000 tokens
+// 18.0 -> 13.5 us per call, 8190 18.0 -> 14.4, 131060 30.3 -> 29.5; 64 sequences of 2000 62 -> 47).
+//
+// New tokens of the step are read from the caller's buffers: their ring rows are being written.
+template <int BITS, int W>
+__device__ inline void tail_pieces(const MfmaParams& p, const uintx4 (&bq)[4], float* sc, int b, int h, size_t bh, int nq,
+                                   int n, int ring, int wave, int lane, floatx4 (&acc_o)[8], floatx4& acc_z,
+                                   float& m_run) {
+  const int slot = lane % 16, rb = lane / 16, hs = slot % 4, us = slot / 4;
+  const int n_old = p.k_new != nullptr ? n - p.n_add.n[b] : n;
+  const int s0 = nq % ring;  // ring slot of the tail's first token
+  auto row = [&](const __half* ring_rows, const __half* new_rows, int tok) -> const __half* {
+    int s = s0 + (tok - nq);
+    s = s >= ring ? s - ring : s;
+    const __half* old_row = ring_rows + (bh * ring + (size_t)s) * TKV_D;
+    const __half* new_row = new_rows + (((size_t)b * p.n_stride + (size_t)(tok - n_old)) * p.hkv + h) * TKV_D;
+    return tok < n_old ? old_row : new_row;
+  };
+  float L = 0.f;
+  floatx4 acc[8];  // channel 8 slot + y of the tokens 4 j + rb, rows = heads
 #pragma unroll
-  for (int hh = 0; hh < 4; ++hh) M[hh] = -INFINITY, Ls[hh] = 0.f, acc[hh][0] = 0.f, acc[hh][1] = 0.f;
-  for (int sb = wave; sb * 32 < r_total; sb += kTailWaves) {
-    const int cnt = min(32, r_total - 32 * sb);
-    const int t0 = nq + 32 * sb;
-    float x[4];
-    {
-      const int tok = t0 + min(t, cnt - 1);
-      const uintx4* krow = reinterpret_cast<const uintx4*>(p.k_resid + (bh * ring + (size_t)(tok % ring)) * TKV_D + 64 * half);
-      uintx4 kv[8];
+  for (int y = 0; y < 8; ++y) acc[y] = floatx4{0.f, 0.f, 0.f, 0.f};
+  for (int t0 = nq + 32 * wave; t0 < n; t0 += 32 * W) {
+    const int cnt = min(32, n - t0);
+    uintx4 kf[2][4], vf[8];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) kv[i] = krow[i];
-      __builtin_amdgcn_sched_barrier(0);  // all eight loads in flight before the first is used
-      float a[4] = {0.f, 0.f, 0.f, 0.f};
+    for (int tau = 0; tau < 2; ++tau) {
+      const int t = 8 * (slot / 4) + 4 * tau + slot % 4;  // rows past the end re-read the last one with weight 0
+      const __half* kr = row(p.k_resid, p.k_new, t0 + min(t, cnt - 1)) + 8 * rb;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-#pragma unroll
-        for (int hh = 0; hh < 4; ++hh) {
-          const uintx4 q4 = *reinterpret_cast<const uintx4*>(q_h + hh * 64 + 32 * half + 4 * i);
-#pragma unroll
-          for (int y = 0; y < 4; ++y) {
-            const uint32_t kw = kv[i][y], qw = q4[y];
-            a[hh] = __builtin_amdgcn_fdot2(as_half2(kw), as_half2(qw), a[hh], false);
-          }
-        }
-      }
-#pragma unroll
-      for (int hh = 0; hh < 4; ++hh) {
-        a[hh] += __shfl_xor(a[hh], 1, 64);
-        x[hh] = t < cnt ? a[hh] * p.scale2 : -INFINITY;
-      }
+      for (int m = 0; m < 4; ++m) kf[tau][m] = *reinterpret_cast<const uintx4*>(kr + 32 * m);
     }
-    float pw[4];
 #pragma unroll
-    for (int hh = 0; hh < 4; ++hh) {
-      float mx = x[hh];
-      for (int m = 32; m >= 2; m >>= 1) mx = fmaxf(mx, __shfl_xor(mx, m, 64));
-      const float mn = fmaxf(M[hh], mx);  // finite: the sub-block holds at least one token
-      const float alpha = exp2f(M[hh] - mn);
-      pw[hh] = t < cnt ? exp2f(x[hh] - mn) : 0.f;
-      float sum = half == 0 ? pw[hh] : 0.f;
-      for (int m = 32; m >= 1; m >>= 1) sum += __shfl_xor(sum, m, 64);
-      Ls[hh] = Ls[hh] * alpha + sum;
-      acc[hh][0] *= alpha;
-      acc[hh][1] *= alpha;
-      M[hh] = mn;
+    for (int j = 0; j < 8; ++j)
+      vf[j] = *reinterpret_cast<const uintx4*>(row(p.v_resid, p.v_new, t0 + min(4 * j + rb, cnt - 1)) + 8 * slot);
+    __builtin_amdgcn_sched_barrier(0);  // all loads in flight before the first is used
+    floatx4 s[2];
+#pragma unroll
+    for (int tau = 0; tau < 2; ++tau) {
+      s[tau] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int m = 0; m < 4; ++m) s[tau] = mfma(kf[tau][m], bq[m], s[tau]);
     }
-    uint32_t v2[32];  // this lane's channel pair of every row
+    // this lane: head hs, tokens 8 rb + i (the same in all four column groups)
+    float x[8], mx = -INFINITY;
 #pragma unroll
-    for (int y = 0; y < 32; ++y) {
-      const int tokv = t0 + min(y, cnt - 1);  // rows past the end re-read the last one with weight 0
-      v2[y] = reinterpret_cast<const uint32_t*>(p.v_resid + (bh * ring + (size_t)(tokv % ring)) * TKV_D)[lane];
+    for (int i = 0; i < 8; ++i) {
+      x[i] = 8 * rb + i < cnt ? s[i / 4][i % 4] * p.scale2 : -INFINITY;
+      mx = fmaxf(mx, x[i]);
     }
-    __builtin_amdgcn_sched_barrier(0);
+    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    const float mn = fmaxf(m_run, mx);  // finite: the piece holds at least one token
+    const float alpha = __builtin_amdgcn_exp2f(m_run - mn);
+    float sum = 0.f;
 #pragma unroll
-    for (int y = 0; y < 32; ++y) {
-      const half2_t vv = as_half2(v2[y]);
-      const float v0 = (float)vv[0], v1 = (float)vv[1];
+    for (int i = 0; i < 8; ++i) {
+      x[i] = __builtin_amdgcn_exp2f(x[i] - mn);
+      sum += x[i];
+    }
+    sum += __shfl_xor(sum, 16, 64);
+    sum += __shfl_xor(sum, 32, 64);
+    L = __builtin_fmaf(L, alpha, sum);
+    m_run = mn;
+    // weights to [token][head]; a wave's LDS operations execute in order
+    if (us == 0) {
 #pragma unroll
-      for (int hh = 0; hh < 4; ++hh) {
-        const float pp = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, pw[hh]), 2 * y));
-        acc[hh][0] = __builtin_fmaf(pp, v0, acc[hh][0]);
-        acc[hh][1] = __builtin_fmaf(pp, v1, acc[hh][1]);
+      for (int i = 0; i < 8; ++i) sc[(8 * rb + i) * 4 + hs] = x[i];
+      if (rb == 0) sc[128 + hs] = alpha;
+    }
+    float w[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) w[j] = sc[(4 * j + rb) * 4 + lane % 4];
+    const floatx4 al = *reinterpret_cast<const floatx4*>(sc + 128);
+#pragma unroll
+    for (int y = 0; y < 8; ++y) acc[y] *= al;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+#pragma unroll
+      for (int y = 0; y < 8; ++y) {
+        const uint32_t vw = vf[j][y / 2];
+        acc[y] = __builtin_amdgcn_mfma_f32_4x4x1f32(w[j], (float)as_half2(vw)[y % 2], acc[y], 0, 0, 0);
       }
     }
   }
+  // sum over the four token classes rb: every exchange halves the values a lane keeps; in the end
+  // it holds channels 8 slot + 2 rb', + 1 of the four heads (rb' = 2 (lane / 32) + (lane / 16) % 2)
+  float v[32];
 #pragma unroll
-  for (int hh = 0; hh < 4; ++hh) {
-    te.o[hh][2 * lane] = acc[hh][0];
-    te.o[hh][2 * lane + 1] = acc[hh][1];
-    if (lane == 0) te.m[hh] = M[hh], te.l[hh] = Ls[hh];
+  for (int i = 0; i < 32; ++i) v[i] = acc[i / 4][i % 4];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, v[i]), __builtin_bit_cast(uint32_t, v[i + 16]), false, false);
+    const uint32_t r0 = r[0], r1 = r[1];
+    v[i] = __builtin_bit_cast(float, r0) + __builtin_bit_cast(float, r1);
   }
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, v[i]), __builtin_bit_cast(uint32_t, v[i + 8]), false, false);
+    const uint32_t r0 = r[0], r1 = r[1];
+    v[i] = __builtin_bit_cast(float, r0) + __builtin_bit_cast(float, r1);
+  }
+#pragma unroll
+  for (int hh = 0; hh < 4; ++hh)
+    *reinterpret_cast<float2_t*>(sc + hh * TKV_D + 8 * slot + 2 * rb) = float2_t{v[hh], v[4 + hh]};
+#pragma unroll
+  for (int cb = 0; cb < 8; ++cb) {
+    const float scale = 1.0f / (float)(1 << (24 - kEP - (BITS == 1 && cb % 2 ? 4 : 0)));
+    const floatx4 o = *reinterpret_cast<const floatx4*>(sc + hs * TKV_D + 16 * (2 * us + cb % 2) + 4 * rb) * scale;
+    acc_o[cb] = cb / 2 == us ? o : floatx4{0.f, 0.f, 0.f, 0.f};
+  }
+  acc_z[0] = rb == 1 ? L : 0.f;
 }
 
 #ifdef TKV_PHASE
@@ -352,13 +393,13 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
   const size_t bh = (size_t)b * p.hkv + h;
   const size_t grp_base = bh * (size_t)(p.capacity / TKV_BLK);   // first packed block of this head
   const size_t kgrp_base = bh * (size_t)(p.capacity / GRP);      // first key group
-  // Work split of this sequence: a 32-token piece of the tail counts as two groups and the
+  // Work split of this sequence: a 32-token piece of the tail counts as kTailBlocks groups and the
   // tail belongs to the last chunk, which gets correspondingly fewer quantized groups.
   const bool has_tail = chunk == n_chunks - 1;
-  const int tail_equiv = 2 * ((n - nq + 31) / 32);
-  const int gpc = max(1, (jq + tail_equiv + n_chunks - 1) / n_chunks);
-  const int blk0 = min(chunk * gpc, jq);
-  const int blk1 = has_tail ? jq : min(blk0 + gpc, jq);
+  const int tail_equiv = kTailBlocks * ((n - nq + 31) / 32);
+  const uint32_t work = (uint32_t)(jq + tail_equiv);
+  const int blk0 = min((int)(work * (uint32_t)chunk / (uint32_t)n_chunks), jq);
+  const int blk1 = has_tail ? jq : min((int)(work * (uint32_t)(chunk + 1) / (uint32_t)n_chunks), jq);
   const int last = max(blk1 - 1, blk0);  // groups past the chunk are clamped (and ignored); jq >= 1 here
 
   const int slot = lane % 16, rb = lane / 16;
@@ -367,8 +408,6 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
   typedef uint32_t BkArr[2][4][kBkStride];
   uint32_t(*bk_s)[4][kBkStride] = reinterpret_cast<BkArr*>(smem)[wave];
   float* cz_s = reinterpret_cast<float*>(smem + C::oCz);
-  TailEntry* tail_s = reinterpret_cast<TailEntry*>(smem + C::oTail);
-  uint32_t* q_h = reinterpret_cast<uint32_t*>(smem + C::oQ);
   // Byte offsets (wave-uniform) of this wave's ring slots; the roles rotate every step.
   const uint32_t ring_off = C::oRing + wave * C::kWaveRing;
   const uint32_t lane16 = 16u * (uint32_t)lane, lane4 = 4u * (uint32_t)lane;  // unsigned: scalar base + 32-bit lane offset
@@ -425,10 +464,10 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
   uintx4 bq[4];     // exact fp16 query as MFMA B operand (zero-point term)
   uintx4 az[4];     // zero-point rows of 16 groups as MFMA A operand
   if (has_tail && p.k_new != nullptr) {
-    // Eq. 2 in this launch: the step's new rows go into the fp16 ring (slots whose tokens were
-    // quantized long ago: nothing reads them) before the workgroup's set-up barrier, behind which
-    // the tail waves read the ring.  Every workgroup that reads the head's tail writes the rows
-    // itself (the workgroups of a group of more than 4 query heads write the same bytes).
+    // Eq. 2 in this launch: the step's new rows go into the fp16 ring, into slots whose tokens were
+    // quantized long ago.  Nothing in this launch reads those slots: the tail waves take the new
+    // rows from the caller's buffers (the workgroups of a group of more than 4 query heads write
+    // the same bytes).
     const int add = p.n_add.n[b], ring = p.residual + GRP;
     for (int x = tid; x < add * 32; x += 64 * W) {
       const int i = x / 32, kv = (x % 32) / 16, part = x % 16;
@@ -462,15 +501,6 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
   }
   __builtin_amdgcn_sched_barrier(0);
   if (tid == 0) s_next = blk0 + 3 * W;
-  if (tid < kTailWaves * 4) {
-    tail_s[tid / 4].m[tid % 4] = -INFINITY;
-    tail_s[tid / 4].l[tid % 4] = 0.f;
-  }
-  if (tid < 4 * TKV_D / 2) {
-    const int hh = tid / (TKV_D / 2);
-    const uint32_t w = reinterpret_cast<const uint32_t*>(qrow + (size_t)(hh < G ? hh : G - 1) * TKV_D)[tid % (TKV_D / 2)];
-    q_h[tid] = hh < G ? w : 0u;
-  }
 
   // ---- zero-point term of every group of the chunk: cz[g][head] = scale2 * sum_c q[c] z_g[c],
   // 16 groups per MFMA (A rows = groups, B = the exact fp16 query)
@@ -505,21 +535,23 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
     }
   }
   TKV_PH();  // 1 this wave's set-up work done
-  __syncthreads();  // cz table, tail slots, query copy and group counter are in place
+  // cz table and group counter are in place (a bare barrier: __syncthreads() would also wait for
+  // every load in flight)
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
   TKV_PH();  // 2 set-up done
-
-  if (has_tail && wave < kTailWaves && wave * 32 < n - nq)
-    tail_wave(p, tail_s[wave], q_h, bh, nq, n, p.residual + GRP, wave, lane);
-  TKV_PH();  // 3 tail done
-
-  // codes carry 2^-24, query side 2^kEK, so S = acc * 2^(24-kEK)
-  const float K1 = p.scale2 * (float)(1 << (24 - kEK));
 
   floatx4 acc_o[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) acc_o[i] = floatx4{0.f, 0.f, 0.f, 0.f};
   floatx4 acc_z = {0.f, 0.f, 0.f, 0.f};
   float m_run = -INFINITY;
+  if (has_tail && wave * 32 < n - nq)
+    tail_pieces<BITS, W>(p, bq, reinterpret_cast<float*>(smem) + wave * (C::kBkWave / 4), b, h, bh, nq, n, p.residual + GRP,
+                         wave, lane, acc_o, acc_z, m_run);
+  TKV_PH();  // 3 tail done
+
+  // codes carry 2^-24, query side 2^kEK, so S = acc * 2^(24-kEK)
+  const float K1 = p.scale2 * (float)(1 << (24 - kEK));
 
   // A operand of the z_v / denominator MFMA: rows 0..NU-1 hold z_v[u = row] (loaded per group)
   // times the constant that undoes the weight-side scaling, row 4 holds that constant
@@ -809,9 +841,9 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
   }
   __syncthreads();
   TKV_PH();  // 5 all waves done, results in LDS
-  // merge weights of the W wave entries and the tail entries: every wave works them out for
-  // itself (lane = (entry, head)) into arrays of its own, which spares the workgroup a barrier
-  constexpr int NE = W + kTailWaves;
+  // merge weights of the W wave entries: every wave works them out for itself (lane = (entry,
+  // head)) into arrays of its own, which spares the workgroup a barrier
+  constexpr int NE = W;
   __shared__ float s_w_all[W][NE][4];
   __shared__ float s_ml_all[W][2][4];
   static_assert(NE <= 16, "one wave covers all (entry, head) pairs");
@@ -823,9 +855,6 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
     if (e < W) {
       me = merge_of(e).m[hh];
       le = merge_of(e).l[hh];
-    } else if (e < NE) {
-      me = tail_s[e - W].m[hh];
-      le = tail_s[e - W].l[hh];
     }
     float M = me;
     for (int m = 4; m <= 32; m <<= 1) M = fmaxf(M, __shfl_xor(M, m, 64));
@@ -843,10 +872,10 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
     float O = 0.f;
 #pragma unroll
     for (int w = 0; w < W; ++w) O = __builtin_fmaf(merge_of(w).o[hh][c], s_w[w][hh], O);
-#pragma unroll
-    for (int w = 0; w < kTailWaves; ++w) {  // unused tail slots hold no data, only a zero weight
-      const float wgt = s_w[W + w][hh];
-      O = __builtin_fmaf(wgt != 0.f ? tail_s[w].o[hh][c] : 0.f, wgt, O);
+    if (n_chunks == 1) {  // nothing to merge with
+      const float Lsum = s_ml[1][hh];
+      p.out[((size_t)b * p.hq + (size_t)qh0 + hh) * TKV_D + c] = __float2half_rn(Lsum > 0.f ? O / Lsum : 0.f);
+      continue;
     }
     float* dst = p.parts + (((size_t)chunk_base * p.hq + ((size_t)qh0 + hh) * n_chunks) + chunk) * TKV_PART_STRIDE;
     // device-scope stores: visible to the merging workgroup without a cache write-back
@@ -857,6 +886,7 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
     }
   }
 
+  if (n_chunks == 1) return;
   // ---- the last workgroup of this (sequence, KV head) to arrive merges all chunks.
   // Partials travel through device-scope (cache-bypassing) stores and loads, ordered by
   // waiting for the stores to complete before the arrival counter is bumped: a release /
@@ -912,6 +942,7 @@ int32_t launch_quant_attn_mfma(const tkv_quant_desc* d, const tkv_quant_cache* c
   const int variant = d->bits * 100 + d->group_size;
   if (variant != 232 && variant != 432 && variant != 164 && variant != 264) return TKV_E_UNSUPPORTED;
   const int waves = d->bits == 4 ? 8 : 12;
+  auto most_chunks = [waves](int blocks) { return blocks <= kOneChunkRounds * waves ? 1 : (blocks + waves - 1) / waves; };
   // Chunks per KV head over the whole batch: about target_blocks workgroups in all, shared out
   // among the sequences in proportion to their work (32-token blocks, a 32-token piece of the
   // fp16 tail counting as two), so that every workgroup sweeps about the same number of blocks
@@ -931,13 +962,13 @@ int32_t launch_quant_attn_mfma(const tkv_quant_desc* d, const tkv_quant_cache* c
   for (int b = 0; b < d->batch; ++b) {
     const int n = lens.n[b];
     const int g = tkv::n_quantized(n, d->residual, d->group_size) / TKV_BLK;
-    work[b] = g + 2 * ((n - g * TKV_BLK + 31) / 32);
+    work[b] = g + kTailBlocks * ((n - g * TKV_BLK + 31) / 32);
     total_work += work[b];
   }
   int total_chunks = 0;
   for (int b = 0; b < d->batch; ++b) {
     int nc = total_work > 0 ? (int)(((long long)per_head * work[b] + total_work / 2) / total_work) : 1;
-    const int c_work = (work[b] + waves - 1) / waves;
+    const int c_work = most_chunks(work[b]);
     if (nc > c_work) nc = c_work;
     if (nc > chunk_cap) nc = chunk_cap;
     if (nc < 1) nc = 1;
@@ -964,7 +995,7 @@ int32_t launch_quant_attn_mfma(const tkv_quant_desc* d, const tkv_quant_cache* c
     int pick = -1;
     for (int b = 0; b < d->batch; ++b) {
       const int nc = p.chunks.n[b];
-      if (nc >= chunk_cap || nc >= (work[b] + waves - 1) / waves) continue;
+      if (nc >= chunk_cap || nc >= most_chunks(work[b])) continue;
       if (pick < 0 || (long long)work[b] * p.chunks.n[pick] > (long long)work[pick] * nc) pick = b;
     }
     if (pick < 0) break;

@@ -1,0 +1,54 @@
+"""The fp16 tail of a quantized layer (pieces of 32 tokens on the matrix cores, new tokens read from the
+caller's buffers) and the split of short sequences into one or more workgroups, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2505_19586_amd as tkv
+from oracle import attention
+from synth import HeadShape, make_layer
+
+from gpu_util import attn_err, check_quant_cache, to_new
+
+pytestmark = pytest.mark.gpu
+SM = 1.0 / np.sqrt(128.0)
+TOL = 2e-3
+# nothing quantized: what is left of the error is the fp16 rounding of the output (2^-11 of an
+# element, so at most 2^-11 of a head's largest) and float32 sums over at most 1023 tokens
+TOL_TAIL = 2.0 ** -11 + 1e-4
+
+
+@pytest.mark.parametrize("bits,g,residual,n,n_new,heads", [
+    (2, 32, 128, 1, 1, (32, 8)),        # a single token, from the call itself
+    (2, 32, 128, 8, 8, (32, 8)),        # all tokens are new
+    (2, 32, 128, 33, 1, (16, 2)),       # second piece of one token
+    (2, 32, 128, 159, 8, (3, 1)),       # nothing quantized, last piece one short of full
+    (4, 32, 992, 1023, 3, (32, 8)),     # 32 pieces: four per wave of 8
+    (1, 64, 960, 1023, 1, (8, 8)),      # one query head per KV head, three pieces per wave of 12
+    (2, 64, 128, 191, 5, (64, 8)),      # two workgroups per KV head read (and write) the same tail
+    (2, 32, 128, 800, 1, (32, 8)),      # 21 blocks and 4 pieces: near the longest that one workgroup sweeps
+    (2, 32, 128, 928, 1, (32, 8)),      # past it: several, merged
+    (4, 32, 128, 512, 1, (32, 8)),      # the same line for workgroups of 8 waves
+    (4, 32, 128, 544, 2, (32, 8)),
+    (2, 32, 256, 5000, 1, (10, 2)),     # nine pieces behind many blocks, ring wrapped
+    (1, 64, 128, 3010, 7, (28, 4)),
+])
+def test_tail(bits, g, residual, n, n_new, heads):
+    print(f"case tail bits={bits} g={g} W={residual} n={n} new={n_new} heads={heads}", flush=True)
+    shape = HeadShape(heads[0], heads[1], 128)
+    inp = make_layer(n, config=3, layer=1, seq=n % 89, shape=shape)
+    layer = tkv.QuantLayer(n_q_heads=heads[0], n_kv_heads=heads[1], bits=bits, group_size=g, residual=residual,
+                           capacity=(n + g) // g * g)
+    kd, vd = to_new(inp.k), to_new(inp.v)
+    if n > n_new:
+        layer.append(kd[:, :n - n_new].contiguous(), vd[:, :n - n_new].contiguous())
+    q = torch.from_numpy(inp.q)[None].cuda()
+    out = layer.decode(q, SM, kd[:, n - n_new:].contiguous(), vd[:, n - n_new:].contiguous())
+    ref = check_quant_cache(layer, 0, inp.k, inp.v)   # the new rows are in the ring, bit for bit
+    want = attention.quant_attention(inp.q, ref, SM)
+    tol = TOL_TAIL if ref.n_quant == 0 else TOL
+    err = attn_err(out[0], want)
+    print(f"   err {err:.3e}", flush=True)
+    assert err <= tol
+    again = layer.attn_decode(q, SM)                  # the same tokens, now all from the ring
+    assert attn_err(again[0], want) <= tol
