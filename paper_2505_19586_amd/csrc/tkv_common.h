@@ -146,14 +146,18 @@ struct AgentBuf {
 };
 
 // head0: partials of the G heads of this KV head, [G][n_chunks][TKV_PART_STRIDE]; out0: fp16
-// [G][128].  lds: 3 * G * n_chunks + 4 * 4 * 128 + 4 floats.  Called by every thread of the
-// workgroup (nthr a multiple of 64, at least 64 * G).
+// [G][128].  lds: merge_lds_floats(G, n_chunks) floats.  Called by every thread of the
+// workgroup (nthr a multiple of 64, at least 64 * G).  KS: chunk classes summed side by side (2 to
+// 4, so that the 32 G KS items are at most one per thread); kPer: loads in flight per thread.  64
+// chunks come in one round of loads where KS kPer >= 64.
+constexpr int merge_lds_floats(int G, int n_chunks) { return 3 * G * n_chunks + 4 * G * TKV_D + G; }
+template <int KS = 4, int kPer = 16>
 __device__ inline void merge_chunks(const float* head0, int G, int n_chunks, __half* out0, float* lds, int tid,
                                     int nthr) {
   float* ml = lds;                       // [G][n_chunks][2]
   float* cw = ml + 2 * G * n_chunks;     // [G][n_chunks] weights
-  float* red = cw + G * n_chunks;        // [4 heads][4 classes][128]
-  float* Ls = red + 4 * 4 * TKV_D;       // [4]
+  float* red = cw + G * n_chunks;        // [G][KS][128]
+  float* Ls = red + G * KS * TKV_D;      // [G]
   const int lane = tid % 64, wave = tid / 64;
   const AgentBuf pb(head0, (uint32_t)((size_t)G * n_chunks * TKV_PART_STRIDE * sizeof(float)));
   // first pass: maxima and sums of all chunks, and (for up to 64 chunks) this thread's channels
@@ -165,20 +169,20 @@ __device__ inline void merge_chunks(const float* head0, int G, int n_chunks, __h
     ml[2 * i] = __uint_as_float(v_max);
     ml[2 * i + 1] = __uint_as_float(v_sum);
   }
-  // item = (head, chunk class ks, channel quad c4): chunks ks, ks + 4, ...
-  constexpr int kPer = 16;
-  for (int item0 = 0; item0 < G * TKV_D; item0 += nthr) {
+  // item = (head, chunk class ks, channel quad c4): chunks ks, ks + KS, ...
+  constexpr int kItems = 32 * KS;
+  for (int item0 = 0; item0 < G * kItems; item0 += nthr) {
     const int item = item0 + tid;
-    const bool on = item < G * TKV_D;
-    const int hh = on ? item / TKV_D : 0, r = item % TKV_D;
+    const bool on = item < G * kItems;
+    const int hh = on ? item / kItems : 0, r = item % kItems;
     const int ks = r / 32, c4 = r % 32;
     const uint32_t base = (uint32_t)((hh * n_chunks) * TKV_PART_STRIDE + TKV_PART_O + 4 * c4) * 4u;
     tkv_floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int k0 = 0; k0 < n_chunks; k0 += 4 * kPer) {
+    for (int k0 = 0; k0 < n_chunks; k0 += KS * kPer) {
       tkv_u32x4 ov[kPer];
 #pragma unroll
       for (int y = 0; y < kPer; ++y) {
-        const int k = k0 + 4 * y + ks;
+        const int k = k0 + KS * y + ks;
         ov[y] = pb.x4(on && k < n_chunks ? base + (uint32_t)k * TKV_PART_STRIDE * 4u : AgentBuf::kNone);
       }
       if (item0 == 0 && k0 == 0) {
@@ -202,18 +206,19 @@ __device__ inline void merge_chunks(const float* head0, int G, int n_chunks, __h
       }
 #pragma unroll
       for (int y = 0; y < kPer; ++y) {
-        const int k = k0 + 4 * y + ks;
+        const int k = k0 + KS * y + ks;
         const float w = (on && k < n_chunks) ? cw[hh * n_chunks + k] : 0.f;
         acc += __builtin_bit_cast(tkv_floatx4, ov[y]) * w;
       }
     }
-    if (on) *reinterpret_cast<tkv_floatx4*>(red + (hh * 4 + ks) * TKV_D + 4 * c4) = acc;
+    if (on) *reinterpret_cast<tkv_floatx4*>(red + (hh * KS + ks) * TKV_D + 4 * c4) = acc;
   }
   __syncthreads();
   for (int i = tid; i < G * TKV_D; i += nthr) {
     const int hh = i / TKV_D, c = i % TKV_D;
-    const float O = (red[(hh * 4 + 0) * TKV_D + c] + red[(hh * 4 + 1) * TKV_D + c]) +
-                    (red[(hh * 4 + 2) * TKV_D + c] + red[(hh * 4 + 3) * TKV_D + c]);
+    float O = red[hh * KS * TKV_D + c] + red[(hh * KS + 1) * TKV_D + c];
+    if (KS == 3) O += red[(hh * KS + 2) * TKV_D + c];
+    if (KS == 4) O += red[(hh * KS + 2) * TKV_D + c] + red[(hh * KS + 3) * TKV_D + c];
     const float Lsum = Ls[hh];
     out0[(size_t)hh * TKV_D + c] = __float2half_rn(Lsum > 0.f ? O / Lsum : 0.f);
   }

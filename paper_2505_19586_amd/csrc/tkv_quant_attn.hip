@@ -348,7 +348,7 @@ int32_t quant_attn_decode_impl(const tkv_quant_desc* d, const tkv_quant_cache* c
     if (st != TKV_E_UNSUPPORTED) return st;
   }
   if (fresh != nullptr) return TKV_E_UNSUPPORTED;
-  // reference kernel: on request, and for the settings the matrix-core kernel is not built for
+  // reference kernel, on request
   if ((size_t)d->batch * d->n_q_heads * (n_chunks + 1) * TKV_PART_STRIDE > parts_floats) return TKV_E_WORKSPACE;
   p.chunk_offset = 0;
   const int split = (d->n_q_heads / d->n_kv_heads + 3) / 4;
@@ -396,17 +396,13 @@ extern "C" int32_t tkv_quant_decode(const tkv_quant_desc* d, tkv_quant_cache* c,
   if (workspace_bytes < need) return TKV_E_WORKSPACE;
   if (n_new == 0) return tkv_quant_attn_decode(d, c, q, out, sm_scale, workspace, workspace_bytes, stream);
   // One launch when no sequence completes a quantization group with these tokens (the new rows
-  // then only join the fp16 ring, which the attention kernel does itself) and the matrix-core
-  // kernel serves the descriptor; else the append's launches, then the attention's.
+  // then only join the fp16 ring, which the matrix-core kernel does itself); else the append's
+  // launches, then the attention's.
   tkv::QuantNewTokens fresh;
   fresh.k_new = (const __half*)k_new;
   fresh.v_new = (const __half*)v_new;
   fresh.n_stride = n_new;
-  bool one_launch = g_kernel_choice.load() == 0 && d->head_dim == TKV_D;
-  {
-    const int variant = d->bits * 100 + d->group_size;
-    if (variant != 232 && variant != 432 && variant != 164 && variant != 264) one_launch = false;
-  }
+  bool one_launch = g_kernel_choice.load() == 0;
   for (int b = 0; b < d->batch; ++b) {
     const int64_t n0 = c->seq_len_host[b];
     const int32_t add = n_valid_host ? n_valid_host[b] : n_new;

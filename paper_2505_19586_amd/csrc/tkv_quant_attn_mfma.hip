@@ -1,6 +1,7 @@
 // Matrix-core kernel of tkv_quant_attn_decode (Sec. 2.1 Eq. 3 over the quantized cache
-// of Sec. 4.3) for gfx950, 4 query heads of a KV head per workgroup, D = 128, bits 1, 2 or 4, quantization group 32
-// or 64 (Sec. 5.1 runs 1 and 2 bits with groups of 64).
+// of Sec. 4.3) for gfx950: all query heads of a KV head (H = 4 or 8 operand columns' worth) per
+// workgroup, D = 128, bits 1, 2 or 4, quantization group 32 or 64 (Sec. 5.1 runs 1 and 2 bits with
+// groups of 64).
 //
 // One wave64 owns one packed block of 32 tokens at a time (half a key group when the
 // quantization group is 64; "group" below means such a block).  Both contractions run on
@@ -12,16 +13,26 @@
 //     compensated in the other operand;
 //   * q.K-hat = sum_c code[t][c] * (q[c] s[c]) + sum_c q[c] z[c]: the scaler moves into
 //     the query operand, split into fp16 hi + lo parts so the product keeps ~22 bits.
-//     The 16 operand columns are 4 query heads x 4 column groups; even groups carry the hi
-//     part and odd groups the lo part, so ONE MFMA per (16 tokens, 32 channels) produces
+//     The 16 operand columns are H query heads x 16 / H column groups; even groups carry the
+//     hi part and odd groups the lo part, so ONE MFMA per (16 tokens, 32 channels) produces
 //     both partial sums and a single cross-lane add joins them.  The zero-point term does
 //     not depend on the token: it is computed once per workgroup for all of its groups
 //     (16 groups per MFMA) and kept in an LDS table;
-//   * p.V-hat = sum_t code[t][d] * (p[t] s_v[t][u]) + sum_t p[t] z_v[t][u]: here the 4
-//     column groups are the 4 channel groups u, so the weights never leave the lanes that
-//     produced them (the D layout of the first product is the B layout of the second);
-//     z_v and the softmax denominator ride on one more MFMA.  The weights go in as one
-//     fp16 number each (the product p s_v is rounded once).
+//   * p.V-hat = sum_t code[t][d] * (p[t] s_v[t][u]) + sum_t p[t] z_v[t][u]: here the column
+//     groups are the channel groups u, so the weights never leave the lanes that produced
+//     them (the D layout of the first product is the B layout of the second); z_v and the
+//     softmax denominator ride on one more MFMA.  A 16-channel block of V needs one u only:
+//     with 8 heads, whose columns hold two u, four channel groups (group 32) take a second
+//     set of weights for the blocks of u = 2, 3, and no MFMA more.  The weights go in as one
+//     fp16 number each (the product p s_v is rounded once), or as hi + lo pairs (HILO: the
+//     settings that float32 weights served before).
+//
+// Groups of 5 to 8 query heads per KV head (H = 8) cost the operand preparation of four more
+// heads; served as two workgroups of 4 heads each they cost everything twice (64 / 8 heads, 2 bit,
+// 65500 tokens: 28.9 -> 26.1 us per call; 32 / 4 heads, 1 bit, 98413 tokens: 25.3 -> 23.4, of which
+// the merge of 64 chunks x 8 heads by one workgroup, 270 KB, is 5).  4 bits with groups of 64 and
+// 1 bit with groups of 32 cost what their neighbours do (65500 tokens: 24.4 and 23.8 us; 225 and 229
+// on the float32 kernel that served them).
 //
 // The machine issues one vector or matrix instruction per SIMD at a time and a wave issues
 // in order, so the cost of a group is close to the plain sum of its instructions: the
@@ -52,7 +63,7 @@ struct MfmaParams {
   const __half* v_resid;
   const __half* q;
   float* parts;        // sequence after sequence: [Hq][chunks of the sequence][D + 4]
-  uint32_t* arrivals;  // [B][Hkv * quarters of a group], zero between calls
+  uint32_t* arrivals;  // [B][Hkv], zero between calls
   __half* out;         // [B][Hq][D]
   float scale2;
   int32_t hq, hkv, residual, capacity;
@@ -85,9 +96,10 @@ __device__ inline uint32_t pack2(_Float16 lo, _Float16 hi) {
   return __builtin_bit_cast(uint32_t, v);
 }
 
-// v + (value of the lane 4 places away in the same row of 16 lanes)
-__device__ inline float ror4_add(float v) {
-  const int r = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x124 /* row_ror:4 */, 0xF, 0xF, false);
+// v + (value of the lane H = 4 or 8 places away in the same row of 16 lanes)
+template <int H>
+__device__ inline float ror_add(float v) {
+  const int r = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x120 + H /* row_ror:H */, 0xF, 0xF, false);
   return v + __builtin_bit_cast(float, r);
 }
 
@@ -161,8 +173,8 @@ constexpr int kEK = 0;
 constexpr int kEP = 2;
 constexpr int kHeadroomLog2 = 4;  // lazy rescale: weights may reach 2^kHeadroomLog2
 constexpr int kRefBelowMax = 3;   // a rescale puts the reference this far under the largest logit (< headroom)
-constexpr int kBkStride = 80;     // words per head row of the query-side operand in LDS
-constexpr int kMaxGpc = 512;      // groups per chunk that the zero-point table holds
+constexpr int kBkStride = 68;     // words per head row of the query-side operand in LDS (16 rows x 4 words: all 64 banks)
+constexpr int max_gpc(int heads) { return heads <= 4 ? 512 : 256; }  // groups per chunk that the zero-point table holds
 constexpr int kTailBlocks = 3;    // blocks that a 32-token piece of the fp16 tail counts as in the split (2 to 5: no difference)
 // Sequences of up to this many blocks (tail pieces counted as above) per wave are one workgroup's:
 // no partials to write, no arrival, no merge.  2 bit, 8 KV heads, batch 1: 600 tokens (29 blocks)
@@ -171,24 +183,26 @@ constexpr int kOneChunkRounds = 3;
 
 // Results of one wave for the merge inside the workgroup; it takes the place of the start of
 // the wave's own load ring once the wave has left the group loop.
+template <int H>
 struct MergeWave {
-  float m[4];
-  float l[4];
-  float z[4][4];
-  float o[4][TKV_D];
+  float m[H];
+  float l[H];
+  float z[H][4];
+  float o[H][TKV_D];
 };
 
 // ---- LDS plan (dynamic shared memory) ---------------------------------------------------
-//   bk     per wave [hi/lo][4 heads][80 words]: query-side operands of the next group
+//   bk     per wave [hi/lo][H heads][68 words]: query-side operands of the next group
 //   ring   per wave 3 K slots (codes, scalers) then 3 V slots (codes, scalers, zero-points);
 //          the direct global->LDS loads put lane l's bytes at slot + 16*l (codes) or
 //          slot + 4*l (fp16 rows), i.e. a slot is a copy of the group's packed block.  After
 //          the main loop the start of a wave's ring holds its results for the workgroup merge.
-//   cz     zero-point term of every group of the chunk, [group][4 heads] float
-// (a wave that has pieces of the fp16 tail uses its bk area as scratch before its first group)
+//   cz     zero-point term of every group of the chunk, [group][H heads] float
+// (a wave's bk area is its scratch for pieces of the fp16 tail before its first group, and for the
+// merge weights after its last one)
 // GS = quantization group / 32: the K scalers of a slot are those of the block's key group,
 // the V scalers and zero-points [128 / (32 GS)][32 tokens] fp16 each.
-template <int BITS, int GS, int W>
+template <int BITS, int GS, int W, int H>
 struct Cfg {
   static constexpr int kThreads = 64 * W;
   static constexpr int kCode = 512 * BITS;  // bytes of K (or V) codes of one block
@@ -204,15 +218,25 @@ struct Cfg {
   static constexpr int kKLoads = kCodeLoads + 1;
   static constexpr int kVLoads = kCodeLoads + (GS == 1 ? 2 : 1);
   static constexpr int kCodeWords = BITS == 1 ? 2 : 2 * BITS;  // code words per lane and part
-  static constexpr int kBkWave = 2 * 4 * kBkStride * 4;
+  static constexpr int kBkWave = 2 * H * kBkStride * 4;
+  static constexpr int kMaxGpc = max_gpc(H);
   static constexpr int oRing = W * kBkWave;
   static constexpr int oCz = oRing + W * kWaveRing;
-  static constexpr int kLdsBytes = oCz + kMaxGpc * 16;
-  static_assert(4 * TKV_D * 4 <= kBkWave, "the tail's scratch fits in a wave's operand area");
-  static_assert(sizeof(MergeWave) <= (size_t)kWaveRing, "a wave's results fit in its own ring");
-  static_assert((3 * 4 * TKV_MAX_CHUNKS + 4 * 4 * TKV_D + 4) * 4 <= (size_t)W * kWaveRing, "merge scratch must fit in the ring");
+  static constexpr int kLdsBytes = oCz + kMaxGpc * H * 4;
+  static_assert(H * TKV_D * 4 <= kBkWave && (TKV_BLK + 1) * H * 4 <= kBkWave, "the tail's scratch fits in a wave's operand area");
+  static_assert((W + 2) * H * 4 <= kBkWave, "so do the merge weights");
+  static_assert(sizeof(MergeWave<H>) <= (size_t)kWaveRing, "a wave's results fit in its own ring");
+  static_assert(tkv::merge_lds_floats(H, TKV_MAX_CHUNKS) * 4 <= W * kWaveRing, "merge scratch must fit in the ring");
+  static_assert(kThreads >= 64 * H, "the cross-chunk merge takes a wave per head");
   static_assert(kLdsBytes + 64 <= 160 * 1024, "LDS budget of one compute unit");
 };
+
+// Column group whose column of acc_o[cb] counts: one that carries the weights of the block's
+// channel group u = cb / (2 GS) (H = 8: u % 2; the other columns hold products with another u).
+template <int GS, int H>
+__device__ constexpr int owner_group(int cb) {
+  return H == 4 ? cb / 2 : GS == 1 ? (cb / 2) % 2 : cb / 4;
+}
 
 // fp16 tail (the unquantized tokens): wave w of the last chunk takes the 32-token pieces w,
 // w + W, ... and leaves its result as the state its block loop starts from: reference m_run =
@@ -221,9 +245,10 @@ struct Cfg {
 //
 // Everything runs on the matrix cores: the logits as K rows (A operand, straight from memory)
 // against the exact fp16 query (the set-up's B operand), in the token order of a block's tiles;
-// P.V in float32 on v_mfma_f32_4x4x1 (16 independent 4 heads x 4 channels products of one token
-// each): its B operand is one channel of one token per lane, so a lane's 16-byte piece of a V row
-// feeds eight of them with no transpose, and the weights keep all their bits.  A wave is bound by
+// P.V in float32, on v_mfma_f32_4x4x1 for 4 heads (16 independent 4 heads x 4 channels products of
+// one token each) and v_mfma_f32_16x16x4 for 8: either's B operand is one channel of one token per
+// lane, so a lane's 16-byte piece of a V row feeds eight of them with no transpose, and the
+// weights keep all their bits.  A wave is bound by
 // the latency of its loads (16 in flight per lane) and then by some 300 instructions: 3.8 us from the
 // set-up barrier at 2000 tokens, all pieces in parallel.  Plain float math with one token per lane
 // pair and the weights broadcast lane by lane, on 4 waves, took 9 to 12.5 us, longer than
@@ -231,50 +256,71 @@ struct Cfg {
 // 18.0 -> 13.5 us per call, 8190 18.0 -> 14.4, 131060 30.3 -> 29.5; 64 sequences of 2000 62 -> 47).
 //
 // New tokens of the step are read from the caller's buffers: their ring rows are being written.
-template <int BITS, int W>
-__device__ inline void tail_pieces(const MfmaParams& p, const uintx4 (&bq)[4], float* sc, int b, int h, size_t bh, int nq,
-                                   int n, int ring, int wave, int lane, floatx4 (&acc_o)[8], floatx4& acc_z,
-                                   float& m_run) {
-  const int slot = lane % 16, rb = lane / 16, hs = slot % 4, us = slot / 4;
-  const int n_old = p.k_new != nullptr ? n - p.n_add.n[b] : n;
-  const int s0 = nq % ring;  // ring slot of the tail's first token
-  auto row = [&](const __half* ring_rows, const __half* new_rows, int tok) -> const __half* {
+struct TailPiece {
+  uintx4 kf[2][4];  // K rows as A operands of the two 16-token tiles
+  uintx4 vf[8];     // V: channels 8 slot .. 8 slot + 7 of tokens 4 j + rb
+};
+struct TailRows {
+  const char *k_ring, *v_ring, *k_new, *v_new;  // this head's rows
+  uint32_t new_pitch;                           // bytes between a head's new rows
+  int nq, n_old, n, s0, ring;
+  __device__ TailRows(const MfmaParams& p, int b, int h, size_t bh, int nq_, int n_, int ring_) {
+    nq = nq_, n = n_, ring = ring_;
+    n_old = p.k_new != nullptr ? n - p.n_add.n[b] : n;
+    s0 = nq % ring;  // ring slot of the tail's first token
+    k_ring = reinterpret_cast<const char*>(p.k_resid + bh * ring * TKV_D);
+    v_ring = reinterpret_cast<const char*>(p.v_resid + bh * ring * TKV_D);
+    const size_t first = p.k_new != nullptr ? ((size_t)b * p.n_stride * p.hkv + h) * TKV_D : 0;
+    k_new = reinterpret_cast<const char*>(p.k_new + first);
+    v_new = reinterpret_cast<const char*>(p.v_new + first);
+    new_pitch = (uint32_t)p.hkv * TKV_D * 2u;
+  }
+  __device__ const uintx4* row(const char* ring_rows, const char* new_rows, int tok, int lane_bytes) const {
     int s = s0 + (tok - nq);
     s = s >= ring ? s - ring : s;
-    const __half* old_row = ring_rows + (bh * ring + (size_t)s) * TKV_D;
-    const __half* new_row = new_rows + (((size_t)b * p.n_stride + (size_t)(tok - n_old)) * p.hkv + h) * TKV_D;
-    return tok < n_old ? old_row : new_row;
-  };
-  float L = 0.f;
-  floatx4 acc[8];  // channel 8 slot + y of the tokens 4 j + rb, rows = heads
-#pragma unroll
-  for (int y = 0; y < 8; ++y) acc[y] = floatx4{0.f, 0.f, 0.f, 0.f};
-  for (int t0 = nq + 32 * wave; t0 < n; t0 += 32 * W) {
-    const int cnt = min(32, n - t0);
-    uintx4 kf[2][4], vf[8];
+    const bool old = tok < n_old;
+    const uint32_t off = (old ? (uint32_t)s * (TKV_D * 2u) : (uint32_t)(tok - n_old) * new_pitch) + (uint32_t)lane_bytes;
+    return reinterpret_cast<const uintx4*>((old ? ring_rows : new_rows) + off);
+  }
+  __device__ void load(TailPiece& t, int t0, int lane) const {
+    const int slot = lane % 16, rb = lane / 16, cnt = min(32, n - t0);  // rows past the end re-read the last one with weight 0
 #pragma unroll
     for (int tau = 0; tau < 2; ++tau) {
-      const int t = 8 * (slot / 4) + 4 * tau + slot % 4;  // rows past the end re-read the last one with weight 0
-      const __half* kr = row(p.k_resid, p.k_new, t0 + min(t, cnt - 1)) + 8 * rb;
+      const int y = 8 * (slot / 4) + 4 * tau + slot % 4;
+      const uintx4* r = row(k_ring, k_new, t0 + min(y, cnt - 1), 16 * rb);
 #pragma unroll
-      for (int m = 0; m < 4; ++m) kf[tau][m] = *reinterpret_cast<const uintx4*>(kr + 32 * m);
+      for (int m = 0; m < 4; ++m) t.kf[tau][m] = r[4 * m];
     }
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
-      vf[j] = *reinterpret_cast<const uintx4*>(row(p.v_resid, p.v_new, t0 + min(4 * j + rb, cnt - 1)) + 8 * slot);
+    for (int j = 0; j < 8; ++j) t.vf[j] = *row(v_ring, v_new, t0 + min(4 * j + rb, cnt - 1), 16 * slot);
+  }
+};
+
+template <int BITS, int GS, int W, int H>
+__device__ inline void tail_pieces(const TailRows& rows, float scale2, const uintx4 (&bq)[4], float* sc, int wave,
+                                   int lane, floatx4 (&acc_o)[8], floatx4& acc_z, float& m_run) {
+  const int slot = lane % 16, rb = lane / 16, hs = slot % H, us = slot / H;
+  float L = 0.f;
+  floatx4 acc[8];  // channel 8 slot + y; H = 4: tokens 4 j + rb, rows = heads; H = 8: rows = heads 4 (rb % 2) + x
+#pragma unroll
+  for (int y = 0; y < 8; ++y) acc[y] = floatx4{0.f, 0.f, 0.f, 0.f};
+  for (int t0 = rows.nq + 32 * wave; t0 < rows.n; t0 += 32 * W) {
+    const int cnt = min(32, rows.n - t0);
+    TailPiece t;
+    rows.load(t, t0, lane);
     __builtin_amdgcn_sched_barrier(0);  // all loads in flight before the first is used
     floatx4 s[2];
 #pragma unroll
     for (int tau = 0; tau < 2; ++tau) {
       s[tau] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int m = 0; m < 4; ++m) s[tau] = mfma(kf[tau][m], bq[m], s[tau]);
+      for (int m = 0; m < 4; ++m) s[tau] = mfma(t.kf[tau][m], bq[m], s[tau]);
     }
-    // this lane: head hs, tokens 8 rb + i (the same in all four column groups)
+    // this lane: head hs, tokens 8 rb + i (the same in all column groups)
     float x[8], mx = -INFINITY;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      x[i] = 8 * rb + i < cnt ? s[i / 4][i % 4] * p.scale2 : -INFINITY;
+      x[i] = 8 * rb + i < cnt ? s[i / 4][i % 4] * scale2 : -INFINITY;
       mx = fmaxf(mx, x[i]);
     }
     mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
@@ -294,24 +340,34 @@ __device__ inline void tail_pieces(const MfmaParams& p, const uintx4 (&bq)[4], f
     // weights to [token][head]; a wave's LDS operations execute in order
     if (us == 0) {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) sc[(8 * rb + i) * 4 + hs] = x[i];
-      if (rb == 0) sc[128 + hs] = alpha;
+      for (int i = 0; i < 8; ++i) sc[(8 * rb + i) * H + hs] = x[i];
+      if (rb == 0) sc[TKV_BLK * H + hs] = alpha;
     }
     float w[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) w[j] = sc[(4 * j + rb) * 4 + lane % 4];
-    const floatx4 al = *reinterpret_cast<const floatx4*>(sc + 128);
+    for (int j = 0; j < 8; ++j) w[j] = sc[(4 * j + rb) * H + lane % H];
+    const floatx4 al = *reinterpret_cast<const floatx4*>(sc + TKV_BLK * H + (H == 4 ? 0 : 4 * (rb % 2)));
 #pragma unroll
     for (int y = 0; y < 8; ++y) acc[y] *= al;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
 #pragma unroll
       for (int y = 0; y < 8; ++y) {
-        const uint32_t vw = vf[j][y / 2];
-        acc[y] = __builtin_amdgcn_mfma_f32_4x4x1f32(w[j], (float)as_half2(vw)[y % 2], acc[y], 0, 0, 0);
+        const uint32_t vw = t.vf[j][y / 2];
+        const float vv = (float)as_half2(vw)[y % 2];
+        acc[y] = H == 4 ? __builtin_amdgcn_mfma_f32_4x4x1f32(w[j], vv, acc[y], 0, 0, 0)
+                        : __builtin_amdgcn_mfma_f32_16x16x4f32(w[j], vv, acc[y], 0, 0, 0);
       }
     }
   }
+  if (H == 8) {
+    if (rb < 2) {
+#pragma unroll
+      for (int y = 0; y < 8; ++y)
+#pragma unroll
+        for (int x = 0; x < 4; ++x) sc[(4 * rb + x) * TKV_D + 8 * slot + y] = acc[y][x];
+    }
+  } else {
   // sum over the four token classes rb: every exchange halves the values a lane keeps; in the end
   // it holds channels 8 slot + 2 rb', + 1 of the four heads (rb' = 2 (lane / 32) + (lane / 16) % 2)
   float v[32];
@@ -332,11 +388,12 @@ __device__ inline void tail_pieces(const MfmaParams& p, const uintx4 (&bq)[4], f
 #pragma unroll
   for (int hh = 0; hh < 4; ++hh)
     *reinterpret_cast<float2_t*>(sc + hh * TKV_D + 8 * slot + 2 * rb) = float2_t{v[hh], v[4 + hh]};
+  }
 #pragma unroll
   for (int cb = 0; cb < 8; ++cb) {
     const float scale = 1.0f / (float)(1 << (24 - kEP - (BITS == 1 && cb % 2 ? 4 : 0)));
-    const floatx4 o = *reinterpret_cast<const floatx4*>(sc + hs * TKV_D + 16 * (2 * us + cb % 2) + 4 * rb) * scale;
-    acc_o[cb] = cb / 2 == us ? o : floatx4{0.f, 0.f, 0.f, 0.f};
+    const floatx4 o = *reinterpret_cast<const floatx4*>(sc + hs * TKV_D + 16 * cb + 4 * rb) * scale;
+    acc_o[cb] = owner_group<GS, H>(cb) == us ? o : floatx4{0.f, 0.f, 0.f, 0.f};
   }
   acc_z[0] = rb == 1 ? L : 0.f;
 }
@@ -354,9 +411,9 @@ __device__ inline void tail_pieces(const MfmaParams& p, const uintx4 (&bq)[4], f
   } while (0)
 #endif
 
-template <int BITS, int GS, int W>
+template <int BITS, int GS, int W, int H, bool HILO>
 __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
-  using C = Cfg<BITS, GS, W>;
+  using C = Cfg<BITS, GS, W, H>;
   constexpr int KSH = GS - 1;          // key group of a block = block >> KSH
   constexpr int NU = 4 / GS;           // channel groups of a value row
   constexpr int GRP = TKV_BLK * GS;    // quantization group
@@ -378,15 +435,11 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
     ++b;
   }
   const int n_chunks = p.chunks.n[b];
-  // Groups of more than 4 query heads per KV head are served 4 heads at a time (the operand
-  // columns hold 4 heads): blockIdx.y runs over (KV head, quarter of its group), and the
-  // quarters of a head read the same codes.
-  const int split = (p.hq / p.hkv + 3) / 4;
-  const int h = blockIdx.y / split;
+  const int h = blockIdx.y;
   const int tid = threadIdx.x, lane = tid % 64;
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64);  // wave-uniform: keeps group addresses scalar
-  const int qh0 = h * (p.hq / p.hkv) + 4 * (blockIdx.y % split);  // first query head of this workgroup
-  const int G = min(4, (h + 1) * (p.hq / p.hkv) - qh0);
+  const int G = p.hq / p.hkv;  // at most H
+  const int qh0 = h * G;       // first query head of this workgroup
   const int n = p.lens.n[b];
   const int nq = tkv::n_quantized(n, p.residual, GRP);
   const int jq = nq / TKV_BLK;
@@ -403,10 +456,10 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
   const int last = max(blk1 - 1, blk0);  // groups past the chunk are clamped (and ignored); jq >= 1 here
 
   const int slot = lane % 16, rb = lane / 16;
-  const int hs = slot % 4, us = slot / 4;  // this lane's operand column: head, column group
+  const int hs = slot % H, us = slot / H;  // this lane's operand column: head, column group
   const __half* qrow = p.q + ((size_t)b * p.hq + (size_t)qh0) * TKV_D;
-  typedef uint32_t BkArr[2][4][kBkStride];
-  uint32_t(*bk_s)[4][kBkStride] = reinterpret_cast<BkArr*>(smem)[wave];
+  typedef uint32_t BkArr[2][H][kBkStride];
+  uint32_t(*bk_s)[H][kBkStride] = reinterpret_cast<BkArr*>(smem)[wave];
   float* cz_s = reinterpret_cast<float*>(smem + C::oCz);
   // Byte offsets (wave-uniform) of this wave's ring slots; the roles rotate every step.
   const uint32_t ring_off = C::oRing + wave * C::kWaveRing;
@@ -460,14 +513,13 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
   // Set-up loads first (query rows, zero-points of this wave's first 16 groups), then the
   // ring prologue: one memory round trip covers both.
   const int ng = blk1 - blk0;
-  uint32_t q2[4];   // K-prep role: this lane owns channels 2*lane, 2*lane+1
+  uint32_t q2[H];   // K-prep role: this lane owns channels 2*lane, 2*lane+1
   uintx4 bq[4];     // exact fp16 query as MFMA B operand (zero-point term)
   uintx4 az[4];     // zero-point rows of 16 groups as MFMA A operand
   if (has_tail && p.k_new != nullptr) {
     // Eq. 2 in this launch: the step's new rows go into the fp16 ring, into slots whose tokens were
     // quantized long ago.  Nothing in this launch reads those slots: the tail waves take the new
-    // rows from the caller's buffers (the workgroups of a group of more than 4 query heads write
-    // the same bytes).
+    // rows from the caller's buffers.
     const int add = p.n_add.n[b], ring = p.residual + GRP;
     for (int x = tid; x < add * 32; x += 64 * W) {
       const int i = x / 32, kv = (x % 32) / 16, part = x % 16;
@@ -478,7 +530,7 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
     }
   }
 #pragma unroll
-  for (int hh = 0; hh < 4; ++hh)  // heads >= G re-read head G-1 (in bounds) and are zeroed below
+  for (int hh = 0; hh < H; ++hh)  // heads >= G re-read head G-1 (in bounds); their results are not used
     q2[hh] = reinterpret_cast<const uint32_t*>(qrow + (size_t)(hh < G ? hh : G - 1) * TKV_D)[lane];
 #pragma unroll
   for (int m = 0; m < 4; ++m)
@@ -504,10 +556,6 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
 
   // ---- zero-point term of every group of the chunk: cz[g][head] = scale2 * sum_c q[c] z_g[c],
   // 16 groups per MFMA (A rows = groups, B = the exact fp16 query)
-  if (hs >= G) {
-#pragma unroll
-    for (int m = 0; m < 4; ++m) bq[m] = uintx4{0u, 0u, 0u, 0u};
-  }
   for (int t0 = 16 * wave; t0 < ng; t0 += 16 * W) {
     if (t0 != 16 * wave) load_az(t0);
     floatx4 acc = {0.f, 0.f, 0.f, 0.f};
@@ -517,18 +565,18 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
 #pragma unroll
       for (int x = 0; x < 4; ++x) {
         const int gl = t0 + 4 * rb + x;
-        if (gl < ng) cz_s[gl * 4 + hs] = acc[x] * p.scale2;
+        if (gl < ng) cz_s[gl * H + hs] = acc[x] * p.scale2;
       }
     }
   }
   // query times the factor that undoes the field position of this lane's channels
   // (1 bit: 2^(lane%4), times 2^4 in odd 32-channel blocks; 2 bit: 4^(lane%4); 4 bit: 16^(lane%2))
-  float qf[4][2];
+  float qf[H][2];
   {
     const int shift = BITS == 1 ? lane % 4 + 4 * ((lane / 16) % 2) : BITS == 2 ? 2 * (lane % 4) : 4 * (lane % 2);
     const float comp = (float)(1 << kEK) / (float)(1 << shift);
 #pragma unroll
-    for (int hh = 0; hh < 4; ++hh) {
+    for (int hh = 0; hh < H; ++hh) {
       const half2_t qq = as_half2(q2[hh]);
       qf[hh][0] = hh < G ? (float)qq[0] * comp : 0.f;
       qf[hh][1] = hh < G ? (float)qq[1] * comp : 0.f;
@@ -540,14 +588,28 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
   TKV_PH();  // 2 set-up done
 
+  // Next group index from the workgroup's LDS counter.  Written as inline assembly: the
+  // compiler orders every LDS atomic it knows of behind all outstanding direct-to-LDS
+  // loads (vmcnt(0)), which would drain the prefetch ring at every step.
+  const uint32_t next_addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) int*)&s_next;
+  auto grab = [&]() -> int {
+    int v = 0;
+    if (lane == 0) {
+      const int one = 1;
+      asm volatile("ds_add_rtn_u32 %0, %1, %2\n\ts_waitcnt lgkmcnt(0)" : "=v"(v) : "v"(next_addr), "v"(one) : "memory");
+    }
+    return __builtin_amdgcn_readfirstlane(v);
+  };
+
+  // state of the block loop: accumulators and the head's softmax reference
   floatx4 acc_o[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) acc_o[i] = floatx4{0.f, 0.f, 0.f, 0.f};
   floatx4 acc_z = {0.f, 0.f, 0.f, 0.f};
   float m_run = -INFINITY;
   if (has_tail && wave * 32 < n - nq)
-    tail_pieces<BITS, W>(p, bq, reinterpret_cast<float*>(smem) + wave * (C::kBkWave / 4), b, h, bh, nq, n, p.residual + GRP,
-                         wave, lane, acc_o, acc_z, m_run);
+    tail_pieces<BITS, GS, W, H>(TailRows(p, b, h, bh, nq, n, p.residual + GRP), p.scale2, bq,
+                                reinterpret_cast<float*>(smem) + wave * (C::kBkWave / 4), wave, lane, acc_o, acc_z, m_run);
   TKV_PH();  // 3 tail done
 
   // codes carry 2^-24, query side 2^kEK, so S = acc * 2^(24-kEK)
@@ -577,19 +639,6 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
     off[i] = BITS == 1 ? (float)(kEP - j) : BITS == 2 ? (float)(kEP - 2 * j) : (float)(kEP - 4 * (j % 2));
   }
 
-  // Next group index from the workgroup's LDS counter.  Written as inline assembly: the
-  // compiler orders every LDS atomic it knows of behind all outstanding direct-to-LDS
-  // loads (vmcnt(0)), which would drain the prefetch ring at every step.
-  const uint32_t next_addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) int*)&s_next;
-  auto grab = [&]() -> int {
-    int v = 0;
-    if (lane == 0) {
-      const int one = 1;
-      asm volatile("ds_add_rtn_u32 %0, %1, %2\n\ts_waitcnt lgkmcnt(0)" : "=v"(v) : "v"(next_addr), "v"(one) : "memory");
-    }
-    return __builtin_amdgcn_readfirstlane(v);
-  };
-
   // ---- pipeline stages of one group.  Every stage is split into its LDS reads and its
   // arithmetic, so that a step can issue the reads well ahead of their use (a wave issues in
   // order: a read that is waited for right away stalls it for the whole LDS latency).
@@ -599,7 +648,7 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
   };
   auto stage_k = [&](uint32_t ks2) {
 #pragma unroll
-    for (int hh = 0; hh < 4; ++hh) {
+    for (int hh = 0; hh < H; ++hh) {
       const uint32_t hi = mix_hi_pair(qf[hh][0], qf[hh][1], ks2);  // products are exact in float32
       bk_s[0][hh][lane] = hi;
       bk_s[1][hh][lane] = mix_lo_pair(qf[hh][0], qf[hh][1], ks2, hi);
@@ -660,20 +709,24 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
     }
   };
   // weights and weight-side operands
+  constexpr bool kTwoSets = H == 8 && GS == 1;  // weights for u = 0, 1 and for u = 2, 3
   struct PvIn {
-    uintx4 sv, zv;
+    uintx4 sv, sv2, zv;
     uint32_t vw[C::kCodeWords];
     float cz;
   };
   auto read_pv = [&](uint32_t so, int gc, PvIn& in) {
     const unsigned char* s = smem + so;
-    in.sv = *reinterpret_cast<const uintx4*>(s + C::oVs + ((us / GS) * TKV_BLK + 8 * rb) * 2);
+    in.sv = *reinterpret_cast<const uintx4*>(s + C::oVs + ((H == 4 ? us / GS : us) * TKV_BLK + 8 * rb) * 2);
+    if (kTwoSets) in.sv2 = *reinterpret_cast<const uintx4*>(s + C::oVs + ((2 + us) * TKV_BLK + 8 * rb) * 2);
     in.zv = *reinterpret_cast<const uintx4*>(s + C::oVz + (zrow_ld * TKV_BLK + 8 * rb) * 2);
     read_codes(s, in.vw);
-    in.cz = cz_s[(gc - blk0) * 4 + hs];
+    in.cz = cz_s[(gc - blk0) * H + hs];
   };
   struct POps {
     uintx4 b2, bp, a_zv;
+    uintx4 b3;            // kTwoSets: the weights for u = 2, 3
+    uintx4 b2l, b3l, bpl; // HILO: low parts
   };
   // The weights 2^(x - m_run) go to the matrix cores as fp16, so m_run (a per-head reference,
   // not necessarily the running maximum) only has to keep them below 2^kHeadroomLog2: that
@@ -684,7 +737,7 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
     const float cz = in.cz;
     float xs[8];  // hi + lo partial sums: every lane of a head ends up with the full logit
 #pragma unroll
-    for (int x = 0; x < 8; ++x) xs[x] = ror4_add(acc_s[x / 4][x % 4]);
+    for (int x = 0; x < 8; ++x) xs[x] = ror_add<H>(acc_s[x / 4][x % 4]);
     float pw[8];
     auto weights = [&]() {
       const float czm = cz - m_run;
@@ -721,9 +774,26 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
     for (int j = 0; j < 4; ++j) {
       const float2_t w2 = {pw[2 * j], pw[2 * j + 1]};
       o.bp[j] = __builtin_bit_cast(uint32_t, __builtin_convertvector(w2, half2_t));
-      // weight x scaler: one rounding of the exact product of two fp16 numbers
       const uint32_t bpj = o.bp[j], svj = in.sv[j], zvj = in.zv[j];
-      o.b2[j] = __builtin_bit_cast(uint32_t, as_half2(bpj) * as_half2(svj));
+      if (HILO) {
+        o.bpl[j] = mix_lo_pair(pw[2 * j], pw[2 * j + 1], 0x3C003C00u /* 1, 1 */, bpj);
+        o.b2[j] = mix_hi_pair(pw[2 * j], pw[2 * j + 1], svj);
+        const uint32_t b2j = o.b2[j];
+        o.b2l[j] = mix_lo_pair(pw[2 * j], pw[2 * j + 1], svj, b2j);
+        if (kTwoSets) {
+          const uint32_t sv2j = in.sv2[j];
+          o.b3[j] = mix_hi_pair(pw[2 * j], pw[2 * j + 1], sv2j);
+          const uint32_t b3j = o.b3[j];
+          o.b3l[j] = mix_lo_pair(pw[2 * j], pw[2 * j + 1], sv2j, b3j);
+        }
+      } else {
+        // weight x scaler: one rounding of the exact product of two fp16 numbers
+        o.b2[j] = __builtin_bit_cast(uint32_t, as_half2(bpj) * as_half2(svj));
+        if (kTwoSets) {
+          const uint32_t sv2j = in.sv2[j];
+          o.b3[j] = __builtin_bit_cast(uint32_t, as_half2(bpj) * as_half2(sv2j));
+        }
+      }
       const half2_t t = __builtin_elementwise_fma(as_half2(zvj), zmul[j], zadd[j]);
       o.a_zv[j] = __builtin_bit_cast(uint32_t, t);
     }
@@ -731,13 +801,19 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
   // P.V: 8 blocks of 16 channels + the z_v / denominator MFMA
   auto stage_pv = [&](const PvIn& in, const POps& o) {
     acc_z = mfma(o.a_zv, o.bp, acc_z);
+    if (HILO) acc_z = mfma(o.a_zv, o.bpl, acc_z);
+    auto block = [&](int cb, uintx4 a) {
+      const bool second = kTwoSets && cb >= 4;
+      acc_o[cb] = mfma(a, second ? o.b3 : o.b2, acc_o[cb]);
+      if (HILO) acc_o[cb] = mfma(a, second ? o.b3l : o.b2l, acc_o[cb]);
+    };
     if (BITS == 1) {
 #pragma unroll
       for (int wd = 0; wd < 2; ++wd) {
         uintx4 a[4];
         extract1(in.vw[wd], a);
 #pragma unroll
-        for (int y = 0; y < 4; ++y) acc_o[4 * wd + y] = mfma(a[y], o.b2, acc_o[4 * wd + y]);
+        for (int y = 0; y < 4; ++y) block(4 * wd + y, a[y]);
       }
       return;
     }
@@ -751,7 +827,7 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
         extract4(in.vw[((wd / 2) * 4 + 2 * (wd % 2) + 1) % C::kCodeWords], a[1]);
       }
 #pragma unroll
-      for (int y = 0; y < 2; ++y) acc_o[2 * wd + y] = mfma(a[y], o.b2, acc_o[2 * wd + y]);
+      for (int y = 0; y < 2; ++y) block(2 * wd + y, a[y]);
     }
   };
 #define TKV_WAIT_VMCNT(N) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory")
@@ -817,72 +893,75 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
   // ---- per-wave results -> LDS, each wave into its own (now idle) ring, so no wave waits for
   // another before writing.  acc_z rows: lanes 0..15 (rb 0) hold rows 0..3 = z-terms for
   // u = row; lanes 16..31 register 0 hold row 4 = denominator.
-  auto merge_of = [&](int w) -> MergeWave& { return *reinterpret_cast<MergeWave*>(smem + C::oRing + w * C::kWaveRing); };
-  MergeWave& mw = merge_of(wave);
-  if (rb == 0) {
+  auto merge_of = [&](int w) -> MergeWave<H>& {
+    return *reinterpret_cast<MergeWave<H>*>(smem + C::oRing + w * C::kWaveRing);
+  };
+  MergeWave<H>& mw = merge_of(wave);
+  if (rb == 0 && us == 0) {
 #pragma unroll
-    for (int x = 0; x < 4; ++x)
-      if (x == us / GS) mw.z[hs][us] = acc_z[x];
-    if (us == 0) mw.m[hs] = m_run;
+    for (int x = 0; x < NU; ++x) mw.z[hs][x] = acc_z[x];
+    mw.m[hs] = m_run;
   }
   if (rb == 1 && us == 0) mw.l[hs] = acc_z[0];
-  {
-    // written by lanes of this same wave just above: a wave's LDS operations execute in order
-    const float zt = mw.z[hs][us];
 #pragma unroll
-    for (int cb = 0; cb < 8; ++cb) {
-      // 1 bit: the codes of odd 16-channel blocks sit four mantissa bits higher
-      const float unscale = (float)(1 << (24 - kEP - (BITS == 1 && cb % 2 ? 4 : 0)));
-      if (cb / 2 == us) {
-#pragma unroll
-        for (int x = 0; x < 4; ++x) mw.o[hs][16 * cb + 4 * rb + x] = __builtin_fmaf(acc_o[cb][x], unscale, zt);
-      }
+  for (int cb = 0; cb < 8; ++cb) {
+    // 1 bit: the codes of odd 16-channel blocks sit four mantissa bits higher
+    const float unscale = (float)(1 << (24 - kEP - (BITS == 1 && cb % 2 ? 4 : 0)));
+    if (owner_group<GS, H>(cb) == us) {
+      // written by lanes of this same wave just above: a wave's LDS operations execute in order
+      const float zt = mw.z[hs][cb / (2 * GS)];
+      *reinterpret_cast<floatx4*>(&mw.o[hs][16 * cb + 4 * rb]) = acc_o[cb] * unscale + zt;
     }
   }
   __syncthreads();
   TKV_PH();  // 5 all waves done, results in LDS
   // merge weights of the W wave entries: every wave works them out for itself (lane = (entry,
-  // head)) into arrays of its own, which spares the workgroup a barrier
-  constexpr int NE = W;
-  __shared__ float s_w_all[W][NE][4];
-  __shared__ float s_ml_all[W][2][4];
-  static_assert(NE <= 16, "one wave covers all (entry, head) pairs");
-  float(*s_w)[4] = s_w_all[wave];
-  float(*s_ml)[4] = s_ml_all[wave];
+  // head)) into scratch of its own, which spares the workgroup a barrier
+  float(*s_w)[H] = reinterpret_cast<float(*)[H]>(smem + wave * C::kBkWave);  // [W]
+  float(*s_ml)[H] = s_w + W;                                                  // [2]: maximum, sum
   {
-    const int e = lane / 4, hh = lane % 4;
-    float me = -INFINITY, le = 0.f;
-    if (e < W) {
-      me = merge_of(e).m[hh];
-      le = merge_of(e).l[hh];
+    constexpr int EP = 64 / H, NP = (W + EP - 1) / EP;  // entries per pass, passes
+    const int hh = lane % H;
+    float me[NP], le[NP], M = -INFINITY, Lsum = 0.f;
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      const int e = lane / H + EP * i;
+      me[i] = e < W ? merge_of(e).m[hh] : -INFINITY;
+      le[i] = e < W ? merge_of(e).l[hh] : 0.f;
+      M = fmaxf(M, me[i]);
     }
-    float M = me;
-    for (int m = 4; m <= 32; m <<= 1) M = fmaxf(M, __shfl_xor(M, m, 64));
-    const float wgt = me == -INFINITY ? 0.f : exp2f(me - M);
-    float Lsum = le * wgt;
-    for (int m = 4; m <= 32; m <<= 1) Lsum += __shfl_xor(Lsum, m, 64);
-    if (e < NE) s_w[e][hh] = wgt;
-    if (e == 0) {
+    for (int m = H; m <= 32; m <<= 1) M = fmaxf(M, __shfl_xor(M, m, 64));
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      const int e = lane / H + EP * i;
+      const float wgt = me[i] == -INFINITY ? 0.f : exp2f(me[i] - M);
+      Lsum = __builtin_fmaf(le[i], wgt, Lsum);
+      if (e < W) s_w[e][hh] = wgt;
+    }
+    for (int m = H; m <= 32; m <<= 1) Lsum += __shfl_xor(Lsum, m, 64);
+    if (lane < H) {
       s_ml[0][hh] = M;
       s_ml[1][hh] = Lsum;
     }
   }
-  for (int i = tid; i < G * TKV_D; i += C::kThreads) {
-    const int hh = i / TKV_D, c = i % TKV_D;
-    float O = 0.f;
+  static_assert(C::kThreads >= H * TKV_D / 2, "two channels per thread");
+  if (tid < G * TKV_D / 2) {
+    const int hh = tid / (TKV_D / 2), c = 2 * (tid % (TKV_D / 2));
+    float2_t O = {0.f, 0.f};
 #pragma unroll
-    for (int w = 0; w < W; ++w) O = __builtin_fmaf(merge_of(w).o[hh][c], s_w[w][hh], O);
+    for (int w = 0; w < W; ++w) O += *reinterpret_cast<const float2_t*>(&merge_of(w).o[hh][c]) * s_w[w][hh];
     if (n_chunks == 1) {  // nothing to merge with
       const float Lsum = s_ml[1][hh];
-      p.out[((size_t)b * p.hq + (size_t)qh0 + hh) * TKV_D + c] = __float2half_rn(Lsum > 0.f ? O / Lsum : 0.f);
-      continue;
-    }
-    float* dst = p.parts + (((size_t)chunk_base * p.hq + ((size_t)qh0 + hh) * n_chunks) + chunk) * TKV_PART_STRIDE;
-    // device-scope stores: visible to the merging workgroup without a cache write-back
-    __hip_atomic_store(dst + TKV_PART_O + c, O, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (c == 0) {
-      __hip_atomic_store(dst, s_ml[0][hh], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(dst + 1, s_ml[1][hh], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const float inv0 = Lsum > 0.f ? O[0] / Lsum : 0.f, inv1 = Lsum > 0.f ? O[1] / Lsum : 0.f;
+      *reinterpret_cast<uint32_t*>(p.out + ((size_t)b * p.hq + (size_t)qh0 + hh) * TKV_D + c) = pack2((_Float16)inv0, (_Float16)inv1);
+    } else {
+      float* dst = p.parts + (((size_t)chunk_base * p.hq + ((size_t)qh0 + hh) * n_chunks) + chunk) * TKV_PART_STRIDE;
+      // device-scope stores: visible to the merging workgroup without a cache write-back
+      auto store2 = [](float* at, float2_t v) {
+        __hip_atomic_store(reinterpret_cast<uint64_t*>(at), __builtin_bit_cast(uint64_t, v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      };
+      store2(dst + TKV_PART_O + c, O);
+      if (c == 0) store2(dst, float2_t{s_ml[0][hh], s_ml[1][hh]});
     }
   }
 
@@ -901,7 +980,7 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
     if (tid == 0) *arrival = 0u;
     const float* head0 = p.parts + ((size_t)chunk_base * p.hq + (size_t)qh0 * n_chunks) * TKV_PART_STRIDE;
     float* scratch = reinterpret_cast<float*>(smem + C::oRing);  // the waves' results have been consumed
-    tkv::merge_chunks(head0, G, n_chunks, p.out + ((size_t)b * p.hq + (size_t)qh0) * TKV_D, scratch, tid, C::kThreads);
+    tkv::merge_chunks<H == 4 ? 4 : W == 12 ? 3 : 2, H == 4 ? 16 : W == 12 ? 22 : 32>(head0, G, n_chunks, p.out + ((size_t)b * p.hq + (size_t)qh0) * TKV_D, scratch, tid, C::kThreads);
   }
   TKV_PH();  // 7 end
 #ifdef TKV_PHASE
@@ -912,15 +991,20 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
 #endif
 }
 
-template <int BITS, int GS, int W>
-int32_t launch_variant(const MfmaParams& p, dim3 grid, hipStream_t s) {
-  using C = Cfg<BITS, GS, W>;
+template <int BITS, int GS, int W, int H, bool HILO>
+int32_t launch_heads(const MfmaParams& p, dim3 grid, hipStream_t s) {
+  using C = Cfg<BITS, GS, W, H>;
   // more than 64 KiB of dynamic LDS needs an opt-in, once per kernel
-  static const bool lds_ok = hipFuncSetAttribute(reinterpret_cast<const void*>(&quant_attn_mfma_kernel<BITS, GS, W>),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, C::kLdsBytes) == hipSuccess;
+  static const bool lds_ok =
+      hipFuncSetAttribute(reinterpret_cast<const void*>(&quant_attn_mfma_kernel<BITS, GS, W, H, HILO>),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, C::kLdsBytes) == hipSuccess;
   if (!lds_ok) return TKV_E_HIP;
-  TKV_LAUNCH((quant_attn_mfma_kernel<BITS, GS, W>), grid, C::kThreads, C::kLdsBytes, s, p);
+  TKV_LAUNCH((quant_attn_mfma_kernel<BITS, GS, W, H, HILO>), grid, C::kThreads, C::kLdsBytes, s, p);
   return TKV_OK;
+}
+template <int BITS, int GS, int W, bool HILO>
+int32_t launch_variant(const MfmaParams& p, dim3 grid, hipStream_t s) {
+  return p.hq / p.hkv <= 4 ? launch_heads<BITS, GS, W, 4, HILO>(p, grid, s) : launch_heads<BITS, GS, W, 8, HILO>(p, grid, s);
 }
 
 }  // namespace
@@ -938,9 +1022,7 @@ int32_t launch_quant_attn_mfma(const tkv_quant_desc* d, const tkv_quant_cache* c
                                int max_groups, int max_tail, const TkvSeqLens& lens, const QuantNewTokens* fresh,
                                hipStream_t s) {
   if (d->head_dim != TKV_D) return TKV_E_UNSUPPORTED;
-  // built: the benchmark's settings (2 and 4 bit, groups of 32) and the paper's (1 and 2 bit, groups of 64)
   const int variant = d->bits * 100 + d->group_size;
-  if (variant != 232 && variant != 432 && variant != 164 && variant != 264) return TKV_E_UNSUPPORTED;
   const int waves = d->bits == 4 ? 8 : 12;
   auto most_chunks = [waves](int blocks) { return blocks <= kOneChunkRounds * waves ? 1 : (blocks + waves - 1) / waves; };
   // Chunks per KV head over the whole batch: about target_blocks workgroups in all, shared out
@@ -952,8 +1034,8 @@ int32_t launch_quant_attn_mfma(const tkv_quant_desc* d, const tkv_quant_cache* c
   (void)max_groups;
   (void)max_tail;
   MfmaParams p;
-  const int split = (d->n_q_heads / d->n_kv_heads + 3) / 4;  // workgroups per KV head and chunk: 4 query heads each
-  const int heads = d->n_kv_heads * split;
+  const int heads = d->n_kv_heads;
+  const int kMaxGpc = max_gpc(d->n_q_heads / heads);
   int per_head = (target_blocks + heads - 1) / heads;
   if (per_head < d->batch) per_head = d->batch;
   const int chunk_cap = target_blocks > 64 * d->batch * heads ? TKV_MAX_CHUNKS : 64;
@@ -1034,10 +1116,12 @@ int32_t launch_quant_attn_mfma(const tkv_quant_desc* d, const tkv_quant_cache* c
   }
   const dim3 grid(total_chunks, heads, 1);
   switch (variant) {
-    case 232: return launch_variant<2, 1, 12>(p, grid, s);
-    case 432: return launch_variant<4, 1, 8>(p, grid, s);
-    case 164: return launch_variant<1, 2, 12>(p, grid, s);
-    case 264: return launch_variant<2, 2, 12>(p, grid, s);
+    case 232: return launch_variant<2, 1, 12, false>(p, grid, s);
+    case 432: return launch_variant<4, 1, 8, false>(p, grid, s);
+    case 164: return launch_variant<1, 2, 12, false>(p, grid, s);
+    case 264: return launch_variant<2, 2, 12, false>(p, grid, s);
+    case 132: return launch_variant<1, 1, 12, true>(p, grid, s);
+    case 464: return launch_variant<4, 2, 8, true>(p, grid, s);
   }
   return TKV_E_UNSUPPORTED;
 }

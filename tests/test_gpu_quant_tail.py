@@ -25,13 +25,20 @@ TOL_TAIL = 2.0 ** -11 + 1e-4
     (2, 32, 128, 159, 8, (3, 1)),       # nothing quantized, last piece one short of full
     (4, 32, 992, 1023, 3, (32, 8)),     # 32 pieces: four per wave of 8
     (1, 64, 960, 1023, 1, (8, 8)),      # one query head per KV head, three pieces per wave of 12
-    (2, 64, 128, 191, 5, (64, 8)),      # two workgroups per KV head read (and write) the same tail
+    (2, 64, 128, 191, 5, (64, 8)),      # 8 query heads
+    (2, 32, 992, 1020, 5, (40, 8)),     # 5 query heads, three pieces per wave of 12
     (2, 32, 128, 800, 1, (32, 8)),      # 21 blocks and 4 pieces: near the longest that one workgroup sweeps
     (2, 32, 128, 928, 1, (32, 8)),      # past it: several, merged
     (4, 32, 128, 512, 1, (32, 8)),      # the same line for workgroups of 8 waves
     (4, 32, 128, 544, 2, (32, 8)),
     (2, 32, 256, 5000, 1, (10, 2)),     # nine pieces behind many blocks, ring wrapped
     (1, 64, 128, 3010, 7, (28, 4)),
+    (2, 32, 128, 9000, 1, (64, 8)),     # 8 heads: two sets of weights; many chunks, merged 8 heads at a time
+    (4, 32, 128, 2500, 1, (32, 4)),
+    (1, 32, 64, 2222, 1, (32, 4)),      # hi + lo weights, two sets
+    (4, 64, 128, 2500, 3, (32, 4)),     # hi + lo weights
+    (4, 64, 64, 4000, 1, (32, 32)),
+    (1, 32, 96, 4000, 1, (32, 8)),
 ])
 def test_tail(bits, g, residual, n, n_new, heads):
     print(f"case tail bits={bits} g={g} W={residual} n={n} new={n_new} heads={heads}", flush=True)
