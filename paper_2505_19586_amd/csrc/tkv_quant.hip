@@ -35,16 +35,18 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // different float32 numbers d and s h are at least 2^-24 apart relatively, which is more than half
 // an ulp of the quotient at every h, so RN32(d / s) lies on the same side of h as d of s h and
 // equals h exactly when d = s h: rint then goes to the even neighbour.  The clamp is the number of
-// decision points there are.  s = 0: they all lie at infinity, code 0.
+// decision points there are.  Where s is 0 or not finite every comparison is with NaN: code 0, which is
+// what the division gives as well (0 or NaN, and the clamp takes NaN to 0); x = NaN has code 0 likewise.
 template <int BITS>
 struct CodeRule {
   float z, s, inv;
   float t1, t2, t3;
   __device__ CodeRule(_Float16 scale, _Float16 zero) {
     z = (float)zero;
-    s = scale == (_Float16)0.f ? INFINITY : (float)scale;
+    const bool usable = scale > (_Float16)0.f && scale < (_Float16)INFINITY;
+    s = usable ? (float)scale : NAN;
     if (BITS == 4) {
-      inv = scale == (_Float16)0.f ? 0.f : __builtin_amdgcn_rcpf(s);
+      inv = usable ? __builtin_amdgcn_rcpf(s) : 0.f;
       t1 = 0.5f * s;
     } else {
       t1 = 0.5f * s, t2 = 1.5f * s, t3 = 2.5f * s;
@@ -58,23 +60,24 @@ struct CodeRule {
     // than the quarter that it is shifted by), then the one decision point above it; a tie goes up
     // from an odd c0
     const float magic = 12582912.0f;  // 1.5 x 2^23: the sum holds the rounded integer in its low bits
-    const float m = __builtin_fminf(__builtin_fmaf(d, inv, -0.25f), 14.0f) + magic;
+    const float m = __builtin_amdgcn_fmed3f(__builtin_fmaf(d, inv, -0.25f), -0.25f, 14.0f) + magic;  // NaN: the lower end
     const float c0 = m - magic;
-    const float T = __builtin_fmaf(s, c0, t1);  // exact; NaN for s = 0: never passed
+    const float T = __builtin_fmaf(s, c0, t1);  // exact; unordered with d where either is NaN: never passed
     const uint32_t mb = __builtin_bit_cast(uint32_t, m);
     const uint32_t db = __builtin_bit_cast(uint32_t, d) + (mb & 1u);  // d >= 0, T > 0: ordered like integers
-    return (mb & 15u) + (T == T && db > __builtin_bit_cast(uint32_t, T) ? 1u : 0u);
+    return (mb & 15u) + (!__builtin_isunordered(d, T) && db > __builtin_bit_cast(uint32_t, T) ? 1u : 0u);
   }
 };
 
 // x / (2^b - 1) correctly rounded: Markstein's correction of x RN(1/q) (q = 3 and 15 checked for every
-// mantissa; x is a difference of fp16 numbers, far from both ends of the exponent range).
+// mantissa; x is a difference of fp16 numbers, far from both ends of the exponent range, or not finite
+// and then left alone).
 template <int BITS>
 __device__ inline float over_qmax(float x) {
   if (BITS == 1) return x;
   constexpr float q = (float)((1 << BITS) - 1), y = 1.0f / q;
   const float a = x * y;
-  return __builtin_fmaf(__builtin_fmaf(-q, a, x), y, a);
+  return a < INFINITY ? __builtin_fmaf(__builtin_fmaf(-q, a, x), y, a) : a;
 }
 
 // packed fp16 minimum / maximum (as the instruction has them: the library functions quiet NaNs first)

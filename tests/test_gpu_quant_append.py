@@ -7,6 +7,7 @@ import pytest
 import torch
 
 import paper_2505_19586_amd as tkv
+from oracle import quant
 from synth import HeadShape, make_layer
 
 from gpu_util import check_quant_cache, to_new, to_new_batch
@@ -48,6 +49,33 @@ def test_decision_points_flat_and_tiny_groups(bits, g):
     v = (rng.integers(0, 12, (hkv, n, 128)) * 2.0 ** -24).astype(np.float16)
     k[0, :64] = np.float16(1.25)
     v[1, 64:128] = np.float16(-3)
+    layer = tkv.QuantLayer(n_q_heads=4, n_kv_heads=hkv, bits=bits, group_size=g, capacity=n)
+    layer.append(to_new(k), to_new(v))
+    check_quant_cache(layer, 0, k, v)
+
+
+def _eq4_with_specials(x, bits):
+    """The oracle's steps where infinities and NaN occur: minimum and maximum pass NaN by, the clamp takes NaN to 0."""
+    qmax = np.float32((1 << bits) - 1)
+    with np.errstate(all="ignore"):
+        mn, mx = np.fmin.reduce(x, axis=-1), np.fmax.reduce(x, axis=-1)
+        s = ((mx.astype(np.float32) - mn.astype(np.float32)) / qmax).astype(np.float16)
+        t = (x.astype(np.float32) - mn.astype(np.float32)[..., None]) / s.astype(np.float32)[..., None]
+        code = np.fmin(np.fmax(np.rint(t), np.float32(0)), qmax)
+    return np.where(s[..., None] == 0, 0, code).astype(np.uint8), s, mn
+
+
+@pytest.mark.parametrize("bits,g", SETTINGS)
+def test_infinities_and_nan(monkeypatch, bits, g):
+    """Groups that hold infinities, NaN beside numbers, and ranges whose 1-bit scaler overflows fp16."""
+    print(f"case specials bits={bits} g={g}", flush=True)
+    monkeypatch.setattr(quant, "quantize_lastaxis", _eq4_with_specials)
+    rng = np.random.default_rng([bits, g, 7])
+    n, hkv = 512, 2
+    k, v = (rng.standard_normal((hkv, n, 128)).astype(np.float16) for _ in range(2))
+    for x in (k, v):
+        for special in (np.inf, -np.inf, np.nan, 60000.0, -60000.0):
+            x[rng.random(x.shape) < 0.004] = special
     layer = tkv.QuantLayer(n_q_heads=4, n_kv_heads=hkv, bits=bits, group_size=g, capacity=n)
     layer.append(to_new(k), to_new(v))
     check_quant_cache(layer, 0, k, v)
