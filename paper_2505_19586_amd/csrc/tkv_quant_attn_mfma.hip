@@ -63,11 +63,13 @@ struct MfmaParams {
   const __half* v_resid;
   const __half* q;
   float* parts;        // sequence after sequence: [Hq][chunks of the sequence][D + 4]
-  uint32_t* arrivals;  // [B][Hkv], zero between calls
+  uint32_t* arrivals;  // [B][Hkv << split], zero between calls
   __half* out;         // [B][Hq][D]
   float scale2;
   int32_t hq, hkv, residual, capacity;
   int32_t batch;
+  int32_t tail_blocks; // blocks that a 32-token piece of the fp16 tail counts as in the split
+  int32_t split;       // 0: one workgroup takes all query heads of a KV head; 1: two, of up to 4 (blockIdx.y = 2 h + part)
 #ifdef TKV_PHASE
   long long* prof;  // phase time stamps (profiling builds only)
 #endif
@@ -175,7 +177,9 @@ constexpr int kHeadroomLog2 = 4;  // lazy rescale: weights may reach 2^kHeadroom
 constexpr int kRefBelowMax = 3;   // a rescale puts the reference this far under the largest logit (< headroom)
 constexpr int kBkStride = 68;     // words per head row of the query-side operand in LDS (16 rows x 4 words: all 64 banks)
 constexpr int max_gpc(int heads) { return heads <= 4 ? 512 : 256; }  // groups per chunk that the zero-point table holds
-constexpr int kTailBlocks = 3;    // blocks that a 32-token piece of the fp16 tail counts as in the split (2 to 5: no difference)
+// Blocks that a 32-token piece of the fp16 tail counts as in the split (2 bit, 2000 tokens: 12.6 us per
+// call with 3, 13.1 with 2; from 16384 tokens on 2 to 5 make no difference).
+constexpr int kTailBlocks = 3, kTailBlocksLeast = 2;
 // Sequences of up to this many blocks (tail pieces counted as above) per wave are one workgroup's:
 // no partials to write, no arrival, no merge.  2 bit, 8 KV heads, batch 1: 600 tokens (29 blocks)
 // 12.6 us in one workgroup, 13.7 in two; 1000 tokens (42 blocks) 14.1 against 12.9.
@@ -435,21 +439,23 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
     ++b;
   }
   const int n_chunks = p.chunks.n[b];
-  const int h = blockIdx.y;
+  const int part = (int)blockIdx.y & p.split;  // which four query heads of the group (only ever 1 where split is)
+  const int h = (int)blockIdx.y >> p.split;
   const int tid = threadIdx.x, lane = tid % 64;
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64);  // wave-uniform: keeps group addresses scalar
-  const int G = p.hq / p.hkv;  // at most H
-  const int qh0 = h * G;       // first query head of this workgroup
+  const int group = p.hq / p.hkv;
+  const int G = p.split == 0 ? group : part == 0 ? 4 : group - 4;  // query heads of this workgroup, at most H
+  const int qh0 = h * group + 4 * part;                            // the first of them
   const int n = p.lens.n[b];
   const int nq = tkv::n_quantized(n, p.residual, GRP);
   const int jq = nq / TKV_BLK;
   const size_t bh = (size_t)b * p.hkv + h;
   const size_t grp_base = bh * (size_t)(p.capacity / TKV_BLK);   // first packed block of this head
   const size_t kgrp_base = bh * (size_t)(p.capacity / GRP);      // first key group
-  // Work split of this sequence: a 32-token piece of the tail counts as kTailBlocks groups and the
+  // Work split of this sequence: a 32-token piece of the tail counts as tail_blocks groups and the
   // tail belongs to the last chunk, which gets correspondingly fewer quantized groups.
   const bool has_tail = chunk == n_chunks - 1;
-  const int tail_equiv = kTailBlocks * ((n - nq + 31) / 32);
+  const int tail_equiv = p.tail_blocks * ((n - nq + 31) / 32);
   const uint32_t work = (uint32_t)(jq + tail_equiv);
   const int blk0 = min((int)(work * (uint32_t)chunk / (uint32_t)n_chunks), jq);
   const int blk1 = has_tail ? jq : min((int)(work * (uint32_t)(chunk + 1) / (uint32_t)n_chunks), jq);
@@ -1004,7 +1010,7 @@ int32_t launch_heads(const MfmaParams& p, dim3 grid, hipStream_t s) {
 }
 template <int BITS, int GS, int W, bool HILO>
 int32_t launch_variant(const MfmaParams& p, dim3 grid, hipStream_t s) {
-  return p.hq / p.hkv <= 4 ? launch_heads<BITS, GS, W, 4, HILO>(p, grid, s) : launch_heads<BITS, GS, W, 8, HILO>(p, grid, s);
+  return p.hq / p.hkv <= 4 || p.split != 0 ? launch_heads<BITS, GS, W, 4, HILO>(p, grid, s) : launch_heads<BITS, GS, W, 8, HILO>(p, grid, s);
 }
 
 }  // namespace
@@ -1027,64 +1033,78 @@ int32_t launch_quant_attn_mfma(const tkv_quant_desc* d, const tkv_quant_cache* c
   auto most_chunks = [waves](int blocks) { return blocks <= kOneChunkRounds * waves ? 1 : (blocks + waves - 1) / waves; };
   // Chunks per KV head over the whole batch: about target_blocks workgroups in all, shared out
   // among the sequences in proportion to their work (32-token blocks, a 32-token piece of the
-  // fp16 tail counting as two), so that every workgroup sweeps about the same number of blocks
+  // fp16 tail counting as kTailBlocks), so that every workgroup sweeps about the same number of blocks
   // whatever the mix of lengths.  Per sequence: at least one block per wave, at most 64 chunks
   // (unless the tuning hook asks for more workgroups than that gives), no more blocks per chunk
   // than the zero-point table of a workgroup holds.
   (void)max_groups;
   (void)max_tail;
   MfmaParams p;
-  const int heads = d->n_kv_heads;
-  const int kMaxGpc = max_gpc(d->n_q_heads / heads);
-  int per_head = (target_blocks + heads - 1) / heads;
-  if (per_head < d->batch) per_head = d->batch;
-  const int chunk_cap = target_blocks > 64 * d->batch * heads ? TKV_MAX_CHUNKS : 64;
-  long long total_work = 0;
-  int work[TKV_MAX_BATCH];
-  for (int b = 0; b < d->batch; ++b) {
-    const int n = lens.n[b];
-    const int g = tkv::n_quantized(n, d->residual, d->group_size) / TKV_BLK;
-    work[b] = g + kTailBlocks * ((n - g * TKV_BLK + 31) / 32);
-    total_work += work[b];
-  }
-  int total_chunks = 0;
-  for (int b = 0; b < d->batch; ++b) {
-    int nc = total_work > 0 ? (int)(((long long)per_head * work[b] + total_work / 2) / total_work) : 1;
-    const int c_work = most_chunks(work[b]);
-    if (nc > c_work) nc = c_work;
-    if (nc > chunk_cap) nc = chunk_cap;
-    if (nc < 1) nc = 1;
-    if ((work[b] + nc - 1) / nc > kMaxGpc) nc = (work[b] + kMaxGpc - 1) / kMaxGpc;
-    if (nc > TKV_MAX_CHUNKS) return TKV_E_UNSUPPORTED;
-    p.chunks.n[b] = nc;
-    total_chunks += nc;
-  }
-  // Rounding may leave a few chunks too many (a second round of workgroups for a handful of
-  // them) or too few (idle compute units): take them from the sequences whose chunks are the
-  // lightest, give them to those whose chunks are the heaviest.
-  while (total_chunks > per_head) {
-    int pick = -1;
+  int heads = 0, total_chunks = 0;
+  auto plan = [&](int split, int tail_blocks) -> int32_t {
+    const int kMaxGpc = max_gpc(split ? 4 : d->n_q_heads / d->n_kv_heads);
+    p.split = split;
+    p.tail_blocks = tail_blocks;
+    heads = d->n_kv_heads << split;
+    int per_head = (target_blocks + heads - 1) / heads;
+    if (per_head < d->batch) per_head = d->batch;
+    const int chunk_cap = target_blocks > 64 * d->batch * heads ? TKV_MAX_CHUNKS : 64;
+    long long total_work = 0;
+    int work[TKV_MAX_BATCH];
     for (int b = 0; b < d->batch; ++b) {
-      const int nc = p.chunks.n[b];
-      if (nc <= 1 || (work[b] + nc - 2) / (nc - 1) > kMaxGpc) continue;
-      if (pick < 0 || (long long)work[b] * (p.chunks.n[pick] - 1) < (long long)work[pick] * (nc - 1)) pick = b;
+      const int n = lens.n[b];
+      const int g = tkv::n_quantized(n, d->residual, d->group_size) / TKV_BLK;
+      work[b] = g + tail_blocks * ((n - g * TKV_BLK + 31) / 32);
+      total_work += work[b];
     }
-    if (pick < 0) break;
-    --p.chunks.n[pick];
-    --total_chunks;
-  }
-  while (total_chunks < per_head) {
-    int pick = -1;
+    total_chunks = 0;
     for (int b = 0; b < d->batch; ++b) {
-      const int nc = p.chunks.n[b];
-      if (nc >= chunk_cap || nc >= most_chunks(work[b])) continue;
-      if (pick < 0 || (long long)work[b] * p.chunks.n[pick] > (long long)work[pick] * nc) pick = b;
+      int nc = total_work > 0 ? (int)(((long long)per_head * work[b] + total_work / 2) / total_work) : 1;
+      const int c_work = most_chunks(work[b]);
+      if (nc > c_work) nc = c_work;
+      if (nc > chunk_cap) nc = chunk_cap;
+      if (nc < 1) nc = 1;
+      if ((work[b] + nc - 1) / nc > kMaxGpc) nc = (work[b] + kMaxGpc - 1) / kMaxGpc;
+      if (nc > TKV_MAX_CHUNKS) return TKV_E_UNSUPPORTED;
+      p.chunks.n[b] = nc;
+      total_chunks += nc;
     }
-    if (pick < 0) break;
-    ++p.chunks.n[pick];
-    ++total_chunks;
-  }
-  if ((size_t)total_chunks * d->n_q_heads * TKV_PART_STRIDE > parts_floats) return TKV_E_WORKSPACE;
+    // Rounding may leave a few chunks too many (a second round of workgroups for a handful of
+    // them) or too few (idle compute units): take them from the sequences whose chunks are the
+    // lightest, give them to those whose chunks are the heaviest.
+    while (total_chunks > per_head) {
+      int pick = -1;
+      for (int b = 0; b < d->batch; ++b) {
+        const int nc = p.chunks.n[b];
+        if (nc <= 1 || (work[b] + nc - 2) / (nc - 1) > kMaxGpc) continue;
+        if (pick < 0 || (long long)work[b] * (p.chunks.n[pick] - 1) < (long long)work[pick] * (nc - 1)) pick = b;
+      }
+      if (pick < 0) break;
+      --p.chunks.n[pick];
+      --total_chunks;
+    }
+    while (total_chunks < per_head) {
+      int pick = -1;
+      for (int b = 0; b < d->batch; ++b) {
+        const int nc = p.chunks.n[b];
+        if (nc >= chunk_cap || nc >= most_chunks(work[b])) continue;
+        if (pick < 0 || (long long)work[b] * p.chunks.n[pick] > (long long)work[pick] * nc) pick = b;
+      }
+      if (pick < 0) break;
+      ++p.chunks.n[pick];
+      ++total_chunks;
+    }
+    if ((size_t)total_chunks * d->n_q_heads * TKV_PART_STRIDE > parts_floats) return TKV_E_WORKSPACE;
+    return TKV_OK;
+  };
+  // What else there is where that makes more chunks than may be or than the partials' room takes: a
+  // smaller allowance for the tail; and for groups of 5 to 8 query heads, whose one workgroup has a
+  // zero-point table of half as many blocks, two workgroups of up to 4 heads that each read the codes
+  // (half the chunks; slower by the second reading, see the top of the file).
+  int32_t st = plan(0, kTailBlocks);
+  if (st != TKV_OK) st = plan(0, kTailBlocksLeast);
+  if (st != TKV_OK && d->n_q_heads / d->n_kv_heads > 4) st = plan(1, kTailBlocksLeast);
+  if (st != TKV_OK) return st;
   p.k_codes = (const uint32_t*)c->k_codes;
   p.v_codes = (const uint32_t*)c->v_codes;
   p.k_scale = (const __half*)c->k_scale;
