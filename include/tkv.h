@@ -149,6 +149,8 @@ int32_t tkv_quantize_append_ragged(const tkv_quant_desc* desc, tkv_quant_cache* 
  * logits = sm_scale * q . (code*s + z) over the quantized tokens and sm_scale * q . k
  * over the fp16 tail, one softmax over all N tokens, out = weights . V-hat.
  * q, out: fp16 [B][Hq][128].  A sequence with 0 tokens yields zeros.
+ * 4 bits with groups of 64 and 1 bit with groups of 32 are evaluated in float32 throughout: the
+ * same bits on every call, any fp16 input.  For the other settings:
  * Input range: the matrix-core kernel feeds fp16 products to the matrix cores: softmax
  * weight x value scaler, and query element x key scaler.  Cached values of magnitude up
  * to about 1000 and query-times-key-scaler products up to 65504 are safe at every bit
@@ -197,7 +199,7 @@ int32_t tkv_quant_decode(const tkv_quant_desc* desc, tkv_quant_cache* cache, con
  * Limits: batch * n_kv_heads (twice that for groups of more than 4 query heads) <=
  * TKV_STATIC_MAX_HEADS and the launch's partials
  * (batch * n_q_heads * chunks * 528 bytes; chunks is about compute units / (batch * n_kv_heads),
- * at most 64) must fit in TKV_STATIC_PARTS_BYTES, else TKV_E_WORKSPACE and nothing is enqueued.
+ * at most 64; for 4 bits with groups of 64 and 1 bit with groups of 32 at least 2) must fit in TKV_STATIC_PARTS_BYTES, else TKV_E_WORKSPACE and nothing is enqueued.
  * Batch 1 to 64 with 32 query heads fits at every context length.
  * The device that owns `stream` and the buffers must be the calling thread's current device.
  * All calls on one GPU share that GPU's array: calls that overlap in time on one GPU (different

@@ -12,8 +12,9 @@ extern "C" {
 #endif
 
 /* Test and tuning hook (process-wide; the two settings are atomics, a call that runs
- * concurrently with the change may see either value): kernel_choice 0 = matrix-core
- * kernel, which also covers the fp16 tail (default), 1 = shape-generic
+ * concurrently with the change may see either value): kernel_choice 0 = the setting's
+ * own kernel (default): the matrix-core kernel, which also covers the fp16 tail, or for 4 bits
+ * with groups of 64 and 1 bit with groups of 32 the float32 kernel; 1 = shape-generic
  * reference kernel for everything.  By default the split-K launch aims at one workgroup per
  * compute unit that the stream may use (all of them, or those of its compute-unit mask);
  * target_blocks > 0 fixes the number of workgroups instead, -1 returns to the default, 0

@@ -17,7 +17,7 @@ int32_t launch_quant_attn_mfma(const tkv_quant_desc* d, const tkv_quant_cache* c
 
 namespace {
 
-std::atomic<int> g_kernel_choice{0};      // 0: matrix-core kernel (+ reference kernel for the tail), 1: reference kernel only
+std::atomic<int> g_kernel_choice{0};      // 0: the setting's own kernel, 1: shape-generic reference kernel
 std::atomic<int> g_target_blocks{0};      // workgroups the split-K launch aims at; 0 = one per compute unit of the stream
 
 struct QuantAttnParams {
@@ -45,8 +45,8 @@ __device__ inline float wave_half_max(float v) {
 }
 
 // Shape-generic reference kernel: plain float32 arithmetic, one wave per 32-token
-// block, no matrix cores.  Correct for every supported descriptor; the tuned
-// kernel takes over where it applies.
+// block, no matrix cores.  Correct for every supported descriptor and any alignment of the query;
+// serves calls only on request and where quant_attn_f32_kernel's 32-bit query loads do not fit.
 __global__ __launch_bounds__(256) void quant_attn_generic_kernel(QuantAttnParams p) {
   __shared__ float qs[4][TKV_D];            // query heads of this KV head, zero padded
   __shared__ float ksz[4][TKV_D][2];        // per wave: K scale, zero of the current group
@@ -229,6 +229,384 @@ __global__ __launch_bounds__(256) void quant_attn_generic_kernel(QuantAttnParams
   }
 }
 
+// ---- quant_attn_f32_kernel -----------------------------------------------------------------
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
+
+__device__ inline half2_t as_half2(uint32_t w) { return __builtin_bit_cast(half2_t, w); }
+
+// The eight codes of a field octet: field f = i / 2 + 4 (i % 2) (4 bits: nibbles of one word) or
+// i / 2 + 16 (i % 2) + base (1 bit).
+template <int BITS>
+__device__ inline void codes_of(uint32_t w, int base, float (&code)[8]) {
+  if (BITS == 4) {
+    uint32_t even = w & 0x0F0F0F0Fu, odd = (w >> 4) & 0x0F0F0F0Fu;  // nibble f is byte f / 2 of one of them
+    asm("" : "+v"(even), "+v"(odd));  // (else every nibble gets an extraction of its own)
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int f = i / 2 + 4 * (i % 2);
+      code[i] = (float)(((f % 2 ? odd : even) >> (8 * (f / 2))) & 0xFFu);
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) code[i] = (float)((w >> (base + i / 2 + 16 * (i % 2))) & 1u);
+  }
+}
+
+// Float32 kernel of the settings (4 bits, groups of 64) and (1 bit, groups of 32): every logit, weight
+// and partial sum is the float32 number that quant_attn_generic_kernel computes, operation for
+// operation (one fused multiply-add per element of q.K-hat in channel order, per element of p.V-hat in
+// token order; 32-token blocks dealt to four accumulation streams per chunk, merged in the same order),
+// so the results are the same bits on every call and the same as that kernel's.  What differs is who
+// does the work.  The generic kernel gives each stream a wave whose halves hold two heads each, reads
+// every code from memory where it is used and every operand from LDS.  Here a wave takes two streams,
+// one per half, and a lane one token for all H heads (logits) or four channels of all heads (values): no
+// lane works for a head that does not exist, packed words and scalers of the next block are
+// loaded into registers while this one is worked on, codes unpack eight at a time, query elements are
+// scalar operands.  Bound by vector instructions: 2.4 + H per element and contraction.
+//
+// 4 bits, 32 / 32 heads, 20479 + 16857 tokens: 66 us per call, 542 on the generic kernel; 32 / 8 heads, 65500
+// tokens: 61 and 256; 1 bit, 57 and 252.  The matrix cores serve the same in 45, 26 and 25 us, but
+// their operands are fp16: scalers above 1024 overflow, weights below 2^-14 lose bits, and the order of
+// the blocks is decided at run time.
+template <int BITS, int GRP, int H>
+__global__ __launch_bounds__(128) void quant_attn_f32_kernel(QuantAttnParams p) {
+#pragma clang fp contract(off)
+  constexpr int NU = TKV_D / GRP;        // channel groups of a value row
+  constexpr int NWORDS = TKV_D * BITS;   // words of a packed block
+  constexpr int BPG = GRP / TKV_BLK;     // blocks per key group
+  // With 4 heads the loads of all pieces, hoisted above one another, would not fit the registers: they
+  // are kept piece by piece.  With fewer heads that only costs (16 / 8 heads, 4 x 30000 tokens: 66 us with
+  // the pieces kept apart, 56 without).
+  constexpr bool kApart = H == 4;
+  constexpr int KW = BITS == 4 ? 4 : 1;  // words per lane and 8-channel (8-token) class
+  __shared__ __attribute__((aligned(16))) uint32_t ksz[2][2][TKV_D];            // per wave, half: key (scaler, zero) pairs
+  __shared__ __attribute__((aligned(16))) uint32_t vsz[2][2][NU * TKV_BLK];     // per wave, half: value (scaler, zero) pairs
+  __shared__ __attribute__((aligned(16))) float pws[2][2][H][TKV_BLK];          // per wave, half: weights
+  __shared__ float red_m[4][H], red_l[4][H];
+  __shared__ float red_o[4][H][TKV_D];
+
+  const int group = p.hq / p.hkv, split = (group + 3) / 4;
+  const int b = blockIdx.z, h = blockIdx.y / split, chunk = blockIdx.x;
+  const int tid = threadIdx.x, lane = tid % 64;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
+  const int half = lane / 32, t = lane % 32;          // stream of this wave, token of its block
+  const int vh = t / 16, l16 = t % 16;                // values: channels 64 vh + 16 j + l16
+  const int stream = 2 * wave + half;
+  const int qh0 = h * group + 4 * (blockIdx.y % split);
+  const int G = min(4, (h + 1) * group - qh0);        // at most H
+  const int n = p.lens.n[b];
+  const int nq = tkv::n_quantized(n, p.residual, GRP);
+  const int jq = nq / TKV_BLK;
+  const size_t bh = (size_t)b * p.hkv + h;
+  const int ring = p.residual + GRP;
+  const bool tail = chunk == p.n_chunks;
+  const int blk0 = tail ? 0 : chunk * p.groups_per_chunk;
+  const int blk1 = tail ? (n - nq + TKV_BLK - 1) / TKV_BLK : min(blk0 + p.groups_per_chunk, jq);
+
+  // query rows through the constant address space: uniform loads, scalar operands
+  typedef const __attribute__((address_space(4))) uint32_t* ScalarWords;
+  uint64_t qrow[H];
+#pragma unroll
+  for (int hh = 0; hh < H; ++hh)  // heads past the group re-read its last one; their results are not used
+    qrow[hh] = (uint64_t)(uintptr_t)(p.q + ((size_t)b * p.hq + (size_t)qh0 + min(hh, G - 1)) * TKV_D);
+  // (the loads stay inside the block loop: kept across it the elements would take 64 H registers)
+  auto pin_query = [&]() {
+#pragma unroll
+    for (int hh = 0; hh < H; ++hh) asm volatile("" : "+s"(qrow[hh]));
+  };
+
+  float m_run[H], l_run[H], o_run[H][4];
+#pragma unroll
+  for (int hh = 0; hh < H; ++hh) {
+    m_run[hh] = -INFINITY, l_run[hh] = 0.f;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) o_run[hh][j] = 0.f;
+  }
+
+  // q . k of one token, eight channels at a time
+  auto dot8 = [&](float (&acc)[H], int c, const float (&kh)[8]) {
+#pragma unroll
+    for (int hh = 0; hh < H; ++hh) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const half2_t q2 = as_half2(((ScalarWords)qrow[hh])[c / 2 + i / 2]);
+        acc[hh] = __builtin_fmaf((float)q2[i % 2], kh[i], acc[hh]);
+      }
+    }
+  };
+  // logits -> weights (in LDS for the half's lanes) and the factor for what is accumulated so far
+  auto soften = [&](const float (&acc)[H], bool valid, bool on, float (&al)[H]) {
+#pragma unroll
+    for (int hh = 0; hh < H; ++hh) {
+      const float x = valid ? acc[hh] * p.scale2 : -INFINITY;
+      const float mn = fmaxf(m_run[hh], wave_half_max(x));
+      pws[wave][half][hh][t] = exp2f(x - mn);
+      al[hh] = exp2f(m_run[hh] - mn);
+      m_run[hh] = on ? mn : m_run[hh];
+    }
+    __builtin_amdgcn_wave_barrier();
+  };
+  // weights of eight tokens, then one token's share of p . V
+  auto weights8 = [&](float (&pp)[H][8], int t0) {
+#pragma unroll
+    for (int hh = 0; hh < H; ++hh) {
+#pragma unroll
+      for (int i = 0; i < 8; i += 4) {
+        const f32x4 w = *reinterpret_cast<const f32x4*>(&pws[wave][half][hh][t0 + i]);
+#pragma unroll
+        for (int y = 0; y < 4; ++y) pp[hh][i + y] = w[y];
+      }
+    }
+  };
+  auto accumulate = [&](bool on, const float (&al)[H], const float (&s)[H][4], const float (&ls)[H]) {
+    // (selects: behind a branch the compiler moves all of p . V there, its operands waiting in registers)
+#pragma unroll
+    for (int hh = 0; hh < H; ++hh) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float o = __builtin_fmaf(o_run[hh][j], al[hh], s[hh][j]);
+        o_run[hh][j] = on ? o : o_run[hh][j];
+      }
+      const float l = __builtin_fmaf(l_run[hh], al[hh], ls[hh]);
+      l_run[hh] = on ? l : l_run[hh];
+    }
+    __builtin_amdgcn_wave_barrier();
+  };
+
+  if (!tail) {
+    const size_t blk_base = bh * (size_t)(p.capacity / TKV_BLK), grp_base = bh * (size_t)(p.capacity / GRP);
+    const int r = 4 * (t / 8) + t % 4, tau = (t % 8) / 4;
+    uint32_t kw[4][KW], vw[4][KW];  // packed words of the block: keys by 8-channel class, values by 8-token class
+    u32x2 ks, kz;
+    uint32_t vs[NU / 2], vz[NU / 2];
+    auto load_k = [&](int blk) {
+      const size_t g = blk_base + blk;
+      const uint32_t* src = p.k_codes + g * NWORDS;
+#pragma unroll
+      for (int kb = 0; kb < 4; ++kb) {
+        if constexpr (BITS == 4) {
+          const u32x4 w = *reinterpret_cast<const u32x4*>(src + 256 * tau + 4 * (r + 16 * kb));
+#pragma unroll
+          for (int y = 0; y < 4; ++y) kw[kb][y] = w[y];
+        } else {
+          kw[kb][0] = src[64 * tau + r + 16 * kb];
+        }
+      }
+      const size_t o = (grp_base + blk / BPG) * TKV_D + 4 * t;
+      ks = *reinterpret_cast<const u32x2*>(p.k_scale + o);
+      kz = *reinterpret_cast<const u32x2*>(p.k_zero + o);
+    };
+    auto load_v = [&](int blk) {
+      const size_t g = blk_base + blk;
+      const uint32_t* src = p.v_codes + g * NWORDS;
+#pragma unroll
+      for (int tb = 0; tb < 4; ++tb) {
+        if constexpr (BITS == 4) {
+          const u32x4 w = *reinterpret_cast<const u32x4*>(src + 256 * vh + 4 * (l16 + 16 * tb));
+#pragma unroll
+          for (int y = 0; y < 4; ++y) vw[tb][y] = w[y];
+        } else {
+          vw[tb][0] = src[64 * vh + l16 + 16 * tb];
+        }
+      }
+      const size_t o = g * (NU * TKV_BLK) + NU * t;
+#pragma unroll
+      for (int i = 0; i < NU / 2; ++i) {
+        vs[i] = *reinterpret_cast<const uint32_t*>(p.v_scale + o + 2 * i);
+        vz[i] = *reinterpret_cast<const uint32_t*>(p.v_zero + o + 2 * i);
+      }
+    };
+    auto pair_lo = [](uint32_t s, uint32_t z) { return (s & 0xFFFFu) | (z << 16); };
+    auto pair_hi = [](uint32_t s, uint32_t z) { return (s >> 16) | (z & 0xFFFF0000u); };
+    const int first = blk0 + 2 * wave;  // first block of this wave's lower half
+    auto mine = [&](int base) { return min(base + half, blk1 - 1); };  // (a half past the end repeats the last block and drops the result)
+    if (first < blk1) {
+      load_k(mine(first));
+      load_v(mine(first));
+    }
+    for (int base = first; base < blk1; base += 4) {
+      pin_query();
+      const bool on = base + half < blk1;
+      const int next = min(base + 4, blk1 - 1);
+      *reinterpret_cast<u32x4*>(&ksz[wave][half][4 * t]) =
+          u32x4{pair_lo(ks[0], kz[0]), pair_hi(ks[0], kz[0]), pair_lo(ks[1], kz[1]), pair_hi(ks[1], kz[1])};
+#pragma unroll
+      for (int i = 0; i < NU / 2; ++i)
+        *reinterpret_cast<u32x2*>(&vsz[wave][half][NU * t + 2 * i]) = u32x2{pair_lo(vs[i], vz[i]), pair_hi(vs[i], vz[i])};
+      __builtin_amdgcn_wave_barrier();
+      float acc[H];
+#pragma unroll
+      for (int hh = 0; hh < H; ++hh) acc[hh] = 0.f;
+#pragma unroll
+      for (int c = 0; c < TKV_D; c += 8) {
+        const int kb = (c / 8) % 4;
+        float kh[8];
+        codes_of<BITS>(kw[kb][BITS == 4 ? c / 32 : 0], 4 * ((c / 32) % 2) + 8 * (c / 64), kh);
+#pragma unroll
+        for (int i = 0; i < 8; i += 4) {
+          const u32x4 sz = *reinterpret_cast<const u32x4*>(&ksz[wave][half][c + i]);
+#pragma unroll
+          for (int y = 0; y < 4; ++y) {
+            const uint32_t szy = sz[y];
+            kh[i + y] = __builtin_fmaf(kh[i + y], (float)as_half2(szy)[0], (float)as_half2(szy)[1]);
+          }
+        }
+        dot8(acc, c, kh);
+        if (c % 32 == 24 && (kApart || c == 120)) __builtin_amdgcn_sched_barrier(0);
+      }
+      load_k(mine(next));
+      float al[H];
+      soften(acc, true, on, al);
+      float s[H][4], ls[H];
+#pragma unroll
+      for (int hh = 0; hh < H; ++hh) {
+        ls[hh] = 0.f;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) s[hh][j] = 0.f;
+      }
+#pragma unroll
+      for (int tb = 0; tb < 4; ++tb) {
+        float pp[H][8];
+        weights8(pp, 8 * tb);
+        uint32_t sz[NU / 2][8];  // (scaler, zero) of the eight tokens in this lane's channel groups
+#pragma unroll
+        for (int y = 0; y < NU / 2; ++y) {
+          const int u = NU == 2 ? vh : 2 * vh + y;
+#pragma unroll
+          for (int i = 0; i < 8; i += 4) {
+            const u32x4 w = *reinterpret_cast<const u32x4*>(&vsz[wave][half][u * TKV_BLK + 8 * tb + i]);
+#pragma unroll
+            for (int x = 0; x < 4; ++x) sz[y][i + x] = w[x];
+          }
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          float v[8];
+          codes_of<BITS>(vw[tb][BITS == 4 ? j : 0], 4 * j, v);
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            const uint32_t szi = sz[NU == 2 ? 0 : j / 2][i];
+            const float vi = __builtin_fmaf(v[i], (float)as_half2(szi)[0], (float)as_half2(szi)[1]);
+#pragma unroll
+            for (int hh = 0; hh < H; ++hh) s[hh][j] = __builtin_fmaf(pp[hh][i], vi, s[hh][j]);
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+#pragma unroll
+          for (int hh = 0; hh < H; ++hh) ls[hh] = ls[hh] + pp[hh][i];
+        }
+        if (kApart || tb == 3) __builtin_amdgcn_sched_barrier(0);
+      }
+      load_v(mine(next));
+      accumulate(on, al, s, ls);
+    }
+  } else {
+    // the fp16 tail: rows from the ring, the lane's four channels side by side (4 t ..) for the values
+    auto row = [&](const __half* rows, int tok) { return rows + (bh * ring + (size_t)(tok % ring)) * TKV_D; };
+    for (int base = 2 * wave; base < blk1; base += 4) {
+      pin_query();
+      const bool on = base + half < blk1;
+      const int tok0 = nq + TKV_BLK * min(base + half, blk1 - 1), tok = tok0 + t;
+      const u32x4* krow = reinterpret_cast<const u32x4*>(row(p.k_resid, min(tok, n - 1)));
+      float acc[H];
+#pragma unroll
+      for (int hh = 0; hh < H; ++hh) acc[hh] = 0.f;
+#pragma unroll
+      for (int c = 0; c < TKV_D; c += 32) {
+        u32x4 w[4];
+#pragma unroll
+        for (int y = 0; y < 4; ++y) w[y] = krow[c / 8 + y];
+#pragma unroll
+        for (int y = 0; y < 4; ++y) {
+          float kh[8];
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            const uint32_t wi = w[y][i / 2];
+            kh[i] = (float)as_half2(wi)[i % 2];
+          }
+          dot8(acc, c + 8 * y, kh);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      float al[H];
+      soften(acc, tok < n, on, al);
+      float s[H][4], ls[H];
+#pragma unroll
+      for (int hh = 0; hh < H; ++hh) {
+        ls[hh] = 0.f;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) s[hh][j] = 0.f;
+      }
+#pragma unroll 1
+      for (int t0 = 0; t0 < TKV_BLK; t0 += 8) {
+        u32x2 w[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+          w[i] = reinterpret_cast<const u32x2*>(row(p.v_resid, min(tok0 + t0 + i, n - 1)))[t];
+        float pp[H][8];
+        weights8(pp, t0);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const bool valid = tok0 + t0 + i < n;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const uint32_t wj = w[i][j / 2];
+            const float v = valid ? (float)as_half2(wj)[j % 2] : 0.f;
+#pragma unroll
+            for (int hh = 0; hh < H; ++hh) s[hh][j] = __builtin_fmaf(pp[hh][i], v, s[hh][j]);
+          }
+#pragma unroll
+          for (int hh = 0; hh < H; ++hh) ls[hh] = ls[hh] + pp[hh][i];
+        }
+      }
+      accumulate(on, al, s, ls);
+    }
+  }
+
+  // merge the four streams
+#pragma unroll
+  for (int hh = 0; hh < H; ++hh) {
+    if (t == 0) {
+      red_m[stream][hh] = m_run[hh];
+      red_l[stream][hh] = l_run[hh];
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) red_o[stream][hh][tail ? 4 * t + j : 64 * vh + 16 * j + l16] = o_run[hh][j];
+  }
+  __syncthreads();
+  const int c = tid;
+  for (int hh = 0; hh < G; ++hh) {
+    float M = -INFINITY;
+    for (int w = 0; w < 4; ++w) M = fmaxf(M, red_m[w][hh]);
+    float L = 0.f, O = 0.f;
+    for (int w = 0; w < 4; ++w) {
+      const float mw = red_m[w][hh];
+      const float wgt = mw == -INFINITY ? 0.f : exp2f(mw - M);
+      L = __builtin_fmaf(red_l[w][hh], wgt, L);
+      O = __builtin_fmaf(red_o[w][hh][c], wgt, O);
+    }
+    float* dst = p.parts + (((size_t)b * p.hq + (size_t)qh0 + hh) * (p.n_chunks + 1) + chunk) * TKV_PART_STRIDE;
+    dst[TKV_PART_O + c] = O;
+    if (c == 0) {
+      dst[0] = M;
+      dst[1] = L;
+    }
+  }
+}
+
+template <int BITS, int GRP>
+int32_t launch_f32(const QuantAttnParams& p, dim3 grid, hipStream_t s) {
+  const int group = p.hq / p.hkv;
+  if (group == 1) TKV_LAUNCH((quant_attn_f32_kernel<BITS, GRP, 1>), grid, 128, 0, s, p);
+  else if (group == 2) TKV_LAUNCH((quant_attn_f32_kernel<BITS, GRP, 2>), grid, 128, 0, s, p);
+  else TKV_LAUNCH((quant_attn_f32_kernel<BITS, GRP, 4>), grid, 128, 0, s, p);
+  return TKV_OK;
+}
+
 // Log-sum-exp merge of the chunk partials of one query head; writes fp16.
 // One workgroup per query head, one thread per channel; the per-part maxima and sums
 // are staged in LDS so that the channel loop issues independent loads.
@@ -288,6 +666,12 @@ extern "C" int32_t tkv_debug_quant_attn_config(int32_t kernel_choice, int32_t ta
 
 namespace {
 
+// Settings of the matrix-core kernel.  4 bits with groups of 64 and 1 bit with groups of 32 stay in
+// float32 (quant_attn_f32_kernel).
+bool on_matrix_cores(const tkv_quant_desc* d) {
+  return d->bits == 2 || d->group_size == (d->bits == 4 ? 32 : 64);
+}
+
 // Body of both entry points.  parts: room for parts_floats floats of split-K partials; arrivals:
 // one zero word per (sequence, KV head, four query heads of its group).  TKV_E_WORKSPACE if the launch's partials do not fit.
 // fresh: the step's new tokens, already counted in seq_len_host but not yet in the fp16 ring (the
@@ -337,7 +721,8 @@ int32_t quant_attn_decode_impl(const tkv_quant_desc* d, const tkv_quant_cache* c
   p.groups_per_chunk = gpc;
   p.n_chunks = n_chunks;
 
-  if (g_kernel_choice.load() == 0) {
+  const int choice = g_kernel_choice.load();
+  if (choice == 0 && on_matrix_cores(d)) {
     // matrix-core kernel: one launch covers the quantized groups and the fp16 tail
     int target_blocks = g_target_blocks.load();
     // one workgroup per compute unit that the stream may use: on a stream with a compute-unit
@@ -348,11 +733,27 @@ int32_t quant_attn_decode_impl(const tkv_quant_desc* d, const tkv_quant_cache* c
     if (st != TKV_E_UNSUPPORTED) return st;
   }
   if (fresh != nullptr) return TKV_E_UNSUPPORTED;
-  // reference kernel, on request
-  if ((size_t)d->batch * d->n_q_heads * (n_chunks + 1) * TKV_PART_STRIDE > parts_floats) return TKV_E_WORKSPACE;
+  // float32 kernels; fewer chunks where the partials' room is the fixed array and takes no more
+  auto fits = [&]() { return (size_t)d->batch * d->n_q_heads * (n_chunks + 1) * TKV_PART_STRIDE <= parts_floats; };
+  while (!fits() && n_chunks > 1) {
+    p.groups_per_chunk = (max_groups + n_chunks - 2) / (n_chunks - 1);
+    p.n_chunks = n_chunks = (max_groups + p.groups_per_chunk - 1) / p.groups_per_chunk;
+  }
+  if (!fits()) return TKV_E_WORKSPACE;
   p.chunk_offset = 0;
   const int split = (d->n_q_heads / d->n_kv_heads + 3) / 4;
-  TKV_LAUNCH(quant_attn_generic_kernel, dim3(n_chunks + 1, d->n_kv_heads * split, d->batch), 256, 0, s, p);
+  const dim3 grid(n_chunks + 1, d->n_kv_heads * split, d->batch);
+  // the float32 kernel of the two settings reads the query in 32-bit scalar words; the generic one
+  // takes it at any fp16 address
+  const bool f32 = choice == 0 && (uintptr_t)q % 4 == 0;
+  const int variant = d->bits * 100 + d->group_size;
+  if (f32 && variant == 464) {
+    if (const int32_t st = launch_f32<4, 64>(p, grid, s); st != TKV_OK) return st;
+  } else if (f32 && variant == 132) {
+    if (const int32_t st = launch_f32<1, 32>(p, grid, s); st != TKV_OK) return st;
+  } else {
+    TKV_LAUNCH(quant_attn_generic_kernel, grid, 256, 0, s, p);
+  }
   return tkv::launch_attn_merge(p.parts, (__half*)out, d->batch * d->n_q_heads, n_chunks + 1, s);
 }
 
@@ -396,13 +797,13 @@ extern "C" int32_t tkv_quant_decode(const tkv_quant_desc* d, tkv_quant_cache* c,
   if (workspace_bytes < need) return TKV_E_WORKSPACE;
   if (n_new == 0) return tkv_quant_attn_decode(d, c, q, out, sm_scale, workspace, workspace_bytes, stream);
   // One launch when no sequence completes a quantization group with these tokens (the new rows
-  // then only join the fp16 ring, which the matrix-core kernel does itself); else the append's
-  // launches, then the attention's.
+  // then only join the fp16 ring, which the matrix-core kernel does itself) and the matrix-core
+  // kernel serves the descriptor; else the append's launches, then the attention's.
   tkv::QuantNewTokens fresh;
   fresh.k_new = (const __half*)k_new;
   fresh.v_new = (const __half*)v_new;
   fresh.n_stride = n_new;
-  bool one_launch = g_kernel_choice.load() == 0;
+  bool one_launch = g_kernel_choice.load() == 0 && on_matrix_cores(d);
   for (int b = 0; b < d->batch; ++b) {
     const int64_t n0 = c->seq_len_host[b];
     const int32_t add = n_valid_host ? n_valid_host[b] : n_new;

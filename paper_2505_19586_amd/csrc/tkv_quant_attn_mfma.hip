@@ -24,15 +24,13 @@
 //     softmax denominator ride on one more MFMA.  A 16-channel block of V needs one u only:
 //     with 8 heads, whose columns hold two u, four channel groups (group 32) take a second
 //     set of weights for the blocks of u = 2, 3, and no MFMA more.  The weights go in as one
-//     fp16 number each (the product p s_v is rounded once), or as hi + lo pairs (HILO: the
-//     settings that float32 weights served before).
+//     fp16 number each (the product p s_v is rounded once).
 //
 // Groups of 5 to 8 query heads per KV head (H = 8) cost the operand preparation of four more
 // heads; served as two workgroups of 4 heads each they cost everything twice (64 / 8 heads, 2 bit,
 // 65500 tokens: 28.9 -> 26.1 us per call; 32 / 4 heads, 1 bit, 98413 tokens: 25.3 -> 23.4, of which
 // the merge of 64 chunks x 8 heads by one workgroup, 270 KB, is 5).  4 bits with groups of 64 and
-// 1 bit with groups of 32 cost what their neighbours do (65500 tokens: 24.4 and 23.8 us; 225 and 229
-// on the float32 kernel that served them).
+// 1 bit with groups of 32 are not served here: they keep float32 weights (tkv_quant_attn.hip).
 //
 // The machine issues one vector or matrix instruction per SIMD at a time and a wave issues
 // in order, so the cost of a group is close to the plain sum of its instructions: the
@@ -415,7 +413,7 @@ __device__ inline void tail_pieces(const TailRows& rows, float scale2, const uin
   } while (0)
 #endif
 
-template <int BITS, int GS, int W, int H, bool HILO>
+template <int BITS, int GS, int W, int H>
 __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
   using C = Cfg<BITS, GS, W, H>;
   constexpr int KSH = GS - 1;          // key group of a block = block >> KSH
@@ -731,8 +729,7 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
   };
   struct POps {
     uintx4 b2, bp, a_zv;
-    uintx4 b3;            // kTwoSets: the weights for u = 2, 3
-    uintx4 b2l, b3l, bpl; // HILO: low parts
+    uintx4 b3;  // kTwoSets: the weights for u = 2, 3
   };
   // The weights 2^(x - m_run) go to the matrix cores as fp16, so m_run (a per-head reference,
   // not necessarily the running maximum) only has to keep them below 2^kHeadroomLog2: that
@@ -781,24 +778,11 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
       const float2_t w2 = {pw[2 * j], pw[2 * j + 1]};
       o.bp[j] = __builtin_bit_cast(uint32_t, __builtin_convertvector(w2, half2_t));
       const uint32_t bpj = o.bp[j], svj = in.sv[j], zvj = in.zv[j];
-      if (HILO) {
-        o.bpl[j] = mix_lo_pair(pw[2 * j], pw[2 * j + 1], 0x3C003C00u /* 1, 1 */, bpj);
-        o.b2[j] = mix_hi_pair(pw[2 * j], pw[2 * j + 1], svj);
-        const uint32_t b2j = o.b2[j];
-        o.b2l[j] = mix_lo_pair(pw[2 * j], pw[2 * j + 1], svj, b2j);
-        if (kTwoSets) {
-          const uint32_t sv2j = in.sv2[j];
-          o.b3[j] = mix_hi_pair(pw[2 * j], pw[2 * j + 1], sv2j);
-          const uint32_t b3j = o.b3[j];
-          o.b3l[j] = mix_lo_pair(pw[2 * j], pw[2 * j + 1], sv2j, b3j);
-        }
-      } else {
-        // weight x scaler: one rounding of the exact product of two fp16 numbers
-        o.b2[j] = __builtin_bit_cast(uint32_t, as_half2(bpj) * as_half2(svj));
-        if (kTwoSets) {
-          const uint32_t sv2j = in.sv2[j];
-          o.b3[j] = __builtin_bit_cast(uint32_t, as_half2(bpj) * as_half2(sv2j));
-        }
+      // weight x scaler: one rounding of the exact product of two fp16 numbers
+      o.b2[j] = __builtin_bit_cast(uint32_t, as_half2(bpj) * as_half2(svj));
+      if (kTwoSets) {
+        const uint32_t sv2j = in.sv2[j];
+        o.b3[j] = __builtin_bit_cast(uint32_t, as_half2(bpj) * as_half2(sv2j));
       }
       const half2_t t = __builtin_elementwise_fma(as_half2(zvj), zmul[j], zadd[j]);
       o.a_zv[j] = __builtin_bit_cast(uint32_t, t);
@@ -807,11 +791,9 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
   // P.V: 8 blocks of 16 channels + the z_v / denominator MFMA
   auto stage_pv = [&](const PvIn& in, const POps& o) {
     acc_z = mfma(o.a_zv, o.bp, acc_z);
-    if (HILO) acc_z = mfma(o.a_zv, o.bpl, acc_z);
     auto block = [&](int cb, uintx4 a) {
       const bool second = kTwoSets && cb >= 4;
       acc_o[cb] = mfma(a, second ? o.b3 : o.b2, acc_o[cb]);
-      if (HILO) acc_o[cb] = mfma(a, second ? o.b3l : o.b2l, acc_o[cb]);
     };
     if (BITS == 1) {
 #pragma unroll
@@ -997,20 +979,20 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
 #endif
 }
 
-template <int BITS, int GS, int W, int H, bool HILO>
+template <int BITS, int GS, int W, int H>
 int32_t launch_heads(const MfmaParams& p, dim3 grid, hipStream_t s) {
   using C = Cfg<BITS, GS, W, H>;
   // more than 64 KiB of dynamic LDS needs an opt-in, once per kernel
   static const bool lds_ok =
-      hipFuncSetAttribute(reinterpret_cast<const void*>(&quant_attn_mfma_kernel<BITS, GS, W, H, HILO>),
+      hipFuncSetAttribute(reinterpret_cast<const void*>(&quant_attn_mfma_kernel<BITS, GS, W, H>),
                           hipFuncAttributeMaxDynamicSharedMemorySize, C::kLdsBytes) == hipSuccess;
   if (!lds_ok) return TKV_E_HIP;
-  TKV_LAUNCH((quant_attn_mfma_kernel<BITS, GS, W, H, HILO>), grid, C::kThreads, C::kLdsBytes, s, p);
+  TKV_LAUNCH((quant_attn_mfma_kernel<BITS, GS, W, H>), grid, C::kThreads, C::kLdsBytes, s, p);
   return TKV_OK;
 }
-template <int BITS, int GS, int W, bool HILO>
+template <int BITS, int GS, int W>
 int32_t launch_variant(const MfmaParams& p, dim3 grid, hipStream_t s) {
-  return p.hq / p.hkv <= 4 || p.split != 0 ? launch_heads<BITS, GS, W, 4, HILO>(p, grid, s) : launch_heads<BITS, GS, W, 8, HILO>(p, grid, s);
+  return p.hq / p.hkv <= 4 || p.split != 0 ? launch_heads<BITS, GS, W, 4>(p, grid, s) : launch_heads<BITS, GS, W, 8>(p, grid, s);
 }
 
 }  // namespace
@@ -1136,12 +1118,10 @@ int32_t launch_quant_attn_mfma(const tkv_quant_desc* d, const tkv_quant_cache* c
   }
   const dim3 grid(total_chunks, heads, 1);
   switch (variant) {
-    case 232: return launch_variant<2, 1, 12, false>(p, grid, s);
-    case 432: return launch_variant<4, 1, 8, false>(p, grid, s);
-    case 164: return launch_variant<1, 2, 12, false>(p, grid, s);
-    case 264: return launch_variant<2, 2, 12, false>(p, grid, s);
-    case 132: return launch_variant<1, 1, 12, true>(p, grid, s);
-    case 464: return launch_variant<4, 2, 8, true>(p, grid, s);
+    case 232: return launch_variant<2, 1, 12>(p, grid, s);
+    case 432: return launch_variant<4, 1, 8>(p, grid, s);
+    case 164: return launch_variant<1, 2, 12>(p, grid, s);
+    case 264: return launch_variant<2, 2, 12>(p, grid, s);
   }
   return TKV_E_UNSUPPORTED;
 }

@@ -35,8 +35,8 @@ TOL_TAIL = 2.0 ** -11 + 1e-4
     (1, 64, 128, 3010, 7, (28, 4)),
     (2, 32, 128, 9000, 1, (64, 8)),     # 8 heads: two sets of weights; many chunks, merged 8 heads at a time
     (4, 32, 128, 2500, 1, (32, 4)),
-    (1, 32, 64, 2222, 1, (32, 4)),      # hi + lo weights, two sets
-    (4, 64, 128, 2500, 3, (32, 4)),     # hi + lo weights
+    (1, 32, 64, 2222, 1, (32, 4)),      # float32 settings
+    (4, 64, 128, 2500, 3, (32, 4)),
     (4, 64, 64, 4000, 1, (32, 32)),
     (1, 32, 96, 4000, 1, (32, 8)),
 ])
