@@ -757,8 +757,8 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
       if (__builtin_amdgcn_ballot_w64(mm >= kLimit) != 0ull) {
         const float mx = fmaxf(fmaxf(fmaxf(xs[0], xs[1]), fmaxf(xs[2], xs[3])), fmaxf(fmaxf(xs[4], xs[5]), fmaxf(xs[6], xs[7])));
         float mn = __builtin_fmaf(mx, K1, cz);  // largest logit among this lane's 8 tokens
-        mn = fmaxf(mn, __shfl_xor(mn, 4, 64));
-        mn = fmaxf(mn, __shfl_xor(mn, 8, 64));
+        // over the lanes that hold other tokens of the same head (the column groups of a head hold the
+        // same logits, and its neighbours in the row of 16 lanes are other heads)
         mn = fmaxf(mn, __shfl_xor(mn, 16, 64));
         mn = fmaxf(mn, __shfl_xor(mn, 32, 64));
         // New reference: kRefBelowMax under the head's largest logit (never lower than before).
