@@ -173,6 +173,9 @@ constexpr int kEK = 0;
 constexpr int kEP = 2;
 constexpr int kHeadroomLog2 = 4;  // lazy rescale: weights may reach 2^kHeadroomLog2
 constexpr int kRefBelowMax = 3;   // a rescale puts the reference this far under the largest logit (< headroom)
+// The fp16 tail's accumulators start the block loop scaled by 2^kTailRoomLog2.  Blocks whose logits are
+// further below change an output by less than 65504 * 2^-32, a subnormal number.
+constexpr int kTailRoomLog2 = 32;
 constexpr int kBkStride = 68;     // words per head row of the query-side operand in LDS (16 rows x 4 words: all 64 banks)
 constexpr int max_gpc(int heads) { return heads <= 4 ? 512 : 256; }  // groups per chunk that the zero-point table holds
 // Blocks that a 32-token piece of the fp16 tail counts as in the split (2 bit, 2000 tokens: 12.6 us per
@@ -241,9 +244,14 @@ __device__ constexpr int owner_group(int cb) {
 }
 
 // fp16 tail (the unquantized tokens): wave w of the last chunk takes the 32-token pieces w,
-// w + W, ... and leaves its result as the state its block loop starts from: reference m_run =
-// largest logit, accumulators in the layout and units of the block loop (acc_o: channel rows of
-// the column group that owns them, codes' 2^-24 and weights' 2^kEP included; acc_z: denominator).
+// w + W, ... and leaves its result as the state its block loop starts from: accumulators in the
+// layout and units of the block loop (acc_o: channel rows of the column group that owns them, codes'
+// 2^-24 and weights' 2^kEP included; acc_z: denominator) and their reference m_run, kTailRoomLog2
+// under the largest logit.  The blocks' weights are fp16 and need a reference of their own: the first
+// block sets it like any wave's first block does, kRefBelowMax under its largest logit, unless that
+// is more than the room below the tail's.  With the tail's largest logit as the reference they lose
+// their bits in fp16's subnormals wherever the recent tokens weigh most or the values are small (2 bit,
+// 800 tokens, values of 1e-3: relative error 1.8e-3 to 3.7e-3, 3e-4 with their own).
 //
 // Everything runs on the matrix cores: the logits as K rows (A operand, straight from memory)
 // against the exact fp16 query (the set-up's B operand), in the token order of a block's tiles;
@@ -327,7 +335,8 @@ __device__ inline void tail_pieces(const TailRows& rows, float scale2, const uin
     }
     mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    const float mn = fmaxf(m_run, mx);  // finite: the piece holds at least one token
+    // finite: the piece holds at least one token; a whole number, so that the room below is taken off exactly
+    const float mn = ceilf(fmaxf(m_run, mx));
     const float alpha = __builtin_amdgcn_exp2f(m_run - mn);
     float sum = 0.f;
 #pragma unroll
@@ -391,13 +400,15 @@ __device__ inline void tail_pieces(const TailRows& rows, float scale2, const uin
   for (int hh = 0; hh < 4; ++hh)
     *reinterpret_cast<float2_t*>(sc + hh * TKV_D + 8 * slot + 2 * rb) = float2_t{v[hh], v[4 + hh]};
   }
+  constexpr float room = (float)(1ull << kTailRoomLog2);
 #pragma unroll
   for (int cb = 0; cb < 8; ++cb) {
-    const float scale = 1.0f / (float)(1 << (24 - kEP - (BITS == 1 && cb % 2 ? 4 : 0)));
+    const float scale = room / (float)(1 << (24 - kEP - (BITS == 1 && cb % 2 ? 4 : 0)));
     const floatx4 o = *reinterpret_cast<const floatx4*>(sc + hs * TKV_D + 16 * cb + 4 * rb) * scale;
     acc_o[cb] = owner_group<GS, H>(cb) == us ? o : floatx4{0.f, 0.f, 0.f, 0.f};
   }
-  acc_z[0] = rb == 1 ? L : 0.f;
+  acc_z[0] = rb == 1 ? L * room : 0.f;
+  m_run -= (float)kTailRoomLog2;
 }
 
 #ifdef TKV_PHASE

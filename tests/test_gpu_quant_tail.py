@@ -81,3 +81,31 @@ def test_large_groups_where_the_partials_do_not_fit(heads, n, target):
     finally:
         tkv.debug_quant_attn_config(0, -1)
     assert attn_err(got[0], want[0].float().cpu().numpy().astype(np.float64)) <= 2 * TOL
+
+
+@pytest.mark.parametrize("bits,g", [(2, 32), (4, 32), (1, 64), (2, 64)])
+@pytest.mark.parametrize("heads,n", [((8, 2), 800), ((16, 2), 800), ((16, 2), 2500)])
+@pytest.mark.parametrize("gap", [0.0, 8.0, 16.0])
+@pytest.mark.parametrize("v_old,v_recent", [(1e-3, 1e-3), (1.0, 1e-3)])
+def test_blocks_keep_their_bits_beside_the_tail(bits, g, heads, n, gap, v_old, v_recent):
+    """Recent tokens whose logits are `gap` nats above the rest, and small values: the quantized tokens of the waves
+    that also take a piece of the tail keep a softmax reference of their own.  Bound, relative to the norm of a head's
+    output: three roundings of at most 2^-11 (weight, weight times scaler, output; independent from token to token, as
+    the values are, so averaging does not raise their share) and the output's spacing of 2^-24 where it is subnormal."""
+    print(f"case beside the tail bits={bits} g={g} heads={heads} n={n} gap={gap} v={v_old},{v_recent}", flush=True)
+    hq, hkv = heads
+    inp = make_layer(n, config=2, layer=0, seq=n % 61, shape=HeadShape(hq, hkv, 128))
+    k, q, v = inp.k.astype(np.float32), inp.q, inp.v.astype(np.float32) * v_old
+    recent = slice(n - 129, n)
+    mean = q.reshape(hkv, -1, 128).astype(np.float32).mean(axis=1)
+    k[:, recent] += (gap / SM * mean / (mean ** 2).sum(axis=-1, keepdims=True))[:, None]
+    v[:, recent] *= v_recent / v_old
+    k, v = k.astype(np.float16), v.astype(np.float16)
+    layer = tkv.QuantLayer(n_q_heads=hq, n_kv_heads=hkv, bits=bits, group_size=g, capacity=(n + g) // g * g)
+    layer.append(to_new(k), to_new(v))
+    want = attention.quant_attention(q, check_quant_cache(layer, 0, k, v), SM)
+    out = layer.attn_decode(torch.from_numpy(q)[None].cuda(), SM)[0].float().cpu().numpy()
+    norm = np.linalg.norm(want, axis=-1)
+    err = np.linalg.norm(out - want, axis=-1) / norm
+    print(f"   err {err.max():.3e}", flush=True)
+    assert (err <= 3 * 2.0 ** -11 + 2.0 ** -25 * np.sqrt(128) / norm).all()
