@@ -28,9 +28,10 @@
  *     a call returns.  At most TKV_MAX_BATCH sequences per call.
  *   - fp16 is IEEE binary16 everywhere.  head_dim must be 128, the quantization
  *     group g 32 or 64.  n_q_heads / n_kv_heads: any number from 1 to 8 (quantized layers:
- *     a workgroup takes the whole group, so the codes are read once; sparse layers: a row is
- *     fetched once whatever the group; tkv_sparse_decode is one launch for groups of up to 4
- *     and two above); any number for the dense preference score.
+ *     groups of 5 to 8 are one workgroup per chunk, or two of up to 4 heads that each read the
+ *     codes where that is shorter; sparse layers: a row is fetched once whatever the group;
+ *     tkv_sparse_decode is one launch for groups of up to 4 and two above); any number for the
+ *     dense preference score.
  *   - Token t of sequence b, KV head h.  "group j" is tokens [g j, g j + g); codes are
  *     stored in "blocks" of 32 tokens whatever g is.
  */

@@ -1,7 +1,7 @@
 // Matrix-core kernel of tkv_quant_attn_decode (Sec. 2.1 Eq. 3 over the quantized cache
-// of Sec. 4.3) for gfx950: all query heads of a KV head (H = 4 or 8 operand columns' worth) per
-// workgroup, D = 128, bits 1, 2 or 4, quantization group 32 or 64 (Sec. 5.1 runs 1 and 2 bits with
-// groups of 64).
+// of Sec. 4.3) for gfx950: up to H = 4 or 8 query heads of a KV head per workgroup, D = 128, 2 bits with
+// quantization groups of 32 or 64, 4 bits with groups of 32, 1 bit with groups of 64 (Sec. 5.1 runs 1
+// and 2 bits with groups of 64).
 //
 // One wave64 owns one packed block of 32 tokens at a time (half a key group when the
 // quantization group is 64; "group" below means such a block).  Both contractions run on
@@ -26,11 +26,10 @@
 //     set of weights for the blocks of u = 2, 3, and no MFMA more.  The weights go in as one
 //     fp16 number each (the product p s_v is rounded once).
 //
-// Groups of 5 to 8 query heads per KV head (H = 8) cost the operand preparation of four more
-// heads; served as two workgroups of 4 heads each they cost everything twice (64 / 8 heads, 2 bit,
-// 65500 tokens: 28.9 -> 26.1 us per call; 32 / 4 heads, 1 bit, 98413 tokens: 25.3 -> 23.4, of which
-// the merge of 64 chunks x 8 heads by one workgroup, 270 KB, is 5).  4 bits with groups of 64 and
-// 1 bit with groups of 32 are not served here: they keep float32 weights (tkv_quant_attn.hip).
+// Groups of 5 to 8 query heads per KV head (H = 8) cost the operand preparation of four more heads
+// and a merge of twice the partials; served as two workgroups of up to 4 heads they cost the reading and unpacking of
+// the codes twice.  The launch takes whichever is shorter (see its rule).  4 bits with groups of 64 and 1 bit
+// with groups of 32 are not served here: they keep float32 weights (tkv_quant_attn.hip).
 //
 // The machine issues one vector or matrix instruction per SIMD at a time and a wave issues
 // in order, so the cost of a group is close to the plain sum of its instructions: the
@@ -1034,6 +1033,7 @@ int32_t launch_quant_attn_mfma(const tkv_quant_desc* d, const tkv_quant_cache* c
   (void)max_tail;
   MfmaParams p;
   int heads = 0, total_chunks = 0;
+  long long total_work = 0;
   auto plan = [&](int split, int tail_blocks) -> int32_t {
     const int kMaxGpc = max_gpc(split ? 4 : d->n_q_heads / d->n_kv_heads);
     p.split = split;
@@ -1042,7 +1042,7 @@ int32_t launch_quant_attn_mfma(const tkv_quant_desc* d, const tkv_quant_cache* c
     int per_head = (target_blocks + heads - 1) / heads;
     if (per_head < d->batch) per_head = d->batch;
     const int chunk_cap = target_blocks > 64 * d->batch * heads ? TKV_MAX_CHUNKS : 64;
-    long long total_work = 0;
+    total_work = 0;
     int work[TKV_MAX_BATCH];
     for (int b = 0; b < d->batch; ++b) {
       const int n = lens.n[b];
@@ -1090,13 +1090,25 @@ int32_t launch_quant_attn_mfma(const tkv_quant_desc* d, const tkv_quant_cache* c
     if ((size_t)total_chunks * d->n_q_heads * TKV_PART_STRIDE > parts_floats) return TKV_E_WORKSPACE;
     return TKV_OK;
   };
-  // What else there is where that makes more chunks than may be or than the partials' room takes: a
-  // smaller allowance for the tail; and for groups of 5 to 8 query heads, whose one workgroup has a
-  // zero-point table of half as many blocks, two workgroups of up to 4 heads that each read the codes
-  // (half the chunks; slower by the second reading, see the top of the file).
+  // Groups of 5 to 8 query heads go to one workgroup, or to two of up to 4 heads that each read the
+  // codes (twice the unpacking, half the operand preparation, merge and chunks per workgroup).  Two
+  // where one would leave a quarter of the compute units idle (at most 64 chunks per sequence) or
+  // where two have few blocks each, so that the second reading costs less than the longer chain of 8
+  // heads.  us per call, two against one, blocks per workgroup of two:
+  //   64 / 8 heads, 2 bit: 3000 tokens (7) 13.0, 14.9; 20000 (41) 17.7, 18.6; 30000 (60) 19.7, 20.1;
+  //     45000 (89) 23.1, 22.1; 131000 (257) 39.9, 33.3
+  //   32 / 4 heads, 4 bit: 20000 (20) 14.5, 17.0; 65000 (64) 20.3, 21.2; 131000 (128) 28.6, 26.8
+  //   8 / 1 heads, 4 bit (never more than 64 compute units busy in one): 65000 (16) 16.7, 27.6; 131000 18.9, 28.9
+  constexpr int kTwoWorkgroupsBlocks = 80;
+  const bool large_group = d->n_q_heads / d->n_kv_heads > 4;
   int32_t st = plan(0, kTailBlocks);
-  if (st != TKV_OK) st = plan(0, kTailBlocksLeast);
-  if (st != TKV_OK && d->n_q_heads / d->n_kv_heads > 4) st = plan(1, kTailBlocksLeast);
+  if (large_group && (st != TKV_OK || 4ll * total_chunks * heads < 3ll * target_blocks ||
+                      2 * total_work * d->n_kv_heads < (long long)kTwoWorkgroupsBlocks * target_blocks))
+    st = plan(1, kTailBlocks);
+  // What else there is where that makes more chunks than may be or than the partials' room takes: a
+  // smaller allowance for the tail (two workgroups never take more chunks than one: their zero-point
+  // table holds twice the blocks).
+  if (st != TKV_OK) st = plan(large_group ? 1 : 0, kTailBlocksLeast);
   if (st != TKV_OK) return st;
   p.k_codes = (const uint32_t*)c->k_codes;
   p.v_codes = (const uint32_t*)c->v_codes;

@@ -173,8 +173,8 @@ def test_empty_sequence_gives_zeros():
 @pytest.mark.parametrize("shape", [HeadShape(64, 8, 128), HeadShape(56, 8, 128), HeadShape(10, 2, 128),
                                    HeadShape(6, 1, 128), HeadShape(3, 1, 128)])
 def test_groups_of_up_to_eight_query_heads(shape, bits, g):
-    """Groups of 5 to 8 query heads per KV head are served 4 heads at a time (two workgroups per
-    KV head and chunk); groups of 3 leave a column of the kernel's four unused."""
+    """Groups of 5 to 8 query heads per KV head are served by two workgroups of up to 4 heads per KV head and
+    chunk at this length; groups of 3 leave a column of the kernel's four unused."""
     print(f"case quant attention Hq={shape.n_q_heads} Hkv={shape.n_kv_heads} bits={bits} g={g}", flush=True)
     n = 2500
     inp = make_layer(n, shape=shape, seq=3)
