@@ -20,9 +20,10 @@ struct QuantAppendParams {
   __half* v_resid;
   const __half* k_new;
   const __half* v_new;
-  int32_t hkv, bits, group, residual, capacity;
-  int32_t n_stride;   // rows per sequence in k_new / v_new
-  int32_t unit_blocks;  // workgroups in x that quantize (four units of 64 tokens each); those behind them copy to the ring
+  int32_t hkv, residual, capacity;
+  int32_t n_stride;      // rows per sequence in k_new / v_new
+  int32_t quant_blocks;  // workgroups in x that quantize; those behind them copy to the ring
+  int32_t ring_tokens;   // tokens that each of those takes
   TkvSeqLens n_old;
   TkvSeqLens n_add;   // valid new rows per sequence (<= n_stride)
 };
@@ -101,7 +102,175 @@ __device__ inline uint32_t pack2(_Float16 lo, _Float16 hi) {
   return __builtin_bit_cast(uint32_t, v);
 }
 
-// The append in one launch; blockIdx.y = 2 head + (0: keys, 1: values).  blockIdx.x < unit_blocks
+// New tokens that stay unquantized, from the caller's rows to the fp16 ring: p.ring_tokens of those of sequence
+// b, keys or values of one head, 256 threads (a token is 16 of them).
+__device__ inline void ring_rows(const QuantAppendParams& p, int b, int h, bool is_v, int group, int piece, int tid) {
+  constexpr int kPass = 64, kLoads = kPass / 16;
+  const int n0 = p.n_old.n[b], n1 = n0 + p.n_add.n[b], ring = p.residual + group, part = tid % 16;
+  const int first = max(n0, tkv::n_quantized(n1, p.residual, group)) + p.ring_tokens * piece, end = min(n1, first + p.ring_tokens);
+  const __half* news = (is_v ? p.v_new : p.k_new) + ((size_t)b * p.n_stride * p.hkv + h) * TKV_D;
+  __half* olds = (is_v ? p.v_resid : p.k_resid) + ((size_t)b * p.hkv + h) * ring * TKV_D;
+  if (p.ring_tokens == 16) {  // one each (the pass below would load this token four times)
+    const int tok = first + tid / 16;
+    if (tok < end)
+      reinterpret_cast<u32x4*>(olds + (size_t)(tok % ring) * TKV_D)[part] =
+          reinterpret_cast<const u32x4*>(news + (size_t)(tok - n0) * p.hkv * TKV_D)[part];
+    return;
+  }
+  for (int t0 = first + tid / 16; t0 < end; t0 += kPass) {
+    u32x4 w[kLoads];
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i)
+      w[i] = reinterpret_cast<const u32x4*>(news + (size_t)(min(t0 + 16 * i, end - 1) - n0) * p.hkv * TKV_D)[part];
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) {
+      const int tok = t0 + 16 * i;
+      if (tok < end) reinterpret_cast<u32x4*>(olds + (size_t)(tok % ring) * TKV_D)[part] = w[i];
+    }
+  }
+}
+
+// The same where nothing is quantized, or after quantize_group_kernel: blockIdx.y = 0: keys, 1: values.  A thread takes 16 bytes of one token and
+// head, so that a decode step's token of 8 heads is one workgroup (64 sequences, 32 heads: 2.2 us per
+// call; 3.7 with a workgroup per head).
+__global__ __launch_bounds__(256) void ring_kernel(QuantAppendParams p, int group) {
+  const int b = blockIdx.z, i = blockIdx.x * 256 + threadIdx.x;
+  const bool is_v = blockIdx.y != 0;
+  const int n0 = p.n_old.n[b], n1 = n0 + p.n_add.n[b], ring = p.residual + group;
+  const int first = max(n0, tkv::n_quantized(n1, p.residual, group));
+  const int row = i / 16, part = i % 16, tok = first + row / p.hkv, h = row % p.hkv;
+  if (tok >= n1) return;
+  const __half* src = (is_v ? p.v_new : p.k_new) + (((size_t)b * p.n_stride + (size_t)(tok - n0)) * p.hkv + h) * TKV_D;
+  __half* dst = (is_v ? p.v_resid : p.k_resid) + (((size_t)b * p.hkv + h) * ring + (size_t)(tok % ring)) * TKV_D;
+  reinterpret_cast<uint4*>(dst)[part] = reinterpret_cast<const uint4*>(src)[part];
+}
+
+// Eq. 4's code with the stored fp16 s and z, literally: one subtraction, one division, rint.
+__device__ inline float quant_code(float x, float z, float s, float qmax) {
+  const float d = x - z;
+  const float t = d / s;
+  float c = rintf(t);
+  c = fminf(fmaxf(c, 0.0f), qmax);
+  return s == 0.0f ? 0.0f : c;
+}
+
+// The append of a few groups of 32 in one launch: blockIdx.x < quant_blocks is one group of one KV head, keys and
+// values, whose elements 256 threads stage in LDS and pick out 32 each.  Bound by latency: a lane of
+// quantize_append_kernel has 128 elements, which is less work in all but a longer chain (a decode step
+// that completes a group of 8 heads: 4.1 us per call at 2 bit, 6.3 with that kernel; 4.5 and 7.3 at 4; the
+// host's rule for which of them has more).  blockIdx.x >= quant_blocks copies
+// to the ring, keys and values of one head, under the same condition as there.
+template <int BITS>
+__global__ __launch_bounds__(256) void quantize_group_kernel(QuantAppendParams p) {
+  constexpr int GRP = TKV_BLK;        // a token group is one code block
+  constexpr int NU = TKV_D / GRP;     // channel groups of a value row
+  __shared__ __half kt[GRP][TKV_D];
+  __shared__ __half vt[GRP][TKV_D];
+  __shared__ float ks[TKV_D], kz[TKV_D];
+  __shared__ float vs[GRP][NU], vz[GRP][NU];
+
+  const int b = blockIdx.z, h = blockIdx.y, tid = threadIdx.x;
+  const int n0 = p.n_old.n[b], n1 = n0 + p.n_add.n[b];
+  if ((int)blockIdx.x >= p.quant_blocks) {
+    ring_rows(p, b, h, false, GRP, (int)blockIdx.x - p.quant_blocks, tid);
+    ring_rows(p, b, h, true, GRP, (int)blockIdx.x - p.quant_blocks, tid);
+    return;
+  }
+  const int j0 = tkv::n_quantized(n0, p.residual, GRP) / GRP;
+  const int j1 = tkv::n_quantized(n1, p.residual, GRP) / GRP;
+  const int j = j0 + (int)blockIdx.x;
+  if (j >= j1) return;
+  const int ring = p.residual + GRP;
+  const size_t bh = (size_t)b * p.hkv + h;
+  const size_t n_groups_cap = (size_t)(p.capacity / GRP), n_blocks_cap = n_groups_cap;
+
+  // stage the group's K rows and V rows (16-byte chunks)
+  for (int i = tid; i < GRP * 16; i += 256) {
+    const int t = i / 16, part = i % 16;
+    const int tok = GRP * j + t;
+    const uint4 *ksrc, *vsrc;
+    if (tok < n0) {
+      const size_t row = (bh * ring + (size_t)(tok % ring)) * TKV_D;
+      ksrc = reinterpret_cast<const uint4*>(p.k_resid + row);
+      vsrc = reinterpret_cast<const uint4*>(p.v_resid + row);
+    } else {
+      const size_t row = (((size_t)b * p.n_stride + (size_t)(tok - n0)) * p.hkv + h) * TKV_D;
+      ksrc = reinterpret_cast<const uint4*>(p.k_new + row);
+      vsrc = reinterpret_cast<const uint4*>(p.v_new + row);
+    }
+    reinterpret_cast<uint4*>(&kt[t][0])[part] = ksrc[part];
+    reinterpret_cast<uint4*>(&vt[t][0])[part] = vsrc[part];
+  }
+  __syncthreads();
+
+  constexpr float qmax = (float)((1 << BITS) - 1);
+  if (tid < TKV_D) {
+    // keys: one (s, z) per channel over the group's tokens
+    const int c = tid;
+    float mn = __half2float(kt[0][c]), mx = mn;
+    for (int t = 1; t < GRP; ++t) {
+      const float x = __half2float(kt[t][c]);
+      mn = fminf(mn, x);
+      mx = fmaxf(mx, x);
+    }
+    const float range = mx - mn;
+    const float s32 = range / qmax;
+    const __half s16 = __float2half_rn(s32);
+    const __half z16 = __float2half_rn(mn);  // exact: mn is an fp16 value
+    const size_t o = (bh * n_groups_cap + j) * TKV_D + c;
+    p.k_scale[o] = s16;
+    p.k_zero[o] = z16;
+    ks[c] = __half2float(s16);
+    kz[c] = __half2float(z16);
+  } else {
+    // values: one (s, z) per token and channel group; 128 threads cover GRP * NU = 128 pairs
+    const int pr = tid - TKV_D;
+    const int t = pr / NU, u = pr % NU;
+    float mn = 0.f, mx = 0.f;
+    for (int i = 0; i < GRP; ++i) {
+      const int c = GRP * u + ((i + pr) % GRP);  // rotated start: fewer LDS bank conflicts
+      const float x = __half2float(vt[t][c]);
+      mn = i == 0 ? x : fminf(mn, x);
+      mx = i == 0 ? x : fmaxf(mx, x);
+    }
+    const float range = mx - mn;
+    const float s32 = range / qmax;
+    const __half s16 = __float2half_rn(s32);
+    const __half z16 = __float2half_rn(mn);
+    const size_t o = ((bh * n_blocks_cap + j) * NU + u) * TKV_BLK + t;  // stored per block as [u][t]
+    p.v_scale[o] = s16;
+    p.v_zero[o] = z16;
+    vs[t][u] = __half2float(s16);
+    vz[t][u] = __half2float(z16);
+  }
+  __syncthreads();
+
+  constexpr int nwords = TKV_D * BITS;  // words of one packed block: 32*128*bits/32
+  constexpr int nfields = 32 / BITS;
+  uint32_t* kdst = p.k_codes + (bh * n_blocks_cap + j) * (size_t)nwords;
+  uint32_t* vdst = p.v_codes + (bh * n_blocks_cap + j) * (size_t)nwords;
+#pragma unroll
+  for (int w0 = 0; w0 < nwords; w0 += 256) {
+    const int w = w0 + tid;
+    if (nwords % 256 != 0 && w >= nwords) break;
+    uint32_t kw = 0, vw = 0;
+#pragma unroll
+    for (int f = 0; f < nfields; ++f) {
+      int t, c;
+      tkv::k_code_elem(BITS, w, f, t, c);
+      const float kc = quant_code(__half2float(kt[t][c]), kz[c], ks[c], qmax);
+      kw |= (uint32_t)kc << (BITS * f);
+      tkv::v_code_elem(BITS, w, f, t, c);
+      const float vc = quant_code(__half2float(vt[t][c]), vz[t][c / GRP], vs[t][c / GRP], qmax);
+      vw |= (uint32_t)vc << (BITS * f);
+    }
+    kdst[w] = kw;
+    vdst[w] = vw;
+  }
+}
+
+
+// The append in one launch; blockIdx.y = 2 head + (0: keys, 1: values).  blockIdx.x < quant_blocks
 // quantizes: a wave takes one unit, two code blocks of 32 tokens (two groups of 32 or one of 64).  Lane cp + 8 tb holds tokens
 // 8 tb .. 8 tb + 7 of two 8-channel pieces in registers (16 loads of 16 bytes in flight), the pieces
 // being those that share a word of packed codes; minima and maxima are packed fp16 operations over
@@ -111,7 +280,7 @@ __device__ inline uint32_t pack2(_Float16 lo, _Float16 hi) {
 // tokens of 8 KV heads take 127 us at 2 bit (5.0 TB/s; a plain copy of a GiB runs at 5.2 on this card),
 // 138 at 4.  With the divisions of Eq. 4 taken literally, the elements staged in LDS and picked out one
 // by one, and a second launch for the ring, it was bound by vector instructions: 187 and 189 us.
-// blockIdx.x >= unit_blocks copies new tokens that stay unquantized into the fp16 ring, 16 tokens per
+// blockIdx.x >= quant_blocks copies new tokens that stay unquantized into the fp16 ring, p.ring_tokens per
 // workgroup.  In the same launch only where no slot that it writes is still read as a
 // token to quantize (the host checks).
 template <int BITS, int GRP>
@@ -127,13 +296,8 @@ __global__ __launch_bounds__(256, 4) void quantize_append_kernel(QuantAppendPara
   const int n0 = p.n_old.n[b], n1 = n0 + p.n_add.n[b];
   const int ring = p.residual + GRP;
   const size_t bh = (size_t)b * p.hkv + h;
-  if ((int)blockIdx.x >= p.unit_blocks) {
-    const int nq1 = tkv::n_quantized(n1, p.residual, GRP);
-    const int tok = max(n0, nq1) + 16 * ((int)blockIdx.x - p.unit_blocks) + tid / 16, part = tid % 16;
-    if (tok >= n1) return;
-    const __half* src = (is_v ? p.v_new : p.k_new) + (((size_t)b * p.n_stride + (size_t)(tok - n0)) * p.hkv + h) * TKV_D;
-    __half* dst = (is_v ? p.v_resid : p.k_resid) + (bh * ring + (size_t)(tok % ring)) * TKV_D;
-    reinterpret_cast<uint4*>(dst)[part] = reinterpret_cast<const uint4*>(src)[part];
+  if ((int)blockIdx.x >= p.quant_blocks) {
+    ring_rows(p, b, h, is_v, GRP, (int)blockIdx.x - p.quant_blocks, tid);
     return;
   }
   const int j0 = tkv::n_quantized(n0, p.residual, GRP) / GRP;
@@ -377,19 +541,37 @@ extern "C" int32_t tkv_quantize_append_ragged(const tkv_quant_desc* d, tkv_quant
   p.k_new = (const __half*)k_new;
   p.v_new = (const __half*)v_new;
   p.hkv = d->n_kv_heads;
-  p.bits = d->bits;
-  p.group = d->group_size;
   p.residual = d->residual;
   p.capacity = d->capacity;
   p.n_stride = n_new;
 
   hipStream_t s = (hipStream_t)stream;
-  const int units = (max_groups * d->group_size + 63) / 64, unit_blocks = (units + 3) / 4, ring_blocks = (max_copy + 15) / 16;
-  auto run = [&](int x_units, int x_ring) -> int32_t {
-    if (x_units + x_ring == 0) return TKV_OK;
-    p.unit_blocks = x_units;
-    const dim3 grid(x_units + x_ring, 2 * d->n_kv_heads, d->batch);
-    switch (d->bits * 100 + d->group_size) {
+  const int g = d->group_size, hkv = d->n_kv_heads, variant = d->bits * 100 + g;
+  auto copy = [&]() -> int32_t {
+    if (max_copy > 0) TKV_LAUNCH(ring_kernel, dim3((max_copy * hkv + 15) / 16, 2, d->batch), 256, 0, s, p, g);
+    return TKV_OK;
+  };
+  // Which kernel: quantize_group_kernel up to two groups of 32 per compute unit (2 bits), three (4 bits)
+  // or four (4 bits and the ring in a launch of its own), quantize_append_kernel beyond, for 1 bit (its
+  // codes are one comparison) and for groups of 64 (of which a unit has no half to leave empty).  us per
+  // call, the group kernel against the other, 8 heads from an empty cache: 2 bit, 400 tokens (64 groups)
+  // 4.3, 6.3; 2000 (464) 5.7, 6.5; 3000 (712) 7.1, 6.6; 8200 (2016) 15.2, 11.5; 4 bit, 400 4.6, 7.3; 2000 6.1,
+  // 7.6; 3000 7.5, 7.7; 6000 (1464) 11.8, 10.7; 1 bit, 400 6.8, 4.2; 1 bit with groups of 64, 500 tokens 9.4 and 4.5.
+  const int few_groups = g == 64 || d->bits == 1 ? 0 : d->bits == 2 ? 512 : together ? 768 : 1024;
+  const bool few = max_groups * hkv * d->batch <= few_groups;
+  const int quant_blocks = few ? max_groups : ((max_groups * g + 63) / 64 + 3) / 4;
+  // Tokens per workgroup that copies: many behind a few workgroups that quantize (the copy is over long before
+  // those are; 32 sequences of 300 tokens, 8 heads: 13.7 us per call, 21.7 with 64, 19.9 with 16), a few where
+  // it is what the launch ends with (8 x 8000 tokens, 1 bit / 64: 45 us, 48 with 256).
+  p.ring_tokens = few ? 32 : together && quant_blocks <= 16 ? 256 : 16;
+  const int ring_blocks = (max_copy + p.ring_tokens - 1) / p.ring_tokens;
+  auto run = [&](int x_quant, int x_ring) -> int32_t {
+    if (x_quant + x_ring == 0) return TKV_OK;
+    p.quant_blocks = x_quant;
+    const dim3 grid(x_quant + x_ring, few ? hkv : 2 * hkv, d->batch);
+    switch (variant + (few ? 1000 : 0)) {
+      case 1232: TKV_LAUNCH((quantize_group_kernel<2>), grid, 256, 0, s, p); break;
+      case 1432: TKV_LAUNCH((quantize_group_kernel<4>), grid, 256, 0, s, p); break;
       case 132: TKV_LAUNCH((quantize_append_kernel<1, 32>), grid, 256, 0, s, p); break;
       case 232: TKV_LAUNCH((quantize_append_kernel<2, 32>), grid, 256, 0, s, p); break;
       case 432: TKV_LAUNCH((quantize_append_kernel<4, 32>), grid, 256, 0, s, p); break;
@@ -400,11 +582,13 @@ extern "C" int32_t tkv_quantize_append_ragged(const tkv_quant_desc* d, tkv_quant
     }
     return TKV_OK;
   };
-  if (together) {
-    st = run(unit_blocks, ring_blocks);
+  if (max_groups == 0) {
+    st = copy();
+  } else if (together) {
+    st = run(quant_blocks, ring_blocks);
   } else {  // long appends onto a cache that already holds a tail: quantize first, then reuse its slots
-    st = run(unit_blocks, 0);
-    if (st == TKV_OK) st = run(0, ring_blocks);
+    st = run(quant_blocks, 0);
+    if (st == TKV_OK) st = few ? copy() : run(0, ring_blocks);
   }
   if (st != TKV_OK) return st;
   for (int b = 0; b < d->batch; ++b) c->seq_len_host[b] += p.n_add.n[b];

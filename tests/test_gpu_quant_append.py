@@ -81,6 +81,29 @@ def test_infinities_and_nan(monkeypatch, bits, g):
     check_quant_cache(layer, 0, k, v)
 
 
+@pytest.mark.parametrize("bits,g", SETTINGS)
+@pytest.mark.parametrize("steps", [
+    [(129, 500)],               # up to 11 groups of 32 per sequence from an empty cache: odd and even numbers of them
+    [(130, 190), (300, 700)],   # onto a tail whose ring slots are read while others are to be written
+    [(500, 650), (0, 2), (40, 96)],
+])
+def test_many_groups(bits, g, steps):
+    """Batches whose groups are more than the kernel for a few groups takes (the last step of the third case is not)."""
+    print(f"case many groups bits={bits} g={g} steps={steps}", flush=True)
+    batch, hkv = 64, 4
+    inp = make_layer(2200, config=2, layer=1, seq=5, shape=HeadShape(8, hkv, 128))
+    kd, vd = to_new(inp.k)[0], to_new(inp.v)[0]                       # sequence b: tokens 11 b and on
+    layer = tkv.QuantLayer(n_q_heads=8, n_kv_heads=hkv, bits=bits, group_size=g, capacity=1024, batch=batch)
+    at = np.zeros(batch, np.int64)
+    for lo, hi in steps:
+        add = np.array([lo + (37 * b) % (hi - lo + 1) for b in range(batch)], np.int32)
+        k, v = (torch.stack([x[11 * b + at[b]:][:hi] for b in range(batch)]) for x in (kd, vd))
+        layer.append(k, v, n_valid=add)
+        at += add
+        for b in (0, 1, 2, 13, 37, 63):
+            check_quant_cache(layer, b, inp.k[:, 11 * b:11 * b + at[b]], inp.v[:, 11 * b:11 * b + at[b]])
+
+
 def test_ragged_batch():
     """Sequences with no group, one group and many in one launch."""
     lens = [7, 160, 161, 1000]
