@@ -153,10 +153,11 @@ int32_t tkv_quantize_append_ragged(const tkv_quant_desc* desc, tkv_quant_cache* 
  * 4 bits with groups of 64 and 1 bit with groups of 32 are evaluated in float32 throughout: the
  * same bits on every call, any fp16 input.  For the other settings:
  * Input range: the matrix-core kernel feeds fp16 products to the matrix cores: softmax
- * weight x value scaler, and query element x key scaler.  Cached values of magnitude up
- * to about 1000 and query-times-key-scaler products up to 65504 are safe at every bit
- * width; far larger ones overflow fp16 and give wrong or non-finite outputs (the
- * reference kernel that tkv_debug.h can switch to has no such limit).
+ * weight x value scaler, and query element x key scaler.  Cached values of magnitude up to
+ * 4000 whose groups have scalers up to 1023 (a range of 1023 at 1 bit, 3069 at 2, 15345 at 4)
+ * and query-times-key-scaler products up to 65504 are safe; larger ones can overflow fp16 and
+ * give wrong or non-finite outputs (the reference kernel that tkv_debug.h can switch to has no
+ * such limit).
  * Context length: the rounding error of the matrix-core path grows slowly with the number of
  * tokens (the softmax weights enter the matrix cores as fp16); against a float64 evaluation it
  * measures 5e-4 .. 1e-3 up to 32768 tokens, 1.0e-3 .. 1.5e-3 at 131072 and at 262144, the
@@ -180,8 +181,9 @@ int32_t tkv_quant_attn_decode(const tkv_quant_desc* desc, const tkv_quant_cache*
  * tkv_quant_attn_decode's run-to-run variation) as the two calls one after the other.  When no
  * sequence completes a quantization group with these tokens -- all but one decode step in
  * group_size -- the whole step is ONE launch: the attention kernel copies the new rows from
- * k_new / v_new into the fp16 ring itself before it reads the ring; otherwise the append's
- * launches come first.  k_new, v_new must stay valid until the call has run on the stream.  n_new == 0: the
+ * k_new / v_new into the fp16 ring itself and attends to them where the caller has them; otherwise
+ * (and always for 4 bits with groups of 64 and 1 bit with groups of 32) the append's launches come
+ * first.  k_new, v_new must stay valid until the call has run on the stream.  n_new == 0: the
  * attention alone.  Errors: those of the two calls; on an error nothing has been enqueued and
  * seq_len_host is unchanged, except that an error of the attention after a separate append
  * leaves the tokens appended.

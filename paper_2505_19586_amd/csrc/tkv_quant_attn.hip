@@ -11,8 +11,7 @@ namespace tkv {
 // shape is not one it is built for.
 int32_t launch_quant_attn_mfma(const tkv_quant_desc* d, const tkv_quant_cache* c, const __half* q, __half* out,
                                float scale2, float* parts, size_t parts_floats, uint32_t* arrivals, int target_blocks,
-                               int max_groups, int max_tail, const TkvSeqLens& lens, const QuantNewTokens* fresh,
-                               hipStream_t s);
+                               const TkvSeqLens& lens, const QuantNewTokens* fresh, hipStream_t s);
 }  // namespace tkv
 
 namespace {
@@ -681,7 +680,7 @@ int32_t quant_attn_decode_impl(const tkv_quant_desc* d, const tkv_quant_cache* c
                                float sm_scale, float* parts, size_t parts_floats, uint32_t* arrivals,
                                hipStream_t s, const tkv::QuantNewTokens* fresh = nullptr) {
   QuantAttnParams p;
-  int max_groups = 0, max_tail = 0;
+  int max_groups = 0;
   for (int b = 0; b < d->batch; ++b) {
     const int32_t n = c->seq_len_host[b];
     if (n < 0) return TKV_E_INVAL;
@@ -689,9 +688,8 @@ int32_t quant_attn_decode_impl(const tkv_quant_desc* d, const tkv_quant_cache* c
     p.lens.n[b] = n;
     const int g = tkv::n_quantized(n, d->residual, d->group_size) / TKV_BLK;  // in blocks of 32 tokens
     if (g > max_groups) max_groups = g;
-    if (n - g * TKV_BLK > max_tail) max_tail = n - g * TKV_BLK;
   }
-  // Chunking of the reference kernel: about 1024 workgroups over the whole launch.
+  // Chunking of the float32 kernels: about 1024 workgroups over the whole launch.
   const int bh = d->batch * d->n_kv_heads;
   int target = (1024 + bh - 1) / bh;
   if (target > TKV_MAX_CHUNKS) target = TKV_MAX_CHUNKS;
@@ -729,7 +727,7 @@ int32_t quant_attn_decode_impl(const tkv_quant_desc* d, const tkv_quant_cache* c
     // mask a launch sized for the whole machine would leave a few workgroups for a second round
     if (target_blocks == 0) target_blocks = tkv::stream_compute_units(s);
     const int32_t st = tkv::launch_quant_attn_mfma(d, c, p.q, (__half*)out, p.scale2, p.parts, parts_floats, arrivals,
-                                                   target_blocks, max_groups, max_tail, p.lens, fresh, s);
+                                                   target_blocks, p.lens, fresh, s);
     if (st != TKV_E_UNSUPPORTED) return st;
   }
   if (fresh != nullptr) return TKV_E_UNSUPPORTED;

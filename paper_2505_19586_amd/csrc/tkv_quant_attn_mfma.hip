@@ -165,10 +165,11 @@ __device__ inline void lds_load4(const void* g, void* l) {
 // fp16's subnormal range keep an absolute precision (2^-25 per operand) that is worth less
 // than 1e-5 in the logit, so nothing is gained by a larger kEK (measured 0 to 4).
 constexpr int kEK = 0;
-// Weight-side operands carry 2^kEP: fp16 weights p 2^(kEP - position shift) (p up to
+// Weight-side operands carry 2^kEP: fp16 weights p 2^(kEP - position shift) (p below
 // 2^kHeadroomLog2) times the value scaler must stay below 65504, and so must the zero-point
-// times 2^(position shift - kEP).  kEP = 2 keeps both finite for value magnitudes up to about
-// 1000 at every bit width; the attention error does not depend on it (measured 0 to 6).
+// times 2^(position shift - kEP).  kEP = 2 keeps both finite for value scalers up to 1023 (a group's
+// range up to 1023 at 1 bit, 3069 at 2, 15345 at 4) and zero-points up to 4000; the attention
+// error does not depend on it (measured 0 to 6).
 constexpr int kEP = 2;
 constexpr int kHeadroomLog2 = 4;  // lazy rescale: weights may reach 2^kHeadroomLog2
 constexpr int kRefBelowMax = 3;   // a rescale puts the reference this far under the largest logit (< headroom)
@@ -467,7 +468,7 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
   const uint32_t work = (uint32_t)(jq + tail_equiv);
   const int blk0 = min((int)(work * (uint32_t)chunk / (uint32_t)n_chunks), jq);
   const int blk1 = has_tail ? jq : min((int)(work * (uint32_t)(chunk + 1) / (uint32_t)n_chunks), jq);
-  const int last = max(blk1 - 1, blk0);  // groups past the chunk are clamped (and ignored); jq >= 1 here
+  const int last = max(blk1 - 1, blk0);  // groups past the chunk are clamped (and ignored)
 
   const int slot = lane % 16, rb = lane / 16;
   const int hs = slot % H, us = slot / H;  // this lane's operand column: head, column group
@@ -1017,8 +1018,7 @@ void* g_mfma_prof = nullptr;
 // the zero-point table of a workgroup holds.
 int32_t launch_quant_attn_mfma(const tkv_quant_desc* d, const tkv_quant_cache* c, const __half* q, __half* out,
                                float scale2, float* parts, size_t parts_floats, uint32_t* arrivals, int target_blocks,
-                               int max_groups, int max_tail, const TkvSeqLens& lens, const QuantNewTokens* fresh,
-                               hipStream_t s) {
+                               const TkvSeqLens& lens, const QuantNewTokens* fresh, hipStream_t s) {
   if (d->head_dim != TKV_D) return TKV_E_UNSUPPORTED;
   const int variant = d->bits * 100 + d->group_size;
   const int waves = d->bits == 4 ? 8 : 12;
@@ -1029,8 +1029,6 @@ int32_t launch_quant_attn_mfma(const tkv_quant_desc* d, const tkv_quant_cache* c
   // whatever the mix of lengths.  Per sequence: at least one block per wave, at most 64 chunks
   // (unless the tuning hook asks for more workgroups than that gives), no more blocks per chunk
   // than the zero-point table of a workgroup holds.
-  (void)max_groups;
-  (void)max_tail;
   MfmaParams p;
   int heads = 0, total_chunks = 0;
   long long total_work = 0;

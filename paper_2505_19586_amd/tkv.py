@@ -126,7 +126,7 @@ def lib() -> C.CDLL:
 
 
 def debug_quant_attn_config(kernel_choice: int = 0, target_blocks: int = 0) -> None:
-    """0 = matrix-core kernel (default), 1 = reference kernel; see tkv.h."""
+    """0 = the setting's own kernel (default), 1 = reference kernel; see tkv_debug.h."""
     _check(lib().tkv_debug_quant_attn_config(int(kernel_choice), int(target_blocks)), "tkv_debug_quant_attn_config")
 
 

@@ -17,14 +17,14 @@ TOL = 2e-3
 
 @pytest.fixture(autouse=True, params=["mfma", "reference"])
 def kernel_choice(request):
-    """Every case runs with the matrix-core kernel and with the reference kernel."""
+    """Every case runs with the setting's own kernel (for most the matrix-core kernel) and with the reference kernel."""
     tkv.debug_quant_attn_config(0 if request.param == "mfma" else 1)
     yield request.param
     tkv.debug_quant_attn_config(0)
 
 SM = 1.0 / np.sqrt(128.0)
 # (bits, quantization group): the benchmark's settings, the paper's (Sec. 5.1: 1 and 2 bits,
-# groups of 64), and two that only the reference kernel is built for
+# groups of 64), and two that are evaluated in float32 throughout
 SETTINGS = [(2, 32), (4, 32), (1, 64), (2, 64), (1, 32), (4, 64)]
 MAIN_SETTINGS = SETTINGS[:4]
 
@@ -72,7 +72,7 @@ def test_decode_step_in_one_call(bits, g):
     """tkv_quant_decode over 70 single-token steps (which cross group boundaries: those steps take
     the separate append) and a few multi-token ones: after every step the attention output is
     within the bound of the oracle's over the grown prefix; the cache is the oracle's cache bit
-    for bit at checkpoints.  (1, 32) is served by the reference kernel only: always two calls.)"""
+    for bit at checkpoints.  (1, 32) is evaluated in float32: always two calls.)"""
     print(f"case decode step bits={bits} g={g}", flush=True)
     n0 = 3000
     steps = [1] * 70 + [3, 1, 1, 40, 1, 1]
@@ -112,8 +112,8 @@ def test_decode_steps_from_an_empty_cache(bits, g):
 
 def test_decode_step_ragged_batch_and_groups_of_eight():
     """tkv_quant_decode on a padded batch (one sequence gets no token, one completes a group in
-    some steps) with 8 query heads per KV head (two workgroups per KV head read the new rows,
-    one writes them)."""
+    some steps) with 8 query heads per KV head (two workgroups per KV head read the new rows from
+    the caller's buffers and write the same bytes to the ring)."""
     shape = HeadShape(16, 2, 128)
     lens = [700, 129, 2040, 333]
     adds = [[1, 0, 1, 1]] * 12 + [[2, 1, 0, 3]] * 3
