@@ -1092,7 +1092,9 @@ int32_t launch_quant_attn_mfma(const tkv_quant_desc* d, const tkv_quant_cache* c
   // codes (twice the unpacking, half the operand preparation, merge and chunks per workgroup).  Two
   // where one would leave a quarter of the compute units idle (at most 64 chunks per sequence) or
   // where two have few blocks each, so that the second reading costs less than the longer chain of 8
-  // heads.  us per call, two against one, blocks per workgroup of two:
+  // heads; but not where one per sequence and head is more than half a round already (64 sequences of
+  // 900 tokens, 32 / 4 heads, 2 bit: 32.5 us per call in two, 19.4 in one).  us per call, two against
+  // one, blocks per workgroup of two:
   //   64 / 8 heads, 2 bit: 3000 tokens (7) 13.0, 14.9; 20000 (41) 17.7, 18.6; 30000 (60) 19.7, 20.1;
   //     45000 (89) 23.1, 22.1; 131000 (257) 39.9, 33.3
   //   32 / 4 heads, 4 bit: 20000 (20) 14.5, 17.0; 65000 (64) 20.3, 21.2; 131000 (128) 28.6, 26.8
@@ -1100,8 +1102,10 @@ int32_t launch_quant_attn_mfma(const tkv_quant_desc* d, const tkv_quant_cache* c
   constexpr int kTwoWorkgroupsBlocks = 80;
   const bool large_group = d->n_q_heads / d->n_kv_heads > 4;
   int32_t st = plan(0, kTailBlocks);
-  if (large_group && (st != TKV_OK || 4ll * total_chunks * heads < 3ll * target_blocks ||
-                      2 * total_work * d->n_kv_heads < (long long)kTwoWorkgroupsBlocks * target_blocks))
+  if (large_group &&
+      (st != TKV_OK || (2 * d->n_kv_heads * d->batch <= target_blocks &&
+                        (4ll * total_chunks * heads < 3ll * target_blocks ||
+                         2 * total_work * d->n_kv_heads < (long long)kTwoWorkgroupsBlocks * target_blocks))))
     st = plan(1, kTailBlocks);
   // What else there is where that makes more chunks than may be or than the partials' room takes: a
   // smaller allowance for the tail (two workgroups never take more chunks than one: their zero-point

@@ -87,6 +87,20 @@ def test_decode_step(bits, g, heads, lens, n_new, route):
 
 
 @pytest.mark.parametrize("bits,g", [(2, 32), (4, 32), (1, 64), (2, 64)])
+@pytest.mark.parametrize("batch", [32, 33])
+def test_many_short_sequences(bits, g, batch):
+    """32 sequences of 4 KV heads take 256 workgroups in two per group, 33 are served by one each."""
+    n = 300
+    inps = [make_layer(n - 7 * (b % 5), config=3, layer=1, seq=b, shape=HeadShape(32, 4, 128)) for b in range(batch)]
+    layer = tkv.QuantLayer(n_q_heads=32, n_kv_heads=4, bits=bits, group_size=g, capacity=320, batch=batch)
+    layer.append(to_new_batch([i.k for i in inps], n), to_new_batch([i.v for i in inps], n), n_valid=[i.k.shape[1] for i in inps])
+    out = layer.attn_decode(torch.from_numpy(np.stack([i.q for i in inps])).cuda(), SM)
+    for b in range(0, batch, 4):
+        ref = check_quant_cache(layer, b, inps[b].k, inps[b].v)
+        assert attn_err(out[b], attention.quant_attention(inps[b].q, ref, SM)) <= TOL
+
+
+@pytest.mark.parametrize("bits,g", [(2, 32), (4, 32), (1, 64), (2, 64)])
 @pytest.mark.parametrize("k_scale,q_scale,v_scale", [(64.0, 1.0, 1.0), (1.0, 64.0, 1.0), (1.0, 1.0, 100.0)])
 def test_large_magnitudes(bits, g, k_scale, q_scale, v_scale, route):
     """Large key scalers, queries and values stay inside fp16 on their way to the matrix cores."""
