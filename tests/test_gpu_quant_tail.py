@@ -131,3 +131,21 @@ def test_blocks_keep_their_bits_beside_the_tail(bits, g, heads, n, gap, v_old, v
     err = np.linalg.norm(out - want, axis=-1) / norm
     print(f"   err {err.max():.3e}", flush=True)
     assert (err <= 3 * 2.0 ** -11 + 2.0 ** -25 * np.sqrt(128) / norm).all()
+
+
+@pytest.mark.parametrize("bits,g", [(2, 32), (4, 32), (1, 64), (2, 64), (1, 32), (4, 64)])
+@pytest.mark.parametrize("n", [300, 2500])
+def test_rows_and_outputs_at_odd_addresses(bits, g, n):
+    """Query, new rows and output at fp16 addresses that are no multiple of 4: sequences of one workgroup (whose threads
+    write two channels each) and of several."""
+    def odd(x):
+        return torch.empty(x.numel() + 1, dtype=torch.float16, device="cuda")[1:].view_as(x).copy_(x)
+    inp = make_layer(n, config=3, layer=1, seq=n % 89, shape=HeadShape(16, 4, 128))
+    layer = tkv.QuantLayer(n_q_heads=16, n_kv_heads=4, bits=bits, group_size=g, capacity=2560)
+    kd, vd = to_new(inp.k), to_new(inp.v)
+    layer.append(odd(kd[:, :n - 3]), odd(vd[:, :n - 3]))
+    q = torch.from_numpy(inp.q)[None].cuda()
+    out = odd(torch.full_like(q, float("nan")))
+    layer.decode(odd(q), SM, odd(kd[:, n - 3:]), odd(vd[:, n - 3:]), out=out)
+    ref = check_quant_cache(layer, 0, inp.k, inp.v)
+    assert attn_err(out[0], attention.quant_attention(inp.q, ref, SM)) <= TOL
