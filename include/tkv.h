@@ -202,7 +202,9 @@ int32_t tkv_quant_decode(const tkv_quant_desc* desc, tkv_quant_cache* cache, con
  * Limits: batch * n_kv_heads (twice that for groups of more than 4 query heads) <=
  * TKV_STATIC_MAX_HEADS and the launch's partials
  * (batch * n_q_heads * chunks * 528 bytes; chunks is about compute units / (batch * n_kv_heads),
- * at most 64; for 4 bits with groups of 64 and 1 bit with groups of 32 at least 2) must fit in TKV_STATIC_PARTS_BYTES, else TKV_E_WORKSPACE and nothing is enqueued.
+ * at most 64; for 4 bits with groups of 64 and 1 bit with groups of 32 at least 2, and where the
+ * usual number does not fit, as many as do: float32 sums in another order) must fit in
+ * TKV_STATIC_PARTS_BYTES, else TKV_E_WORKSPACE and nothing is enqueued.
  * Batch 1 to 64 with 32 query heads fits at every context length.
  * The device that owns `stream` and the buffers must be the calling thread's current device.
  * All calls on one GPU share that GPU's array: calls that overlap in time on one GPU (different

@@ -182,8 +182,10 @@ constexpr int max_gpc(int heads) { return heads <= 4 ? 512 : 256; }  // groups p
 // call with 3, 13.1 with 2; from 16384 tokens on 2 to 5 make no difference).
 constexpr int kTailBlocks = 3, kTailBlocksLeast = 2;
 // Sequences of up to this many blocks (tail pieces counted as above) per wave are one workgroup's:
-// no partials to write, no arrival, no merge.  2 bit, 8 KV heads, batch 1: 600 tokens (29 blocks)
-// 12.6 us in one workgroup, 13.7 in two; 1000 tokens (42 blocks) 14.1 against 12.9.
+// no partials to write, no arrival, no merge.  us per call with 3 rounds against 1, 8 KV heads: 2 bit, one
+// sequence, 200 tokens 9.1, 11.4; 520 10.8, 11.7; 896 11.0, 12.2; 16 sequences of 800 11.8, 13.7; 4 bit, 200 tokens 8.7,
+// 10.3, 400 10.7, 10.4.  Over 200 to 896 tokens, 1 to 32 KV heads and all settings at most 5 % longer, at most
+// 30 % shorter.  With more rounds the loop outgrows the merge (2 bit, 1000 tokens: 14.1 in one, 12.9 in several).
 constexpr int kOneChunkRounds = 3;
 
 // Results of one wave for the merge inside the workgroup; it takes the place of the start of
