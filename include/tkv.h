@@ -29,9 +29,8 @@
  *   - fp16 is IEEE binary16 everywhere.  head_dim must be 128, the quantization
  *     group g 32 or 64.  n_q_heads / n_kv_heads: any number from 1 to 8 (quantized layers:
  *     groups of 5 to 8 are one workgroup per chunk, or two of up to 4 heads that each read the
- *     codes where that is shorter; sparse layers: a row is fetched once whatever the group;
- *     tkv_sparse_decode is one launch for groups of up to 4 and two above); any number for the
- *     dense preference score.
+ *     codes where that is shorter; sparse layers: a row is fetched once whatever the group); any
+ *     number for the dense preference score.
  *   - Token t of sequence b, KV head h.  "group j" is tokens [g j, g j + g); codes are
  *     stored in "blocks" of 32 tokens whatever g is.
  */
@@ -290,7 +289,7 @@ int32_t tkv_sparse_append_estimate_topk(const tkv_sparse_desc* desc, tkv_sparse_
                                         size_t workspace_bytes, void* stream);
 
 /*
- * A sparsity-friendly layer's whole decode step in ONE launch: Eq. 2 for the step's new tokens
+ * A sparsity-friendly layer's whole decode step in ONE launch (two where heads are few, below): Eq. 2 for the step's new tokens
  * (n_new 0..min(8, n_window); n_new == 0: k_new, v_new, n_valid_host are ignored), Stage 2
  * scoring and Top-K as in tkv_sparse_estimate_topk, fetch of the selected rows from the host
  * cache and exact attention as in tkv_sparse_gather_attn (Sec. 4.2, Sec. 5.1; Eq. 3).  Same
@@ -299,9 +298,10 @@ int32_t tkv_sparse_append_estimate_topk(const tkv_sparse_desc* desc, tkv_sparse_
  * calls cannot overlap with anything: the workgroup that finishes a head's selection goes on to
  * fetch that head's rows and attends to them, so no launch boundary and no cross-workgroup
  * hand-off sits between the selection and the transfer that cannot be hidden.
- * Groups of 5 to 8 query heads per KV head: the same call, same results, as two launches
- * (tkv_sparse_append_estimate_topk, then tkv_sparse_gather_attn on this stream); the hint is
- * not used then.
+ * Few heads (batch * n_kv_heads below 4, below 8 with groups of 5 to 8 query heads) and more than 256
+ * attended tokens: the same call, same results, as two launches (tkv_sparse_append_estimate_topk,
+ * then tkv_sparse_gather_attn on this stream, which shares a head's rows out over several
+ * workgroups); the hint is not used then.
  * The key summary must be token-major (cache->key_summary).  workspace: as for
  * tkv_sparse_estimate_topk.  seq_len_host[b] += n_valid on success.
  * next_key_summary: NULL, or the key summary (device, same descriptor, hence same layout as

@@ -109,9 +109,6 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(GatherParams p) {
 struct SparseAttnParams {
   const __half* q;
   const __half* staging;
-  const __half* kv_host;    // fused variant: device-visible view of the pinned host rows
-  const int32_t* topk_idx;  // fused variant
-  int32_t capacity;
   uint32_t* arrivals;  // [B][Hkv] stride 8 words, zero between calls
   __half* out;         // [B][Hq][D]
   const __half* kv_local;
@@ -122,27 +119,23 @@ struct SparseAttnParams {
   TkvSeqLens lens;
 };
 
-constexpr int kAttnMaxWaves = 4;  // a workgroup of W waves handles 32*W attended tokens
+constexpr int kAttnWaves = 4;                 // a workgroup handles 32 attended tokens per wave
+constexpr int kAttnThreads = 64 * kAttnWaves;
 
 __device__ inline float half_wave_max(float v) {
   for (int m = 16; m >= 1; m >>= 1) v = fmaxf(v, __shfl_xor(v, m, 64));
   return v;
 }
 
-constexpr int kRowPitch = 2 * TKV_D * 2 + 16;  // LDS bytes per staged K|V row (padded against bank conflicts)
-
-// Exact attention over sinks + gathered rows + window.  One workgroup of W <= 4 waves
-// handles 32*W attended tokens of one KV head; lane (t, hp) scores token t for the query heads
+// Exact attention over sinks + gathered rows (in the staging buffer) + window.  One workgroup of 4 waves
+// handles 128 attended tokens of one KV head; lane (t, hp) scores token t for the query heads
 // [GH/2 hp, GH/2 hp + GH/2) of the group (GH = 4, or 8 for groups of 5 to 8 heads); then every
 // lane accumulates two output channels of all heads.
-// FUSED: the selected rows are not read from the staging buffer but fetched by this kernel
-// from pinned host memory (one 512-byte row per load instruction, all 32 rows of a wave in
-// flight) into LDS, so the transfer and the attention are one launch.
-template <bool FUSED, int GH>
-__global__ __launch_bounds__(256) void sparse_attn_kernel(SparseAttnParams p) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char rows_s[];  // FUSED: [W][32][kRowPitch]
+// (Few attended tokens used to go to workgroups of one wave, whose merge walked the chunks one device-scope
+// load after the other: 64/8 heads, 128 + 68 tokens, 62.2 us per call, 16.8 here; 32/8 heads 33.1, 10.5.)
+template <int GH>
+__global__ __launch_bounds__(kAttnThreads) void sparse_attn_kernel(SparseAttnParams p) {
   constexpr int HPH = GH / 2;  // heads per half-wave
-  __shared__ const __half* src_s[4][32];
   __shared__ float qs[GH][TKV_D];
   __shared__ float pw[4][GH][32];
   __shared__ const __half* vrow_s[4][32];
@@ -158,7 +151,7 @@ __global__ __launch_bounds__(256) void sparse_attn_kernel(SparseAttnParams p) {
   const int w0 = max(n - p.n_window, n_sk);
   const int n_att = n_sk + cnt + (n - w0);
 
-  const int nthr = blockDim.x, W = nthr / 64;
+  constexpr int nthr = kAttnThreads, W = kAttnWaves;
   for (int i = tid; i < GH * TKV_D; i += nthr) {
     const int hh = i / TKV_D, c = i % TKV_D;
     qs[hh][c] = hh < G ? __half2float(p.q[((size_t)b * p.hq + (size_t)h * G + hh) * TKV_D + c]) : 0.f;
@@ -174,27 +167,11 @@ __global__ __launch_bounds__(256) void sparse_attn_kernel(SparseAttnParams p) {
     if (i < n_sk)
       krow = p.kv_local + (bh * (p.n_sink + p.n_window) + i) * 2 * TKV_D;
     else if (i < n_sk + cnt) {
-      if (FUSED) {
-        const int tok = min(max(p.topk_idx[bh * p.top_k + (i - n_sk)], 0), p.capacity - 1);
-        krow = p.kv_host + (bh * p.capacity + (size_t)tok) * 2 * TKV_D;
-      } else {
-        krow = p.staging + (bh * p.top_k + (size_t)(i - n_sk)) * 2 * TKV_D;
-      }
+      krow = p.staging + (bh * p.top_k + (size_t)(i - n_sk)) * 2 * TKV_D;
     } else {
       const int tok = w0 + (i - n_sk - cnt);
       krow = p.kv_local + (bh * (p.n_sink + p.n_window) + p.n_sink + tok % p.n_window) * 2 * TKV_D;
     }
-  }
-  if (FUSED) {
-    // every row of this wave (host or device memory alike): 64 lanes x 8 bytes per row
-    unsigned char* rows = rows_s + (size_t)wave * 32 * kRowPitch;
-    if (hp == 0) src_s[wave][t] = krow;
-    uint2 r[32];
-#pragma unroll
-    for (int y = 0; y < 32; ++y) r[y] = reinterpret_cast<const uint2*>(src_s[wave][y])[lane];
-#pragma unroll
-    for (int y = 0; y < 32; ++y) *reinterpret_cast<uint2*>(rows + y * kRowPitch + 8 * lane) = r[y];
-    krow = reinterpret_cast<const __half*>(rows + t * kRowPitch);
   }
   float xs[HPH];
 #pragma unroll
@@ -289,30 +266,11 @@ __global__ __launch_bounds__(256) void sparse_attn_kernel(SparseAttnParams p) {
   if (tid == 0) __hip_atomic_store(arrive, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __shared__ float merge_s[3 * 4 * 64 + 4 * 4 * TKV_D + 4];
   const float* head0 = p.parts + ((size_t)b * p.hq + (size_t)h * G) * p.n_chunks * TKV_PART_STRIDE;
-  if (nthr >= 64 * min(G, 4)) {
-    // (four heads at a time: the merge's LDS scratch is laid out for that many)
-    for (int g0 = 0; g0 < G; g0 += 4) {
-      if (g0 > 0) __syncthreads();
-      tkv::merge_chunks(head0 + (size_t)g0 * p.n_chunks * TKV_PART_STRIDE, min(4, G - g0), p.n_chunks,
-                        p.out + ((size_t)b * p.hq + (size_t)h * G + g0) * TKV_D, merge_s, tid, nthr);
-    }
-  } else {  // one-wave workgroups (few attended tokens): plain loop over the chunks
-    auto ld = [](const float* ptr) { return __hip_atomic_load(ptr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
-    for (int x = tid; x < G * TKV_D; x += nthr) {
-      const int hh = x / TKV_D, c = x % TKV_D;
-      const float* base = head0 + (size_t)hh * p.n_chunks * TKV_PART_STRIDE;
-      float M = -INFINITY;
-      for (int k = 0; k < p.n_chunks; ++k) M = fmaxf(M, ld(base + (size_t)k * TKV_PART_STRIDE));
-      float L = 0.f, O = 0.f;
-      for (int k = 0; k < p.n_chunks; ++k) {
-        const float* pk = base + (size_t)k * TKV_PART_STRIDE;
-        const float mk = ld(pk);
-        const float w = mk == -INFINITY ? 0.f : exp2f(mk - M);
-        L = __builtin_fmaf(ld(pk + 1), w, L);
-        O = __builtin_fmaf(ld(pk + TKV_PART_O + c), w, O);
-      }
-      p.out[((size_t)b * p.hq + (size_t)h * G + hh) * TKV_D + c] = __float2half_rn(L > 0.f ? O / L : 0.f);
-    }
+  // (four heads at a time: the merge's LDS scratch is laid out for that many)
+  for (int g0 = 0; g0 < G; g0 += 4) {
+    if (g0 > 0) __syncthreads();
+    tkv::merge_chunks(head0 + (size_t)g0 * p.n_chunks * TKV_PART_STRIDE, min(4, G - g0), p.n_chunks,
+                      p.out + ((size_t)b * p.hq + (size_t)h * G + g0) * TKV_D, merge_s, tid, nthr);
   }
 }
 
@@ -427,13 +385,13 @@ namespace tkv {
 // tkv_sparse_topk.hip: the one-launch step's fetch + attention phase for a selection made earlier
 int32_t launch_fetch_attn(const tkv_sparse_desc* d, const TkvSeqLens& lens, const __half* q, const int32_t* topk_idx,
                           const int32_t* topk_count, const __half* host_rows, const __half* local_rows, __half* out,
-                          float scale2, hipStream_t s);
+                          float scale2, void* workspace, hipStream_t s);
 }  // namespace tkv
 
 namespace {
 // Attention over sinks + selected rows + window.  topk_idx_fused == nullptr: the selected
-// rows are in `staging`; otherwise they are fetched from the pinned host cache by the
-// attention kernel itself.
+// rows are in `staging`; otherwise the attention phase of the one-launch step fetches them from the
+// pinned host cache itself.
 int32_t sparse_attn_launch(const tkv_sparse_desc* d, const tkv_sparse_cache* c, const void* q,
                            const int32_t* topk_idx_fused, const int32_t* topk_count, const void* staging, void* out,
                            float sm_scale, void* workspace, size_t workspace_bytes, void* stream) {
@@ -447,12 +405,18 @@ int32_t sparse_attn_launch(const tkv_sparse_desc* d, const tkv_sparse_cache* c, 
   int max_n = 0;
   st = fill_lens(d, c, p.lens, max_n);
   if (st != TKV_OK) return st;
+  hipStream_t s = (hipStream_t)stream;
+  if (topk_idx_fused) {
+    const void* host_dev = nullptr;
+    st = tkv::device_view(c->kv_host, tkv::kDevHostOnly, &host_dev);
+    if (st != TKV_OK) return st;
+    return tkv::launch_fetch_attn(d, p.lens, (const __half*)q, topk_idx_fused, topk_count, (const __half*)host_dev,
+                                  (const __half*)c->kv_local, (__half*)out, sm_scale * 1.44269504088896340736f,
+                                  workspace, s);
+  }
   const int max_att = d->n_sink + d->top_k + d->n_window;
-  // four waves per workgroup once there is work for them: few chunks keep the final merge
-  // short (and their number must stay within the 64 partial slots)
-  int W = max_att > 256 ? kAttnMaxWaves : 1;
-  const int n_chunks = (max_att + 32 * W - 1) / (32 * W);
-  if (n_chunks > 64) return TKV_E_UNSUPPORTED;
+  const int n_chunks = (max_att + 32 * kAttnWaves - 1) / (32 * kAttnWaves);
+  if (n_chunks > 64) return TKV_E_UNSUPPORTED;  // the partials' slots
   // partials live behind the Top-K scratch so that one workspace serves both calls
   float* parts = tkv::carve_sparse_ws(d, workspace).parts;
   p.q = (const __half*)q;
@@ -467,40 +431,13 @@ int32_t sparse_attn_launch(const tkv_sparse_desc* d, const tkv_sparse_cache* c, 
   p.n_sink = d->n_sink;
   p.n_window = d->n_window;
   p.n_chunks = n_chunks;
-  hipStream_t s = (hipStream_t)stream;
-  const bool big_group = d->n_q_heads / d->n_kv_heads > 4;  // 5 to 8 query heads per KV head
-  p.kv_host = nullptr;
-  p.topk_idx = nullptr;
-  p.capacity = d->capacity;
   p.arrivals = tkv::carve_sparse_ws(d, workspace).ctrl;  // word 4 of each head's 8 control words
   p.out = (__half*)out;
-  if (topk_idx_fused) {
-    const void* host_dev = nullptr;
-    st = tkv::device_view(c->kv_host, tkv::kDevHostOnly, &host_dev);
-    if (st != TKV_OK) return st;
-    p.kv_host = (const __half*)host_dev;
-    p.topk_idx = topk_idx_fused;
-    // Groups of up to 4 query heads: one workgroup per head whose 16 waves keep two passes of
-    // rows in flight each (the attention phase of tkv_sparse_decode): the link-bound loop without
-    // a cross-workgroup merge behind it.
-    st = tkv::launch_fetch_attn(d, p.lens, p.q, topk_idx_fused, topk_count, p.kv_host, p.kv_local, p.out, p.scale2, s);
-    if (st != TKV_E_UNSUPPORTED) return st;
-    static const bool lds_ok =
-        hipFuncSetAttribute(reinterpret_cast<const void*>(&sparse_attn_kernel<true, 4>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, kAttnMaxWaves * 32 * kRowPitch) == hipSuccess &&
-        hipFuncSetAttribute(reinterpret_cast<const void*>(&sparse_attn_kernel<true, 8>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, kAttnMaxWaves * 32 * kRowPitch) == hipSuccess;
-    if (!lds_ok) return TKV_E_HIP;
-    const dim3 grid(n_chunks, d->n_kv_heads, d->batch);
-    if (big_group) {
-      TKV_LAUNCH((sparse_attn_kernel<true, 8>), grid, 64 * W, W * 32 * kRowPitch, s, p);
-    } else {
-      TKV_LAUNCH((sparse_attn_kernel<true, 4>), grid, 64 * W, W * 32 * kRowPitch, s, p);
-    }
-  } else if (big_group) {
-    TKV_LAUNCH((sparse_attn_kernel<false, 8>), dim3(n_chunks, d->n_kv_heads, d->batch), 64 * W, 0, s, p);
+  const dim3 grid(n_chunks, d->n_kv_heads, d->batch);
+  if (d->n_q_heads / d->n_kv_heads > 4) {  // 5 to 8 query heads per KV head
+    TKV_LAUNCH(sparse_attn_kernel<8>, grid, kAttnThreads, 0, s, p);
   } else {
-    TKV_LAUNCH((sparse_attn_kernel<false, 4>), dim3(n_chunks, d->n_kv_heads, d->batch), 64 * W, 0, s, p);
+    TKV_LAUNCH(sparse_attn_kernel<4>, grid, kAttnThreads, 0, s, p);
   }
   return TKV_OK;
 }

@@ -30,6 +30,7 @@
 // call leaves them zero.
 // Inside a launch, data crosses workgroups only through device-scope stores, loads and
 // atomics, ordered by waiting for them to complete before an arrival counter is bumped.
+#include <algorithm>
 #include <type_traits>
 
 #include "tkv_common.h"
@@ -37,6 +38,8 @@
 namespace {
 
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
+// four fp16 of a row; the rows of the step's new tokens may lie at any fp16 address
+typedef uint32_t row_piece __attribute__((ext_vector_type(2), aligned(2)));
 
 constexpr int kThreads = 1024;
 constexpr int kWavesPerBlock = kThreads / 64;
@@ -51,11 +54,14 @@ constexpr int kListCap = 8192;  // candidate entries kept in LDS; further ones g
 // fused kernel: local / head histogram, list offsets, list (the channel-major variant also
 // stages its keys there to put them into token order)
 constexpr int kFusedLds = kBins * 4 + 1024 * 4 + kListCap * 8;
+// (the attention of 8 heads: its waves' results need a little more than the list)
+constexpr int kMergeLds8 = kBins * 4 + 1024 * 4 + kWavesPerBlock * 8 * (TKV_D + 4) * 4;
+static_assert(kWavesPerBlock * 4 * (TKV_D + 4) * 4 <= kListCap * 8 && kFusedLds <= kMergeLds8, "LDS of the attention phase");
 constexpr int kFastShift = 14;  // first radix digit of the common path: key bits [14, 32) minus a base
 constexpr int kCountBits = 14;  // a workgroup's list length (<= kMaxTpw) in its control word, L above it
 static_assert(kMaxTpw < (1 << kCountBits), "list length field");
 
-enum Ctrl { kDone2 = 1, kCtrlWords = 8 };
+enum Ctrl { kDone2 = 1, kDoneAtt = 4, kCtrlWords = 8 };
 
 struct TopkParams {
   const __half* summary;       // token-major [B][Hkv][capacity][d_s], or channel-major rows (below)
@@ -90,7 +96,7 @@ struct TopkParams {
   // heads' last workgroups are busy with the host link
   const __half* pf;
   // (ATT kernels) non-zero: topk_idx / topk_count are INPUTS, the selection of an earlier call;
-  // the launch (one workgroup per sequence and KV head) only fetches the rows and attends
+  // the launch only fetches the rows and attends, a head's rows shared by the gridDim.x workgroups
   int32_t given;
 #ifdef TKV_PHASE
   long long* prof;
@@ -263,11 +269,11 @@ __device__ inline void append_tokens(const TopkParams& p, int b, int h, int tid)
 
 // CM: the critical key cache is channel-major (one row of `capacity` tokens per channel):
 // a thread then scores four consecutive tokens, one 8-byte load per channel row.
-// GH: query heads per KV head the scores are summed over: 4 (groups of up to 4; their channels
-// sit in registers), or 8 (groups of 5 to 8: read from LDS term by term; no ATT form).
+// GH: query heads per KV head: 4 (groups of up to 4; their channels sit in registers while the
+// scores are computed), or 8 (groups of 5 to 8: read from LDS term by term).
 template <int DS, bool CM, bool ATT, int GH = 4>
 __global__ __launch_bounds__(kThreads) void score_select_kernel(TopkParams p) {
-  static_assert(GH == 4 || (GH == 8 && !ATT), "the attention phase holds four heads per lane");
+  static_assert(GH == 4 || GH == 8, "heads per lane");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   uint32_t* hist = reinterpret_cast<uint32_t*>(smem);                            // kBins words
   uint32_t* offs = reinterpret_cast<uint32_t*>(smem + kBins * 4);                // 1024 words
@@ -301,15 +307,16 @@ __global__ __launch_bounds__(kThreads) void score_select_kernel(TopkParams p) {
   // Sec. 4.2) and attention in the launch that selected them.  A wave takes 4 attended tokens
   // per pass and has the next two passes on their way: one load instruction per 512-byte row
   // (lanes 0..31 its K half, lanes 32..63 its V half: the request shape the host link serves
-  // fastest), the 4 x 4 logits are partial sums of 4 channels per lane, reduced over the 32 key
+  // fastest), the 4 x GH logits are partial sums of 4 channels per lane, reduced over the 32 key
   // lanes by a butterfly that halves the number of values with every exchange; online softmax
-  // per wave, the waves' results meet in LDS.  Rows of the step's new tokens come from the
+  // per wave, the waves' results meet in LDS.  A key lane's query channels and a value lane's
+  // weighted sums share registers (qo): a lane is only ever one of the two.  Rows of the step's new tokens come from the
   // call's k_new / v_new (another workgroup writes them to the cache meanwhile), everything else
   // that is resident from kv_local.  sel: the selected tokens in LDS (ascending), cnt of them.
   auto attend = [&](const int32_t* sel, int cnt) {
     constexpr int R = 4;  // rows per wave and pass
-    float* xs = reinterpret_cast<float*>(smem + kBins * 4) + wave * (R * 4);                   // [R][4] logits of this wave
-    float* mrg = reinterpret_cast<float*>(smem + kBins * 4 + 1024 * 4);                         // [waves][4][TKV_D + 4]
+    float* xs = reinterpret_cast<float*>(smem + kBins * 4) + wave * (R * GH);                  // [R][GH] logits of this wave
+    float* mrg = reinterpret_cast<float*>(smem + kBins * 4 + 1024 * 4);                         // [waves][GH][TKV_D + 4]
     const int n_sk = min(p.n_sink, n), w0 = max(n - p.n_window, n_sk);
     // order of the attended tokens: sinks, window, selected -- the resident rows first, worked on
     // while the first host rows are on their way
@@ -319,22 +326,20 @@ __global__ __launch_bounds__(kThreads) void score_select_kernel(TopkParams p) {
     const int n_loc = p.n_sink + p.n_window;
     const __half* local0 = p.att_local + bh * (size_t)n_loc * 2 * TKV_D;
     const int half = lane / 32, l32 = lane % 32;
-    float qv[4][4];  // key lanes: this lane's 4 channels of the 4 query heads, times scale2
+    // key lanes: this lane's 4 channels of the query heads, times scale2; value lanes: the weighted
+    // sums of this lane's 4 channels
+    float qo[GH][4];
+    // the logit that a key lane is left with (below), its head's running maximum, its sum of weights
+    const int y_mine = l32 / 8, j_mine = GH == 8 ? l32 % 8 : (l32 / 2) % 4;
+    float m_run = -INFINITY, l_run = 0.f;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < GH; ++j) {
       uint2 w = make_uint2(0u, 0u);
-      if (j < G && half == 0) w = reinterpret_cast<const uint2*>(p.q + ((size_t)b * p.hq + (size_t)h * G + j) * TKV_D)[l32];
+      if (j < G && half == 0) __builtin_memcpy(&w, p.q + ((size_t)b * p.hq + (size_t)h * G + j) * TKV_D + 4 * l32, 8);
       const uint32_t wx = w.x, wy = w.y;
       const half2_t a = __builtin_bit_cast(half2_t, wx), c = __builtin_bit_cast(half2_t, wy);
-      qv[j][0] = (float)a[0] * p.att_scale2, qv[j][1] = (float)a[1] * p.att_scale2;
-      qv[j][2] = (float)c[0] * p.att_scale2, qv[j][3] = (float)c[1] * p.att_scale2;
-    }
-    float m_run[4], l_run[4], o_run[4][4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      m_run[j] = -INFINITY, l_run[j] = 0.f;
-#pragma unroll
-      for (int c = 0; c < 4; ++c) o_run[j][c] = 0.f;
+      qo[j][0] = (float)a[0] * p.att_scale2, qo[j][1] = (float)a[1] * p.att_scale2;
+      qo[j][2] = (float)c[0] * p.att_scale2, qo[j][3] = (float)c[1] * p.att_scale2;
     }
     // the R rows of the pass that starts at attended token i0: lane y < R works out where row
     // i0 + y lives (its K half and its V half), then one load instruction per row
@@ -374,25 +379,24 @@ __global__ __launch_bounds__(kThreads) void score_select_kernel(TopkParams p) {
         const uint64_t va = (uint64_t)read_lane((uint32_t)(uintptr_t)vp, y) | ((uint64_t)read_lane((uint32_t)((uintptr_t)vp >> 32), y) << 32);
         // (named as global memory, which pinned host memory is too: loads through generic pointers
         // cannot be counted one by one, and every wait for a row would wait for all rows in flight)
-        const tkv::tkv_u32x2 w = reinterpret_cast<const __attribute__((address_space(1))) tkv::tkv_u32x2*>(half == 0 ? ka : va)[l32];
+        const row_piece w = reinterpret_cast<const __attribute__((address_space(1))) row_piece*>(half == 0 ? ka : va)[l32];
         r[y] = make_uint2(w.x, w.y);
       }
     };
     // one pass: the wave's R rows that start at attended token i0
     auto pass = [&](int i0, const uint2 (&r)[R]) {
-      // partial logits of this lane's 4 channels: v[4 y + j]
-      float v[R * 4];
+      // partial logits of this lane's 4 channels: v[GH y + j]
+      float v[R * GH];
 #pragma unroll
       for (int y = 0; y < R; ++y) {
         const uint32_t rx = r[y].x, ry = r[y].y;  // (copied out: a bit cast applied to a vector element reads element 0)
         const half2_t a = __builtin_bit_cast(half2_t, rx), c = __builtin_bit_cast(half2_t, ry);
         const float k0 = (float)a[0], k1 = (float)a[1], k2 = (float)c[0], k3 = (float)c[1];
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-          v[4 * y + j] = __builtin_fmaf(qv[j][3], k3, __builtin_fmaf(qv[j][2], k2, __builtin_fmaf(qv[j][1], k1, qv[j][0] * k0)));
+        for (int j = 0; j < GH; ++j)
+          v[GH * y + j] = __builtin_fmaf(qo[j][3], k3, __builtin_fmaf(qo[j][2], k2, __builtin_fmaf(qo[j][1], k1, qo[j][0] * k0)));
       }
       // sum over the 32 key lanes: every exchange halves the values a lane is responsible for
-      int base = 0;
       auto halve = [&](auto dist, auto count) {  // lanes that differ in bit `dist` split `2 count` values between them
         constexpr int D = decltype(dist)::value, C = decltype(count)::value;
         const bool up = (lane & D) != 0;
@@ -402,57 +406,62 @@ __global__ __launch_bounds__(kThreads) void score_select_kernel(TopkParams p) {
             const float lo = v[x], hi = v[x + C];
             v[x] = (up ? hi : lo) + swap_xor<D>(up ? lo : hi);
           }
-          base += up ? C : 0;
         } else {  // one value left per lane: both partners keep the sum
           v[0] += swap_xor<D>(v[0]);
         }
       };
       using std::integral_constant;
-      halve(integral_constant<int, 16>{}, integral_constant<int, R * 2>{});
-      halve(integral_constant<int, 8>{}, integral_constant<int, R>{});
-      halve(integral_constant<int, 4>{}, integral_constant<int, R / 2>{});
-      halve(integral_constant<int, 2>{}, integral_constant<int, R / 4>{});
-      halve(integral_constant<int, 1>{}, integral_constant<int, R / 8>{});
-      if (half == 0) {  // logits base, base + 1, ... of this key lane
+      constexpr int V = R * GH;
+      static_assert(V == 16 || V == 32, "one logit per key lane, or per pair of them");
+      halve(integral_constant<int, 16>{}, integral_constant<int, V / 2>{});
+      halve(integral_constant<int, 8>{}, integral_constant<int, V / 4>{});
+      halve(integral_constant<int, 4>{}, integral_constant<int, V / 8>{});
+      halve(integral_constant<int, 2>{}, integral_constant<int, V / 16>{});
+      halve(integral_constant<int, 1>{}, integral_constant<int, V / 32>{});
+      // Key lane l32 now holds the logit of row y_mine and head j_mine (GH = 4: two lanes each).
+      // Online softmax there, once per logit: running maximum of the head (the same in all of its
+      // lanes) and this lane's share of the sum of weights.
+      const float x = i0 + y_mine < n_att ? v[0] : -INFINITY;
+      float mx = fmaxf(x, swap_xor<8>(x));  // (rows differ in lane bits 3 and 4)
+      mx = fmaxf(mx, swap_xor<16>(mx));
+      // (a wave's LDS operations execute in order: every read below sees the writes above it)
+      if ((uint32_t)__builtin_amdgcn_ballot_w64(mx > m_run) != 0u) {  // some head has a new maximum: its sums so far shrink
+        const float m_new = fmaxf(m_run, mx);
+        const float alpha = m_run == m_new ? 1.f : __builtin_amdgcn_exp2f(m_run - m_new);
+        l_run *= alpha;
+        m_run = m_new;
+        if (half == 0 && y_mine == 0) xs[j_mine] = alpha;
 #pragma unroll
-        for (int z = 0; z < (R >= 8 ? R / 8 : 1); ++z) xs[base + z] = v[z];
-      }
-      // (a wave's LDS operations execute in order: the reads below see the writes above)
-      // online softmax and weighted V sum; value lanes own 4 channels each
-      float xa[R * 4];  // logits [y][j]
+        for (int j4 = 0; j4 < GH; j4 += 4) {
+          const float4 t = *reinterpret_cast<const float4*>(xs + j4);
+          const float al[4] = {t.x, t.y, t.z, t.w};
 #pragma unroll
-      for (int z = 0; z < R; ++z) {
-        const float4 t = *reinterpret_cast<const float4*>(xs + 4 * z);
-        xa[4 * z] = t.x, xa[4 * z + 1] = t.y, xa[4 * z + 2] = t.z, xa[4 * z + 3] = t.w;
+          for (int jj = 0; jj < 4; ++jj) {
+            const float shrink = half != 0 ? al[jj] : 1.f;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) qo[j4 + jj][c] *= shrink;
+          }
+        }
       }
-      float vf[R][4];  // this lane's 4 channels of the rows (value lanes: of V)
+      const float pw = __builtin_amdgcn_exp2f(x - m_run);
+      l_run += pw;
+      if (half == 0) xs[GH * y_mine + j_mine] = pw;
+      // weighted V sum: value lanes own 4 channels each (key lanes add 0 to their qo)
 #pragma unroll
       for (int y = 0; y < R; ++y) {
-        const uint32_t rx = r[y].x, ry = r[y].y;
+        const uint32_t rx = half != 0 ? r[y].x : 0u, ry = half != 0 ? r[y].y : 0u;
         const half2_t a = __builtin_bit_cast(half2_t, rx), c = __builtin_bit_cast(half2_t, ry);
-        vf[y][0] = (float)a[0], vf[y][1] = (float)a[1], vf[y][2] = (float)c[0], vf[y][3] = (float)c[1];
-      }
+        const float v0 = (float)a[0], v1 = (float)a[1], v2 = (float)c[0], v3 = (float)c[1];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        float x[R], mx = -INFINITY;
+        for (int j4 = 0; j4 < GH; j4 += 4) {
+          const float4 t = *reinterpret_cast<const float4*>(xs + GH * y + j4);
+          const float w[4] = {t.x, t.y, t.z, t.w};
 #pragma unroll
-        for (int y = 0; y < R; ++y) {
-          x[y] = i0 + y < n_att ? xa[4 * y + j] : -INFINITY;
-          mx = fmaxf(mx, x[y]);
-        }
-        if (mx > m_run[j]) {  // (uniform over the wave) a new maximum: the sums so far shrink
-          const float alpha = __builtin_amdgcn_exp2f(m_run[j] - mx);
-          l_run[j] *= alpha;
-#pragma unroll
-          for (int c = 0; c < 4; ++c) o_run[j][c] *= alpha;
-          m_run[j] = mx;  // finite: the pass holds at least one token
-        }
-#pragma unroll
-        for (int y = 0; y < R; ++y) {
-          const float pw = __builtin_amdgcn_exp2f(x[y] - m_run[j]);
-          l_run[j] += pw;
-#pragma unroll
-          for (int c = 0; c < 4; ++c) o_run[j][c] = __builtin_fmaf(pw, vf[y][c], o_run[j][c]);
+          for (int jj = 0; jj < 4; ++jj) {
+            float* o = qo[j4 + jj];
+            o[0] = __builtin_fmaf(w[jj], v0, o[0]), o[1] = __builtin_fmaf(w[jj], v1, o[1]);
+            o[2] = __builtin_fmaf(w[jj], v2, o[2]), o[3] = __builtin_fmaf(w[jj], v3, o[3]);
+          }
         }
       }
     };
@@ -460,56 +469,79 @@ __global__ __launch_bounds__(kThreads) void score_select_kernel(TopkParams p) {
     // way while it computes leaves the host link idle for that long.  Every request is issued
     // whether or not the pass exists (past the end: the head's first resident row, unused), so
     // that the number of loads behind the rows a pass waits for is the same on every path.
-    constexpr int kStride = kWavesPerBlock * R;
+    // (a given selection may be shared by several workgroups, a pass of all their waves after the other)
+    const int n_parts = p.given != 0 ? (int)gridDim.x : 1, part = p.given != 0 ? (int)blockIdx.x : 0;
+    const int first = (part * kWavesPerBlock + wave) * R, stride = n_parts * kWavesPerBlock * R;
     uint2 ra[R], rb[R];
     TKV_PH(8);
-    fetch(wave * R, ra);
-    fetch(wave * R + kStride, rb);
-    for (int i0 = wave * R; i0 < n_att; i0 += 2 * kStride) {
+    fetch(first, ra);
+    fetch(first + stride, rb);
+    for (int i0 = first; i0 < n_att; i0 += 2 * stride) {
       pass(i0, ra);
-      fetch(i0 + 2 * kStride, ra);
-      if (i0 + kStride < n_att) pass(i0 + kStride, rb);
-      fetch(i0 + 3 * kStride, rb);
+      fetch(i0 + 2 * stride, ra);
+      if (i0 + stride < n_att) pass(i0 + stride, rb);
+      fetch(i0 + 3 * stride, rb);
     }
     TKV_PH(9);
     TKV_PHW(16 + wave);
     // The waves' results meet in the list area, which nothing has used since the selection.
+    l_run += swap_xor<8>(l_run);
+    l_run += swap_xor<16>(l_run);
+    if (half == 0 && y_mine == 0)
+      *reinterpret_cast<float2*>(mrg + (wave * GH + j_mine) * (TKV_D + 4)) = make_float2(m_run, l_run);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      float* dst = mrg + (wave * 4 + j) * (TKV_D + 4);
-      if (lane == 0) *reinterpret_cast<float2*>(dst) = make_float2(m_run[j], l_run[j]);
-      if (half == 1) *reinterpret_cast<float4*>(dst + 4 + 4 * l32) = make_float4(o_run[j][0], o_run[j][1], o_run[j][2], o_run[j][3]);
+    for (int j = 0; j < GH; ++j) {
+      float* dst = mrg + (wave * GH + j) * (TKV_D + 4);
+      if (half == 1) *reinterpret_cast<float4*>(dst + 4 + 4 * l32) = make_float4(qo[j][0], qo[j][1], qo[j][2], qo[j][3]);
     }
     __syncthreads();
     TKV_PH(10);
     // one thread per query head and four channels: 16-byte reads of the waves' partial sums,
     // every element summed over the waves in ascending order
-    if (tid < 4 * (TKV_D / 4) && tid / (TKV_D / 4) < G) {
+    if (tid < GH * (TKV_D / 4) && tid / (TKV_D / 4) < G) {
       const int j = tid / (TKV_D / 4), c4 = tid % (TKV_D / 4);
       float2 ml[kWavesPerBlock];
       float M = -INFINITY;
 #pragma unroll
       for (int w = 0; w < kWavesPerBlock; ++w) {
-        ml[w] = *reinterpret_cast<const float2*>(mrg + (w * 4 + j) * (TKV_D + 4));
+        ml[w] = *reinterpret_cast<const float2*>(mrg + (w * GH + j) * (TKV_D + 4));
         M = fmaxf(M, ml[w].x);
       }
       float L = 0.f, O[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int w = 0; w < kWavesPerBlock; ++w) {
-        const float4 o = *reinterpret_cast<const float4*>(mrg + (w * 4 + j) * (TKV_D + 4) + 4 + 4 * c4);
+        const float4 o = *reinterpret_cast<const float4*>(mrg + (w * GH + j) * (TKV_D + 4) + 4 + 4 * c4);
         const float wgt = ml[w].x == -INFINITY ? 0.f : exp2f(ml[w].x - M);
         L = __builtin_fmaf(ml[w].y, wgt, L);
         O[0] = __builtin_fmaf(o.x, wgt, O[0]), O[1] = __builtin_fmaf(o.y, wgt, O[1]);
         O[2] = __builtin_fmaf(o.z, wgt, O[2]), O[3] = __builtin_fmaf(o.w, wgt, O[3]);
       }
-      __half r[4];
+      if (n_parts == 1) {
+        __half r[4];
 #pragma unroll
-      for (int c = 0; c < 4; ++c) r[c] = __float2half_rn(L > 0.f ? O[c] / L : 0.f);
-      uint2 packed;
-      __builtin_memcpy(&packed, r, 8);
-      *reinterpret_cast<uint2*>(p.att_out + ((size_t)b * p.hq + (size_t)h * G + j) * TKV_D + 4 * c4) = packed;
+        for (int c = 0; c < 4; ++c) r[c] = __float2half_rn(L > 0.f ? O[c] / L : 0.f);
+        __builtin_memcpy(p.att_out + ((size_t)b * p.hq + (size_t)h * G + j) * TKV_D + 4 * c4, r, 8);
+      } else {
+        // device-scope stores: visible to the merging workgroup without a cache write-back
+        uint32_t* dst = reinterpret_cast<uint32_t*>(p.ws.parts + (((size_t)b * p.hq + (size_t)h * G + j) * n_parts + part) * TKV_PART_STRIDE);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) st_agent(dst + TKV_PART_O + 4 * c4 + c, __float_as_uint(O[c]));
+        if (c4 == 0) st_agent(dst, __float_as_uint(M)), st_agent(dst + 1, __float_as_uint(L));
+      }
     }
     TKV_PH(11);
+    if (n_parts == 1) return;
+    // the last workgroup of this (sequence, KV head) to arrive merges the partials, which are
+    // ordered before the arrival counter by waiting for their stores to complete
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    uint32_t* arrive = p.ws.ctrl + bh * kCtrlWords + kDoneAtt;
+    if (tid == 0) scratch[0] = atomicAdd(arrive, 1u) == (uint32_t)n_parts - 1u;
+    __syncthreads();
+    if (scratch[0] == 0u) return;
+    if (tid == 0) st_agent(arrive, 0u);  // left zero for the next call
+    tkv::merge_chunks(p.ws.parts + ((size_t)b * p.hq + (size_t)h * G) * n_parts * TKV_PART_STRIDE, G, n_parts,
+                      p.att_out + ((size_t)b * p.hq + (size_t)h * G) * TKV_D, mrg, tid, kThreads);
   };
 
   // Scoring, listing and, in the head's last workgroup, the selection.  Returns true in the
@@ -517,7 +549,6 @@ __global__ __launch_bounds__(kThreads) void score_select_kernel(TopkParams p) {
   int given_cnt = 0;
   auto select_tokens = [&]() -> bool {
     if (ATT && p.given != 0) {  // selected by an earlier call: copy the list, then fetch and attend
-      if (blockIdx.x != 0) return false;
       given_cnt = max(0, min(p.topk_count[bh], p.top_k));
       for (int i = tid; i < given_cnt; i += kThreads) sel_s[i] = out[i];
       return true;
@@ -1066,10 +1097,11 @@ namespace {
 template <int DS, bool CM, bool ATT, int GH = 4>
 int32_t launch_fused(const TopkParams& p, dim3 grid, hipStream_t s) {
   // more than 64 KiB of dynamic LDS needs an opt-in, once per kernel
+  constexpr int lds = ATT && GH == 8 ? kMergeLds8 : kFusedLds;
   static const bool lds_ok = hipFuncSetAttribute(reinterpret_cast<const void*>(&score_select_kernel<DS, CM, ATT, GH>),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, kFusedLds) == hipSuccess;
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, lds) == hipSuccess;
   if (!lds_ok) return TKV_E_HIP;
-  TKV_LAUNCH((score_select_kernel<DS, CM, ATT, GH>), grid, kThreads, kFusedLds, s, p);
+  TKV_LAUNCH((score_select_kernel<DS, CM, ATT, GH>), grid, kThreads, lds, s, p);
   return TKV_OK;
 }
 
@@ -1167,15 +1199,16 @@ int32_t estimate_topk_launch(const tkv_sparse_desc* d, const tkv_sparse_cache* c
   if (nblk >= 1024) return TKV_E_UNSUPPORTED;  // 4 Mi tokens per sequence
   const bool big_group = d->n_q_heads / d->n_kv_heads > 4;  // 5 to 8 query heads per KV head
   if (att != nullptr) {  // token-major summary only
-    if (big_group) return TKV_E_UNSUPPORTED;  // (the attention phase holds four heads per lane)
     p.att_host = att->att_host;
     p.att_local = att->att_local;
     p.att_out = att->att_out;
     p.att_scale2 = att->att_scale2;
     p.pf = att->pf;
-    if (d->n_channels == 16) return launch_fused<16, false, true>(p, grid, s);
-    if (d->n_channels == 12) return launch_fused<12, false, true>(p, grid, s);
-    return launch_fused<8, false, true>(p, grid, s);
+    if (d->n_channels == 16)
+      return big_group ? launch_fused<16, false, true, 8>(p, grid, s) : launch_fused<16, false, true>(p, grid, s);
+    if (d->n_channels == 12)
+      return big_group ? launch_fused<12, false, true, 8>(p, grid, s) : launch_fused<12, false, true>(p, grid, s);
+    return big_group ? launch_fused<8, false, true, 8>(p, grid, s) : launch_fused<8, false, true>(p, grid, s);
   }
   if (big_group) {
     if (d->n_channels == 16)
@@ -1192,15 +1225,30 @@ int32_t estimate_topk_launch(const tkv_sparse_desc* d, const tkv_sparse_cache* c
 }
 }  // namespace
 
+namespace {
+// Workgroups that share a head's attended tokens where the selection is given.  One keeps 64 KiB of rows
+// in flight and works 0.027 us per row (0.053 with 8 heads), against 0.009 us per row and head on the host
+// link: with fewer heads in the launch than query heads a lane holds, a workgroup per head is slower than
+// the link and a head's rows go to several, at the price of a merge across them (about 3 us).  Measured, us
+// per call, one / 16 workgroups per head: 8/1 heads, 1024 tokens 60.8 / 21.2, 128 tokens 17.1 / 16.1; 16/2,
+// 256 tokens 23.8 / 17.5; 32/4, 896 tokens 57.7 / 43.7, 512 tokens 36.5 / 29.9, 128 tokens 17.4 / 17.5; 64/8, 1024 tokens
+// 82.9 / 84.8; 4/1, 1024 tokens 40.2 / 20.4, 128 tokens 13.0 / 14.5; 16/4, 1024 tokens 47.3 / 47.2; 32/8,
+// 1024 tokens 80.8 / 83.5.
+int fetch_workgroups(const tkv_sparse_desc* d) {
+  const int heads_per_lane = d->n_q_heads / d->n_kv_heads > 4 ? 8 : 4;
+  const int max_att = d->n_sink + d->top_k + d->n_window;
+  if (d->batch * d->n_kv_heads >= heads_per_lane || max_att <= 256) return 1;
+  return std::min(16, (max_att + 63) / 64);  // at least one pass of 16 waves x 4 rows each
+}
+}  // namespace
+
 namespace tkv {
 // Fetch of the rows of a selection made earlier (topk_idx / topk_count of the same descriptor)
-// from the pinned host cache and exact attention, by the attention phase of the one-launch step:
-// one workgroup per (sequence, KV head).  Groups of up to 4 query heads, top_k <= 8192 (the list
-// is staged in LDS); TKV_E_UNSUPPORTED otherwise, nothing launched.
+// from the pinned host cache and exact attention, by the attention phase of the one-launch step.
 int32_t launch_fetch_attn(const tkv_sparse_desc* d, const TkvSeqLens& lens, const __half* q, const int32_t* topk_idx,
                           const int32_t* topk_count, const __half* host_rows, const __half* local_rows, __half* out,
-                          float scale2, hipStream_t s) {
-  if (d->n_q_heads / d->n_kv_heads > 4 || d->top_k > kBins) return TKV_E_UNSUPPORTED;
+                          float scale2, void* workspace, hipStream_t s) {
+  static_assert(kBins >= 4096, "any descriptor's list is staged in LDS");
   TopkParams p = {};
   p.q = q;
   p.topk_idx = const_cast<int32_t*>(topk_idx);
@@ -1218,7 +1266,10 @@ int32_t launch_fetch_attn(const tkv_sparse_desc* d, const TkvSeqLens& lens, cons
   p.att_out = out;
   p.att_scale2 = scale2;
   p.given = 1;
-  return launch_fused<16, false, true>(p, dim3(1, d->n_kv_heads, d->batch), s);
+  p.ws = carve_sparse_ws(d, workspace);
+  const dim3 grid(fetch_workgroups(d), d->n_kv_heads, d->batch);
+  if (d->n_q_heads / d->n_kv_heads > 4) return launch_fused<8, false, true, 8>(p, grid, s);
+  return launch_fused<16, false, true>(p, grid, s);
 }
 }  // namespace tkv
 
@@ -1300,10 +1351,10 @@ extern "C" int32_t tkv_sparse_decode(const tkv_sparse_desc* d, tkv_sparse_cache*
   if ((uintptr_t)next_key_summary % 16 != 0) return TKV_E_INVAL;
   if (n_new < 0 || n_new > 8 || n_new > d->n_window) return TKV_E_INVAL;
   if (n_new > 0 && (!k_new || !v_new)) return TKV_E_INVAL;
-  if (d->n_q_heads / d->n_kv_heads > 4) {
-    // Groups of 5 to 8 query heads: the attention phase of the one-launch kernel holds four heads
-    // per lane.  Two launches instead: append + scoring + Top-K, then fetch + attention (the
-    // selection's outputs are the second launch's inputs; `staging` is not used on one stream).
+  if (fetch_workgroups(d) > 1) {
+    // Few heads, many rows: the workgroup that selects a head's tokens would be slower than the link, so a
+    // second launch shares the rows out (one launch / two, us: 32/4 heads, 896 tokens 69.2 / 56.8; 16/2,
+    // 256 tokens 34.7 / 29.7; 4/1, 1024 tokens 53.1 / 33.5; below the rule's line 32/4, 128 tokens 28.0 / 29.5).
     if (!q || !topk_idx || !topk_count || !workspace) return TKV_E_INVAL;
     st = n_new > 0 ? tkv_sparse_append_estimate_topk(d, c, k_new, v_new, n_new, n_valid_host, q, topk_idx, topk_count,
                                                      workspace, workspace_bytes, stream)

@@ -169,7 +169,7 @@ def test_groups_of_up_to_eight_query_heads(shape, n_channels):
         _check_layer(layer, 0, inp, ch, q, layer.gather_attn(q, SM, gather_stream=side.cuda_stream))
         layer.gather()
         _check_layer(layer, 0, inp, ch, q, layer.attn(q, SM))
-        # tkv_sparse_decode: one launch for groups of up to 4, two launches behind the same call above
+        # tkv_sparse_decode: one launch, or two behind the same call (few heads, many rows)
         layer.topk_idx.fill_(-7)
         _check_layer(layer, 0, inp, ch, q, layer.decode(q, SM))
         # ... and with the step's append: one more token, then the same checks on the grown prefix
