@@ -27,37 +27,46 @@ struct AppendParams {
 // and a launch that is no wider than the link needs leaves the rest of the machine to the
 // kernels of other streams (the next layers' computation) instead of parking tens of thousands
 // of workgroups that wait for the link on every compute unit.
+// A short append (a decode step) is bound by the chain of round trips of a workgroup's loops instead:
+// there every KV head has a workgroup of its own (gridDim.z == hkv).  One token, Stage 1 buffers updated too, us
+// per call in a graph, one workgroup / one per head: 32 heads 9.3 / 2.5, 8 heads 3.8 / 2.4, 4 heads 3.6 / 2.3; 8 tokens of
+// 32 heads 11.0 / 4.7.  Without the Stage 1 buffers: 32 heads 3.3 / 2.3, 4 heads the same.
 constexpr int kAppendGrid = 1024;
+constexpr int kAppendByHead = 8;  // appends up to this long: a workgroup per token and head
 __global__ __launch_bounds__(256) void sparse_append_kernel(AppendParams p) {
   const int b = blockIdx.y, tid = threadIdx.x;
+  const bool by_head = gridDim.z > 1;
+  const int h0 = by_head ? blockIdx.z : 0, n_heads = by_head ? 1 : p.hkv;
   for (int i = blockIdx.x; i < p.n_add.n[b]; i += gridDim.x) {
   const int n0 = p.n_old.n[b], n1 = n0 + p.n_add.n[b];
   const int tok = n0 + i;
-  const int chunks = p.hkv * 16;
+  const int chunks = n_heads * 16;
   const bool local = tok < p.n_sink || tok >= n1 - p.n_window;
   const int slot = tok < p.n_sink ? tok : p.n_sink + tok % p.n_window;
+  const size_t row0 = ((size_t)b * p.n_stride + i) * p.hkv + h0;  // the first head's row of the token
+  const size_t bh0 = (size_t)b * p.hkv + h0;
   for (int x = tid; x < 2 * chunks; x += 256) {
     const int kv = x / chunks, rem = x % chunks, h = rem / 16, part = rem % 16;
-    const size_t bh = (size_t)b * p.hkv + h;
-    const uint4 v = reinterpret_cast<const uint4*>((kv ? p.v_new : p.k_new) +
-                                                   (((size_t)b * p.n_stride + i) * p.hkv + h) * TKV_D)[part];
+    const size_t bh = bh0 + h;
+    const uint4 v = reinterpret_cast<const uint4*>((kv ? p.v_new : p.k_new) + (row0 + h) * TKV_D)[part];
     reinterpret_cast<uint4*>(p.kv_host + ((bh * p.capacity + tok) * 2 + kv) * TKV_D)[part] = v;
     if (local)
       reinterpret_cast<uint4*>(p.kv_local + ((bh * (p.n_sink + p.n_window) + slot) * 2 + kv) * TKV_D)[part] = v;
   }
-  for (int x = tid; x < p.hkv * p.ds; x += 256) {
+  // (each loop starts at another wave, so that a head's three chains run side by side)
+  for (int x = (tid + 64) % 256; x < n_heads * p.ds; x += 256) {
     const int h = x / p.ds, ci = x % p.ds;
-    const size_t bh = (size_t)b * p.hkv + h;
+    const size_t bh = bh0 + h;
     const int c = p.channel_idx[bh * p.ds + ci];
-    p.summary[(bh * p.capacity + tok) * p.ds + ci] = p.k_new[(((size_t)b * p.n_stride + i) * p.hkv + h) * TKV_D + c];
+    p.summary[(bh * p.capacity + tok) * p.ds + ci] = p.k_new[(row0 + h) * TKV_D + c];
   }
   if (p.keys_cm != nullptr) {
     // Stage 1 (Sec. 4.2): the token's column of the channel-major keys and the running maxima
     // of Eq. 10 (bit patterns of non-negative floats order like integers)
-    for (int x = tid; x < p.hkv * TKV_D; x += 256) {
+    for (int x = (tid + 192) % 256; x < n_heads * TKV_D; x += 256) {
       const int h = x / TKV_D, c = x % TKV_D;
-      const size_t bh = (size_t)b * p.hkv + h;
-      const __half v = p.k_new[(((size_t)b * p.n_stride + i) * p.hkv + h) * TKV_D + c];
+      const size_t bh = bh0 + h;
+      const __half v = p.k_new[(row0 + h) * TKV_D + c];
       p.keys_cm[(bh * TKV_D + c) * (size_t)p.capacity + tok] = v;
       atomicMax(reinterpret_cast<uint32_t*>(p.k_absmax + bh * TKV_D + c), __float_as_uint(fabsf(__half2float(v))));
     }
@@ -340,7 +349,8 @@ extern "C" int32_t tkv_sparse_append_dynamic(const tkv_sparse_desc* d, tkv_spars
   p.n_window = d->n_window;
   p.capacity = d->capacity;
   p.n_stride = n_new;
-  TKV_LAUNCH(sparse_append_kernel, dim3(n_new < kAppendGrid ? n_new : kAppendGrid, d->batch), 256, 0, (hipStream_t)stream, p);
+  const dim3 grid(n_new < kAppendGrid ? n_new : kAppendGrid, d->batch, n_new <= kAppendByHead ? d->n_kv_heads : 1);
+  TKV_LAUNCH(sparse_append_kernel, grid, 256, 0, (hipStream_t)stream, p);
   for (int b = 0; b < d->batch; ++b) c->seq_len_host[b] += p.n_add.n[b];
   return TKV_OK;
 }
