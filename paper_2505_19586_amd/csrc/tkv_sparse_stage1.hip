@@ -56,14 +56,15 @@ struct SelectParams {
   int32_t hq, hkv, ds;
 };
 
-// One workgroup of 128 threads per (sequence, KV head); thread c owns channel c.
-__global__ __launch_bounds__(TKV_D) void select_channels_kernel(SelectParams p) {
+// One workgroup per (sequence, KV head).
+constexpr int kSelectThreads = 256;
+__global__ __launch_bounds__(kSelectThreads) void select_channels_kernel(SelectParams p) {
   __shared__ float s_s[TKV_D];
   __shared__ uint32_t s_sel[TKV_D];
   const int b = blockIdx.y, h = blockIdx.x;
   const int G = p.hq / p.hkv;
   const size_t bh = (size_t)b * p.hkv + h;
-  tkv::select_channels_block(p.q_hat + ((size_t)b * p.hq + (size_t)h * G) * TKV_D, G, p.k_absmax + bh * TKV_D, p.ds,
+  tkv::select_channels_block<kSelectThreads>(p.q_hat + ((size_t)b * p.hq + (size_t)h * G) * TKV_D, G, p.k_absmax + bh * TKV_D, p.ds,
                              s_s, s_sel, p.channel_idx + bh * p.ds, nullptr);
 }
 
@@ -160,7 +161,7 @@ extern "C" int32_t tkv_sparse_select_channels(const tkv_sparse_desc* d, const tk
   p.hq = d->n_q_heads;
   p.hkv = d->n_kv_heads;
   p.ds = d->n_channels;
-  TKV_LAUNCH(select_channels_kernel, dim3(d->n_kv_heads, d->batch), TKV_D, 0, (hipStream_t)stream, p);
+  TKV_LAUNCH(select_channels_kernel, dim3(d->n_kv_heads, d->batch), kSelectThreads, 0, (hipStream_t)stream, p);
   return TKV_OK;
 }
 

@@ -578,7 +578,7 @@ __global__ __launch_bounds__(kThreads) void score_select_kernel(TopkParams p) {
         const uint32_t v = j < G ? reinterpret_cast<const uint32_t*>(p.q + ((size_t)b * p.hq + (size_t)h * G + j) * TKV_D)[w] : 0u;
         reinterpret_cast<uint32_t*>(&q_all[j][0])[w] = v;
       }
-      tkv::select_channels_block(p.q_hat + ((size_t)b * p.hq + (size_t)h * G) * TKV_D, G, p.k_absmax + bh * TKV_D, DS,
+      tkv::select_channels_block<kThreads>(p.q_hat + ((size_t)b * p.hq + (size_t)h * G) * TKV_D, G, p.k_absmax + bh * TKV_D, DS,
                                  s_s, s_sel, s_chan, blockIdx.x == 0 ? p.channel_out + bh * DS : nullptr);
       if (tid < GH * DS) {
         const int j = tid / DS, i = tid % DS;
