@@ -820,14 +820,21 @@ __global__ __launch_bounds__(kThreads) void score_select_kernel(TopkParams p) {
 
     // ---- the head's last workgroup.  One round of device-scope loads brings the workgroups'
     // control words and the first `spec` entries of every list (entry e = i * kThreads + tid of
-    // the round belongs to share e / spec, so ascending e is token order); spec is a power of two
-    // a quarter above the nominal list length, the round never fetches more than kSub entries per thread.
-    int spec_shift = 0;
+    // the round belongs to share e / spec, so ascending e is token order).  A list holds the nominal
+    // length (its workgroup's r) and the rest of the bin that the r-th key lies in: at z standard
+    // deviations and bins of up to 1/16 of the value r z^2 / 16 more on average, up to 0.45 r, give or take; hence
+    // spec = 1.5 times the nominal length plus 12.  (Powers of two from 1.25 times the nominal
+    // length were overrun now and then, and the slow path costs 2 to 20 us: 32/8 heads, 131000 tokens, k = 128 31.1 -> 14.4 us,
+    // k = 512 32 to 35 -> 15.0; 32/4 heads, k = 256 32.6 -> 14.7.)  The round never fetches more than kSub entries per thread.
+    uint32_t spec;
     {
       const uint32_t nominal = (3u * k) / (2u * (uint32_t)nblk) + 16u;
-      while ((1u << spec_shift) < nominal + nominal / 4u) ++spec_shift;
-      while (spec_shift > 0 && ((size_t)nblk << spec_shift) > (size_t)kSub * kThreads) --spec_shift;
+      spec = min(nominal * 3u / 2u + 12u, (uint32_t)(kSub * kThreads) / (uint32_t)nblk);
     }
+    // e / spec for e < kSub * kThreads: the quotient is at least 1 / (2 spec) away from an integer, thousands
+    // of times the rounding errors
+    const float spec_rcp = 1.0f / (float)spec;
+    auto share_of = [&](uint32_t e) { return (uint32_t)(((float)e + 0.5f) * spec_rcp); };
     uint32_t ek[kSub], et[kSub];  // this thread's entries: key and token
     bool fits;
     {
@@ -835,7 +842,7 @@ __global__ __launch_bounds__(kThreads) void score_select_kernel(TopkParams p) {
       const uint32_t cw = cb.x1((uint32_t)tid * 4u);  // 0 beyond the head's workgroups (fewer than 1024)
   #pragma unroll
       for (int i = 0; i < kSub; ++i) {
-        const uint32_t e = (uint32_t)(i * kThreads + tid), x = e >> spec_shift, off = e & ((1u << spec_shift) - 1u);
+        const uint32_t e = (uint32_t)(i * kThreads + tid), x = share_of(e), off = e - x * spec;
         const bool want = x < (uint32_t)nblk && off < (uint32_t)p.tpw;
         const tkv::tkv_u32x2 v = lb.x2(want ? (x * (uint32_t)p.tpw + off) * 8u : tkv::AgentBuf::kNone);
         ek[i] = v.x;
@@ -857,7 +864,7 @@ __global__ __launch_bounds__(kThreads) void score_select_kernel(TopkParams p) {
   #pragma unroll
       for (int m = 32; m >= 1; m >>= 1) ln = min(ln, (uint32_t)__shfl_xor((int)ln, m, 64));
       if (lane == 0) atomicMin(&s_lmin, ln);
-      fits = __syncthreads_or(len > (1u << spec_shift) ? 1 : 0) == 0;
+      fits = __syncthreads_or(len > spec ? 1 : 0) == 0;
     }
     TKV_PH(4);
 
@@ -937,18 +944,26 @@ __global__ __launch_bounds__(kThreads) void score_select_kernel(TopkParams p) {
       // ---- every list entry is in a register of some thread
   #pragma unroll
       for (int i = 0; i < kSub; ++i) {
-        const uint32_t e = (uint32_t)(i * kThreads + tid), x = e >> spec_shift, off = e & ((1u << spec_shift) - 1u);
+        const uint32_t e = (uint32_t)(i * kThreads + tid), x = share_of(e), off = e - x * spec;
         if (!(x < (uint32_t)nblk && off < lens[x])) ek[i] = 0u;  // beyond the list: below every key
       }
       uint32_t T, take;
-      const bool found = kth_key([&](auto f) {
+      auto each_key = [&](auto f) {
   #pragma unroll
         for (int i = 0; i < kSub; ++i) f(ek[i]);
-      }, kFastShift, s_lmin << (kLowBits - kFastShift), T, take);
+      };
+      if (!kth_key(each_key, kFastShift, s_lmin << (kLowBits - kFastShift), T, take)) {
+        // (some list reaches far below the k-th key, as where half of the candidates is selected: 4000 tokens,
+        // k = 2048 24.0 us through the slow path, 15.9 here)
+        __syncthreads();
+        for (int i = tid; i < 2048; i += kThreads) r1[i] = 0u;
+        __syncthreads();
+        kth_key(each_key, 21, 0u, T, take);
+      }
       TKV_PH(5);
       // Every list is complete down to its bin L, so T is the head's exact k-th key if no L lies
       // above T's bin (a token missing from a list is then below T).
-      if (found && (T >> kLowBits) >= s_lmax) {
+      if ((T >> kLowBits) >= s_lmax) {
         // ordered compaction: every key above T, and the first `take` equal to T
         unsigned long long mg[kSub], me[kSub];
   #pragma unroll
