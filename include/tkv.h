@@ -444,7 +444,8 @@ typedef struct {
 } tkv_pref_desc;
 
 /* Workspace bytes of tkv_dense_preference: n_q * Hq rows, each with room for
- * min(capacity, 32 * top_k) candidate logits and capacity / 32 partial maxima. */
+ * min(capacity, 32 * top_k) candidate logits, the candidates by workgroup, and capacity / 32 partial
+ * maxima. */
 int32_t tkv_dense_preference_sizes(const tkv_pref_desc* desc, size_t* workspace_bytes);
 
 /*
@@ -455,11 +456,11 @@ int32_t tkv_dense_preference_sizes(const tkv_pref_desc* desc, size_t* workspace_
  * k: fp16 [B][n][Hkv][128] (device), the prompt's keys (the layout of the append calls);
  * query head j reads KV head j / (Hq/Hkv), any group size.  p_out: float32 [B][Hq] (device).
  * sm_scale > 0 (TKV_E_INVAL otherwise).
- * Logits are float32 (fp16 products accumulated in float32) and are never written to memory:
- * they are computed twice, once for a per-row lower bound of the top_k-th largest logit and
- * once for the softmax denominator and the logits above that bound, among which the top_k
- * largest are then selected exactly; the mass of a row's top_k entries does not depend on how
- * ties are broken.  The result is the same bit for bit from call to call.  workspace:
+ * Logits are float32 (fp16 products accumulated in float32) and are never written to memory: a
+ * sample of the keys gives a per-row bound below the top_k-th largest logit, one evaluation the softmax
+ * denominator and the logits above that bound, among which the top_k largest are then selected
+ * exactly; where the sample's bound turns out not to do, the rows concerned are evaluated twice more with
+ * an exact one.  The mass of a row's top_k entries does not depend on how ties are broken.  The result is the same bit for bit from call to call.  workspace:
  * ZERO-FILLED before its first use, left consistent by every call; concurrent calls need
  * separate workspaces.  Sequences of a batch are processed one after the other.
  */
