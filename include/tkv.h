@@ -177,11 +177,12 @@ int32_t tkv_quant_attn_decode(const tkv_quant_desc* desc, const tkv_quant_cache*
  * join the cache, as tkv_quantize_append_ragged with the same k_new, v_new, n_new,
  * n_valid_host) and then Eq. 3 over the grown cache (as tkv_quant_attn_decode with the same q,
  * out, sm_scale, workspace).  Same cache contents, same seq_len_host and the same results (to
- * tkv_quant_attn_decode's run-to-run variation) as the two calls one after the other.  When no
- * sequence completes a quantization group with these tokens -- all but one decode step in
- * group_size -- the whole step is ONE launch: the attention kernel copies the new rows from
- * k_new / v_new into the fp16 ring itself and attends to them where the caller has them; otherwise
- * (and always for 4 bits with groups of 64 and 1 bit with groups of 32) the append's launches come
+ * tkv_quant_attn_decode's run-to-run variation) as the two calls one after the other.  The whole step
+ * is ONE launch: the attention kernel copies the new rows from
+ * k_new / v_new into the fp16 ring itself, attends to them where the caller has them and quantizes a
+ * group that they complete.  Where more than one group of a sequence is completed, where new rows take the ring
+ * slots of a group's tokens (a few steps of several tokens), where such a step has more workgroups than compute
+ * units, and always for 4 bits with groups of 64 and 1 bit with groups of 32, the append's launches come
  * first.  k_new, v_new must stay valid until the call has run on the stream.  n_new == 0: the
  * attention alone.  Errors: those of the two calls; on an error nothing has been enqueued and
  * seq_len_host is unchanged, except that an error of the attention after a separate append

@@ -42,6 +42,7 @@ struct QuantNewTokens {
   const __half* k_new;
   const __half* v_new;
   int32_t n_stride;
+  bool complete;  // some sequence completes a quantization group with them (one, of tokens that are in the ring already)
   TkvSeqLens n_add;
 };
 

@@ -2,6 +2,7 @@
 // groups that become complete (Sec. 2.2, Eq. 4; Sec. 4.3: keys per channel, values
 // per token; fp16 zero-point and scaler, Sec. 4.4).
 #include "tkv_common.h"
+#include "tkv_quantizer.h"
 
 // The quantizer's float32 operations are part of the contract (each a single
 // rounded operation); keep the compiler from fusing any of them.
@@ -28,79 +29,7 @@ struct QuantAppendParams {
   TkvSeqLens n_add;   // valid new rows per sequence (<= n_stride)
 };
 
-typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-// Eq. 4's code with the stored fp16 s and z: clamp(rint(RN32(d / s)), 0, 2^b - 1), d = RN32(x - z), without
-// the division.  The decision points h = j - 1/2 make s h exact in float32 (11 + 5 bits), and two
-// different float32 numbers d and s h are at least 2^-24 apart relatively, which is more than half
-// an ulp of the quotient at every h, so RN32(d / s) lies on the same side of h as d of s h and
-// equals h exactly when d = s h: rint then goes to the even neighbour.  The clamp is the number of
-// decision points there are.  Where s is 0 or not finite every comparison is with NaN: code 0, which is
-// what the division gives as well (0 or NaN, and the clamp takes NaN to 0); x = NaN has code 0 likewise.
-template <int BITS>
-struct CodeRule {
-  float z, s, inv;
-  float t1, t2, t3;
-  __device__ CodeRule(_Float16 scale, _Float16 zero) {
-    z = (float)zero;
-    const bool usable = scale > (_Float16)0.f && scale < (_Float16)INFINITY;
-    s = usable ? (float)scale : NAN;
-    if (BITS == 4) {
-      inv = usable ? __builtin_amdgcn_rcpf(s) : 0.f;
-      t1 = 0.5f * s;
-    } else {
-      t1 = 0.5f * s, t2 = 1.5f * s, t3 = 2.5f * s;
-    }
-  }
-  __device__ uint32_t code(_Float16 x) const {
-    const float d = (float)x - z;
-    if (BITS == 1) return d > t1 ? 1u : 0u;
-    if (BITS == 2) return (d > t1 ? 1u : 0u) + (d >= t2 ? 1u : 0u) + (d > t3 ? 1u : 0u);
-    // 4 bits: a lower neighbour c0 in {code - 1, code} from an approximate quotient (off by far less
-    // than the quarter that it is shifted by), then the one decision point above it; a tie goes up
-    // from an odd c0
-    const float magic = 12582912.0f;  // 1.5 x 2^23: the sum holds the rounded integer in its low bits
-    const float m = __builtin_amdgcn_fmed3f(__builtin_fmaf(d, inv, -0.25f), -0.25f, 14.0f) + magic;  // NaN: the lower end
-    const float c0 = m - magic;
-    const float T = __builtin_fmaf(s, c0, t1);  // exact; unordered with d where either is NaN: never passed
-    const uint32_t mb = __builtin_bit_cast(uint32_t, m);
-    const uint32_t db = __builtin_bit_cast(uint32_t, d) + (mb & 1u);  // d >= 0, T > 0: ordered like integers
-    return (mb & 15u) + (!__builtin_isunordered(d, T) && db > __builtin_bit_cast(uint32_t, T) ? 1u : 0u);
-  }
-};
-
-// x / (2^b - 1) correctly rounded: Markstein's correction of x RN(1/q) (q = 3 and 15 checked for every
-// mantissa; x is a difference of fp16 numbers, far from both ends of the exponent range, or not finite
-// and then left alone).
-template <int BITS>
-__device__ inline float over_qmax(float x) {
-  if (BITS == 1) return x;
-  constexpr float q = (float)((1 << BITS) - 1), y = 1.0f / q;
-  const float a = x * y;
-  return a < INFINITY ? __builtin_fmaf(__builtin_fmaf(-q, a, x), y, a) : a;
-}
-
-// packed fp16 minimum / maximum (as the instruction has them: the library functions quiet NaNs first)
-__device__ inline uint32_t pk_min(uint32_t a, uint32_t b) {
-  uint32_t r;
-  asm("v_pk_min_f16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-  return r;
-}
-__device__ inline uint32_t pk_max(uint32_t a, uint32_t b) {
-  uint32_t r;
-  asm("v_pk_max_f16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-  return r;
-}
-template <int CTRL>
-__device__ inline uint32_t dpp(uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, false);
-}
-__device__ inline half2_t as_half2(uint32_t w) { return __builtin_bit_cast(half2_t, w); }
-__device__ inline uint32_t pack2(_Float16 lo, _Float16 hi) {
-  const half2_t v = {lo, hi};
-  return __builtin_bit_cast(uint32_t, v);
-}
+using namespace tkv::quantizer;
 
 // New tokens that stay unquantized, from the caller's rows to the fp16 ring: p.ring_tokens of those of sequence
 // b, keys or values of one head, 256 threads (a token is 16 of them).

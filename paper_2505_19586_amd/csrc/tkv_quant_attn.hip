@@ -794,13 +794,15 @@ extern "C" int32_t tkv_quant_decode(const tkv_quant_desc* d, tkv_quant_cache* c,
   tkv_quant_cache_sizes(d, nullptr, &need);
   if (workspace_bytes < need) return TKV_E_WORKSPACE;
   if (n_new == 0) return tkv_quant_attn_decode(d, c, q, out, sm_scale, workspace, workspace_bytes, stream);
-  // One launch when no sequence completes a quantization group with these tokens (the new rows
-  // then only join the fp16 ring, which the matrix-core kernel does itself) and the matrix-core
-  // kernel serves the descriptor; else the append's launches, then the attention's.
+  // One launch where the matrix-core kernel serves the descriptor: the new rows join the fp16 ring there, and a
+  // group that they complete is quantized there as well if it is one, if all of its tokens are in the ring
+  // already and if no slot that the new rows take is one of theirs (any step of up to residual tokens but
+  // for some of several).  Else the append's launches, then the attention's.
   tkv::QuantNewTokens fresh;
   fresh.k_new = (const __half*)k_new;
   fresh.v_new = (const __half*)v_new;
   fresh.n_stride = n_new;
+  fresh.complete = false;
   bool one_launch = g_kernel_choice.load() == 0 && on_matrix_cores(d);
   for (int b = 0; b < d->batch; ++b) {
     const int64_t n0 = c->seq_len_host[b];
@@ -808,15 +810,19 @@ extern "C" int32_t tkv_quant_decode(const tkv_quant_desc* d, tkv_quant_cache* c,
     if (n0 < 0 || add < 0 || add > n_new) return TKV_E_INVAL;
     if (n0 + add > d->capacity) return TKV_E_CAPACITY;
     fresh.n_add.n[b] = add;
-    const int32_t g = d->group_size;
-    if (tkv::n_quantized((int32_t)n0 + add, d->residual, g) != tkv::n_quantized((int32_t)n0, d->residual, g))
-      one_launch = false;
+    const int32_t g = d->group_size, n1 = (int32_t)n0 + add;
+    const int32_t nq0 = tkv::n_quantized((int32_t)n0, d->residual, g), nq1 = tkv::n_quantized(n1, d->residual, g);
+    if (nq1 != nq0) {
+      fresh.complete = true;
+      if (nq1 - nq0 != g || add > d->residual || n1 - nq0 > d->residual + g) one_launch = false;
+    }
   }
-  if (!one_launch) {
+  auto two_calls = [&]() -> int32_t {
     st = tkv_quantize_append_ragged(d, c, k_new, v_new, n_new, n_valid_host, stream);
     if (st != TKV_OK) return st;
     return tkv_quant_attn_decode(d, c, q, out, sm_scale, workspace, workspace_bytes, stream);
-  }
+  };
+  if (!one_launch) return two_calls();
   const size_t parts_floats = (size_t)d->batch * d->n_q_heads * (TKV_MAX_CHUNKS + 1) * TKV_PART_STRIDE;
   uint32_t* arrivals = (uint32_t*)((char*)workspace + ((parts_floats * sizeof(float) + 255) & ~(size_t)255));
   for (int b = 0; b < d->batch; ++b) c->seq_len_host[b] += fresh.n_add.n[b];
@@ -824,6 +830,7 @@ extern "C" int32_t tkv_quant_decode(const tkv_quant_desc* d, tkv_quant_cache* c,
                               &fresh);
   if (st != TKV_OK)  // nothing was launched: the cache is as it was
     for (int b = 0; b < d->batch; ++b) c->seq_len_host[b] -= fresh.n_add.n[b];
+  if (st == TKV_E_UNSUPPORTED && fresh.complete) return two_calls();
   return st;
 }
 

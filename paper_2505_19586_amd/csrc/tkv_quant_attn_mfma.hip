@@ -40,6 +40,7 @@
 // of a sequence are merged with log-sum-exp merges, the last workgroup of a (sequence, KV
 // head) to finish doing the cross-chunk merge.
 #include "tkv_common.h"
+#include "tkv_quantizer.h"
 
 namespace {
 
@@ -78,6 +79,7 @@ struct MfmaParams {
   const __half* k_new;
   const __half* v_new;
   int32_t n_stride;
+  int32_t complete;  // non-zero: they may complete a group, which this launch then quantizes
   TkvSeqLens n_add;
 };
 
@@ -181,6 +183,11 @@ constexpr int max_gpc(int heads) { return heads <= 4 ? 512 : 256; }  // groups p
 // Blocks that a 32-token piece of the fp16 tail counts as in the split (2 bit, 2000 tokens: 12.6 us per
 // call with 3, 13.1 with 2; from 16384 tokens on 2 to 5 make no difference).
 constexpr int kTailBlocks = 3, kTailBlocksLeast = 2;
+// ... and that quantizing a group which the step's new tokens complete counts as, where a sequence has several chunks.  us per
+// call of such a step, with a launch of its own for the append / here: 2 bit, 32/8 heads, 131071 tokens 35.6, 30.6; 32767 22.7,
+// 18.0; 2047 17.2, 15.3; 255 14.2, 12.1; 4 bit, 131071 44.7, 38.8; 2 bit / 64, 32767 24.6, 17.6; 1 bit / 64, 98431, 32/4 heads
+// 28.3, 22.9; 8 sequences of 16383 36.8, 31.6.  (Counting as 40 blocks instead of 24: the same within 2 %; as none: 2 to 4 us longer.)
+constexpr int kCompleteBlocks = 24;
 // Sequences of up to this many blocks (tail pieces counted as above) per wave are one workgroup's:
 // no partials to write, no arrival, no merge.  us per call with 3 rounds against 1, 8 KV heads: 2 bit, one
 // sequence, 200 tokens 9.1, 11.4; 520 10.8, 11.7; 896 11.0, 12.2; 16 sequences of 800 11.8, 13.7; 4 bit, 200 tokens 8.7,
@@ -466,10 +473,23 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
   // Work split of this sequence: a 32-token piece of the tail counts as tail_blocks groups and the
   // tail belongs to the last chunk, which gets correspondingly fewer quantized groups.
   const bool has_tail = chunk == n_chunks - 1;
-  const int tail_equiv = p.tail_blocks * ((n - nq + 31) / 32);
+  // A group that the step's new tokens complete is quantized by the workgroup of the last chunk, which owns it.
+  const int jq_old = p.complete == 0 ? jq : tkv::n_quantized(n - p.n_add.n[b], p.residual, GRP) / TKV_BLK;
+  const int tail_equiv = p.tail_blocks * ((n - nq + 31) / 32) + (jq_old != jq ? kCompleteBlocks : 0);
   const uint32_t work = (uint32_t)(jq + tail_equiv);
-  const int blk0 = min((int)(work * (uint32_t)chunk / (uint32_t)n_chunks), jq);
-  const int blk1 = has_tail ? jq : min((int)(work * (uint32_t)(chunk + 1) / (uint32_t)n_chunks), jq);
+  const int blk0 = min((int)(work * (uint32_t)chunk / (uint32_t)n_chunks), jq_old);
+  const int blk1 = has_tail ? jq : min((int)(work * (uint32_t)(chunk + 1) / (uint32_t)n_chunks), jq_old);
+  if (has_tail && jq_old != jq) {  // (GS blocks: the host sees to it that it is one group, of old tokens only)
+    const int ring = p.residual + GRP;
+    const size_t first = grp_base + jq_old, kgrp = kgrp_base + (jq_old >> KSH);
+    const tkv::quantizer::GroupOut out = {
+        const_cast<uint32_t*>(p.k_codes) + first * NWORDS,       const_cast<uint32_t*>(p.v_codes) + first * NWORDS,
+        const_cast<__half*>(p.k_scale) + kgrp * TKV_D,           const_cast<__half*>(p.k_zero) + kgrp * TKV_D,
+        const_cast<__half*>(p.v_scale) + first * (TKV_D / GS),   const_cast<__half*>(p.v_zero) + first * (TKV_D / GS)};
+    static_assert(tkv::quantizer::group_lds(GRP) <= C::kLdsBytes, "LDS of the group");
+    tkv::quantizer::quantize_group_block<BITS, GRP, 64 * W>(p.k_resid + bh * ring * TKV_D, p.v_resid + bh * ring * TKV_D, ring,
+                                                           jq_old * TKV_BLK, out, smem, tid);
+  }
   const int last = max(blk1 - 1, blk0);  // groups past the chunk are clamped (and ignored)
 
   const int slot = lane % 16, rb = lane / 16;
@@ -1043,17 +1063,21 @@ int32_t launch_quant_attn_mfma(const tkv_quant_desc* d, const tkv_quant_cache* c
     if (per_head < d->batch) per_head = d->batch;
     const int chunk_cap = target_blocks > 64 * d->batch * heads ? TKV_MAX_CHUNKS : 64;
     total_work = 0;
-    int work[TKV_MAX_BATCH];
+    int work[TKV_MAX_BATCH], extra[TKV_MAX_BATCH];  // extra: a group that this launch quantizes, for the tail's workgroup
     for (int b = 0; b < d->batch; ++b) {
       const int n = lens.n[b];
       const int g = tkv::n_quantized(n, d->residual, d->group_size) / TKV_BLK;
-      work[b] = g + tail_blocks * ((n - g * TKV_BLK + 31) / 32);
+      extra[b] = fresh != nullptr && fresh->complete &&
+                         g != tkv::n_quantized(n - fresh->n_add.n[b], d->residual, d->group_size) / TKV_BLK
+                     ? kCompleteBlocks
+                     : 0;
+      work[b] = g + tail_blocks * ((n - g * TKV_BLK + 31) / 32) + extra[b];
       total_work += work[b];
     }
     total_chunks = 0;
     for (int b = 0; b < d->batch; ++b) {
       int nc = total_work > 0 ? (int)(((long long)per_head * work[b] + total_work / 2) / total_work) : 1;
-      const int c_work = most_chunks(work[b]);
+      const int c_work = most_chunks(work[b] - extra[b]);
       if (nc > c_work) nc = c_work;
       if (nc > chunk_cap) nc = chunk_cap;
       if (nc < 1) nc = 1;
@@ -1080,7 +1104,7 @@ int32_t launch_quant_attn_mfma(const tkv_quant_desc* d, const tkv_quant_cache* c
       int pick = -1;
       for (int b = 0; b < d->batch; ++b) {
         const int nc = p.chunks.n[b];
-        if (nc >= chunk_cap || nc >= most_chunks(work[b])) continue;
+        if (nc >= chunk_cap || nc >= most_chunks(work[b] - extra[b])) continue;
         if (pick < 0 || (long long)work[b] * p.chunks.n[pick] > (long long)work[pick] * nc) pick = b;
       }
       if (pick < 0) break;
@@ -1114,6 +1138,9 @@ int32_t launch_quant_attn_mfma(const tkv_quant_desc* d, const tkv_quant_cache* c
   // table holds twice the blocks).
   if (st != TKV_OK) st = plan(large_group ? 1 : 0, kTailBlocksLeast);
   if (st != TKV_OK) return st;
+  // Quantizing a completed group in this launch keeps one workgroup per head busy for 2 to 3 us, a launch of its own takes 5
+  // to 8 once: not where the workgroups come in several rounds, each of which would wait for that.
+  if (fresh != nullptr && fresh->complete && total_chunks * heads > target_blocks) return TKV_E_UNSUPPORTED;
   p.k_codes = (const uint32_t*)c->k_codes;
   p.v_codes = (const uint32_t*)c->v_codes;
   p.k_scale = (const __half*)c->k_scale;
@@ -1137,6 +1164,7 @@ int32_t launch_quant_attn_mfma(const tkv_quant_desc* d, const tkv_quant_cache* c
 #endif
   p.lens = lens;
   p.k_new = nullptr;
+  p.complete = fresh != nullptr && fresh->complete ? 1 : 0;
   if (fresh != nullptr) {
     p.k_new = fresh->k_new;
     p.v_new = fresh->v_new;
