@@ -1,6 +1,7 @@
 // tkv_quant_attn_decode: Eq. 3 (Sec. 2.1) over the dequantized cache of a
 // quantization-friendly layer (Sec. 4.3), split over token chunks with a
 // log-sum-exp merge.
+#include <algorithm>
 #include <atomic>
 #include <mutex>
 
@@ -266,12 +267,16 @@ __device__ inline void codes_of(uint32_t w, int base, float (&code)[8]) {
 // loaded into registers while this one is worked on, codes unpack eight at a time, query elements are
 // scalar operands.  Bound by vector instructions: 2.4 + H per element and contraction.
 //
-// 4 bits, 32 / 32 heads, 20479 + 16857 tokens: 66 us per call, 542 on the generic kernel; 32 / 8 heads, 65500
-// tokens: 61 and 256; 1 bit, 57 and 252.  The matrix cores serve the same in 45, 26 and 25 us, but
+// 4 bits, 32 / 32 heads, 20479 + 16857 tokens: 52 us per call, 542 on the generic kernel; 32 / 8 heads, 65500
+// tokens: 48 and 256; 1 bit, 48 and 252.  The matrix cores serve the same in 45, 26 and 25 us, but
 // their operands are fp16: scalers above 1024 overflow, weights below 2^-14 lose bits, and the order of
 // the blocks is decided at run time.
+// Workgroups that a compute unit holds: 2 waves each, 2 to 4 of them per SIMD with the registers of each variant (its launch
+// bounds say so).
+constexpr int f32_waves(int bits, int heads) { return bits == 4 ? (heads == 1 ? 3 : 2) : heads == 4 ? 3 : 4; }
+inline int f32_resident(int bits, int group) { return 2 * f32_waves(bits, group > 2 ? 4 : group); }
 template <int BITS, int GRP, int H>
-__global__ __launch_bounds__(128) void quant_attn_f32_kernel(QuantAttnParams p) {
+__global__ __launch_bounds__(128, f32_waves(BITS, H)) void quant_attn_f32_kernel(QuantAttnParams p) {
 #pragma clang fp contract(off)
   constexpr int NU = TKV_D / GRP;        // channel groups of a value row
   constexpr int NWORDS = TKV_D * BITS;   // words of a packed block
@@ -288,13 +293,23 @@ __global__ __launch_bounds__(128) void quant_attn_f32_kernel(QuantAttnParams p) 
   __shared__ float red_o[4][H][TKV_D];
 
   const int group = p.hq / p.hkv, split = (group + 3) / 4;
-  const int b = blockIdx.z, h = blockIdx.y / split, chunk = blockIdx.x;
+  // blockIdx.x runs over the chunks of all (sequence, KV head, quarter of its group) units and over their tails apart: the
+  // chunks, which are the work, fall evenly on the compute units (with a tail behind every head's chunks, some
+  // dies can get the tails and others the chunks).  Tails, which are a chain of round trips, go first where the chunks
+  // are short, else last: 4 bit, 32/8 heads, 5000 tokens (4 blocks per chunk) 18.5 us per call, 21.7 with the tails last; 32/32,
+  // 16 x 2500 tokens (37 blocks) 53.4 with the tails last, 63.0 first.
+  const int units = p.hkv * split, n_units = (int)gridDim.x / (p.n_chunks + 1);
+  const bool tails_last = p.groups_per_chunk > 9;
+  const int at = (int)blockIdx.x - (tails_last ? 0 : n_units), n_heavy = n_units * p.n_chunks;  // place among the chunks
+  const bool is_tail = at < 0 || at >= n_heavy;
+  const int unit = at < 0 ? at + n_units : is_tail ? at - n_heavy : at / p.n_chunks, chunk = is_tail ? p.n_chunks : at % p.n_chunks;
+  const int b = unit / units, y_unit = unit % units, h = y_unit / split;
   const int tid = threadIdx.x, lane = tid % 64;
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
   const int half = lane / 32, t = lane % 32;          // stream of this wave, token of its block
   const int vh = t / 16, l16 = t % 16;                // values: channels 64 vh + 16 j + l16
   const int stream = 2 * wave + half;
-  const int qh0 = h * group + 4 * (blockIdx.y % split);
+  const int qh0 = h * group + 4 * (y_unit % split);
   const int G = min(4, (h + 1) * group - qh0);        // at most H
   const int n = p.lens.n[b];
   const int nq = tkv::n_quantized(n, p.residual, GRP);
@@ -689,15 +704,28 @@ int32_t quant_attn_decode_impl(const tkv_quant_desc* d, const tkv_quant_cache* c
     const int g = tkv::n_quantized(n, d->residual, d->group_size) / TKV_BLK;  // in blocks of 32 tokens
     if (g > max_groups) max_groups = g;
   }
-  // Chunking of the float32 kernels: about 1024 workgroups over the whole launch.
-  const int bh = d->batch * d->n_kv_heads;
-  int target = (1024 + bh - 1) / bh;
-  if (target > TKV_MAX_CHUNKS) target = TKV_MAX_CHUNKS;
-  if (target < 1) target = 1;
-  int gpc = (max_groups + target - 1) / target;
-  if (gpc < 4) gpc = 4;
-  int n_chunks = (max_groups + gpc - 1) / gpc;
-  if (n_chunks < 1) n_chunks = 1;
+  // Chunking of the float32 kernels.  A compute unit holds 4 to 8 of their workgroups at once (registers), and the
+  // launch ends with the fullest compute unit: the number of chunks is the one that makes its work least (its chunks' blocks
+  // and about 6 more for the fixed part of each, its tails', and another workgroup's where not all are resident at
+  // once), out of those that fill what is resident, tails included, and those with 4 to 8 chunks per compute unit.  (A matter
+  // of the sizes alone, whatever the stream may use of the machine: the chunks decide the order of the sums.)  us per
+  // call with about 1024 chunks, the tails in between and groups of 5 to 8 not counted twice, against this: 4 bit, 32/32 heads,
+  // 2 x 20479 tokens 65.9, 51.4; 16 x 2500 64.1, 52.7; 20000 28.2, 28.2; 32/8, 65500 tokens 57.2, 48.0; 50 x 4000 162.7, 116.5; 32
+  // x 900 36.3, 26.0; 1500 16.7, 17.1; 64/8, 30000 47.1, 41.0; 1 bit, 32/32, 2 x 20000 69.6, 51.7.
+  const int units = d->batch * d->n_kv_heads * ((d->n_q_heads / d->n_kv_heads + 3) / 4);
+  int gpc = 4, n_chunks = 1;
+  long long least = -1;
+  const int resident = 256 * f32_resident(d->bits, d->n_q_heads / d->n_kv_heads);
+  for (int round = 3; round <= 8; ++round) {
+    const int want = round == 3 ? resident / units - 1 : 256 * round / units;
+    const int target = std::min(std::max(want, 1), TKV_MAX_CHUNKS);
+    const int blocks = std::max((max_groups + target - 1) / target, 4);
+    const int chunks = std::max((max_groups + blocks - 1) / blocks, 1);
+    const long long per_cu = std::max(((long long)units * chunks + 255) / 256, 4ll);
+    const long long cost = per_cu * (blocks + 6) + (units + 255) / 256 * 12 +
+                           ((long long)units * (chunks + 1) > resident ? blocks + 18 : 0);
+    if (least < 0 || cost < least) least = cost, gpc = blocks, n_chunks = chunks;
+  }
 
   p.k_codes = (const uint32_t*)c->k_codes;
   p.v_codes = (const uint32_t*)c->v_codes;
@@ -740,15 +768,15 @@ int32_t quant_attn_decode_impl(const tkv_quant_desc* d, const tkv_quant_cache* c
   if (!fits()) return TKV_E_WORKSPACE;
   p.chunk_offset = 0;
   const int split = (d->n_q_heads / d->n_kv_heads + 3) / 4;
-  const dim3 grid(n_chunks + 1, d->n_kv_heads * split, d->batch);
+  const dim3 grid(n_chunks + 1, d->n_kv_heads * split, d->batch), flat((n_chunks + 1) * units);
   // the float32 kernel of the two settings reads the query in 32-bit scalar words; the generic one
   // takes it at any fp16 address
   const bool f32 = choice == 0 && (uintptr_t)q % 4 == 0;
   const int variant = d->bits * 100 + d->group_size;
   if (f32 && variant == 464) {
-    if (const int32_t st = launch_f32<4, 64>(p, grid, s); st != TKV_OK) return st;
+    if (const int32_t st = launch_f32<4, 64>(p, flat, s); st != TKV_OK) return st;
   } else if (f32 && variant == 132) {
-    if (const int32_t st = launch_f32<1, 32>(p, grid, s); st != TKV_OK) return st;
+    if (const int32_t st = launch_f32<1, 32>(p, flat, s); st != TKV_OK) return st;
   } else {
     TKV_LAUNCH(quant_attn_generic_kernel, grid, 256, 0, s, p);
   }
