@@ -271,7 +271,8 @@ __device__ inline void append_tokens(const TopkParams& p, int b, int h, int tid)
 // a thread then scores four consecutive tokens, one 8-byte load per channel row.
 // GH: query heads per KV head: 4 (groups of up to 4; their channels sit in registers while the
 // scores are computed), or 8 (groups of 5 to 8: read from LDS term by term).
-template <int DS, bool CM, bool ATT, int GH = 4>
+// ONE: every sequence is one share (n <= tpw); a second workgroup per head, if there is one, only appends.
+template <int DS, bool CM, bool ATT, int GH, bool ONE>
 __global__ __launch_bounds__(kThreads) void score_select_kernel(TopkParams p) {
   static_assert(GH == 4 || GH == 8, "heads per lane");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -560,7 +561,10 @@ __global__ __launch_bounds__(kThreads) void score_select_kernel(TopkParams p) {
     const int t0 = blockIdx.x * p.tpw;
     appends = k == 0 && blockIdx.x == 0;  // no candidates, no arrivals
     if (ATT && k == 0) return blockIdx.x == 0;  // ... and attends to what is resident
-    if (t0 >= n) return false;
+    if (t0 >= n) {
+      if (ONE && k != 0) appends = true;  // launched for that alone
+      return false;
+    }
     const int t_end = min(n, t0 + p.tpw);  // this workgroup's tokens: [t0, t_end), kTok per pass
     const int nblk = (n + p.tpw - 1) / p.tpw;
     TKV_PH(0);
@@ -753,22 +757,153 @@ __global__ __launch_bounds__(kThreads) void score_select_kernel(TopkParams p) {
     score_share(t0, t_end, true, true, std::false_type{});
     __syncthreads();
     TKV_PH(1);
+    constexpr int kOwn = kBins / kThreads;  // bins per thread, descending: kBins - 1 - (kOwn * tid + i)
+    static_assert(kOwn == 8, "two 16-byte reads per thread");
+    auto own_bins = [&](uint32_t (&c)[kOwn]) {
+      const uint4 w0 = *reinterpret_cast<const uint4*>(&hist[kBins - kOwn * tid - kOwn]);
+      const uint4 w1 = *reinterpret_cast<const uint4*>(&hist[kBins - kOwn * tid - kOwn + 4]);
+      c[7] = w0.x, c[6] = w0.y, c[5] = w0.z, c[4] = w0.w, c[3] = w1.x, c[2] = w1.y, c[1] = w1.z, c[0] = w1.w;
+    };
+    __shared__ uint32_t r1[2048], r2[2048], r3[1024];  // radix-select histograms: 11 + 11 + 10 key bits
+    __shared__ uint32_t lens[kThreads], lbin[kThreads];  // list length and bin L of every share
+    __shared__ uint32_t s_lmax, s_lmin, s_nsame;
+
+    // k-th largest key of a set of keys (each thread offers its own through `each`), by radix
+    // select over three digits of 11, 11 and s1 - 11 bits, the first being (key >> s1) - base,
+    // clamped to 2047; every search is done by the whole workgroup (two or one bin per thread).
+    // s1 = 21, base = 0 covers all 32 bits of any key.  The listed keys share their leading bits,
+    // though, and LDS atomics of a wave on one address are executed one after the other: with
+    // s1 = kFastShift and base = (lowest bin L of any list) << (kLowBits - kFastShift) the first
+    // digits spread over hundreds of values and few keys share the k-th key's digit, at the price
+    // of keys more than four binades above that bin being clamped: returns false if the k-th
+    // key is among those (the caller then falls back to s1 = 21).
+    // T: the key; take: how many keys equal to T belong to the k largest.  The three histograms
+    // and s_nsame must be zero.
+    auto search2 = [&](const uint32_t* hist, uint32_t& k_rem, uint32_t& digit) {  // 2048 bins
+      const uint2 w = *reinterpret_cast<const uint2*>(&hist[2048 - 2 * tid - 2]);
+      const uint32_t c[2] = {w.y, w.x};
+      const uint32_t ranks[1] = {k_rem};
+      find_ranks<1, 2>(c, ranks, s_wtot, s_res, wave, lane);
+      digit = s_res[0];
+      k_rem -= s_res[1];
+    };
+    // ... of which `n_same` share the leading digit `top` (bits from s1 up): the k_rem-th largest of these
+    auto below_digit = [&](auto each, int s1, uint32_t top, uint32_t n_same, uint32_t k_rem, uint32_t& T, uint32_t& take) {
+      const int s2 = s1 - 11;
+      const uint32_t low_mask = (1u << s2) - 1u;
+      uint32_t d2, d3;
+      // Keys that share the first digit: usually a few dozen.  Up to 1024 of them are collected
+      // in LDS (in any order) and ranked against each other directly; more go through two more
+      // digits.
+      if (n_same <= (uint32_t)kThreads) {
+        // (s_nsame is zero: cleared with the histograms)
+        each([&](uint32_t key) { if (key != 0u && (key >> s1) == top) r2[atomicAdd(&s_nsame, 1u)] = key; });
+        __syncthreads();
+        // the k_rem-th largest of them: the key v with fewer than k_rem keys above it and at least
+        // k_rem keys at or above it (every thread that holds such a key reports the same result)
+        if ((uint32_t)tid < n_same) {
+          const uint32_t v = r2[tid];
+          uint32_t gt = 0, ge = 0;
+          for (uint32_t y = 0; y < n_same; ++y) {
+            const uint32_t o = r2[y];
+            gt += o > v ? 1u : 0u;
+            ge += o >= v ? 1u : 0u;
+          }
+          if (gt < k_rem && k_rem <= ge) s_res[0] = v, s_res[1] = k_rem - gt;
+        }
+        __syncthreads();
+        T = s_res[0];
+        take = s_res[1];
+        return;
+      }
+      each([&](uint32_t key) { if ((key >> s1) == top) atomicAdd(&r2[(key >> s2) & 0x7FFu], 1u); });
+      __syncthreads();
+      search2(r2, k_rem, d2);
+      const uint32_t top2 = (top << 11) | d2;
+      each([&](uint32_t key) { if ((key >> s2) == top2) atomicAdd(&r3[key & low_mask], 1u); });
+      __syncthreads();
+      {
+        const uint32_t c[1] = {r3[1023 - tid]};
+        const uint32_t ranks[1] = {k_rem};
+        find_ranks<1, 1>(c, ranks, s_wtot, s_res, wave, lane);
+        d3 = s_res[0];
+        take = k_rem - s_res[1];
+      }
+      T = (top2 << s2) | d3;
+    };
+    auto kth_key = [&](auto each, int s1, uint32_t base, uint32_t& T, uint32_t& take) -> bool {
+      uint32_t k_rem = k;
+      uint32_t d1;
+      each([&](uint32_t key) { if (key != 0u) atomicAdd(&r1[min((key >> s1) - base, 2047u)], 1u); });
+      __syncthreads();
+      TKV_PH(6);
+      search2(r1, k_rem, d1);
+      if (s1 != 21 && d1 == 2047u) return false;
+      below_digit(each, s1, d1 + base, r1[d1], k_rem, T, take);
+      return true;
+    };
+    // Ordered compaction of the keys held in registers (ascending tokens in (i, thread) order): every key above
+    // T, and the first `take` equal to T.
+    auto place = [&](const uint32_t (&ek)[kSub], const uint32_t (&et)[kSub], uint32_t T, uint32_t take) {
+      unsigned long long mg[kSub], me[kSub];
+  #pragma unroll
+      for (int i = 0; i < kSub; ++i) {
+        mg[i] = __builtin_amdgcn_ballot_w64(ek[i] > T);
+        me[i] = __builtin_amdgcn_ballot_w64(ek[i] == T);
+      }
+      uint32_t bg[kSub], be[kSub];
+      subtile_offsets2(mg, me, &s_cnt[0][0], &s_cnt2[0][0], wave, lane, bg, be);
+  #pragma unroll
+      for (int i = 0; i < kSub; ++i) {
+        const uint32_t my_gt = bg[i] + rank_in(mg[i]), my_eq = be[i] + rank_in(me[i]);
+        int pos = -1;
+        if (ek[i] > T) pos = (int)(my_gt + min(my_eq, take));
+        else if (ek[i] == T && my_eq < take) pos = (int)(my_gt + my_eq);
+        if (pos >= 0) {
+          out[pos] = (int32_t)et[i];
+          if (ATT) sel_s[pos] = (int32_t)et[i];
+        }
+      }
+    };
+
+    // ---- a head of one share: its keys are in this workgroup's registers already, counted by their
+    // leading bits, so nothing has to be listed, handed in or fetched again.  Us per scoring launch, the tokens
+    // split over 2 to 5 workgroups / here: 32/8 heads, 4095 tokens, k = 128 11.9, 9.2; 1500 tokens 12.0, 7.9; 64/8,
+    // 3500 tokens 11.7, 10.5.  Bound by its chain of round trips and barriers: 64 KiB of rows per head.
+    if (ONE) {
+      appends = gridDim.x == 1;
+      for (int i = tid; i < 2048; i += kThreads) r2[i] = 0u;
+      r3[tid] = 0u;
+      if (tid == 0) s_nsame = 0u;
+      for (int i = (int)k + tid; i < p.top_k; i += kThreads) out[i] = -1;
+      if (tid == 0) p.topk_count[bh] = (int32_t)k;
+      uint32_t c[kOwn], tok[kSub], T, take;
+      const uint32_t ranks[1] = {k};
+      own_bins(c);
+      find_ranks<1, kOwn>(c, ranks, s_wtot, s_res, wave, lane);
+      const uint32_t bin = s_res[0], above = s_res[1];
+      auto each_key = [&](auto f) {
+  #pragma unroll
+        for (int i = 0; i < kSub; ++i) f(kb[i]);
+      };
+      below_digit(each_key, kLowBits, bin, hist[bin], k - above, T, take);
+      TKV_PH(5);
+  #pragma unroll
+      for (int i = 0; i < kSub; ++i) tok[i] = (uint32_t)(t0 + i * kThreads + tid);
+      place(kb, tok, T, take);
+      TKV_PH(7);
+      return true;
+    }
     // ---- `my_bin`: the bin of this workgroup's r-th key, down to which it lists its tokens
     uint32_t* ctrl = p.ws.ctrl + bh * kCtrlWords;
     uint32_t* cnt_g = p.ws.blk + bh * p.ws.nblk_cap;
-    constexpr int kOwn = kBins / kThreads;  // bins per thread, descending: kBins - 1 - (kOwn * tid + i)
-    static_assert(kOwn == 8, "two 16-byte reads per thread");
     {
       const uint32_t mine = (uint32_t)max(0, min(hi, t_end) - max(lo, t0));  // candidates in this share
       // fair share of k, times 1.5, plus 16
       const uint32_t r = (uint32_t)(((unsigned long long)k * mine * 3ull) / (2ull * (unsigned long long)(hi - lo))) + 16u;
       const uint32_t ranks[1] = {r < mine ? r : 0u};  // (fewer candidates than that: all of them are listed)
       uint32_t c[kOwn];
-      {
-        const uint4 w0 = *reinterpret_cast<const uint4*>(&hist[kBins - kOwn * tid - kOwn]);
-        const uint4 w1 = *reinterpret_cast<const uint4*>(&hist[kBins - kOwn * tid - kOwn + 4]);
-        c[7] = w0.x, c[6] = w0.y, c[5] = w0.z, c[4] = w0.w, c[3] = w1.x, c[2] = w1.y, c[1] = w1.z, c[0] = w1.w;
-      }
+      own_bins(c);
       find_ranks<1, kOwn>(c, ranks, s_wtot, s_res, wave, lane);
       const uint32_t my_bin = s_res[0];
       const uint32_t my_len = list_share(t0, my_bin, true);
@@ -777,9 +912,6 @@ __global__ __launch_bounds__(kThreads) void score_select_kernel(TopkParams p) {
     TKV_PH(2);
     // (what the head's last workgroup needs cleared is cleared by every workgroup here, under the
     // wait for the list stores: one barrier less on the path that everything after waits for)
-    __shared__ uint32_t r1[2048], r2[2048], r3[1024];  // radix-select histograms: 11 + 11 + 10 key bits
-    __shared__ uint32_t lens[kThreads], lbin[kThreads];  // list length and bin L of every share
-    __shared__ uint32_t s_lmax, s_lmin, s_nsame;
     for (int i = tid; i < 2048; i += kThreads) r1[i] = 0u, r2[i] = 0u;
     r3[tid] = 0u;
     if (tid == 0) s_lmax = 0u, s_lmin = kBins - 1, s_nsame = 0u;
@@ -868,78 +1000,6 @@ __global__ __launch_bounds__(kThreads) void score_select_kernel(TopkParams p) {
     }
     TKV_PH(4);
 
-    // k-th largest key of a set of keys (each thread offers its own through `each`), by radix
-    // select over three digits of 11, 11 and s1 - 11 bits, the first being (key >> s1) - base,
-    // clamped to 2047; every search is done by the whole workgroup (two or one bin per thread).
-    // s1 = 21, base = 0 covers all 32 bits of any key.  The listed keys share their leading bits,
-    // though, and LDS atomics of a wave on one address are executed one after the other: with
-    // s1 = kFastShift and base = (lowest bin L of any list) << (kLowBits - kFastShift) the first
-    // digits spread over hundreds of values and few keys share the k-th key's digit, at the price
-    // of keys more than four binades above that bin being clamped: returns false if the k-th
-    // key is among those (the caller then falls back to s1 = 21).
-    // T: the key; take: how many keys equal to T belong to the k largest.  The three histograms
-    // and s_nsame must be zero.
-    auto kth_key = [&](auto each, int s1, uint32_t base, uint32_t& T, uint32_t& take) -> bool {
-      uint32_t k_rem = k;
-      auto search2 = [&](const uint32_t* hist, uint32_t& digit) {  // 2048 bins
-        const uint2 w = *reinterpret_cast<const uint2*>(&hist[2048 - 2 * tid - 2]);
-        const uint32_t c[2] = {w.y, w.x};
-        const uint32_t ranks[1] = {k_rem};
-        find_ranks<1, 2>(c, ranks, s_wtot, s_res, wave, lane);
-        digit = s_res[0];
-        k_rem -= s_res[1];
-      };
-      const int s2 = s1 - 11;
-      const uint32_t low_mask = (1u << s2) - 1u;
-      uint32_t d1, d2, d3;
-      each([&](uint32_t key) { if (key != 0u) atomicAdd(&r1[min((key >> s1) - base, 2047u)], 1u); });
-      __syncthreads();
-      TKV_PH(6);
-      search2(r1, d1);
-      if (s1 != 21 && d1 == 2047u) return false;
-      const uint32_t top = d1 + base;
-      // Keys that share the first digit: usually a few dozen.  Up to 1024 of them are collected
-      // in LDS (in any order) and ranked against each other directly; more go through two more
-      // digits.
-      const uint32_t n_same = r1[d1];
-      if (n_same <= (uint32_t)kThreads) {
-        // (s_nsame is zero: cleared with the histograms)
-        each([&](uint32_t key) { if (key != 0u && (key >> s1) == top) r2[atomicAdd(&s_nsame, 1u)] = key; });
-        __syncthreads();
-        // the k_rem-th largest of them: the key v with fewer than k_rem keys above it and at least
-        // k_rem keys at or above it (every thread that holds such a key reports the same result)
-        if ((uint32_t)tid < n_same) {
-          const uint32_t v = r2[tid];
-          uint32_t gt = 0, ge = 0;
-          for (uint32_t y = 0; y < n_same; ++y) {
-            const uint32_t o = r2[y];
-            gt += o > v ? 1u : 0u;
-            ge += o >= v ? 1u : 0u;
-          }
-          if (gt < k_rem && k_rem <= ge) s_res[0] = v, s_res[1] = k_rem - gt;
-        }
-        __syncthreads();
-        T = s_res[0];
-        take = s_res[1];
-        return true;
-      }
-      each([&](uint32_t key) { if ((key >> s1) == top) atomicAdd(&r2[(key >> s2) & 0x7FFu], 1u); });
-      __syncthreads();
-      search2(r2, d2);
-      const uint32_t top2 = (top << 11) | d2;
-      each([&](uint32_t key) { if ((key >> s2) == top2) atomicAdd(&r3[key & low_mask], 1u); });
-      __syncthreads();
-      {
-        const uint32_t c[1] = {r3[1023 - tid]};
-        const uint32_t ranks[1] = {k_rem};
-        find_ranks<1, 1>(c, ranks, s_wtot, s_res, wave, lane);
-        d3 = s_res[0];
-        take = k_rem - s_res[1];
-      }
-      T = (top2 << s2) | d3;
-      return true;
-    };
-
     if (fits) {
       // ---- every list entry is in a register of some thread
   #pragma unroll
@@ -964,26 +1024,7 @@ __global__ __launch_bounds__(kThreads) void score_select_kernel(TopkParams p) {
       // Every list is complete down to its bin L, so T is the head's exact k-th key if no L lies
       // above T's bin (a token missing from a list is then below T).
       if ((T >> kLowBits) >= s_lmax) {
-        // ordered compaction: every key above T, and the first `take` equal to T
-        unsigned long long mg[kSub], me[kSub];
-  #pragma unroll
-        for (int i = 0; i < kSub; ++i) {
-          mg[i] = __builtin_amdgcn_ballot_w64(ek[i] > T);
-          me[i] = __builtin_amdgcn_ballot_w64(ek[i] == T);
-        }
-        uint32_t bg[kSub], be[kSub];
-        subtile_offsets2(mg, me, &s_cnt[0][0], &s_cnt2[0][0], wave, lane, bg, be);
-  #pragma unroll
-        for (int i = 0; i < kSub; ++i) {
-          const uint32_t my_gt = bg[i] + rank_in(mg[i]), my_eq = be[i] + rank_in(me[i]);
-          int pos = -1;
-          if (ek[i] > T) pos = (int)(my_gt + min(my_eq, take));
-          else if (ek[i] == T && my_eq < take) pos = (int)(my_gt + my_eq);
-          if (pos >= 0) {
-            out[pos] = (int32_t)et[i];
-            if (ATT) sel_s[pos] = (int32_t)et[i];
-          }
-        }
+        place(ek, et, T, take);
         TKV_PH(7);
         return true;
       }
@@ -1109,15 +1150,20 @@ extern "C" void tkv_debug_set_dump_topk(void* ptr) { g_topk_prof = ptr; }
 #endif
 
 namespace {
-template <int DS, bool CM, bool ATT, int GH = 4>
-int32_t launch_fused(const TopkParams& p, dim3 grid, hipStream_t s) {
+template <int DS, bool CM, bool ATT, int GH, bool ONE>
+int32_t launch_fused_as(const TopkParams& p, dim3 grid, hipStream_t s) {
   // more than 64 KiB of dynamic LDS needs an opt-in, once per kernel
   constexpr int lds = ATT && GH == 8 ? kMergeLds8 : kFusedLds;
-  static const bool lds_ok = hipFuncSetAttribute(reinterpret_cast<const void*>(&score_select_kernel<DS, CM, ATT, GH>),
+  static const bool lds_ok = hipFuncSetAttribute(reinterpret_cast<const void*>(&score_select_kernel<DS, CM, ATT, GH, ONE>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, lds) == hipSuccess;
   if (!lds_ok) return TKV_E_HIP;
-  TKV_LAUNCH((score_select_kernel<DS, CM, ATT, GH>), grid, kThreads, lds, s, p);
+  TKV_LAUNCH((score_select_kernel<DS, CM, ATT, GH, ONE>), grid, kThreads, lds, s, p);
   return TKV_OK;
+}
+
+template <int DS, bool CM, bool ATT, int GH = 4>
+int32_t launch_fused(const TopkParams& p, dim3 grid, bool one, hipStream_t s) {
+  return one ? launch_fused_as<DS, CM, ATT, GH, true>(p, grid, s) : launch_fused_as<DS, CM, ATT, GH, false>(p, grid, s);
 }
 
 // All entry points: validation, parameters, the launch.  keys: token-major key summary
@@ -1191,6 +1237,11 @@ int32_t estimate_topk_launch(const tkv_sparse_desc* d, const tkv_sparse_cache* c
       nblk = (full * bh_count / n_cus) * per_head;  // whole rounds, rounded down
     }
   }
+  // What one workgroup holds goes to one: listing, handing in and fetching again costs more (4 us) than
+  // the longer scoring (5000 tokens: 1.5 us with up to 4 query heads, 4.5 with 8, which read their
+  // channels from LDS).
+  const bool big_group = d->n_q_heads / d->n_kv_heads > 4;  // 5 to 8 query heads per KV head
+  if (max_n <= (big_group ? kTok : kMaxTpw)) nblk = 1;
   // (a multiple of 16: every workgroup's list starts on a 128-byte line of its own)
   int tpw = ((max_n + nblk - 1) / nblk + 15) & ~15;
   if (tpw < 16) tpw = 16;
@@ -1210,9 +1261,10 @@ int32_t estimate_topk_launch(const tkv_sparse_desc* d, const tkv_sparse_cache* c
     p.app_stride = app->app_stride;
     p.app_add = app->app_add;
   }
-  const dim3 grid(nblk, d->n_kv_heads, d->batch);
+  const bool one = nblk == 1;
+  // (heads of one share: the append by a workgroup of its own if there are compute units left for it)
+  const dim3 grid(one && app != nullptr && 2 * bh_count <= n_cus ? 2 : nblk, d->n_kv_heads, d->batch);
   if (nblk >= 1024) return TKV_E_UNSUPPORTED;  // 4 Mi tokens per sequence
-  const bool big_group = d->n_q_heads / d->n_kv_heads > 4;  // 5 to 8 query heads per KV head
   if (att != nullptr) {  // token-major summary only
     p.att_host = att->att_host;
     p.att_local = att->att_local;
@@ -1220,23 +1272,23 @@ int32_t estimate_topk_launch(const tkv_sparse_desc* d, const tkv_sparse_cache* c
     p.att_scale2 = att->att_scale2;
     p.pf = att->pf;
     if (d->n_channels == 16)
-      return big_group ? launch_fused<16, false, true, 8>(p, grid, s) : launch_fused<16, false, true>(p, grid, s);
+      return big_group ? launch_fused<16, false, true, 8>(p, grid, one, s) : launch_fused<16, false, true>(p, grid, one, s);
     if (d->n_channels == 12)
-      return big_group ? launch_fused<12, false, true, 8>(p, grid, s) : launch_fused<12, false, true>(p, grid, s);
-    return big_group ? launch_fused<8, false, true, 8>(p, grid, s) : launch_fused<8, false, true>(p, grid, s);
+      return big_group ? launch_fused<12, false, true, 8>(p, grid, one, s) : launch_fused<12, false, true>(p, grid, one, s);
+    return big_group ? launch_fused<8, false, true, 8>(p, grid, one, s) : launch_fused<8, false, true>(p, grid, one, s);
   }
   if (big_group) {
     if (d->n_channels == 16)
-      return cm ? launch_fused<16, true, false, 8>(p, grid, s) : launch_fused<16, false, false, 8>(p, grid, s);
+      return cm ? launch_fused<16, true, false, 8>(p, grid, one, s) : launch_fused<16, false, false, 8>(p, grid, one, s);
     if (d->n_channels == 12)
-      return cm ? launch_fused<12, true, false, 8>(p, grid, s) : launch_fused<12, false, false, 8>(p, grid, s);
-    return cm ? launch_fused<8, true, false, 8>(p, grid, s) : launch_fused<8, false, false, 8>(p, grid, s);
+      return cm ? launch_fused<12, true, false, 8>(p, grid, one, s) : launch_fused<12, false, false, 8>(p, grid, one, s);
+    return cm ? launch_fused<8, true, false, 8>(p, grid, one, s) : launch_fused<8, false, false, 8>(p, grid, one, s);
   }
   if (d->n_channels == 16)
-    return cm ? launch_fused<16, true, false>(p, grid, s) : launch_fused<16, false, false>(p, grid, s);
+    return cm ? launch_fused<16, true, false>(p, grid, one, s) : launch_fused<16, false, false>(p, grid, one, s);
   if (d->n_channels == 12)
-    return cm ? launch_fused<12, true, false>(p, grid, s) : launch_fused<12, false, false>(p, grid, s);
-  return cm ? launch_fused<8, true, false>(p, grid, s) : launch_fused<8, false, false>(p, grid, s);
+    return cm ? launch_fused<12, true, false>(p, grid, one, s) : launch_fused<12, false, false>(p, grid, one, s);
+  return cm ? launch_fused<8, true, false>(p, grid, one, s) : launch_fused<8, false, false>(p, grid, one, s);
 }
 }  // namespace
 
@@ -1283,8 +1335,8 @@ int32_t launch_fetch_attn(const tkv_sparse_desc* d, const TkvSeqLens& lens, cons
   p.given = 1;
   p.ws = carve_sparse_ws(d, workspace);
   const dim3 grid(fetch_workgroups(d), d->n_kv_heads, d->batch);
-  if (d->n_q_heads / d->n_kv_heads > 4) return launch_fused<8, false, true, 8>(p, grid, s);
-  return launch_fused<16, false, true>(p, grid, s);
+  if (d->n_q_heads / d->n_kv_heads > 4) return launch_fused<8, false, true, 8>(p, grid, false, s);
+  return launch_fused<16, false, true>(p, grid, false, s);
 }
 }  // namespace tkv
 
