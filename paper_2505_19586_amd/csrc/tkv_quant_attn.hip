@@ -32,7 +32,7 @@ struct QuantAttnParams {
   const __half* q;
   float* parts;  // [B][Hq][n_chunks + 1][D + 4]
   float scale2;  // sm_scale * log2(e)
-  int32_t hq, hkv, bits, group, residual, capacity;
+  int32_t batch, hq, hkv, bits, group, residual, capacity;
   int32_t groups_per_chunk, n_chunks;  // chunk size in blocks of 32 tokens
   int32_t chunk_offset;  // blockIdx.x + chunk_offset is the chunk; chunk == n_chunks is the fp16 tail
   TkvSeqLens lens;
@@ -292,31 +292,31 @@ __global__ __launch_bounds__(128, f32_waves(BITS, H)) void quant_attn_f32_kernel
   __shared__ float red_m[4][H], red_l[4][H];
   __shared__ float red_o[4][H][TKV_D];
 
-  const int group = p.hq / p.hkv, split = (group + 3) / 4;
-  // blockIdx.x runs over the chunks of all (sequence, KV head, quarter of its group) units and over their tails apart: the
-  // chunks, which are the work, fall evenly on the compute units (with a tail behind every head's chunks, some
+  const int group = p.hq / p.hkv, split = (group + H - 1) / H;
+  // blockIdx.x runs over the chunks of all (sequence, KV head, H query heads of its group) units and over their tails
+  // apart: the chunks, which are the work, fall evenly on the compute units (with a tail behind every head's chunks, some
   // dies can get the tails and others the chunks).  Tails, which are a chain of round trips, go first where the chunks
-  // are short, else last: 4 bit, 32/8 heads, 5000 tokens (4 blocks per chunk) 18.5 us per call, 21.7 with the tails last; 32/32,
+  // are short, else last: 4 bit, 32/8 heads, 5000 tokens (4 blocks per chunk, 4 heads) 18.5 us per call, 21.7 with the tails last; 32/32,
   // 16 x 2500 tokens (37 blocks) 53.4 with the tails last, 63.0 first.
-  const int units = p.hkv * split, n_units = (int)gridDim.x / (p.n_chunks + 1);
+  const int units = p.hkv * split, n_heavy = p.batch * units * p.n_chunks, n_tails = (int)gridDim.x - n_heavy;
   const bool tails_last = p.groups_per_chunk > 9;
-  const int at = (int)blockIdx.x - (tails_last ? 0 : n_units), n_heavy = n_units * p.n_chunks;  // place among the chunks
-  const bool is_tail = at < 0 || at >= n_heavy;
-  const int unit = at < 0 ? at + n_units : is_tail ? at - n_heavy : at / p.n_chunks, chunk = is_tail ? p.n_chunks : at % p.n_chunks;
+  const int at = (int)blockIdx.x - (tails_last ? 0 : n_tails);  // place among the chunks
+  const bool tail = at < 0 || at >= n_heavy;
+  const int x = at < 0 ? at + n_tails : at - n_heavy;           // ... and among the tails
+  const int unit = tail ? x : at / p.n_chunks, chunk = tail ? p.n_chunks : at % p.n_chunks;
   const int b = unit / units, y_unit = unit % units, h = y_unit / split;
   const int tid = threadIdx.x, lane = tid % 64;
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
   const int half = lane / 32, t = lane % 32;          // stream of this wave, token of its block
   const int vh = t / 16, l16 = t % 16;                // values: channels 64 vh + 16 j + l16
   const int stream = 2 * wave + half;
-  const int qh0 = h * group + 4 * (y_unit % split);
-  const int G = min(4, (h + 1) * group - qh0);        // at most H
+  const int qh0 = h * group + H * (y_unit % split);
+  const int G = min(H, (h + 1) * group - qh0);
   const int n = p.lens.n[b];
   const int nq = tkv::n_quantized(n, p.residual, GRP);
   const int jq = nq / TKV_BLK;
   const size_t bh = (size_t)b * p.hkv + h;
   const int ring = p.residual + GRP;
-  const bool tail = chunk == p.n_chunks;
   const int blk0 = tail ? 0 : chunk * p.groups_per_chunk;
   const int blk1 = tail ? (n - nq + TKV_BLK - 1) / TKV_BLK : min(blk0 + p.groups_per_chunk, jq);
 
@@ -519,31 +519,44 @@ __global__ __launch_bounds__(128, f32_waves(BITS, H)) void quant_attn_f32_kernel
       accumulate(on, al, s, ls);
     }
   } else {
-    // the fp16 tail: rows from the ring, the lane's four channels side by side (4 t ..) for the values
-    auto row = [&](const __half* rows, int tok) { return rows + (bh * ring + (size_t)(tok % ring)) * TKV_D; };
+    // the fp16 tail: rows from the ring, the lane's four channels side by side (4 t ..) for the values.  Bound by
+    // its chain of round trips: a block's key rows are requested at once, and the value rows as the keys' registers come
+    // free.  (Loaded in eight pieces, each waited for before the next: 32/32 heads, 168 tokens 13.1 us per call, 11.1 now;
+    // 316 tokens, 32 sequences 59.0, 52.6.)
+    const int slot_n = (n - 1) % ring;
     for (int base = 2 * wave; base < blk1; base += 4) {
       pin_query();
       const bool on = base + half < blk1;
-      const int tok0 = nq + TKV_BLK * min(base + half, blk1 - 1), tok = tok0 + t;
-      const u32x4* krow = reinterpret_cast<const u32x4*>(row(p.k_resid, min(tok, n - 1)));
+      const int tok0 = nq + TKV_BLK * min(base + half, blk1 - 1), tok = tok0 + t, slot0 = tok0 % ring;
+      auto row = [&](const __half* rows, int y) {  // of token tok0 + y, or the last one
+        const int slot = tok0 + y < n ? slot0 + y : slot_n;
+        return rows + (bh * ring + (size_t)(slot < ring ? slot : slot - ring)) * TKV_D;
+      };
+      const u32x4* krow = reinterpret_cast<const u32x4*>(row(p.k_resid, t));
+      u32x4 kr[TKV_D / 8];
+      u32x2 vr[TKV_BLK];
+#pragma unroll
+      for (int y = 0; y < TKV_D / 8; ++y) kr[y] = krow[y];
+      __builtin_amdgcn_sched_barrier(0);
       float acc[H];
 #pragma unroll
       for (int hh = 0; hh < H; ++hh) acc[hh] = 0.f;
 #pragma unroll
       for (int c = 0; c < TKV_D; c += 32) {
-        u32x4 w[4];
-#pragma unroll
-        for (int y = 0; y < 4; ++y) w[y] = krow[c / 8 + y];
 #pragma unroll
         for (int y = 0; y < 4; ++y) {
           float kh[8];
 #pragma unroll
           for (int i = 0; i < 8; ++i) {
-            const uint32_t wi = w[y][i / 2];
+            const uint32_t wi = kr[c / 8 + y][i / 2];
             kh[i] = (float)as_half2(wi)[i % 2];
           }
           dot8(acc, c + 8 * y, kh);
         }
+        __builtin_amdgcn_sched_barrier(0);
+        // eight value rows take the registers of 32 key channels
+#pragma unroll
+        for (int i = c / 4; i < c / 4 + 8; ++i) vr[i] = reinterpret_cast<const u32x2*>(row(p.v_resid, i))[t];
         __builtin_amdgcn_sched_barrier(0);
       }
       float al[H];
@@ -555,12 +568,8 @@ __global__ __launch_bounds__(128, f32_waves(BITS, H)) void quant_attn_f32_kernel
 #pragma unroll
         for (int j = 0; j < 4; ++j) s[hh][j] = 0.f;
       }
-#pragma unroll 1
-      for (int t0 = 0; t0 < TKV_BLK; t0 += 8) {
-        u32x2 w[8];
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
-          w[i] = reinterpret_cast<const u32x2*>(row(p.v_resid, min(tok0 + t0 + i, n - 1)))[t];
+      for (int t0 = 0; t0 < TKV_BLK; t0 += 8) {
         float pp[H][8];
         weights8(pp, t0);
 #pragma unroll
@@ -568,7 +577,7 @@ __global__ __launch_bounds__(128, f32_waves(BITS, H)) void quant_attn_f32_kernel
           const bool valid = tok0 + t0 + i < n;
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
-            const uint32_t wj = w[i][j / 2];
+            const uint32_t wj = vr[t0 + i][j / 2];
             const float v = valid ? (float)as_half2(wj)[j % 2] : 0.f;
 #pragma unroll
             for (int hh = 0; hh < H; ++hh) s[hh][j] = __builtin_fmaf(pp[hh][i], v, s[hh][j]);
@@ -576,6 +585,7 @@ __global__ __launch_bounds__(128, f32_waves(BITS, H)) void quant_attn_f32_kernel
 #pragma unroll
           for (int hh = 0; hh < H; ++hh) ls[hh] = ls[hh] + pp[hh][i];
         }
+        __builtin_amdgcn_sched_barrier(0);
       }
       accumulate(on, al, s, ls);
     }
@@ -612,11 +622,20 @@ __global__ __launch_bounds__(128, f32_waves(BITS, H)) void quant_attn_f32_kernel
   }
 }
 
+// Query heads that a workgroup takes: up to 4, which unpack a code once for all of them; fewer where that leaves compute
+// units idle, up to four workgroups on each: with 4 heads a block costs 4.8 us, a chain of 2500 vector
+// instructions.  4 bit, us per call, always 4 / by this: 32/8 heads, 891 tokens 17.5, 11.9; 1500 tokens 17.1, 12.0; 5000
+// tokens 18.8, 14.7 (17.9 with at most two workgroups each); 64/8, 821 tokens 22.2, 14.2; 8/1, 60000 tokens 30.0, 27.2.
+constexpr int kF32Alone = 1024;
 template <int BITS, int GRP>
-int32_t launch_f32(const QuantAttnParams& p, dim3 grid, hipStream_t s) {
+int32_t launch_f32(const QuantAttnParams& p, hipStream_t s) {
   const int group = p.hq / p.hkv;
-  if (group == 1) TKV_LAUNCH((quant_attn_f32_kernel<BITS, GRP, 1>), grid, 128, 0, s, p);
-  else if (group == 2) TKV_LAUNCH((quant_attn_f32_kernel<BITS, GRP, 2>), grid, 128, 0, s, p);
+  auto units = [&](int heads) { return p.batch * p.hkv * ((group + heads - 1) / heads); };
+  int heads = group > 2 ? 4 : group;
+  while (heads > 1 && (long long)units(heads / 2) * p.n_chunks <= kF32Alone) heads /= 2;
+  const int grid = units(heads) * (p.n_chunks + 1);
+  if (heads == 1) TKV_LAUNCH((quant_attn_f32_kernel<BITS, GRP, 1>), grid, 128, 0, s, p);
+  else if (heads == 2) TKV_LAUNCH((quant_attn_f32_kernel<BITS, GRP, 2>), grid, 128, 0, s, p);
   else TKV_LAUNCH((quant_attn_f32_kernel<BITS, GRP, 4>), grid, 128, 0, s, p);
   return TKV_OK;
 }
@@ -711,7 +730,7 @@ int32_t quant_attn_decode_impl(const tkv_quant_desc* d, const tkv_quant_cache* c
   // of the sizes alone, whatever the stream may use of the machine: the chunks decide the order of the sums.)  us per
   // call with about 1024 chunks, the tails in between and groups of 5 to 8 not counted twice, against this: 4 bit, 32/32 heads,
   // 2 x 20479 tokens 65.9, 51.4; 16 x 2500 64.1, 52.7; 20000 28.2, 28.2; 32/8, 65500 tokens 57.2, 48.0; 50 x 4000 162.7, 116.5; 32
-  // x 900 36.3, 26.0; 1500 16.7, 17.1; 64/8, 30000 47.1, 41.0; 1 bit, 32/32, 2 x 20000 69.6, 51.7.
+  // x 900 36.3, 26.0; 64/8, 30000 47.1, 41.0; 1 bit, 32/32, 2 x 20000 69.6, 51.7.
   const int units = d->batch * d->n_kv_heads * ((d->n_q_heads / d->n_kv_heads + 3) / 4);
   int gpc = 4, n_chunks = 1;
   long long least = -1;
@@ -738,6 +757,7 @@ int32_t quant_attn_decode_impl(const tkv_quant_desc* d, const tkv_quant_cache* c
   p.q = (const __half*)q;
   p.parts = parts;
   p.scale2 = sm_scale * 1.44269504088896340736f;
+  p.batch = d->batch;
   p.hq = d->n_q_heads;
   p.hkv = d->n_kv_heads;
   p.bits = d->bits;
@@ -768,15 +788,15 @@ int32_t quant_attn_decode_impl(const tkv_quant_desc* d, const tkv_quant_cache* c
   if (!fits()) return TKV_E_WORKSPACE;
   p.chunk_offset = 0;
   const int split = (d->n_q_heads / d->n_kv_heads + 3) / 4;
-  const dim3 grid(n_chunks + 1, d->n_kv_heads * split, d->batch), flat((n_chunks + 1) * units);
+  const dim3 grid(n_chunks + 1, d->n_kv_heads * split, d->batch);
   // the float32 kernel of the two settings reads the query in 32-bit scalar words; the generic one
   // takes it at any fp16 address
   const bool f32 = choice == 0 && (uintptr_t)q % 4 == 0;
   const int variant = d->bits * 100 + d->group_size;
   if (f32 && variant == 464) {
-    if (const int32_t st = launch_f32<4, 64>(p, flat, s); st != TKV_OK) return st;
+    if (const int32_t st = launch_f32<4, 64>(p, s); st != TKV_OK) return st;
   } else if (f32 && variant == 132) {
-    if (const int32_t st = launch_f32<1, 32>(p, flat, s); st != TKV_OK) return st;
+    if (const int32_t st = launch_f32<1, 32>(p, s); st != TKV_OK) return st;
   } else {
     TKV_LAUNCH(quant_attn_generic_kernel, grid, 256, 0, s, p);
   }
