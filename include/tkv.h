@@ -181,9 +181,9 @@ int32_t tkv_quant_attn_decode(const tkv_quant_desc* desc, const tkv_quant_cache*
  * is ONE launch: the attention kernel copies the new rows from
  * k_new / v_new into the fp16 ring itself, attends to them where the caller has them and quantizes a
  * group that they complete.  Where more than one group of a sequence is completed, where new rows take the ring
- * slots of a group's tokens (a few steps of several tokens), where such a step has more workgroups than compute
- * units, and always for 4 bits with groups of 64 and 1 bit with groups of 32, the append's launches come
- * first.  k_new, v_new must stay valid until the call has run on the stream.  n_new == 0: the
+ * slots of a group's tokens (a few steps of several tokens) and where such a step has more workgroups than compute
+ * units, the append's launches come first; for 4 bits with groups of 64 and 1 bit with groups of 32 wherever a group is
+ * completed, or the query is not at a multiple of 4 bytes (and there the attention is two launches).  k_new, v_new must stay valid until the call has run on the stream.  n_new == 0: the
  * attention alone.  Errors: those of the two calls; on an error nothing has been enqueued and
  * seq_len_host is unchanged, except that an error of the attention after a separate append
  * leaves the tokens appended.

@@ -27,8 +27,8 @@ struct QuantAttnParams {
   const __half* k_zero;
   const __half* v_scale;
   const __half* v_zero;
-  const __half* k_resid;
-  const __half* v_resid;
+  __half* k_resid;
+  __half* v_resid;
   const __half* q;
   float* parts;  // [B][Hq][n_chunks + 1][D + 4]
   float scale2;  // sm_scale * log2(e)
@@ -36,6 +36,12 @@ struct QuantAttnParams {
   int32_t groups_per_chunk, n_chunks;  // chunk size in blocks of 32 tokens
   int32_t chunk_offset;  // blockIdx.x + chunk_offset is the chunk; chunk == n_chunks is the fp16 tail
   TkvSeqLens lens;
+  // float32 kernel: the step's new tokens when the call also appends them (Eq. 2), the last n_add[b] tokens of sequence b, rows
+  // [B][n_stride][Hkv][D]; nullptr: none
+  const __half* k_new;
+  const __half* v_new;
+  int32_t n_stride;
+  TkvSeqLens n_add;
 };
 
 __device__ inline float wave_half_max(float v) {
@@ -532,6 +538,19 @@ __global__ __launch_bounds__(128, f32_waves(BITS, H)) void quant_attn_f32_kernel
         const int slot = tok0 + y < n ? slot0 + y : slot_n;
         return rows + (bh * ring + (size_t)(slot < ring ? slot : slot - ring)) * TKV_D;
       };
+      if (p.k_new != nullptr) {
+        // The step's new tokens in this block join the ring first, a token per half-wave; every workgroup of the KV head
+        // writes the same bytes and reads back its own.  On the chain of the wave with the newest tokens alone.  us per
+        // decode step, the append in a launch of its own / here: 4 bit, 32/8 heads, 1500 tokens 15.3, 13.0; 65500 tokens 49.8,
+        // 48.1; 32 x 900 28.2, 26.2; 1 bit, 64/8, 4 x 3000 25.7, 23.3.
+        const int n_old = n - p.n_add.n[b];
+        for (int i = max(tok0, n_old); i < min(tok0 + TKV_BLK, n); ++i) {
+          const __half* src = (t < 16 ? p.k_new : p.v_new) + (((size_t)b * p.n_stride + (i - n_old)) * p.hkv + h) * TKV_D;
+          const u32x4 w = reinterpret_cast<const u32x4*>(src)[t % 16];
+          reinterpret_cast<u32x4*>((t < 16 ? p.k_resid : p.v_resid) + (bh * ring + (size_t)(i % ring)) * TKV_D)[t % 16] = w;
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      }
       const u32x4* krow = reinterpret_cast<const u32x4*>(row(p.k_resid, t));
       u32x4 kr[TKV_D / 8];
       u32x2 vr[TKV_BLK];
@@ -705,11 +724,15 @@ bool on_matrix_cores(const tkv_quant_desc* d) {
   return d->bits == 2 || d->group_size == (d->bits == 4 ? 32 : 64);
 }
 
+bool f32_takes(const tkv_quant_desc* d, const void* q) {
+  return (d->group_size == (d->bits == 4 ? 64 : 32)) && d->bits != 2 && (uintptr_t)q % 4 == 0;
+}
+
 // Body of both entry points.  parts: room for parts_floats floats of split-K partials; arrivals:
 // one zero word per (sequence, KV head, four query heads of its group).  TKV_E_WORKSPACE if the launch's partials do not fit.
-// fresh: the step's new tokens, already counted in seq_len_host but not yet in the fp16 ring (the
-// matrix-core kernel reads them from the caller's buffers and writes them into the ring); only
-// with the matrix-core kernel (TKV_E_UNSUPPORTED otherwise, before anything is launched).
+// fresh: the step's new tokens, already counted in seq_len_host but not yet in the fp16 ring, which the
+// matrix-core and float32 kernels write them into; TKV_E_UNSUPPORTED otherwise, and for the float32 kernel where they
+// complete a group, before anything is launched.
 int32_t quant_attn_decode_impl(const tkv_quant_desc* d, const tkv_quant_cache* c, const void* q, void* out,
                                float sm_scale, float* parts, size_t parts_floats, uint32_t* arrivals,
                                hipStream_t s, const tkv::QuantNewTokens* fresh = nullptr) {
@@ -752,8 +775,8 @@ int32_t quant_attn_decode_impl(const tkv_quant_desc* d, const tkv_quant_cache* c
   p.k_zero = (const __half*)c->k_zero;
   p.v_scale = (const __half*)c->v_scale;
   p.v_zero = (const __half*)c->v_zero;
-  p.k_resid = (const __half*)c->k_resid;
-  p.v_resid = (const __half*)c->v_resid;
+  p.k_resid = (__half*)c->k_resid;
+  p.v_resid = (__half*)c->v_resid;
   p.q = (const __half*)q;
   p.parts = parts;
   p.scale2 = sm_scale * 1.44269504088896340736f;
@@ -778,7 +801,14 @@ int32_t quant_attn_decode_impl(const tkv_quant_desc* d, const tkv_quant_cache* c
                                                    target_blocks, p.lens, fresh, s);
     if (st != TKV_E_UNSUPPORTED) return st;
   }
-  if (fresh != nullptr) return TKV_E_UNSUPPORTED;
+  // the float32 kernel of the two settings reads the query in 32-bit scalar words; the generic one
+  // takes it at any fp16 address
+  const bool f32 = choice == 0 && f32_takes(d, q);
+  if (fresh != nullptr && (!f32 || fresh->complete)) return TKV_E_UNSUPPORTED;
+  p.k_new = fresh != nullptr ? fresh->k_new : nullptr;
+  p.v_new = fresh != nullptr ? fresh->v_new : nullptr;
+  p.n_stride = fresh != nullptr ? fresh->n_stride : 0;
+  p.n_add = fresh != nullptr ? fresh->n_add : TkvSeqLens{};
   // float32 kernels; fewer chunks where the partials' room is the fixed array and takes no more
   auto fits = [&]() { return (size_t)d->batch * d->n_q_heads * (n_chunks + 1) * TKV_PART_STRIDE <= parts_floats; };
   while (!fits() && n_chunks > 1) {
@@ -789,13 +819,9 @@ int32_t quant_attn_decode_impl(const tkv_quant_desc* d, const tkv_quant_cache* c
   p.chunk_offset = 0;
   const int split = (d->n_q_heads / d->n_kv_heads + 3) / 4;
   const dim3 grid(n_chunks + 1, d->n_kv_heads * split, d->batch);
-  // the float32 kernel of the two settings reads the query in 32-bit scalar words; the generic one
-  // takes it at any fp16 address
-  const bool f32 = choice == 0 && (uintptr_t)q % 4 == 0;
-  const int variant = d->bits * 100 + d->group_size;
-  if (f32 && variant == 464) {
+  if (f32 && d->bits == 4) {
     if (const int32_t st = launch_f32<4, 64>(p, s); st != TKV_OK) return st;
-  } else if (f32 && variant == 132) {
+  } else if (f32) {
     if (const int32_t st = launch_f32<1, 32>(p, s); st != TKV_OK) return st;
   } else {
     TKV_LAUNCH(quant_attn_generic_kernel, grid, 256, 0, s, p);
@@ -842,8 +868,8 @@ extern "C" int32_t tkv_quant_decode(const tkv_quant_desc* d, tkv_quant_cache* c,
   tkv_quant_cache_sizes(d, nullptr, &need);
   if (workspace_bytes < need) return TKV_E_WORKSPACE;
   if (n_new == 0) return tkv_quant_attn_decode(d, c, q, out, sm_scale, workspace, workspace_bytes, stream);
-  // One launch where the matrix-core kernel serves the descriptor: the new rows join the fp16 ring there, and a
-  // group that they complete is quantized there as well if it is one, if all of its tokens are in the ring
+  // One launch of the matrix-core kernel, or the float32 kernel and its merge: the new rows join the fp16 ring there, and, on
+  // the matrix cores, a group that they complete is quantized there as well if it is one, if all of its tokens are in the ring
   // already and if no slot that the new rows take is one of theirs (any step of up to residual tokens but
   // for some of several).  Else the append's launches, then the attention's.
   tkv::QuantNewTokens fresh;
@@ -851,7 +877,8 @@ extern "C" int32_t tkv_quant_decode(const tkv_quant_desc* d, tkv_quant_cache* c,
   fresh.v_new = (const __half*)v_new;
   fresh.n_stride = n_new;
   fresh.complete = false;
-  bool one_launch = g_kernel_choice.load() == 0 && on_matrix_cores(d);
+  const bool mfma = on_matrix_cores(d);
+  bool one_launch = g_kernel_choice.load() == 0 && (mfma || f32_takes(d, q));
   for (int b = 0; b < d->batch; ++b) {
     const int64_t n0 = c->seq_len_host[b];
     const int32_t add = n_valid_host ? n_valid_host[b] : n_new;
@@ -862,7 +889,7 @@ extern "C" int32_t tkv_quant_decode(const tkv_quant_desc* d, tkv_quant_cache* c,
     const int32_t nq0 = tkv::n_quantized((int32_t)n0, d->residual, g), nq1 = tkv::n_quantized(n1, d->residual, g);
     if (nq1 != nq0) {
       fresh.complete = true;
-      if (nq1 - nq0 != g || add > d->residual || n1 - nq0 > d->residual + g) one_launch = false;
+      if (!mfma || nq1 - nq0 != g || add > d->residual || n1 - nq0 > d->residual + g) one_launch = false;
     }
   }
   auto two_calls = [&]() -> int32_t {

@@ -214,7 +214,7 @@ class QuantLayer:
     def decode(self, q: torch.Tensor, sm_scale: float, k_new: torch.Tensor, v_new: torch.Tensor, n_valid=None,
                out: torch.Tensor | None = None, stream=None):
         """tkv_quant_decode: the step's append and the attention over the grown cache in one call
-        (one launch on the matrix-core settings, but for few steps; see tkv_quant_decode)."""
+        (no launch for the append, but for few steps; see tkv_quant_decode)."""
         d = self.desc
         assert q.dtype == torch.float16 and q.is_cuda and q.is_contiguous()
         assert tuple(q.shape) == (d.batch, d.n_q_heads, d.head_dim)

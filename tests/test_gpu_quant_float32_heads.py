@@ -32,3 +32,30 @@ def test_bits_of_the_reference_kernel(bits, g, hq, hkv, lens):
         finally:
             tkv.debug_quant_attn_config(0)
         assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+
+
+@pytest.mark.parametrize("bits,g", [(4, 64), (1, 32)])
+@pytest.mark.parametrize("hq,hkv,lens", [(8, 8, (1, 700, 150)), (32, 8, (0, 5000, 4223)), (21, 7, (250, 249, 60000)),
+                                         (40, 5, (95, 96, 12000))])
+def test_decode_steps_join_the_ring_in_the_attention(bits, g, hq, hkv, lens):
+    """Several new tokens at once, none for some sequences, the ring's end, steps that complete a group: cache and output of
+    the append and the attention one after the other."""
+    gen = torch.Generator(device="cuda").manual_seed(hq)
+    cap = (max(lens) + 400) // g * g
+    one, two = (tkv.QuantLayer(n_q_heads=hq, n_kv_heads=hkv, bits=bits, group_size=g, residual=64, capacity=cap, batch=3)
+                for _ in range(2))
+    k, v = (torch.randn(3, max(lens), hkv, 128, generator=gen, device="cuda").half() for _ in range(2))
+    for layer in (one, two):
+        layer.append(k, v, n_valid=list(lens))
+    for step, (n_new, n_valid) in enumerate([(1, None), (3, (3, 0, 2)), (1, (0, 0, 0)), (33, (33, 1, 20)), (1, None), (17, None), (20, None)]):
+        print(f"case f32 ring bits={bits} {hq}/{hkv} lens={lens} step={step}", flush=True)
+        kn, vn = (torch.randn(3 * n_new * hkv * 128 + 1, generator=gen, device="cuda").half()[1:].view(3, n_new, hkv, 128)
+                  for _ in range(2))  # (rows at odd fp16 addresses)
+        q = torch.randn(3, hq, 128, generator=gen, device="cuda").half()
+        got = one.decode(q, SM, kn, vn, n_valid=n_valid).clone()
+        two.append(kn, vn, n_valid=n_valid)
+        want = two.attn_decode(q, SM)
+        assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+        assert list(one.seq_len) == list(two.seq_len)
+        for name in ("k_resid", "v_resid"):
+            assert torch.equal(one.buffers[name], two.buffers[name])
