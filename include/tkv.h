@@ -445,7 +445,7 @@ typedef struct {
 } tkv_pref_desc;
 
 /* Workspace bytes of tkv_dense_preference: n_q * Hq rows, each with room for
- * min(capacity, 32 * top_k) candidate logits, the candidates by workgroup, and capacity / 32 partial
+ * min(capacity, max(32 * top_k, 1536)) candidate logits, the candidates by workgroup, and capacity / 32 partial
  * maxima. */
 int32_t tkv_dense_preference_sizes(const tkv_pref_desc* desc, size_t* workspace_bytes);
 

@@ -867,6 +867,13 @@ int pref_sub(int slab_rows) { return slab_rows <= 64 ? 8 : slab_rows == 128 ? 4 
 struct PrefSplit {
   int32_t P, rounds, nblk, s_P, s_rounds, s_per_round, s_nblk, s_rank;
 };
+// Candidates of a row that there is room for at least.  32 top_k hold what the exact bound lets through; of the sample's
+// the least top_k need more: where every logit is a candidate (s_rank 0) up to 1520 of them (top_k below 48; from 48 on the 32
+// top_k are enough), and a rank of 13 to 21 stands for 16 times as many logits on average and seven times that hardly
+// ever (10^-18).  With 32 top_k alone nearly every slab of a prompt took the exact form as well: 32/8 heads, n_q = 64, 131072
+// keys, us per call with 32 top_k / now: top_k = 1 369, 166; 8 376, 169; 16 326, 164; 1100 keys, top_k = 16 82.6, 72.4 (two
+// evaluations of all logits as a rule: 205, 220, 224, 78).
+constexpr size_t kCandLeast = 1536;
 int pref_slabs(const tkv_pref_desc* d) { return (pref_rows(d) + pref_slab_rows(d) - 1) / pref_slab_rows(d); }
 // most workgroups per (KV head, slab): the machine filled once
 int pref_p_cap(const tkv_pref_desc* d) { return std::max(1, 256 / (d->n_kv_heads * pref_slabs(d))); }
@@ -920,7 +927,7 @@ size_t pref_ws_layout(const tkv_pref_desc* d, char* base, PrefWs* out) {
   size_t nblk_max = kSampleBlocks;
   for (int P = 1; P <= p_max; ++P)
     nblk_max = std::max(nblk_max, (size_t)P * pref_rounds(n_chunks, P) * sub * 16);
-  const size_t cand_cap = std::min<size_t>((size_t)d->capacity, (size_t)32 * d->top_k);
+  const size_t cand_cap = std::min<size_t>((size_t)d->capacity, std::max((size_t)32 * d->top_k, kCandLeast));
   // a segment's expected length: the row's candidates (about 1.8 top_k) over the workgroups that share them, and
   // room for what chance adds (a full segment is only slower); at least three whole chunks for short prompts, of which
   // most is a candidate
