@@ -12,7 +12,7 @@
 //   pass 2  all logits: softmax denominator against m, the logits above L to the row's candidates.
 //   exact   the same once more for the slabs with a row that the sample misled (too few or too many
 //           candidates, a denominator beyond float's range), with a bound that cannot fail; these three
-//           launches return at once as a rule:
+//           launches return at once as a rule (short prompts take this form alone, without the sample):
 //     pass 1  block maxima of all keys: every (row, lane slot of a wave) keeps the maximum of
 //             the <= 32 logits it sees in a round of 8 key chunks.  The blocks of a row are
 //             disjoint, so the top_k-th largest block maximum L is a lower bound of the row's
@@ -99,7 +99,7 @@ struct PrefParams {
   int32_t seg_cap, cand_cap;
   int32_t s_P, s_rounds, s_per_round, s_nblk;  // the same of the sample; chunks per round
   int32_t s_rank;        // L: the s_rank-th largest block maximum of the sample or a little below it; 0: -inf
-  int32_t exact;         // the passes and the bound of the exact form, for failed slabs only
+  int32_t exact;         // 1: the passes and the bound of the exact form, for failed slabs only; 2: for all, no sample before
 };
 
 __device__ inline uint32_t float_key(float s) {
@@ -156,7 +156,7 @@ __global__ __launch_bounds__(kThreads) void pref_pass_kernel(PrefParams p) {
   const int G = p.hq / p.hkv, R = G * p.n_q;
   const int rows_here = min(S::ROWS, R - slab * S::ROWS);
   const size_t row_first = (size_t)h * R + (size_t)slab * S::ROWS;
-  if (PASS != 0 && p.exact != 0) {
+  if (PASS != 0 && p.exact == 1) {
     bool bad;
     if (PASS == 1) {
       bad = __syncthreads_or(tid < rows_here && row_failed(p, row_first + tid)) != 0;
@@ -586,7 +586,7 @@ __global__ __launch_bounds__(256) void pref_bound_kernel(PrefParams p) {
   const int tid = threadIdx.x;
   const size_t gr = blockIdx.x;
   const int R = p.hq / p.hkv * p.n_q;
-  if (p.failed[(int)(gr / R) * p.slabs + (int)(gr % R) / ROWS] == 0u) return;
+  if (p.exact == 1 && p.failed[(int)(gr / R) * p.slabs + (int)(gr % R) / ROWS] == 0u) return;
   RowKeys keys;
   keys.load(p.blkmax + gr * p.nblk, (uint32_t)p.nblk);
   uint32_t mk = 0;
@@ -868,11 +868,10 @@ struct PrefSplit {
   int32_t P, rounds, nblk, s_P, s_rounds, s_per_round, s_nblk, s_rank;
 };
 // Candidates of a row that there is room for at least.  32 top_k hold what the exact bound lets through; of the sample's
-// the least top_k need more: where every logit is a candidate (s_rank 0) up to 1520 of them (top_k below 48; from 48 on the 32
-// top_k are enough), and a rank of 13 to 21 stands for 16 times as many logits on average and seven times that hardly
+// the least top_k need more: a rank of 13 to 21 stands for 16 times as many logits on average, and seven times that hardly
 // ever (10^-18).  With 32 top_k alone nearly every slab of a prompt took the exact form as well: 32/8 heads, n_q = 64, 131072
-// keys, us per call with 32 top_k / now: top_k = 1 369, 166; 8 376, 169; 16 326, 164; 1100 keys, top_k = 16 82.6, 72.4 (two
-// evaluations of all logits as a rule: 205, 220, 224, 78).
+// keys, us per call with 32 top_k / now: top_k = 1 369, 166; 8 376, 169; 16 326, 164 (two evaluations of all logits as a
+// rule: 205, 220, 224).
 constexpr size_t kCandLeast = 1536;
 int pref_slabs(const tkv_pref_desc* d) { return (pref_rows(d) + pref_slab_rows(d) - 1) / pref_slab_rows(d); }
 // most workgroups per (KV head, slab): the machine filled once
@@ -959,6 +958,13 @@ size_t pref_ws_layout(const tkv_pref_desc* d, char* base, PrefWs* out) {
   return o;
 }
 
+// Prompts up to this long of which too large a part would have to be sampled (s_rank 0: every logit is a candidate) take the
+// exact form at once, all slabs of it: five launches instead of eight.  Us per call, sample and three launches that
+// return / this: 32/8 heads, n_q = 64: 150 keys, top_k = 1 61.5, 39.3; 1100 keys, 16 72.1, 46.8; 2000, 256 84.7, 62.1; 3000, 256
+// 85.5, 62.5; 2000, 1024 80.2, 75.5; 32/4, n_q = 16: 150, 1 43.2, 29.2; 2000, 1024 51.9, 52.5.  Longer ones have too many block
+// maxima to search: 4000, 1024 99.5, 109.4.
+constexpr int kDirectKeys = 3072;
+
 template <class S>
 int32_t launch_pref(PrefParams p, const PrefSplit& sp, hipStream_t s) {
   static const bool lds_ok =
@@ -971,7 +977,12 @@ int32_t launch_pref(PrefParams p, const PrefSplit& sp, hipStream_t s) {
   if (!lds_ok) return TKV_E_HIP;
   const int rows = p.hq * p.n_q;
   const dim3 grid(sp.P, p.hkv, p.slabs);
-  if (p.n > p.top_k) {
+  if (p.n > p.top_k && p.s_rank == 0 && p.n <= kDirectKeys) {
+    p.exact = 2;
+    TKV_LAUNCH((pref_pass_kernel<1, S>), grid, kThreads, kPass1Lds, s, p);
+    TKV_LAUNCH(pref_bound_kernel<S::ROWS>, dim3(rows), 256, 0, s, p);
+    TKV_LAUNCH((pref_pass_kernel<2, S>), grid, kThreads, kPass2Lds, s, p);
+  } else if (p.n > p.top_k) {
     p.exact = 0;
     TKV_LAUNCH((pref_pass_kernel<0, S>), dim3(sp.s_P, p.hkv, p.slabs), kThreads, kPass1Lds, s, p);
     if (p.s_nblk <= 1024) TKV_LAUNCH(pref_sample_bound_kernel<16>, dim3((rows + 3) / 4), 256, 0, s, p);
