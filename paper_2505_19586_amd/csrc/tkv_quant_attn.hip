@@ -645,13 +645,20 @@ __global__ __launch_bounds__(128, f32_waves(BITS, H)) void quant_attn_f32_kernel
 // units idle, up to four workgroups on each: with 4 heads a block costs 4.8 us, a chain of 2500 vector
 // instructions.  4 bit, us per call, always 4 / by this: 32/8 heads, 891 tokens 17.5, 11.9; 1500 tokens 17.1, 12.0; 5000
 // tokens 18.8, 14.7 (17.9 with at most two workgroups each); 64/8, 821 tokens 22.2, 14.2; 8/1, 60000 tokens 30.0, 27.2.
-constexpr int kF32Alone = 1024;
+// Tails are workgroups too, and read their rows once more for every split: they count as one, and as two before the
+// last split.  Without them counted / with them (always 4): 4 bit, 32/8, 32 x 300 tokens 26.8, 18.3 (17.6); 64 x 200 29.2, 22.5 (22.5), 16 x
+// 300 16.0, 13.4 (16.4); 64/8, 32 x 430 37.5, 26.2 (26.0), 16 x 300 27.5, 18.5 (17.5); 1 bit, 32/8, 32 x 300 22.0, 17.5 (17.3).  (A few
+// more than four for every compute unit, since the longest sequences have just that: 1 bit, 8/1, 98135 tokens, 1028 workgroups
+// 34.1, 37.2 with 4 heads.)
+constexpr int kF32Alone = 1024 + 32;
+// any_group: some sequence has quantized tokens (the one chunk that there is otherwise has nothing to do).
 template <int BITS, int GRP>
-int32_t launch_f32(const QuantAttnParams& p, hipStream_t s) {
+int32_t launch_f32(const QuantAttnParams& p, bool any_group, hipStream_t s) {
   const int group = p.hq / p.hkv;
   auto units = [&](int heads) { return p.batch * p.hkv * ((group + heads - 1) / heads); };
   int heads = group > 2 ? 4 : group;
-  while (heads > 1 && (long long)units(heads / 2) * p.n_chunks <= kF32Alone) heads /= 2;
+  const int chunks = any_group ? p.n_chunks : 0;
+  while (heads > 1 && (long long)units(heads / 2) * (chunks + (heads == 2 ? 2 : 1)) <= kF32Alone) heads /= 2;
   const int grid = units(heads) * (p.n_chunks + 1);
   if (heads == 1) TKV_LAUNCH((quant_attn_f32_kernel<BITS, GRP, 1>), grid, 128, 0, s, p);
   else if (heads == 2) TKV_LAUNCH((quant_attn_f32_kernel<BITS, GRP, 2>), grid, 128, 0, s, p);
@@ -820,9 +827,9 @@ int32_t quant_attn_decode_impl(const tkv_quant_desc* d, const tkv_quant_cache* c
   const int split = (d->n_q_heads / d->n_kv_heads + 3) / 4;
   const dim3 grid(n_chunks + 1, d->n_kv_heads * split, d->batch);
   if (f32 && d->bits == 4) {
-    if (const int32_t st = launch_f32<4, 64>(p, s); st != TKV_OK) return st;
+    if (const int32_t st = launch_f32<4, 64>(p, max_groups > 0, s); st != TKV_OK) return st;
   } else if (f32) {
-    if (const int32_t st = launch_f32<1, 32>(p, s); st != TKV_OK) return st;
+    if (const int32_t st = launch_f32<1, 32>(p, max_groups > 0, s); st != TKV_OK) return st;
   } else {
     TKV_LAUNCH(quant_attn_generic_kernel, grid, 256, 0, s, p);
   }

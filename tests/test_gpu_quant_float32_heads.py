@@ -35,6 +35,31 @@ def test_bits_of_the_reference_kernel(bits, g, hq, hkv, lens):
 
 
 @pytest.mark.parametrize("bits,g", [(4, 64), (1, 32)])
+@pytest.mark.parametrize("hq,hkv,batch,lens", [
+    # tails counted: (sequences, KV heads, groups of 1 head) x (chunks + 2) <= 1056, (... of 2 heads) x (chunks + 1) <= 1056 or not
+    (32, 8, 10, (230,)), (32, 8, 11, (230,)), (32, 8, 32, (150, 300, 430)), (32, 8, 34, (230,)), (24, 8, 16, (230, 300)), (16, 8, 21, (230,)),
+    (16, 8, 23, (230,)), (16, 8, 40, (170,)), (64, 8, 16, (170, 300, 1087)), (12, 2, 64, (300,))])
+def test_bits_of_the_reference_kernel_many_short_sequences(bits, g, hq, hkv, batch, lens):
+    gen = torch.Generator(device="cuda").manual_seed(batch)
+    k, v = (torch.randn(batch, max(lens), hkv, 128, generator=gen, device="cuda").half() for _ in range(2))
+    q = 2.0 * torch.randn(batch, hq, 128, generator=gen, device="cuda").half()
+    layer = tkv.QuantLayer(n_q_heads=hq, n_kv_heads=hkv, bits=bits, group_size=g, residual=128, capacity=(max(lens) + g) // g * g,
+                           batch=batch)
+    at = 0
+    for n in lens:
+        print(f"case f32 short bits={bits} {hq}/{hkv} B={batch} n={n}", flush=True)
+        layer.append(k[:, at:n].contiguous(), v[:, at:n].contiguous())
+        at = n
+        got = layer.attn_decode(q, SM).clone()
+        try:
+            tkv.debug_quant_attn_config(1)
+            want = layer.attn_decode(q, SM).clone()
+        finally:
+            tkv.debug_quant_attn_config(0)
+        assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+
+
+@pytest.mark.parametrize("bits,g", [(4, 64), (1, 32)])
 @pytest.mark.parametrize("hq,hkv,lens", [(8, 8, (1, 700, 150)), (32, 8, (0, 5000, 4223)), (21, 7, (250, 249, 60000)),
                                          (40, 5, (95, 96, 12000))])
 def test_decode_steps_join_the_ring_in_the_attention(bits, g, hq, hkv, lens):
