@@ -912,7 +912,8 @@ extern "C" int32_t tkv_quant_decode(const tkv_quant_desc* d, tkv_quant_cache* c,
                               &fresh);
   if (st != TKV_OK)  // nothing was launched: the cache is as it was
     for (int b = 0; b < d->batch; ++b) c->seq_len_host[b] -= fresh.n_add.n[b];
-  if (st == TKV_E_UNSUPPORTED && fresh.complete) return two_calls();
+  // (a completing step with more workgroups than compute units, or a sequence of more chunks than the matrix-core kernel has)
+  if (st == TKV_E_UNSUPPORTED) return two_calls();
   return st;
 }
 
