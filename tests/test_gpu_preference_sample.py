@@ -17,9 +17,9 @@ def sampled_keys(n):
     x = np.arange((n + 15) // 16, dtype=np.uint64)
     m = np.uint64(0xFFFFFFFF)
     i = x.copy()
-    x = (x * np.uint64(0x9E3779B1) + np.uint64(0x7F4A7C15)) & m
-    x = ((x ^ (x >> np.uint64(15))) * np.uint64(0x2C1B3C6D)) & m
-    x = ((x ^ (x >> np.uint64(12))) * np.uint64(0x297A2D39)) & m
+    x = (x * np.uint64(0x9E3779B9) + np.uint64(0x3C6EF372)) & m
+    x = ((x ^ (x >> np.uint64(16))) * np.uint64(0xBB67AE85)) & m
+    x = ((x ^ (x >> np.uint64(16))) * np.uint64(0x6A09E667)) & m
     s = 16 * i + (x >> np.uint64(28))
     return s[s < n].astype(np.int64)
 
