@@ -971,11 +971,11 @@ size_t pref_ws_layout(const tkv_pref_desc* d, char* base, PrefWs* out) {
   return o;
 }
 
-// Prompts up to this long of which too large a part would have to be sampled (s_rank 0: every logit is a candidate) take the
-// exact form at once, all slabs of it: five launches instead of eight.  Us per call, sample and three launches that
-// return / this: 32/8 heads, n_q = 64: 150 keys, top_k = 1 61.5, 39.3; 1100 keys, 16 72.1, 46.8; 2000, 256 84.7, 62.1; 3000, 256
-// 85.5, 62.5; 2000, 1024 80.2, 75.5; 32/4, n_q = 16: 150, 1 43.2, 29.2; 2000, 1024 51.9, 52.5.  Longer ones have too many block
-// maxima to search: 4000, 1024 99.5, 109.4.
+// Prompts up to this long take the exact form at once, all slabs of it: five launches instead of eight.  Us per call, sample and
+// three launches that return / this: 32/8 heads, n_q = 64: 150 keys, top_k = 1 61.5, 39.3; 1030, 6 66.8, 45.6; 1100, 16 72.1, 46.8;
+// 2000, 256 84.7, 62.1; 2000, 1024 80.2, 75.5; 3072, 16 54.9, 49.5; 3072, 160 71.5, 56.1; 32/4, n_q = 16: 150, 1 43.2, 29.2; 2000,
+// 1024 51.9, 52.5; 3072, 40 44.0, 37.1.  In longer ones the block maxima are many to find and to search: 4000, 1024 99.5,
+// 109.4.
 constexpr int kDirectKeys = 3072;
 
 template <class S>
@@ -990,7 +990,7 @@ int32_t launch_pref(PrefParams p, const PrefSplit& sp, hipStream_t s) {
   if (!lds_ok) return TKV_E_HIP;
   const int rows = p.hq * p.n_q;
   const dim3 grid(sp.P, p.hkv, p.slabs);
-  if (p.n > p.top_k && p.s_rank == 0 && p.n <= kDirectKeys) {
+  if (p.n > p.top_k && p.n <= kDirectKeys) {
     p.exact = 2;
     TKV_LAUNCH((pref_pass_kernel<1, S>), grid, kThreads, kPass1Lds, s, p);
     TKV_LAUNCH(pref_bound_kernel<S::ROWS>, dim3(rows), 256, 0, s, p);
