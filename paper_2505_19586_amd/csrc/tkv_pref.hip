@@ -904,15 +904,14 @@ PrefSplit pref_split(const tkv_pref_desc* d, int32_t n, int32_t n_cus) {
   return sp;
 }
 
-// Candidates that few rows of a prompt exceed (a row with more than its final kernel keeps in registers takes the general form
-// there: the kernel 35 us longer, were it one row; 16 s_rank + 4 s_rank was too few for some: 4/1 heads, n_q = 64, 94961 keys, top_k
-// = 256 98.0 us per call, 63.2 with this).  Up to 9/8 s_rank of the sample's blocks of 4 s_per_round keys have a key above L;
-// as many keys as make that part of the blocks, and two and a half standard deviations.
+// Candidates that hardly a row of a prompt exceeds (a row with more than its final kernel keeps in registers takes the general
+// form there: the kernel 10 to 40 us longer, were it one row of thousands).  Up to 9/8 s_rank of the sample's blocks of 4 s_per_round
+// keys have a key above L; as many keys as make that part of the blocks, and three and a half standard deviations.
 int pref_expect(const PrefSplit& sp, int32_t n) {
   if (sp.s_rank == 0) return n;
   const double above = sp.s_rank * 1.125, m = 4.0 * sp.s_per_round, blocks = std::max(above, (double)n / kStride / m);
   const double part = 1.0 - std::pow(1.0 - above / blocks, 1.0 / m);
-  return (int)std::min<double>(n, n * part * (1.0 + 2.5 / std::sqrt(above)));
+  return (int)std::min<double>(n, n * part * (1.0 + 3.5 / std::sqrt(above)));
 }
 
 // Workspace of one sequence (sequences are processed one after the other); the counters come
@@ -1008,10 +1007,14 @@ int32_t launch_pref(PrefParams p, const PrefSplit& sp, hipStream_t s) {
     TKV_LAUNCH((pref_pass_kernel<2, S>), grid, kThreads, kPass2Lds, s, p);
   }
   const int expect = pref_expect(sp, p.n);
-  // Us per call with the kernel for many candidates above 12 * 256 / with one of 24 * 256 between: 1/1 heads, n_q = 16, 94961 keys,
-  // top_k = 1500 84.5, 49.4; 3000 102.9, 59.1; 4/1, n_q = 64, 30000 keys, 2000 101.6, 64.1; 32/8, 94961, 2000 189.1, 168.2.
+  // Registers for more candidates than there are cost little, a row that does not fit much.  Us per call with 4 / 6 / 12 / 16 / 24 /
+  // many: 28/4 heads, n_q = 32, 46361 keys, top_k = 185 73.6, 64.9, 66.7, 67.5, 70.3, 75.6; 32/8, n_q = 64, 131072 keys, 1024 191.9,
+  // 192.1, 170.2, 172.1, 178.4, 188.0; 11552 keys, 28/4, 911 88.7, 88.4, 86.7, 84.0, 93.1, 97.3; 94961, 2000 200.4, 200.4, 201.1,
+  // 184.4, 165.3, 188.6; 4/1, 94961, 1400 106, 107, 108, 69.4, 70.7, 105.5.
   if (expect <= 4 * 256) TKV_LAUNCH(pref_final_kernel<4>, dim3(rows), 256, 0, s, p);
+  else if (expect <= 6 * 256) TKV_LAUNCH(pref_final_kernel<6>, dim3(rows), 256, 0, s, p);
   else if (expect <= 12 * 256) TKV_LAUNCH(pref_final_kernel<12>, dim3(rows), 256, 0, s, p);
+  else if (expect <= 16 * 256) TKV_LAUNCH(pref_final_kernel<16>, dim3(rows), 256, 0, s, p);
   else if (expect <= 24 * 256) TKV_LAUNCH(pref_final_kernel<24>, dim3(rows), 256, 0, s, p);
   else TKV_LAUNCH(pref_final_big_kernel, dim3(rows), 256, 0, s, p);
   TKV_LAUNCH(pref_sum_kernel, dim3(p.hq), 64, 0, s, p);

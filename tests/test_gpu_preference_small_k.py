@@ -51,10 +51,10 @@ def test_short_prompts(hq, hkv, n_q, n, top_k):
     _exact_slabs(q, k, top_k)
 
 
-@pytest.mark.parametrize("n,top_k", [(20000, 180), (20000, 256), (30000, 1024), (30000, 1200), (30000, 1700), (30000, 2000), (30000, 2400),
-                                     (30000, 3000), (5000, 600), (6144, 1500), (6145, 1500)])
+@pytest.mark.parametrize("n,top_k", [(20000, 130), (20000, 180), (20000, 256), (20000, 400), (30000, 1024), (30000, 1200), (30000, 1700),
+                                     (30000, 2000), (30000, 2400), (30000, 3000), (4096, 600), (4097, 600), (6144, 1500), (6145, 1500)])
 def test_rows_of_every_final_kernel(n, top_k):
-    """Numbers of candidates on both sides of what a final kernel keeps in registers (1024, 3072, 6144), all keys and most."""
+    """Numbers of candidates on both sides of what a final kernel keeps in registers (1024, 1536, 3072, 4096, 6144), all keys and most."""
     print(f"case final n={n} k={top_k}", flush=True)
     rng = np.random.default_rng(n + top_k)
     q = rng.standard_normal((16, 4, 128)).astype(np.float16)
