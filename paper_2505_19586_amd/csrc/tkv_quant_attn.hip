@@ -33,8 +33,7 @@ struct QuantAttnParams {
   float* parts;  // [B][Hq][n_chunks + 1][D + 4]
   float scale2;  // sm_scale * log2(e)
   int32_t batch, hq, hkv, bits, group, residual, capacity;
-  int32_t groups_per_chunk, n_chunks;  // chunk size in blocks of 32 tokens
-  int32_t chunk_offset;  // blockIdx.x + chunk_offset is the chunk; chunk == n_chunks is the fp16 tail
+  int32_t groups_per_chunk, n_chunks;  // chunk size in blocks of 32 tokens; chunk n_chunks is the fp16 tail
   TkvSeqLens lens;
   // float32 kernel: the step's new tokens when the call also appends them (Eq. 2), the last n_add[b] tokens of sequence b, rows
   // [B][n_stride][Hkv][D]; nullptr: none
@@ -65,7 +64,7 @@ __global__ __launch_bounds__(256) void quant_attn_generic_kernel(QuantAttnParams
   // Groups of more than 4 query heads per KV head are served 4 heads at a time: blockIdx.y runs
   // over (KV head, quarter of its group).
   const int split = (p.hq / p.hkv + 3) / 4;
-  const int b = blockIdx.z, h = blockIdx.y / split, chunk = blockIdx.x + p.chunk_offset;
+  const int b = blockIdx.z, h = blockIdx.y / split, chunk = blockIdx.x;
   const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64;
   const int qh0 = h * (p.hq / p.hkv) + 4 * (blockIdx.y % split);  // first query head of this workgroup
   const int G = min(4, (h + 1) * (p.hq / p.hkv) - qh0);
@@ -823,7 +822,6 @@ int32_t quant_attn_decode_impl(const tkv_quant_desc* d, const tkv_quant_cache* c
     p.n_chunks = n_chunks = (max_groups + p.groups_per_chunk - 1) / p.groups_per_chunk;
   }
   if (!fits()) return TKV_E_WORKSPACE;
-  p.chunk_offset = 0;
   const int split = (d->n_q_heads / d->n_kv_heads + 3) / 4;
   const dim3 grid(n_chunks + 1, d->n_kv_heads * split, d->batch);
   if (f32 && d->bits == 4) {
