@@ -634,7 +634,7 @@ def run_step(args, tkv, torch, dev):
                    **({"sparse_layer_calls": "tkv_sparse_append_estimate_topk + tkv_sparse_gather_attn" if args.separate_calls
                        else "tkv_sparse_decode (one launch)",
                        "quant_layer_calls": "tkv_quantize_append + tkv_quant_attn_decode" if args.separate_calls
-                       else "tkv_quant_decode (one launch unless the token completes a group)"}
+                       else "tkv_quant_decode (one launch; a group that the token completes is quantized there)"}
                       if args.schedule == "chained" and args.dynamic_channels == "off" else {}),
                    **({"gather_compute_units": args.gather_cus, "gather_streams": args.gather_streams}
                       if args.schedule == "overlapped" else {}),

@@ -7,8 +7,9 @@
 // change.  Logits are never written to memory.
 //
 //   pass 0  logits of a sample, one key out of every 16, as block maxima of four keys.
-//   bound   per row: L, chosen from the sample so that, whatever the data, fewer than one row in 10^7 has
-//           less than top_k logits above it (about 1.8 top_k are), and a reference m, the sample's maximum.
+//   bound   per row: L, chosen from the sample so that for keys that know nothing of its picks (they are fixed, not drawn)
+//           about one row in 6 x 10^7 has less than top_k logits above it (about 1.8 top_k are; every row is checked), and a
+//           reference m, the sample's maximum.
 //   pass 2  all logits: softmax denominator against m, the logits above L to the row's candidates.
 //   exact   the same once more for the slabs with a row that the sample misled (too few or too many
 //           candidates, a denominator beyond float's range), with a bound that cannot fail; these three
@@ -894,10 +895,11 @@ PrefSplit pref_split(const tkv_pref_desc* d, int32_t n, int32_t n_cus) {
   sp.s_rounds = std::min(mine, slots / sp.s_P);
   sp.s_per_round = (mine + sp.s_rounds - 1) / sp.s_rounds;
   sp.s_nblk = sp.s_P * sp.s_rounds * kSlotBlocks;
-  // Rank in the sample that lies at or below the row's top_k-th logit but for one row in 10^8, whatever the
-  // data: the number of the top_k largest that are drawn, each with probability 1/16, exceeds its mean by t
-  // with probability at most exp(-t^2 / (2 (variance + t / 3))) (Bernstein's bound).  Too large a part of the sample: every
-  // logit is a candidate.
+  // Rank in the sample that lies at or below the row's top_k-th logit but for one row in 6 x 10^7 (exp(-18) = 1.5e-8): were the picks
+  // drawn, the number of the top_k largest that are among them, each with probability 1/16, would exceed its mean by t
+  // with probability at most exp(-t^2 / (2 (variance + t / 3))) (Bernstein's bound).  The picks are fixed, and keys
+  // made against them can defeat any rank: what counts is that the candidates of every row are counted, and the exact form.  Too
+  // large a part of the sample: every logit is a candidate.
   const double mean = (double)d->top_k / kStride, var = mean * (1.0 - 1.0 / kStride), lambda = 18.0;
   const int rank = (int)std::ceil(mean + lambda / 3 + std::sqrt(lambda * lambda / 9 + 2 * lambda * var));
   sp.s_rank = 10 * rank > 9 * (n_s / 4) ? 0 : rank;

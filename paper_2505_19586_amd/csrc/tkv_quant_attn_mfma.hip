@@ -1125,6 +1125,10 @@ int32_t launch_quant_attn_mfma(const tkv_quant_desc* d, const tkv_quant_cache* c
   //     45000 (89) 23.1, 22.1; 131000 (257) 39.9, 33.3
   //   32 / 4 heads, 4 bit: 20000 (20) 14.5, 17.0; 65000 (64) 20.3, 21.2; 131000 (128) 28.6, 26.8
   //   8 / 1 heads, 4 bit (never more than 64 compute units busy in one): 65000 (16) 16.7, 27.6; 131000 18.9, 28.9
+  //   1 bit / 64: 32 / 4 heads: 20000 (20) 15.8, 17.2; 45000 (44) 18.5, 19.6; 65000 (64) 20.7, 20.7; 80000 (78) 22.3, 21.8; 98413 (96)
+  //     24.2, 22.7; 131000 (128) 27.1, 24.8; 64 / 8: 20000 (40) 18.2, 18.3; 30000 (59) 20.1, 19.7; 45000 (89) 23.3, 21.6; 8 / 1: 65000
+  //     (16) 18.0, 23.9
+  //   2 bit / 64: 32 / 4: 65000 (64) 20.4, 20.8; 131000 26.6, 24.8
   constexpr int kTwoWorkgroupsBlocks = 80;
   const bool large_group = d->n_q_heads / d->n_kv_heads > 4;
   int32_t st = plan(0, kTailBlocks);
