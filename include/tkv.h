@@ -181,8 +181,8 @@ int32_t tkv_quant_attn_decode(const tkv_quant_desc* desc, const tkv_quant_cache*
  * is ONE launch: the attention kernel copies the new rows from
  * k_new / v_new into the fp16 ring itself, attends to them where the caller has them and quantizes a
  * group that they complete.  Where more than one group of a sequence is completed, where new rows take the ring
- * slots of a group's tokens (a few steps of several tokens) and where such a step has more workgroups than compute
- * units, the append's launches come first; for 4 bits with groups of 64 and 1 bit with groups of 32 wherever a group is
+ * slots of a group's tokens (a few steps of several tokens), where such a step has more workgroups than compute
+ * units and where a sequence has more than about 4 Mi tokens, the append's launches come first; for 4 bits with groups of 64 and 1 bit with groups of 32 wherever a group is
  * completed, or the query is not at a multiple of 4 bytes (and there the attention is two launches).  k_new, v_new must stay valid until the call has run on the stream.  n_new == 0: the
  * attention alone.  Errors: those of the two calls; on an error nothing has been enqueued and
  * seq_len_host is unchanged, except that an error of the attention after a separate append
@@ -445,8 +445,10 @@ typedef struct {
 } tkv_pref_desc;
 
 /* Workspace bytes of tkv_dense_preference: n_q * Hq rows, each with room for
- * min(capacity, max(32 * top_k, 1536)) candidate logits, the candidates by workgroup, and capacity / 32 partial
- * maxima. */
+ * min(capacity, max(32 * top_k, 1536)) candidate logits, the candidates by workgroup (384 and more for each of up to 256
+ * workgroups that share a row), and capacity / 32 partial maxima: 391 MiB for 32/8 heads, n_q = 64, top_k = 1024, 131072
+ * tokens.  The number belongs to this build of the library: a smaller buffer, such as one sized by another build, is refused
+ * (TKV_E_WORKSPACE). */
 int32_t tkv_dense_preference_sizes(const tkv_pref_desc* desc, size_t* workspace_bytes);
 
 /*
@@ -461,7 +463,7 @@ int32_t tkv_dense_preference_sizes(const tkv_pref_desc* desc, size_t* workspace_
  * sample of the keys gives a per-row bound below the top_k-th largest logit, one evaluation the softmax
  * denominator and the logits above that bound, among which the top_k largest are then selected
  * exactly; where the sample's bound turns out not to do, the rows concerned are evaluated twice more with
- * an exact one.  The mass of a row's top_k entries does not depend on how ties are broken.  The result is the same bit for bit from call to call.  workspace:
+ * an exact one (prompts of up to 3072 keys twice with that alone).  The mass of a row's top_k entries does not depend on how ties are broken.  The result is the same bit for bit from call to call.  workspace:
  * ZERO-FILLED before its first use, left consistent by every call; concurrent calls need
  * separate workspaces.  Sequences of a batch are processed one after the other.
  */
