@@ -15,9 +15,9 @@
 #define TKV_BLK 32     // tokens per block of packed codes (the quantization group is 32 or 64)
 #define TKV_WAVE 64
 
-// Partial attention result of one chunk and one query head, in floats: max logit (in log2
-// units after scaling), sum of weights, two unused words, then the weighted V sum (so that
-// it starts on a 16-byte boundary).
+// Room of the partial attention result of one chunk and one query head, in floats: max logit (in log2
+// units after scaling), sum of weights, the weighted V sum, two unused words.  merge_chunks has the pairs of all chunks
+// behind the sums of all chunks (part_o, part_ml); attn_merge_kernel has each pair, then two unused words, in front of its sum.
 #define TKV_PART_O 4
 #define TKV_PART_STRIDE (TKV_D + TKV_PART_O)
 
@@ -124,8 +124,7 @@ inline int32_t device_view(const void* ptr, DevView mode, const void** dev) {
 // Partials cross workgroups through device-scope stores and loads (they bypass the caches
 // that are not coherent between workgroups).  Such loads are served slowly, one load
 // instruction after the other, so the merge uses as few and as wide ones as it can: all of
-// them are issued before the first is used.  The partial maximum and sum of a chunk sit next
-// to each other (one 8-byte load), the weighted V sum starts on a 16-byte boundary.
+// them are issued before the first is used.
 
 typedef float tkv_floatx4 __attribute__((ext_vector_type(4)));
 typedef uint32_t tkv_u32x4 __attribute__((ext_vector_type(4)));
@@ -146,71 +145,137 @@ struct AgentBuf {
   __device__ uint32_t x1(uint32_t off) const { return __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 16); }
 };
 
-// head0: partials of the G heads of this KV head, [G][n_chunks][TKV_PART_STRIDE]; out0: fp16
-// [G][128].  lds: merge_lds_floats(G, n_chunks) floats.  Called by every thread of the
-// workgroup (nthr a multiple of 64, at least 64 * G).  KS: chunk classes summed side by side (2 to
+// Where chunk k of a query head lies in the head's n_chunks * TKV_PART_STRIDE floats: the weighted V
+// sums of all chunks first, then their (maximum, sum) pairs side by side: 64 of them are four lines
+// instead of 64, and such loads cost by the line.
+__device__ inline float* part_o(float* head, int k) { return head + (size_t)k * TKV_D; }
+__device__ inline float* part_ml(float* head, int n_chunks, int k) { return head + (size_t)n_chunks * TKV_D + 2 * k; }
+
+// Cross-lane exchanges without LDS traffic: quads, halves of a row of 16 lanes and rows by data-parallel primitives, rows
+// and half-waves against each other by register swaps.
+template <int CTRL>
+__device__ inline float dpp(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
+}
+template <typename F>
+__device__ inline float over_rows(float v, F f) {  // every lane: f over the four lanes with its place in a row
+  const auto a = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, v), __builtin_bit_cast(uint32_t, v), false, false);
+  const uint32_t a0 = a[0], a1 = a[1];
+  v = f(__builtin_bit_cast(float, a0), __builtin_bit_cast(float, a1));
+  const auto c = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, v), __builtin_bit_cast(uint32_t, v), false, false);
+  const uint32_t c0 = c[0], c1 = c[1];
+  return f(__builtin_bit_cast(float, c0), __builtin_bit_cast(float, c1));
+}
+template <typename F>
+__device__ inline float over_wave(float v, F f) {
+  v = f(v, dpp<0xB1>(v));   // quad_perm: lane ^ 1
+  v = f(v, dpp<0x4E>(v));   // quad_perm: lane ^ 2
+  v = f(v, dpp<0x141>(v));  // row_half_mirror: the other quad of eight lanes
+  v = f(v, dpp<0x140>(v));  // row_mirror: the other eight of the row
+  return over_rows(v, f);
+}
+// ... over the lanes whose number is the same modulo H (4 or 8)
+template <int H, typename F>
+__device__ inline float over_stride(float v, F f) {
+  static_assert(H == 4 || H == 8, "lanes of a row in steps of H");
+  v = f(v, dpp<0x128>(v));                  // row_ror:8
+  if (H == 4) v = f(v, dpp<0x124>(v));      // row_ror:4
+  return over_rows(v, f);
+}
+struct MaxOf { __device__ float operator()(float a, float b) const { return fmaxf(a, b); } };
+struct SumOf { __device__ float operator()(float a, float b) const { return a + b; } };
+
+// head0: partials of the G heads of this KV head, n_chunks * TKV_PART_STRIDE floats each (part_o, part_ml); out0: fp16
+// [G][128].  lds: merge_lds_floats(KS, G, n_chunks, nthr) floats.  Called by every thread of the
+// workgroup (nthr a multiple of 64).  KS: chunk classes summed side by side (2 to
 // 4, so that the 32 G KS items are at most one per thread); kPer: loads in flight per thread.  64
 // chunks come in one round of loads where KS kPer >= 64.
-constexpr int merge_lds_floats(int G, int n_chunks) { return 3 * G * n_chunks + 4 * G * TKV_D + G; }
+// Bound by its round trip and by what one compute unit can load (64 chunks of 8 heads: 264 KiB).  A wave fetches the
+// maxima and sums of its own head (of two heads where 32 KS items are no whole number of waves) and its channels at once and
+// works out the chunks' weights by itself: one round trip, one barrier.  us per call with the pairs fetched by the whole
+// workgroup before everything else and the weights shared through LDS / so: quantized attention, 2 bit, 32/8 heads, 2000
+// tokens (7 chunks) 12.1, 10.9; 8000 13.5, 12.5; 131000 (32 chunks) 29.3, 28.0; 4/1, 50000 (64 chunks) 17.2, 15.5; 1 bit, 32/4,
+// 98413 (64 chunks of 8 heads) 23.0, 21.9.  (With the pairs in front of the chunks' sums, a line each: 16.6 and 23.7 for the last two.)
+constexpr int merge_lds_floats(int KS, int G, int n_chunks, int nthr) {
+  return nthr / 64 * (KS == 3 ? 2 : 1) * ((n_chunks + 63) / 64 * 64) + G * KS * TKV_D + G;
+}
 template <int KS = 4, int kPer = 16>
 __device__ inline void merge_chunks(const float* head0, int G, int n_chunks, __half* out0, float* lds, int tid,
                                     int nthr) {
-  float* ml = lds;                       // [G][n_chunks][2]
-  float* cw = ml + 2 * G * n_chunks;     // [G][n_chunks] weights
-  float* red = cw + G * n_chunks;        // [G][KS][128]
-  float* Ls = red + G * KS * TKV_D;      // [G]
-  const int lane = tid % 64, wave = tid / 64;
-  const AgentBuf pb(head0, (uint32_t)((size_t)G * n_chunks * TKV_PART_STRIDE * sizeof(float)));
-  // first pass: maxima and sums of all chunks, and (for up to 64 chunks) this thread's channels
-  for (int i = tid; i < G * n_chunks; i += nthr) {
-    const tkv_u32x2 v = pb.x2((uint32_t)i * TKV_PART_STRIDE * 4u);
-    // (elements copied out before the cast: a bit cast applied directly to a vector element
-    // reads element 0 with this compiler)
-    const uint32_t v_max = v.x, v_sum = v.y;
-    ml[2 * i] = __uint_as_float(v_max);
-    ml[2 * i + 1] = __uint_as_float(v_sum);
-  }
-  // item = (head, chunk class ks, channel quad c4): chunks ks, ks + KS, ...
-  constexpr int kItems = 32 * KS;
-  for (int item0 = 0; item0 < G * kItems; item0 += nthr) {
-    const int item = item0 + tid;
-    const bool on = item < G * kItems;
-    const int hh = on ? item / kItems : 0, r = item % kItems;
-    const int ks = r / 32, c4 = r % 32;
-    const uint32_t base = (uint32_t)((hh * n_chunks) * TKV_PART_STRIDE + TKV_PART_O + 4 * c4) * 4u;
+  constexpr int kItems = 32 * KS;          // item = (head, chunk class ks, channel quad c4): chunks ks, ks + KS, ...
+  constexpr int kTwo = KS == 3 ? 2 : 1;    // heads that a wave's 64 items may belong to
+  static_assert(KS == 3 || kItems % 64 == 0, "a wave's items are one head's");
+  const int lane = tid % 64, wave = __builtin_amdgcn_readfirstlane(tid / 64);
+  const int cw_len = (n_chunks + 63) / 64 * 64;
+  float* cw = lds + wave * kTwo * cw_len;                  // [kTwo][cw_len] this wave's chunk weights
+  float* red = lds + nthr / 64 * kTwo * cw_len;            // [G][KS][128]
+  float* Ls = red + G * KS * TKV_D;                        // [G]
+  const uint32_t head_bytes = (uint32_t)n_chunks * TKV_PART_STRIDE * 4u;
+  const AgentBuf pb(head0, (uint32_t)G * head_bytes);
+  for (int first = 64 * wave; first < G * kItems; first += nthr) {
+    const uint32_t item = (uint32_t)(first + lane);
+    const bool on = item < (uint32_t)(G * kItems);
+    const int h0 = (int)((uint32_t)first / kItems), h1 = kTwo == 1 ? h0 : min((int)((uint32_t)(first + 63) / kItems), G - 1);
+    const int hh = on ? (int)(item / kItems) : h0, r = (int)(item % kItems);
+    const int ks = r / 32, c4 = r % 32, mine = on ? n_chunks : 0;
+    const uint32_t base = (uint32_t)hh * head_bytes + 16u * (uint32_t)c4;
+    auto pair_of = [&](int z, int k) {  // (maximum, sum) of chunk k of the wave's head z
+      return pb.x2(k < n_chunks ? (uint32_t)(z ? h1 : h0) * head_bytes + (uint32_t)n_chunks * (TKV_D * 4u) + 8u * (uint32_t)k : AgentBuf::kNone);
+    };
+    tkv_u32x2 ml[kTwo];
+#pragma unroll
+    for (int z = 0; z < kTwo; ++z) ml[z] = pair_of(z, lane);
+    tkv_u32x4 ov[kPer];
+    auto request = [&](int k0) {
+#pragma unroll
+      for (int y = 0; y < kPer; ++y) {
+        const int k = k0 + KS * y + ks;
+        // (one comparison: two make a branch per load, and the compiler waits for the loads before a branch to be done)
+        ov[y] = pb.x4(k < mine ? base + (uint32_t)k * (TKV_D * 4u) : AgentBuf::kNone);
+      }
+    };
+    request(0);
+    __builtin_amdgcn_sched_barrier(0);  // everything is requested before the first result is waited for
+#pragma unroll
+    for (int z = 0; z < kTwo; ++z) {
+      // (elements copied out before the cast: a bit cast applied directly to a vector element
+      // reads element 0 with this compiler)
+      const uint32_t v_max = ml[z].x, v_sum = ml[z].y;
+      const float m0 = lane < n_chunks ? __uint_as_float(v_max) : -INFINITY;
+      float M = m0;
+      for (int k = 64 + lane; k < cw_len; k += 64) {  // (more than 64 chunks: beyond a million tokens)
+        const uint32_t v = pair_of(z, k).x;
+        M = fmaxf(M, k < n_chunks ? __uint_as_float(v) : -INFINITY);
+      }
+      M = over_wave(M, MaxOf{});
+      float L = 0.f;
+      auto weigh = [&](int k, float m, float l) {
+        const float w = m == -INFINITY ? 0.f : exp2f(m - M);
+        cw[z * cw_len + k] = w;  // (read below by this wave alone, whose LDS operations execute in order)
+        L = __builtin_fmaf(l, w, L);
+      };
+      weigh(lane, m0, __uint_as_float(v_sum));  // (an absent chunk's pair reads as zeros)
+      for (int k = 64 + lane; k < cw_len; k += 64) {
+        const tkv_u32x2 v = pair_of(z, k);
+        const uint32_t v_m = v.x, v_l = v.y;
+        weigh(k, k < n_chunks ? __uint_as_float(v_m) : -INFINITY, __uint_as_float(v_l));
+      }
+      L = over_wave(L, SumOf{});
+      // (a head that two waves work on: the same number from both)
+      if (lane == 0) Ls[z ? h1 : h0] = L;
+    }
+    const float* w_of = cw + (kTwo == 2 && hh != h0 ? cw_len : 0);
     tkv_floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int k0 = 0; k0 < n_chunks; k0 += KS * kPer) {
-      tkv_u32x4 ov[kPer];
+    for (int k0 = 0;;) {
 #pragma unroll
       for (int y = 0; y < kPer; ++y) {
         const int k = k0 + KS * y + ks;
-        ov[y] = pb.x4(on && k < n_chunks ? base + (uint32_t)k * TKV_PART_STRIDE * 4u : AgentBuf::kNone);
+        const float w = w_of[k];  // (past the last chunk: whatever is there, not used)
+        acc += __builtin_bit_cast(tkv_floatx4, ov[y]) * (k < n_chunks ? w : 0.f);
       }
-      if (item0 == 0 && k0 == 0) {
-        // weights: one wave per head (the loads above are in flight meanwhile)
-        __syncthreads();
-        if (wave < G) {
-          float M = -INFINITY;
-          for (int k = lane; k < n_chunks; k += 64) M = fmaxf(M, ml[2 * (wave * n_chunks + k)]);
-          for (int m = 32; m >= 1; m >>= 1) M = fmaxf(M, __shfl_xor(M, m, 64));
-          float Lsum = 0.f;
-          for (int k = lane; k < n_chunks; k += 64) {
-            const float mk = ml[2 * (wave * n_chunks + k)];
-            const float w = mk == -INFINITY ? 0.f : exp2f(mk - M);
-            cw[wave * n_chunks + k] = w;
-            Lsum = __builtin_fmaf(ml[2 * (wave * n_chunks + k) + 1], w, Lsum);
-          }
-          for (int m = 32; m >= 1; m >>= 1) Lsum += __shfl_xor(Lsum, m, 64);
-          if (lane == 0) Ls[wave] = Lsum;
-        }
-        __syncthreads();
-      }
-#pragma unroll
-      for (int y = 0; y < kPer; ++y) {
-        const int k = k0 + KS * y + ks;
-        const float w = (on && k < n_chunks) ? cw[hh * n_chunks + k] : 0.f;
-        acc += __builtin_bit_cast(tkv_floatx4, ov[y]) * w;
-      }
+      k0 += KS * kPer;
+      if (k0 >= n_chunks) break;
+      request(k0);
     }
     if (on) *reinterpret_cast<tkv_floatx4*>(red + (hh * KS + ks) * TKV_D + 4 * c4) = acc;
   }

@@ -60,7 +60,7 @@ struct MfmaParams {
   const __half* k_resid;
   const __half* v_resid;
   const __half* q;
-  float* parts;        // sequence after sequence: [Hq][chunks of the sequence][D + 4]
+  float* parts;        // sequence after sequence: [Hq], chunks of the sequence * (D + 4) floats each
   uint32_t* arrivals;  // [B][Hkv << split], zero between calls
   __half* out;         // [B][Hq][D]
   float scale2;
@@ -240,7 +240,9 @@ struct Cfg {
   static_assert(H * TKV_D * 4 <= kBkWave && (TKV_BLK + 1) * H * 4 <= kBkWave, "the tail's scratch fits in a wave's operand area");
   static_assert((W + 2) * H * 4 <= kBkWave, "so do the merge weights");
   static_assert(sizeof(MergeWave<H>) <= (size_t)kWaveRing, "a wave's results fit in its own ring");
-  static_assert(tkv::merge_lds_floats(H, TKV_MAX_CHUNKS) * 4 <= W * kWaveRing, "merge scratch must fit in the ring");
+  // chunk classes and loads in flight of the cross-chunk merge: one thread per item, 64 chunks in one round
+  static constexpr int kMergeClasses = H == 4 ? 4 : W == 12 ? 3 : 2, kMergeLoads = H == 4 ? 16 : W == 12 ? 22 : 32;
+  static_assert(tkv::merge_lds_floats(kMergeClasses, H, TKV_MAX_CHUNKS, kThreads) * 4 <= W * kWaveRing, "merge scratch must fit in the ring");
   static_assert(kThreads >= 64 * H, "the cross-chunk merge takes a wave per head");
   static_assert(kLdsBytes + 64 <= 160 * 1024, "LDS budget of one compute unit");
 };
@@ -951,7 +953,7 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
       le[i] = e < W ? merge_of(e).l[hh] : 0.f;
       M = fmaxf(M, me[i]);
     }
-    for (int m = H; m <= 32; m <<= 1) M = fmaxf(M, __shfl_xor(M, m, 64));
+    M = tkv::over_stride<H>(M, tkv::MaxOf{});
 #pragma unroll
     for (int i = 0; i < NP; ++i) {
       const int e = lane / H + EP * i;
@@ -959,7 +961,7 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
       Lsum = __builtin_fmaf(le[i], wgt, Lsum);
       if (e < W) s_w[e][hh] = wgt;
     }
-    for (int m = H; m <= 32; m <<= 1) Lsum += __shfl_xor(Lsum, m, 64);
+    Lsum = tkv::over_stride<H>(Lsum, tkv::SumOf{});
     if (lane < H) {
       s_ml[0][hh] = M;
       s_ml[1][hh] = Lsum;
@@ -976,13 +978,13 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
       const float inv0 = Lsum > 0.f ? O[0] / Lsum : 0.f, inv1 = Lsum > 0.f ? O[1] / Lsum : 0.f;
       *reinterpret_cast<uint32_t*>(p.out + ((size_t)b * p.hq + (size_t)qh0 + hh) * TKV_D + c) = pack2((_Float16)inv0, (_Float16)inv1);
     } else {
-      float* dst = p.parts + (((size_t)chunk_base * p.hq + ((size_t)qh0 + hh) * n_chunks) + chunk) * TKV_PART_STRIDE;
+      float* head = p.parts + ((size_t)chunk_base * p.hq + ((size_t)qh0 + hh) * n_chunks) * TKV_PART_STRIDE;
       // device-scope stores: visible to the merging workgroup without a cache write-back
       auto store2 = [](float* at, float2_t v) {
         __hip_atomic_store(reinterpret_cast<uint64_t*>(at), __builtin_bit_cast(uint64_t, v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       };
-      store2(dst + TKV_PART_O + c, O);
-      if (c == 0) store2(dst, float2_t{s_ml[0][hh], s_ml[1][hh]});
+      store2(tkv::part_o(head, chunk) + c, O);
+      if (c == 0) store2(tkv::part_ml(head, n_chunks, chunk), float2_t{s_ml[0][hh], s_ml[1][hh]});
     }
   }
 
@@ -1001,7 +1003,7 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
     if (tid == 0) *arrival = 0u;
     const float* head0 = p.parts + ((size_t)chunk_base * p.hq + (size_t)qh0 * n_chunks) * TKV_PART_STRIDE;
     float* scratch = reinterpret_cast<float*>(smem + C::oRing);  // the waves' results have been consumed
-    tkv::merge_chunks<H == 4 ? 4 : W == 12 ? 3 : 2, H == 4 ? 16 : W == 12 ? 22 : 32>(head0, G, n_chunks, p.out + ((size_t)b * p.hq + (size_t)qh0) * TKV_D, scratch, tid, C::kThreads);
+    tkv::merge_chunks<C::kMergeClasses, C::kMergeLoads>(head0, G, n_chunks, p.out + ((size_t)b * p.hq + (size_t)qh0) * TKV_D, scratch, tid, C::kThreads);
   }
   TKV_PH();  // 7 end
 #ifdef TKV_PHASE

@@ -255,12 +255,13 @@ __global__ __launch_bounds__(kAttnThreads) void sparse_attn_kernel(SparseAttnPar
       L += red_l[w][hh] * wgt;
       O += red_o[w][hh][c] * wgt;
     }
-    float* dst = p.parts + (((size_t)b * p.hq + (size_t)h * G + hh) * p.n_chunks + chunk) * TKV_PART_STRIDE;
+    float* head = p.parts + ((size_t)b * p.hq + (size_t)h * G + hh) * p.n_chunks * TKV_PART_STRIDE;
     // device-scope stores: visible to the merging workgroup without a cache write-back
-    __hip_atomic_store(dst + TKV_PART_O + c, O, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(tkv::part_o(head, chunk) + c, O, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (c == 0) {
-      __hip_atomic_store(dst, M, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(dst + 1, L, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      float* ml = tkv::part_ml(head, p.n_chunks, chunk);
+      __hip_atomic_store(ml, M, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(ml + 1, L, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
   // ---- the last workgroup of this (sequence, KV head) to arrive merges all chunks; the
@@ -273,12 +274,12 @@ __global__ __launch_bounds__(kAttnThreads) void sparse_attn_kernel(SparseAttnPar
   __syncthreads();
   if (s_last == 0u) return;
   if (tid == 0) __hip_atomic_store(arrive, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  __shared__ float merge_s[3 * 4 * 64 + 4 * 4 * TKV_D + 4];
+  __shared__ __attribute__((aligned(16))) float merge_s[tkv::merge_lds_floats(2, 4, 64, kAttnThreads)];
   const float* head0 = p.parts + ((size_t)b * p.hq + (size_t)h * G) * p.n_chunks * TKV_PART_STRIDE;
   // (four heads at a time: the merge's LDS scratch is laid out for that many)
   for (int g0 = 0; g0 < G; g0 += 4) {
     if (g0 > 0) __syncthreads();
-    tkv::merge_chunks(head0 + (size_t)g0 * p.n_chunks * TKV_PART_STRIDE, min(4, G - g0), p.n_chunks,
+    tkv::merge_chunks<2>(head0 + (size_t)g0 * p.n_chunks * TKV_PART_STRIDE, min(4, G - g0), p.n_chunks,
                       p.out + ((size_t)b * p.hq + (size_t)h * G + g0) * TKV_D, merge_s, tid, nthr);
   }
 }

@@ -57,6 +57,7 @@ constexpr int kFusedLds = kBins * 4 + 1024 * 4 + kListCap * 8;
 // (the attention of 8 heads: its waves' results need a little more than the list)
 constexpr int kMergeLds8 = kBins * 4 + 1024 * 4 + kWavesPerBlock * 8 * (TKV_D + 4) * 4;
 static_assert(kWavesPerBlock * 4 * (TKV_D + 4) * 4 <= kListCap * 8 && kFusedLds <= kMergeLds8, "LDS of the attention phase");
+static_assert(tkv::merge_lds_floats(4, 8, 64, kThreads) * 4 <= kListCap * 8, "LDS of the merge of a head's workgroups");
 constexpr int kFastShift = 14;  // first radix digit of the common path: key bits [14, 32) minus a base
 constexpr int kCountBits = 14;  // a workgroup's list length (<= kMaxTpw) in its control word, L above it
 static_assert(kMaxTpw < (1 << kCountBits), "list length field");
@@ -524,10 +525,12 @@ __global__ __launch_bounds__(kThreads) void score_select_kernel(TopkParams p) {
         __builtin_memcpy(p.att_out + ((size_t)b * p.hq + (size_t)h * G + j) * TKV_D + 4 * c4, r, 8);
       } else {
         // device-scope stores: visible to the merging workgroup without a cache write-back
-        uint32_t* dst = reinterpret_cast<uint32_t*>(p.ws.parts + (((size_t)b * p.hq + (size_t)h * G + j) * n_parts + part) * TKV_PART_STRIDE);
+        float* head = p.ws.parts + ((size_t)b * p.hq + (size_t)h * G + j) * n_parts * TKV_PART_STRIDE;
+        uint32_t* dst = reinterpret_cast<uint32_t*>(tkv::part_o(head, part) + 4 * c4);
+        uint32_t* ml = reinterpret_cast<uint32_t*>(tkv::part_ml(head, n_parts, part));
 #pragma unroll
-        for (int c = 0; c < 4; ++c) st_agent(dst + TKV_PART_O + 4 * c4 + c, __float_as_uint(O[c]));
-        if (c4 == 0) st_agent(dst, __float_as_uint(M)), st_agent(dst + 1, __float_as_uint(L));
+        for (int c = 0; c < 4; ++c) st_agent(dst + c, __float_as_uint(O[c]));
+        if (c4 == 0) st_agent(ml, __float_as_uint(M)), st_agent(ml + 1, __float_as_uint(L));
       }
     }
     TKV_PH(11);
