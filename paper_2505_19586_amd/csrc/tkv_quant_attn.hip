@@ -237,26 +237,29 @@ __global__ __launch_bounds__(256) void quant_attn_generic_kernel(QuantAttnParams
 // ---- quant_attn_f32_kernel -----------------------------------------------------------------
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 
 __device__ inline half2_t as_half2(uint32_t w) { return __builtin_bit_cast(half2_t, w); }
 
 // The eight codes of a field octet: field f = i / 2 + 4 (i % 2) (4 bits: nibbles of one word) or
-// i / 2 + 16 (i % 2) + base (1 bit).
+// i / 2 + 16 (i % 2) + base (1 bit).  Code i is left where an fp16 number has its lowest mantissa bits, so one instruction
+// yields two codes: half i % 2 of pair i / 2 is the subnormal code * 2^-code_exp(i), and a multiply-add that takes a scaler times
+// 2^code_exp(i), both exact, rounds what code times scaler plus zero-point rounds.
 template <int BITS>
-__device__ inline void codes_of(uint32_t w, int base, float (&code)[8]) {
+__device__ constexpr int code_exp(int i) {
+  return BITS == 4 ? 24 - 4 * (i / 2 % 2) : 24 - i / 2 % 4;
+}
+template <int BITS>
+__device__ inline void codes_of(uint32_t w, int base, half2_t (&pair)[4]) {
   if (BITS == 4) {
-    uint32_t even = w & 0x0F0F0F0Fu, odd = (w >> 4) & 0x0F0F0F0Fu;  // nibble f is byte f / 2 of one of them
-    asm("" : "+v"(even), "+v"(odd));  // (else every nibble gets an extraction of its own)
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int f = i / 2 + 4 * (i % 2);
-      code[i] = (float)(((f % 2 ? odd : even) >> (8 * (f / 2))) & 0xFFu);
-    }
+    const uint32_t hi = w >> 8;
+    pair[0] = as_half2(w & 0x000F000Fu), pair[1] = as_half2(w & 0x00F000F0u);
+    pair[2] = as_half2(hi & 0x000F000Fu), pair[3] = as_half2(hi & 0x00F000F0u);
   } else {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) code[i] = (float)((w >> (base + i / 2 + 16 * (i % 2))) & 1u);
+    for (int k = 0; k < 4; ++k) pair[k] = as_half2((w >> base) & (0x00010001u << k));
   }
 }
 
@@ -269,19 +272,22 @@ __device__ inline void codes_of(uint32_t w, int base, float (&code)[8]) {
 // every code from memory where it is used and every operand from LDS.  Here a wave takes two streams,
 // one per half, and a lane one token for all H heads (logits) or four channels of all heads (values): no
 // lane works for a head that does not exist, packed words and scalers of the next block are
-// loaded into registers while this one is worked on, codes unpack eight at a time, query elements are
-// scalar operands.  Bound by vector instructions: 2.4 + H per element and contraction.
+// loaded into registers while this one is worked on, two codes unpack with one instruction into fp16 subnormals that the
+// multiply-adds take as they are, query elements are scalar operands.  Bound by vector instructions: 1.6 + H per element and contraction.
 //
-// 4 bits, 32 / 32 heads, 20479 + 16857 tokens: 52 us per call, 542 on the generic kernel; 32 / 8 heads, 65500
-// tokens: 48 and 256; 1 bit, 48 and 252.  The matrix cores serve the same in 45, 26 and 25 us, but
+// 4 bits, 32 / 32 heads, 20479 + 16857 tokens: 44 us per call, 542 on the generic kernel; 32 / 8 heads, 65500
+// tokens: 46 and 256; 1 bit, 41 and 252.  With a byte conversion (4 bits) or an extraction and a conversion (1 bit) per code and
+// fp16 scalers 48, 48 and 46; 1 bit, 32 / 32, 20000 tokens 30.0, now 25.0.  The matrix cores serve the first three in 45, 26 and 25 us, but
 // their operands are fp16: scalers above 1024 overflow, weights below 2^-14 lose bits, and the order of
 // the blocks is decided at run time.
-// Workgroups that a compute unit holds: 2 waves each, 2 to 4 of them per SIMD with the registers of each variant (its launch
-// bounds say so).
-constexpr int f32_waves(int bits, int heads) { return bits == 4 ? (heads == 1 ? 3 : 2) : heads == 4 ? 3 : 4; }
+// Workgroups that a compute unit holds: 2 waves each, 2 to 4 of them per SIMD with the registers of each variant (its attribute
+// says so, as the least and the most: aiming at a fourth wave the compiler keeps fewer loads in flight; 4 bit, 32/32 heads, 16 x 900
+// tokens 24.7, with the attribute 23.7; 32/4, 98413 tokens 60.4, 57.4).
+constexpr int f32_waves(int bits, int heads) { return bits == 4 ? (heads == 4 ? 2 : 3) : heads == 1 ? 4 : 3; }
 inline int f32_resident(int bits, int group) { return 2 * f32_waves(bits, group > 2 ? 4 : group); }
 template <int BITS, int GRP, int H>
-__global__ __launch_bounds__(128, f32_waves(BITS, H)) void quant_attn_f32_kernel(QuantAttnParams p) {
+__global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(f32_waves(BITS, H), f32_waves(BITS, H))))
+void quant_attn_f32_kernel(QuantAttnParams p) {
 #pragma clang fp contract(off)
   constexpr int NU = TKV_D / GRP;        // channel groups of a value row
   constexpr int NWORDS = TKV_D * BITS;   // words of a packed block
@@ -291,8 +297,9 @@ __global__ __launch_bounds__(128, f32_waves(BITS, H)) void quant_attn_f32_kernel
   // the pieces kept apart, 56 without).
   constexpr bool kApart = H == 4;
   constexpr int KW = BITS == 4 ? 4 : 1;  // words per lane and 8-channel (8-token) class
-  __shared__ __attribute__((aligned(16))) uint32_t ksz[2][2][TKV_D];            // per wave, half: key (scaler, zero) pairs
-  __shared__ __attribute__((aligned(16))) uint32_t vsz[2][2][NU * TKV_BLK];     // per wave, half: value (scaler, zero) pairs
+  // per wave, half: scalers times 2^code_exp in float32, zero-points in fp16
+  __shared__ __attribute__((aligned(16))) float ksc[2][2][TKV_D], vsc[2][2][NU * TKV_BLK];
+  __shared__ __attribute__((aligned(16))) uint32_t kze[2][2][TKV_D / 2], vze[2][2][NU * TKV_BLK / 2];
   __shared__ __attribute__((aligned(16))) float pws[2][2][H][TKV_BLK];          // per wave, half: weights
   __shared__ float red_m[4][H], red_l[4][H];
   __shared__ float red_o[4][H][TKV_D];
@@ -438,8 +445,9 @@ __global__ __launch_bounds__(128, f32_waves(BITS, H)) void quant_attn_f32_kernel
         vz[i] = *reinterpret_cast<const uint32_t*>(p.v_zero + o + 2 * i);
       }
     };
-    auto pair_lo = [](uint32_t s, uint32_t z) { return (s & 0xFFFFu) | (z << 16); };
-    auto pair_hi = [](uint32_t s, uint32_t z) { return (s >> 16) | (z & 0xFFFF0000u); };
+    // scaler y of the pair w of neighbouring channels or tokens, the first of them at place i of an octet
+    auto scaled = [](uint32_t w, int y, int i) { return (float)as_half2(w)[y] * (float)(1 << code_exp<BITS>(i)); };
+    const int ki = 4 * (t % 2), vi = NU * t % 8;  // places of this lane's first key and value scaler in their octets
     const int first = blk0 + 2 * wave;  // first block of this wave's lower half
     auto mine = [&](int base) { return min(base + half, blk1 - 1); };  // (a half past the end repeats the last block and drops the result)
     if (first < blk1) {
@@ -450,31 +458,44 @@ __global__ __launch_bounds__(128, f32_waves(BITS, H)) void quant_attn_f32_kernel
       pin_query();
       const bool on = base + half < blk1;
       const int next = min(base + 4, blk1 - 1);
-      *reinterpret_cast<u32x4*>(&ksz[wave][half][4 * t]) =
-          u32x4{pair_lo(ks[0], kz[0]), pair_hi(ks[0], kz[0]), pair_lo(ks[1], kz[1]), pair_hi(ks[1], kz[1])};
+      *reinterpret_cast<f32x4*>(&ksc[wave][half][4 * t]) =
+          f32x4{scaled(ks[0], 0, ki), scaled(ks[0], 1, ki), scaled(ks[1], 0, ki + 2), scaled(ks[1], 1, ki + 2)};
+      *reinterpret_cast<u32x2*>(&kze[wave][half][2 * t]) = kz;
 #pragma unroll
-      for (int i = 0; i < NU / 2; ++i)
-        *reinterpret_cast<u32x2*>(&vsz[wave][half][NU * t + 2 * i]) = u32x2{pair_lo(vs[i], vz[i]), pair_hi(vs[i], vz[i])};
+      for (int i = 0; i < NU / 2; ++i) {
+        *reinterpret_cast<f32x2*>(&vsc[wave][half][NU * t + 2 * i]) = f32x2{scaled(vs[i], 0, vi + 2 * i), scaled(vs[i], 1, vi + 2 * i)};
+        vze[wave][half][NU / 2 * t + i] = vz[i];
+      }
       __builtin_amdgcn_wave_barrier();
       float acc[H];
 #pragma unroll
       for (int hh = 0; hh < H; ++hh) acc[hh] = 0.f;
+      // scalers and zero-points of an octet of channels, from LDS two octets ahead (kAhead octets' registers)
+      constexpr int kAhead = kApart ? 1 : 3;
+      f32x4 sc[kAhead][2];
+      u32x4 ze[kAhead];
+      auto request = [&](int c) {
+        if (c >= TKV_D) return;
+        const int o = c / 8 % kAhead;
+        sc[o][0] = *reinterpret_cast<const f32x4*>(&ksc[wave][half][c]);
+        sc[o][1] = *reinterpret_cast<const f32x4*>(&ksc[wave][half][c + 4]);
+        ze[o] = *reinterpret_cast<const u32x4*>(&kze[wave][half][c / 2]);
+      };
+      if (!kApart) request(0), request(8);
 #pragma unroll
       for (int c = 0; c < TKV_D; c += 8) {
-        const int kb = (c / 8) % 4;
+        const int kb = (c / 8) % 4, o = c / 8 % kAhead;
+        request(kApart ? c : c + 16);
+        half2_t code[4];
+        codes_of<BITS>(kw[kb][BITS == 4 ? c / 32 : 0], 4 * ((c / 32) % 2) + 8 * (c / 64), code);
         float kh[8];
-        codes_of<BITS>(kw[kb][BITS == 4 ? c / 32 : 0], 4 * ((c / 32) % 2) + 8 * (c / 64), kh);
 #pragma unroll
-        for (int i = 0; i < 8; i += 4) {
-          const u32x4 sz = *reinterpret_cast<const u32x4*>(&ksz[wave][half][c + i]);
-#pragma unroll
-          for (int y = 0; y < 4; ++y) {
-            const uint32_t szy = sz[y];
-            kh[i + y] = __builtin_fmaf(kh[i + y], (float)as_half2(szy)[0], (float)as_half2(szy)[1]);
-          }
+        for (int i = 0; i < 8; ++i) {
+          const uint32_t zi = ze[o][i / 2];
+          kh[i] = __builtin_fmaf((float)code[i / 2][i % 2], sc[o][i / 4][i % 4], (float)as_half2(zi)[i % 2]);
         }
         dot8(acc, c, kh);
-        if (c % 32 == 24 && (kApart || c == 120)) __builtin_amdgcn_sched_barrier(0);
+        if (!kApart || c % 32 == 24) __builtin_amdgcn_sched_barrier(0);
       }
       load_k(mine(next));
       float al[H];
@@ -490,27 +511,29 @@ __global__ __launch_bounds__(128, f32_waves(BITS, H)) void quant_attn_f32_kernel
       for (int tb = 0; tb < 4; ++tb) {
         float pp[H][8];
         weights8(pp, 8 * tb);
-        uint32_t sz[NU / 2][8];  // (scaler, zero) of the eight tokens in this lane's channel groups
+        float sc[NU / 2][8];  // scalers and zero-points of the eight tokens in this lane's channel groups
+        u32x4 ze[NU / 2];
 #pragma unroll
         for (int y = 0; y < NU / 2; ++y) {
           const int u = NU == 2 ? vh : 2 * vh + y;
+          ze[y] = *reinterpret_cast<const u32x4*>(&vze[wave][half][(u * TKV_BLK + 8 * tb) / 2]);
 #pragma unroll
           for (int i = 0; i < 8; i += 4) {
-            const u32x4 w = *reinterpret_cast<const u32x4*>(&vsz[wave][half][u * TKV_BLK + 8 * tb + i]);
+            const f32x4 w = *reinterpret_cast<const f32x4*>(&vsc[wave][half][u * TKV_BLK + 8 * tb + i]);
 #pragma unroll
-            for (int x = 0; x < 4; ++x) sz[y][i + x] = w[x];
+            for (int x = 0; x < 4; ++x) sc[y][i + x] = w[x];
           }
         }
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          float v[8];
-          codes_of<BITS>(vw[tb][BITS == 4 ? j : 0], 4 * j, v);
+          half2_t code[4];
+          codes_of<BITS>(vw[tb][BITS == 4 ? j : 0], 4 * j, code);
 #pragma unroll
           for (int i = 0; i < 8; ++i) {
-            const uint32_t szi = sz[NU == 2 ? 0 : j / 2][i];
-            const float vi = __builtin_fmaf(v[i], (float)as_half2(szi)[0], (float)as_half2(szi)[1]);
+            const uint32_t zi = ze[NU == 2 ? 0 : j / 2][i / 2];
+            const float v = __builtin_fmaf((float)code[i / 2][i % 2], sc[NU == 2 ? 0 : j / 2][i], (float)as_half2(zi)[i % 2]);
 #pragma unroll
-            for (int hh = 0; hh < H; ++hh) s[hh][j] = __builtin_fmaf(pp[hh][i], vi, s[hh][j]);
+            for (int hh = 0; hh < H; ++hh) s[hh][j] = __builtin_fmaf(pp[hh][i], v, s[hh][j]);
           }
         }
 #pragma unroll
