@@ -198,6 +198,34 @@ __global__ __launch_bounds__(256) void quantize_group_kernel(QuantAppendParams p
   }
 }
 
+// The append of a few groups of 64 in one launch: a group's keys and values per workgroup of 1024 threads, by the quantizer of
+// the attention's launch.  Bound by latency as well; a lane of quantize_append_kernel has eight times the elements: one group of
+// 32 heads, a decode step's, 4.9 us per call at 2 bit, 6.6 with that kernel; 5.9 and 7.6 at 4.
+template <int BITS>
+__global__ __launch_bounds__(1024) void quantize_group64_kernel(QuantAppendParams p) {
+  constexpr int GRP = 64;
+  __shared__ __attribute__((aligned(16))) unsigned char smem[group_lds(GRP)];
+  const int b = blockIdx.z, h = blockIdx.y, tid = threadIdx.x;
+  const int n0 = p.n_old.n[b], n1 = n0 + p.n_add.n[b], ring = p.residual + GRP;
+  if ((int)blockIdx.x >= p.quant_blocks) {  // two pieces of p.ring_tokens, keys and values
+    ring_rows(p, b, h, (tid / 256) % 2 != 0, GRP, 2 * ((int)blockIdx.x - p.quant_blocks) + tid / 512, tid % 256);
+    return;
+  }
+  const int j = tkv::n_quantized(n0, p.residual, GRP) / GRP + (int)blockIdx.x;
+  if (j >= tkv::n_quantized(n1, p.residual, GRP) / GRP) return;
+  const size_t bh = (size_t)b * p.hkv + h, grp = bh * (size_t)(p.capacity / GRP) + j, blk = grp * (GRP / TKV_BLK);
+  const GroupOut out = {p.k_codes + blk * (TKV_D * BITS), p.v_codes + blk * (TKV_D * BITS), p.k_scale + grp * TKV_D,
+                        p.k_zero + grp * TKV_D,           p.v_scale + blk * (TKV_D / 2),    p.v_zero + blk * (TKV_D / 2)};
+  static_assert(TKV_D / GRP * TKV_BLK == TKV_D / 2, "value scalers of a block");
+  quantize_group_block<BITS, GRP, 1024>(
+      [&](int kv, int t) {
+        const int tok = GRP * j + t;
+        return tok < n0 ? (kv ? p.v_resid : p.k_resid) + (bh * ring + (size_t)(tok % ring)) * TKV_D
+                        : (kv ? p.v_new : p.k_new) + (((size_t)b * p.n_stride + (size_t)(tok - n0)) * p.hkv + h) * TKV_D;
+      },
+      out, smem, tid);
+}
+
 
 // The append in one launch; blockIdx.y = 2 head + (0: keys, 1: values).  blockIdx.x < quant_blocks
 // quantizes: a wave takes one unit, two code blocks of 32 tokens (two groups of 32 or one of 64).  Lane cp + 8 tb holds tokens
@@ -481,19 +509,23 @@ extern "C" int32_t tkv_quantize_append_ragged(const tkv_quant_desc* d, tkv_quant
     return TKV_OK;
   };
   // Which kernel: quantize_group_kernel up to two groups of 32 per compute unit (2 bits), three (4 bits)
-  // or four (4 bits and the ring in a launch of its own), quantize_append_kernel beyond, for 1 bit (its
-  // codes are one comparison) and for groups of 64 (of which a unit has no half to leave empty).  us per
+  // or four (4 bits and the ring in a launch of its own), quantize_append_kernel beyond and for 1 bit (its
+  // codes are one comparison).  Groups of 64: quantize_group64_kernel up to one workgroup per compute unit, those that copy included.  us per
   // call, the group kernel against the other, 8 heads from an empty cache: 2 bit, 400 tokens (64 groups)
   // 4.3, 6.3; 2000 (464) 5.7, 6.5; 3000 (712) 7.1, 6.6; 8200 (2016) 15.2, 11.5; 4 bit, 400 4.6, 7.3; 2000 6.1,
-  // 7.6; 3000 7.5, 7.7; 6000 (1464) 11.8, 10.7; 1 bit, 400 6.8, 4.2; 1 bit with groups of 64, 500 tokens 9.4 and 4.5.
-  const int few_groups = g == 64 || d->bits == 1 ? 0 : d->bits == 2 ? 512 : together ? 768 : 1024;
-  const bool few = max_groups * hkv * d->batch <= few_groups;
+  // 7.6; 3000 7.5, 7.7; 6000 (1464) 11.8, 10.7; 1 bit, 400 6.8, 4.2.  Groups of 64: 2 bit, 300 tokens (16 groups) 5.0, 6.1; 2000 (232) 5.5,
+  // 6.7; 3000 (352) 7.7, 6.9; 16 x 300 (256, and 128 copying) 9.5, 8.3; 4 bit, 300 5.9, 7.0; 2000 6.5, 7.8; 3000 9.6, 8.0; 16 x 300 11.2,
+  // 10.2; 1 bit, 300 4.6, 4.0; 2000 5.0, 4.6.
+  const int few_groups = d->bits == 1 ? 0 : g == 64 ? 256 : d->bits == 2 ? 512 : together ? 768 : 1024;
+  const int few_copies = g == 64 && together ? (max_copy + 63) / 64 : 0;
+  const bool few = (max_groups + few_copies) * hkv * d->batch <= few_groups;
   const int quant_blocks = few ? max_groups : ((max_groups * g + 63) / 64 + 3) / 4;
   // Tokens per workgroup that copies: many behind a few workgroups that quantize (the copy is over long before
   // those are; 32 sequences of 300 tokens, 8 heads: 13.7 us per call, 21.7 with 64, 19.9 with 16), a few where
   // it is what the launch ends with (8 x 8000 tokens, 1 bit / 64: 45 us, 48 with 256).
   p.ring_tokens = few ? 32 : together && quant_blocks <= 16 ? 256 : 16;
-  const int ring_blocks = (max_copy + p.ring_tokens - 1) / p.ring_tokens;
+  const int per_block = few && g == 64 ? 2 * p.ring_tokens : p.ring_tokens;
+  const int ring_blocks = (max_copy + per_block - 1) / per_block;
   auto run = [&](int x_quant, int x_ring) -> int32_t {
     if (x_quant + x_ring == 0) return TKV_OK;
     p.quant_blocks = x_quant;
@@ -501,6 +533,8 @@ extern "C" int32_t tkv_quantize_append_ragged(const tkv_quant_desc* d, tkv_quant
     switch (variant + (few ? 1000 : 0)) {
       case 1232: TKV_LAUNCH((quantize_group_kernel<2>), grid, 256, 0, s, p); break;
       case 1432: TKV_LAUNCH((quantize_group_kernel<4>), grid, 256, 0, s, p); break;
+      case 1264: TKV_LAUNCH((quantize_group64_kernel<2>), grid, 1024, 0, s, p); break;
+      case 1464: TKV_LAUNCH((quantize_group64_kernel<4>), grid, 1024, 0, s, p); break;
       case 132: TKV_LAUNCH((quantize_append_kernel<1, 32>), grid, 256, 0, s, p); break;
       case 232: TKV_LAUNCH((quantize_append_kernel<2, 32>), grid, 256, 0, s, p); break;
       case 432: TKV_LAUNCH((quantize_append_kernel<4, 32>), grid, 256, 0, s, p); break;

@@ -489,8 +489,9 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
         const_cast<__half*>(p.k_scale) + kgrp * TKV_D,           const_cast<__half*>(p.k_zero) + kgrp * TKV_D,
         const_cast<__half*>(p.v_scale) + first * (TKV_D / GS),   const_cast<__half*>(p.v_zero) + first * (TKV_D / GS)};
     static_assert(tkv::quantizer::group_lds(GRP) <= C::kLdsBytes, "LDS of the group");
-    tkv::quantizer::quantize_group_block<BITS, GRP, 64 * W>(p.k_resid + bh * ring * TKV_D, p.v_resid + bh * ring * TKV_D, ring,
-                                                           jq_old * TKV_BLK, out, smem, tid);
+    tkv::quantizer::quantize_group_block<BITS, GRP, 64 * W>(
+        [&](int kv, int t) { return (kv ? p.v_resid : p.k_resid) + (bh * ring + (size_t)((jq_old * TKV_BLK + t) % ring)) * TKV_D; },
+        out, smem, tid);
   }
   const int last = max(blk1 - 1, blk0);  // groups past the chunk are clamped (and ignored)
 

@@ -85,8 +85,8 @@ __device__ inline uint32_t pack2(_Float16 lo, _Float16 hi) {
   return __builtin_bit_cast(uint32_t, v);
 }
 
-// One group of GRP tokens of one KV head, all of them in the fp16 ring, quantized by a whole workgroup of NT >= 512
-// threads: codes, scalers and zero-points as quantize_append_kernel writes them.  smem: group_lds(GRP) bytes.  Contains
+// One group of GRP tokens of one KV head quantized by a whole workgroup of NT >= 512 threads (row(kv, t): keys or values of its
+// token t): codes, scalers and zero-points as quantize_append_kernel writes them.  smem: group_lds(GRP) bytes.  Contains
 // barriers; every store has completed at the end, so that the workgroup may load the group like any other.  Bound by
 // latency (one round trip for the rows, three barriers): about 2.5 us in front of the attention of the workgroup that owns the
 // tail.  With unpadded rows and a scaler per element read on its own it was 5 to 8.
@@ -96,9 +96,8 @@ struct GroupOut {
 };
 constexpr int kGroupPitch = TKV_D * 2 + 16;  // LDS bytes of a staged row (padded against bank conflicts)
 constexpr int group_lds(int grp) { return 2 * grp * kGroupPitch + 2 * 4 * 64 * 4 + 2 * 64 * 4 + 2 * 128 * 4; }
-template <int BITS, int GRP, int NT>
-__device__ inline void quantize_group_block(const __half* k_ring, const __half* v_ring, int ring, int tok0,
-                                            const GroupOut& out, unsigned char* smem, int tid) {
+template <int BITS, int GRP, int NT, typename Row>
+__device__ inline void quantize_group_block(const Row& row, const GroupOut& out, unsigned char* smem, int tid) {
 #pragma clang fp contract(off)
   constexpr int NU = TKV_D / GRP;   // channel groups of a value row
   constexpr int NB = GRP / TKV_BLK; // code blocks
@@ -110,8 +109,7 @@ __device__ inline void quantize_group_block(const __half* k_ring, const __half* 
   uint32_t* vsz = ksz + 2 * 64;                                           // [128] (scaler, zero-point) of token t, channel group u
   for (int i = tid; i < 2 * GRP * 16; i += NT) {
     const int kv = i / (GRP * 16), t = i / 16 % GRP, piece = i % 16;
-    const __half* src = (kv ? v_ring : k_ring) + (size_t)((tok0 + t) % ring) * TKV_D;
-    reinterpret_cast<u32x4*>(rows + (kv * GRP + t) * kRow)[piece] = reinterpret_cast<const u32x4*>(src)[piece];
+    reinterpret_cast<u32x4*>(rows + (kv * GRP + t) * kRow)[piece] = reinterpret_cast<const u32x4*>(row(kv, t))[piece];
   }
   __syncthreads();
   if (tid < 256) {  // keys: a wave takes a quarter of the tokens, a lane two channels
