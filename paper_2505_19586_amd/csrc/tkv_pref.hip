@@ -148,6 +148,7 @@ __device__ inline bool row_failed(const PrefParams& p, size_t gr) {
 // same piece) then touch 16 different slots and are free of bank conflicts.
 template <int PASS, class S>
 __global__ __launch_bounds__(kThreads) void pref_pass_kernel(PrefParams p) {
+  tkv::fetch_arguments<sizeof(PrefParams)>();
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   constexpr int QT = S::QT, T = S::T, SUB = S::SUB, kRing = PASS == 2 ? kRing2 : kRing1;
   uint32_t* lcnt = reinterpret_cast<uint32_t*>(smem + kRing2 * kChunkBytes);  // pass 2: candidates per row [kMaxRows]
@@ -441,6 +442,7 @@ struct Bracket {
 // row then has too few).
 template <int kRegs>
 __global__ __launch_bounds__(256) void pref_sample_bound_kernel(PrefParams p) {
+  tkv::fetch_arguments<sizeof(PrefParams)>();
   const int lane = threadIdx.x % 64;
   const size_t gr = (size_t)blockIdx.x * 4 + threadIdx.x / 64;
   if (gr >= (size_t)p.hq * p.n_q) return;
@@ -583,6 +585,7 @@ __device__ inline uint32_t kth_largest_key(const RowKeys& keys, uint32_t rank, u
 // has fewer blocks than that), m = the row maximum.
 template <int ROWS>
 __global__ __launch_bounds__(256) void pref_bound_kernel(PrefParams p) {
+  tkv::fetch_arguments<sizeof(PrefParams)>();
   __shared__ uint32_t hist[256];
   __shared__ uint32_t s_pick[4];
   __shared__ float s_max[4];
@@ -699,6 +702,7 @@ __device__ inline void final_big_row(const PrefParams& p, size_t gr, float* list
 // top_k-th found by narrowing a bracket with counts from ballots.
 template <int kRegs>
 __global__ __launch_bounds__(256) void pref_final_kernel(PrefParams p) {
+  tkv::fetch_arguments<sizeof(PrefParams)>();
   __shared__ float list[kRegs * 256];
   __shared__ uint32_t s_w[2][4], s_few[64], s_n, s_T;
   __shared__ float s_den[4];

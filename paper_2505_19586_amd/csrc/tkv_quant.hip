@@ -63,6 +63,7 @@ __device__ inline void ring_rows(const QuantAppendParams& p, int b, int h, bool 
 // head, so that a decode step's token of 8 heads is one workgroup (64 sequences, 32 heads: 2.2 us per
 // call; 3.7 with a workgroup per head).
 __global__ __launch_bounds__(256) void ring_kernel(QuantAppendParams p, int group) {
+  tkv::fetch_arguments<sizeof(QuantAppendParams)>();
   const int b = blockIdx.z, i = blockIdx.x * 256 + threadIdx.x;
   const bool is_v = blockIdx.y != 0;
   const int n0 = p.n_old.n[b], n1 = n0 + p.n_add.n[b], ring = p.residual + group;
@@ -91,6 +92,7 @@ __device__ inline float quant_code(float x, float z, float s, float qmax) {
 // to the ring, keys and values of one head, under the same condition as there.
 template <int BITS>
 __global__ __launch_bounds__(256) void quantize_group_kernel(QuantAppendParams p) {
+  tkv::fetch_arguments<sizeof(QuantAppendParams)>();
   constexpr int GRP = TKV_BLK;        // a token group is one code block
   constexpr int NU = TKV_D / GRP;     // channel groups of a value row
   __shared__ __half kt[GRP][TKV_D];
@@ -203,6 +205,7 @@ __global__ __launch_bounds__(256) void quantize_group_kernel(QuantAppendParams p
 // 32 heads, a decode step's, 4.9 us per call at 2 bit, 6.6 with that kernel; 5.9 and 7.6 at 4.
 template <int BITS>
 __global__ __launch_bounds__(1024) void quantize_group64_kernel(QuantAppendParams p) {
+  tkv::fetch_arguments<sizeof(QuantAppendParams)>();
   constexpr int GRP = 64;
   __shared__ __attribute__((aligned(16))) unsigned char smem[group_lds(GRP)];
   const int b = blockIdx.z, h = blockIdx.y, tid = threadIdx.x;
@@ -242,6 +245,7 @@ __global__ __launch_bounds__(1024) void quantize_group64_kernel(QuantAppendParam
 // token to quantize (the host checks).
 template <int BITS, int GRP>
 __global__ __launch_bounds__(256, 4) void quantize_append_kernel(QuantAppendParams p) {
+  tkv::fetch_arguments<sizeof(QuantAppendParams)>();
   constexpr int NU = TKV_D / GRP;     // channel groups of a value row
   constexpr int GPU = 64 / GRP;       // token groups per unit
   constexpr int kBlkBytes = 512 * BITS;

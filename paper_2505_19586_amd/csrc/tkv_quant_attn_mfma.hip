@@ -437,6 +437,7 @@ __device__ inline void tail_pieces(const TailRows& rows, float scale2, const uin
 
 template <int BITS, int GS, int W, int H>
 __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
+  tkv::fetch_arguments<sizeof(MfmaParams)>();
   using C = Cfg<BITS, GS, W, H>;
   constexpr int KSH = GS - 1;          // key group of a block = block >> KSH
   constexpr int NU = 4 / GS;           // channel groups of a value row

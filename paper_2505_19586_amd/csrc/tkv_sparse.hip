@@ -34,6 +34,7 @@ struct AppendParams {
 constexpr int kAppendGrid = 1024;
 constexpr int kAppendByHead = 8;  // appends up to this long: a workgroup per token and head
 __global__ __launch_bounds__(256) void sparse_append_kernel(AppendParams p) {
+  tkv::fetch_arguments<sizeof(AppendParams)>();
   const int b = blockIdx.y, tid = threadIdx.x;
   const bool by_head = gridDim.z > 1;
   const int h0 = by_head ? blockIdx.z : 0, n_heads = by_head ? 1 : p.hkv;
@@ -93,6 +94,7 @@ struct GatherParams {
 // run beside it.
 constexpr int kGatherRows = 4;  // rows in flight per wave
 __global__ __launch_bounds__(256) void gather_rows_kernel(GatherParams p) {
+  tkv::fetch_arguments<sizeof(GatherParams)>();
   const int b = blockIdx.z, h = blockIdx.y;
   const size_t bh = (size_t)b * p.hkv + h;
   // (count and indices are the caller's data: kept inside the buffers whatever they hold)
@@ -144,6 +146,7 @@ __device__ inline float half_wave_max(float v) {
 // load after the other: 64/8 heads, 128 + 68 tokens, 62.2 us per call, 16.8 here; 32/8 heads 33.1, 10.5.)
 template <int GH>
 __global__ __launch_bounds__(kAttnThreads) void sparse_attn_kernel(SparseAttnParams p) {
+  tkv::fetch_arguments<sizeof(SparseAttnParams)>();
   constexpr int HPH = GH / 2;  // heads per half-wave
   __shared__ float qs[GH][TKV_D];
   __shared__ float pw[4][GH][32];

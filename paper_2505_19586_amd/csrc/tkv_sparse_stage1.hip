@@ -22,6 +22,7 @@ struct Stage1AppendParams {
 // instruction), and the channel maxima of the tile go to k_absmax with an integer atomic
 // maximum (bit patterns of non-negative floats order like integers).
 __global__ __launch_bounds__(256) void stage1_append_kernel(Stage1AppendParams p) {
+  tkv::fetch_arguments<sizeof(Stage1AppendParams)>();
   __shared__ __half tile[kTile][TKV_D + 2];
   const int b = blockIdx.z, h = blockIdx.y, tid = threadIdx.x;
   const int i0 = blockIdx.x * kTile;
@@ -59,6 +60,7 @@ struct SelectParams {
 // One workgroup per (sequence, KV head).
 constexpr int kSelectThreads = 256;
 __global__ __launch_bounds__(kSelectThreads) void select_channels_kernel(SelectParams p) {
+  tkv::fetch_arguments<sizeof(SelectParams)>();
   __shared__ float s_s[TKV_D];
   __shared__ uint32_t s_sel[TKV_D];
   const int b = blockIdx.y, h = blockIdx.x;
@@ -80,6 +82,7 @@ struct PrefetchParams {
 // instruction (64 lanes x 8 bytes), four pieces in flight per wave.
 constexpr int kPieces = 4;
 __global__ __launch_bounds__(256) void prefetch_rows_kernel(PrefetchParams p) {
+  tkv::fetch_arguments<sizeof(PrefetchParams)>();
   const int b = blockIdx.z, hr = blockIdx.y;  // hr = KV head * d_s + row
   const int h = hr / p.ds, i = hr % p.ds;
   const size_t bh = (size_t)b * p.hkv + h;

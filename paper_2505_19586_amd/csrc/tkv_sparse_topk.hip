@@ -275,6 +275,7 @@ __device__ inline void append_tokens(const TopkParams& p, int b, int h, int tid)
 // ONE: every sequence is one share (n <= tpw); a second workgroup per head, if there is one, only appends.
 template <int DS, bool CM, bool ATT, int GH, bool ONE>
 __global__ __launch_bounds__(kThreads) void score_select_kernel(TopkParams p) {
+  tkv::fetch_arguments<sizeof(TopkParams)>();
   static_assert(GH == 4 || GH == 8, "heads per lane");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   uint32_t* hist = reinterpret_cast<uint32_t*>(smem);                            // kBins words
