@@ -167,6 +167,17 @@ __device__ inline void fetch_arguments() {
                "s"(w[10]), "s"(w[11]), "s"(w[12]), "s"(w[13]), "s"(w[14]), "s"(w[15]));
 }
 
+// One of two of a kernel's pointer arguments.  (Chosen per lane as they stand, the compiler chooses between their addresses among the
+// arguments and loads the pointer from there: a round trip more.  In the append of a completed group and the float32 kernel's tails: 4 bit,
+// 32/32 heads, 20480 + 16857 tokens 54.5 us per decode step, 53.1 now.)
+template <typename T>
+__device__ inline T* pick(bool second, T* a, T* b) {
+  typedef __attribute__((address_space(1))) T Global;  // (named, so that loads and stores through it stay global ones)
+  Global *ga = (Global*)a, *gb = (Global*)b;
+  asm("" : "+s"(ga), "+s"(gb));
+  return (T*)(second ? gb : ga);
+}
+
 // Cross-lane exchanges without LDS traffic: quads, halves of a row of 16 lanes and rows by data-parallel primitives, rows
 // and half-waves against each other by register swaps.
 template <int CTRL>

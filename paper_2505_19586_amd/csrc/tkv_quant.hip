@@ -37,8 +37,8 @@ __device__ inline void ring_rows(const QuantAppendParams& p, int b, int h, bool 
   constexpr int kPass = 64, kLoads = kPass / 16;
   const int n0 = p.n_old.n[b], n1 = n0 + p.n_add.n[b], ring = p.residual + group, part = tid % 16;
   const int first = max(n0, tkv::n_quantized(n1, p.residual, group)) + p.ring_tokens * piece, end = min(n1, first + p.ring_tokens);
-  const __half* news = (is_v ? p.v_new : p.k_new) + ((size_t)b * p.n_stride * p.hkv + h) * TKV_D;
-  __half* olds = (is_v ? p.v_resid : p.k_resid) + ((size_t)b * p.hkv + h) * ring * TKV_D;
+  const __half* news = tkv::pick(is_v, p.k_new, p.v_new) + ((size_t)b * p.n_stride * p.hkv + h) * TKV_D;
+  __half* olds = tkv::pick(is_v, p.k_resid, p.v_resid) + ((size_t)b * p.hkv + h) * ring * TKV_D;
   if (p.ring_tokens == 16) {  // one each (the pass below would load this token four times)
     const int tok = first + tid / 16;
     if (tok < end)
@@ -70,8 +70,8 @@ __global__ __launch_bounds__(256) void ring_kernel(QuantAppendParams p, int grou
   const int first = max(n0, tkv::n_quantized(n1, p.residual, group));
   const int row = i / 16, part = i % 16, tok = first + row / p.hkv, h = row % p.hkv;
   if (tok >= n1) return;
-  const __half* src = (is_v ? p.v_new : p.k_new) + (((size_t)b * p.n_stride + (size_t)(tok - n0)) * p.hkv + h) * TKV_D;
-  __half* dst = (is_v ? p.v_resid : p.k_resid) + (((size_t)b * p.hkv + h) * ring + (size_t)(tok % ring)) * TKV_D;
+  const __half* src = tkv::pick(is_v, p.k_new, p.v_new) + (((size_t)b * p.n_stride + (size_t)(tok - n0)) * p.hkv + h) * TKV_D;
+  __half* dst = tkv::pick(is_v, p.k_resid, p.v_resid) + (((size_t)b * p.hkv + h) * ring + (size_t)(tok % ring)) * TKV_D;
   reinterpret_cast<uint4*>(dst)[part] = reinterpret_cast<const uint4*>(src)[part];
 }
 
@@ -211,7 +211,8 @@ __global__ __launch_bounds__(1024) void quantize_group64_kernel(QuantAppendParam
   const int b = blockIdx.z, h = blockIdx.y, tid = threadIdx.x;
   const int n0 = p.n_old.n[b], n1 = n0 + p.n_add.n[b], ring = p.residual + GRP;
   if ((int)blockIdx.x >= p.quant_blocks) {  // two pieces of p.ring_tokens, keys and values
-    ring_rows(p, b, h, (tid / 256) % 2 != 0, GRP, 2 * ((int)blockIdx.x - p.quant_blocks) + tid / 512, tid % 256);
+    const int part = __builtin_amdgcn_readfirstlane(tid / 256);
+    ring_rows(p, b, h, part % 2 != 0, GRP, 2 * ((int)blockIdx.x - p.quant_blocks) + part / 2, tid % 256);
     return;
   }
   const int j = tkv::n_quantized(n0, p.residual, GRP) / GRP + (int)blockIdx.x;
@@ -223,8 +224,9 @@ __global__ __launch_bounds__(1024) void quantize_group64_kernel(QuantAppendParam
   quantize_group_block<BITS, GRP, 1024>(
       [&](int kv, int t) {
         const int tok = GRP * j + t;
-        return tok < n0 ? (kv ? p.v_resid : p.k_resid) + (bh * ring + (size_t)(tok % ring)) * TKV_D
-                        : (kv ? p.v_new : p.k_new) + (((size_t)b * p.n_stride + (size_t)(tok - n0)) * p.hkv + h) * TKV_D;
+        const __half* olds = tkv::pick(kv != 0, p.k_resid, p.v_resid) + (bh * ring + (size_t)(tok % ring)) * TKV_D;
+        const __half* news = tkv::pick(kv != 0, p.k_new, p.v_new) + (((size_t)b * p.n_stride + (size_t)(tok - n0)) * p.hkv + h) * TKV_D;
+        return tok < n0 ? olds : news;
       },
       out, smem, tid);
 }

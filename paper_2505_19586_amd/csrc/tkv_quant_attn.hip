@@ -567,9 +567,9 @@ void quant_attn_f32_kernel(QuantAttnParams p) {
         // 48.1; 32 x 900 28.2, 26.2; 1 bit, 64/8, 4 x 3000 25.7, 23.3.
         const int n_old = n - p.n_add.n[b];
         for (int i = max(tok0, n_old); i < min(tok0 + TKV_BLK, n); ++i) {
-          const __half* src = (t < 16 ? p.k_new : p.v_new) + (((size_t)b * p.n_stride + (i - n_old)) * p.hkv + h) * TKV_D;
+          const __half* src = tkv::pick(t >= 16, p.k_new, p.v_new) + (((size_t)b * p.n_stride + (i - n_old)) * p.hkv + h) * TKV_D;
           const u32x4 w = reinterpret_cast<const u32x4*>(src)[t % 16];
-          reinterpret_cast<u32x4*>((t < 16 ? p.k_resid : p.v_resid) + (bh * ring + (size_t)(i % ring)) * TKV_D)[t % 16] = w;
+          reinterpret_cast<u32x4*>(tkv::pick(t >= 16, p.k_resid, p.v_resid) + (bh * ring + (size_t)(i % ring)) * TKV_D)[t % 16] = w;
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       }

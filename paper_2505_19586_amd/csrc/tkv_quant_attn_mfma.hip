@@ -153,13 +153,13 @@ __device__ inline void extract4(uint32_t w, uintx4& a) {
   a[3] = w8 & 0x00F000F0u;
 }
 
-__device__ inline void lds_load16(const void* g, void* l) {
-  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g,
-                                   (__attribute__((address_space(3))) void*)l, 16, 0, 0);
-}
-__device__ inline void lds_load4(const void* g, void* l) {
-  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g,
-                                   (__attribute__((address_space(3))) void*)l, 4, 0, 0);
+// SIZE bytes per lane from a descriptor's array straight to LDS, in lane order from `to` on
+template <int SIZE>
+__device__ inline void buffer_to_lds(__amdgpu_buffer_rsrc_t from, void* to, uint32_t lane_offset, uint32_t offset) {
+  auto* lds = (__attribute__((address_space(3))) void*)to;
+  static_assert(SIZE == 4 || SIZE == 16, "sizes used here");
+  if constexpr (SIZE == 4) __builtin_amdgcn_raw_ptr_buffer_load_lds(from, lds, 4, (int)lane_offset, (int)offset, 0, 0);
+  else __builtin_amdgcn_raw_ptr_buffer_load_lds(from, lds, 16, (int)lane_offset, (int)offset, 0, 0);
 }
 
 // Query-side operands q s 2^(kEK - position shift) are fp16 hi + lo pairs.  kEK = 0 leaves the
@@ -230,7 +230,7 @@ struct Cfg {
   // 16-byte-per-lane loads; GS = 2 fetches V scalers and zero-points with one instruction
   static constexpr int kCodeLoads = BITS == 1 ? 2 : BITS / 2;
   static constexpr int kKLoads = kCodeLoads + 1;
-  static constexpr int kVLoads = kCodeLoads + (GS == 1 ? 2 : 1);
+  static constexpr int kVLoads = kCodeLoads + 2;
   static constexpr int kCodeWords = BITS == 1 ? 2 : 2 * BITS;  // code words per lane and part
   static constexpr int kBkWave = 2 * H * kBkStride * 4;
   static constexpr int kMaxGpc = max_gpc(H);
@@ -491,7 +491,7 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
         const_cast<__half*>(p.v_scale) + first * (TKV_D / GS),   const_cast<__half*>(p.v_zero) + first * (TKV_D / GS)};
     static_assert(tkv::quantizer::group_lds(GRP) <= C::kLdsBytes, "LDS of the group");
     tkv::quantizer::quantize_group_block<BITS, GRP, 64 * W>(
-        [&](int kv, int t) { return (kv ? p.v_resid : p.k_resid) + (bh * ring + (size_t)((jq_old * TKV_BLK + t) % ring)) * TKV_D; },
+        [&](int kv, int t) { return tkv::pick(kv != 0, p.k_resid, p.v_resid) + (bh * ring + (size_t)((jq_old * TKV_BLK + t) % ring)) * TKV_D; },
         out, smem, tid);
   }
   const int last = max(blk1 - 1, blk0);  // groups past the chunk are clamped (and ignored)
@@ -507,37 +507,41 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
   const uint32_t lane16 = 16u * (uint32_t)lane, lane4 = 4u * (uint32_t)lane;  // unsigned: scalar base + 32-bit lane offset
 
   // ---- loads: asynchronous global -> LDS copies of a group's K part / V part ------------
-  auto load_codes = [&](unsigned char* s, const unsigned char* src, uint32_t l16, uint32_t l4) {
+  // Through descriptors of the head's arrays, block offsets scalar (as global loads, which the compiler takes for ones that may
+  // return out of order, no load before them could be waited for without them).
+  auto array_of = [&](const void* base, uint32_t bytes) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000); };
+  constexpr uint32_t kCodeBytes = NWORDS * 4, kVMetaBytes = TKV_D / GS * 2;  // of a block
+  const auto k_codes = array_of(p.k_codes + grp_base * NWORDS, (uint32_t)jq * kCodeBytes);
+  const auto v_codes = array_of(p.v_codes + grp_base * NWORDS, (uint32_t)jq * kCodeBytes);
+  const auto k_scale = array_of(p.k_scale + kgrp_base * TKV_D, (uint32_t)(jq >> KSH) * (TKV_D * 2));
+  const auto v_scale = array_of(p.v_scale + grp_base * (TKV_D / GS), (uint32_t)jq * kVMetaBytes);
+  const auto v_zero = array_of(p.v_zero + grp_base * (TKV_D / GS), (uint32_t)jq * kVMetaBytes);
+  auto load_codes = [&](unsigned char* s, auto codes, uint32_t at) {
     if (BITS == 1) {
-      lds_load4(src + l4, s);
-      lds_load4(src + 256 + l4, s + 256);
+      buffer_to_lds<4>(codes, s, lane4, at);
+      buffer_to_lds<4>(codes, s + 256, lane4, at + 256);
     } else {
 #pragma unroll
-      for (int x = 0; x < BITS / 2; ++x) lds_load16(src + 1024 * x + l16, s + 1024 * x);
+      for (int x = 0; x < BITS / 2; ++x) buffer_to_lds<16>(codes, s + 1024 * x, lane16, at + 1024 * x);
     }
   };
-  // GS = 2: lanes 0..31 fetch the block's V scalers, lanes 32..63 its zero-points (128 bytes each)
-  const __half* vmeta_lane = lane < 32 ? p.v_scale + 2 * lane : p.v_zero + 2 * (lane - 32);
   auto load_kpart = [&](uint32_t so, int g) {
-    const int gi = min(g, last);
-    const size_t grp = grp_base + gi;
+    const uint32_t gi = (uint32_t)min(g, last);
     unsigned char* s = smem + so;
-    uint32_t l16 = lane16, l4 = lane4;  // opaque copies: keeps "scalar base + lane offset" addressing
-    asm volatile("" : "+v"(l16), "+v"(l4));
-    load_codes(s, reinterpret_cast<const unsigned char*>(p.k_codes + grp * NWORDS), l16, l4);
-    lds_load4(reinterpret_cast<const unsigned char*>(p.k_scale + (kgrp_base + (gi >> KSH)) * TKV_D) + l4, s + C::kCode);
+    load_codes(s, k_codes, gi * kCodeBytes);
+    buffer_to_lds<4>(k_scale, s + C::kCode, lane4, (gi >> KSH) * (TKV_D * 2));
   };
   auto load_vpart = [&](uint32_t so, int g) {
-    const size_t grp = grp_base + min(g, last);
+    const uint32_t gi = (uint32_t)min(g, last);
     unsigned char* s = smem + so;
-    uint32_t l16 = lane16, l4 = lane4;
-    asm volatile("" : "+v"(l16), "+v"(l4));
-    load_codes(s, reinterpret_cast<const unsigned char*>(p.v_codes + grp * NWORDS), l16, l4);
+    load_codes(s, v_codes, gi * kCodeBytes);
     if (GS == 1) {
-      lds_load4(reinterpret_cast<const unsigned char*>(p.v_scale + grp * TKV_D) + l4, s + C::oVs);
-      lds_load4(reinterpret_cast<const unsigned char*>(p.v_zero + grp * TKV_D) + l4, s + C::oVz);
+      buffer_to_lds<4>(v_scale, s + C::oVs, lane4, gi * kVMetaBytes);
+      buffer_to_lds<4>(v_zero, s + C::oVz, lane4, gi * kVMetaBytes);
+    } else if (lane < 32) {  // 128 bytes each: lanes 0..31 fetch the block's V scalers, lanes 32..63 its zero-points
+      buffer_to_lds<4>(v_scale, s + C::oVs, lane4, gi * kVMetaBytes);
     } else {
-      lds_load4(vmeta_lane + grp * (TKV_D / GS), s + C::oVs);
+      buffer_to_lds<4>(v_zero, s + C::oVs, lane4 - 128u, gi * kVMetaBytes);
     }
   };
 
@@ -556,20 +560,21 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
   const int ng = blk1 - blk0;
   uint32_t q2[H];   // K-prep role: this lane owns channels 2*lane, 2*lane+1
   uintx4 bq[4];     // exact fp16 query as MFMA B operand (zero-point term)
-  uintx4 az[4];     // zero-point rows of 16 groups as MFMA A operand
-  if (has_tail && p.k_new != nullptr) {
-    // Eq. 2 in this launch: the step's new rows go into the fp16 ring, into slots whose tokens were
-    // quantized long ago.  Nothing in this launch reads those slots: the tail waves take the new
-    // rows from the caller's buffers.
-    const int add = p.n_add.n[b], ring = p.residual + GRP;
-    for (int x = tid; x < add * 32; x += 64 * W) {
-      const int i = x / 32, kv = (x % 32) / 16, part = x % 16;
-      const uintx4 v = reinterpret_cast<const uintx4*>((kv ? p.v_new : p.k_new) +
-                                                       (((size_t)b * p.n_stride + i) * p.hkv + h) * TKV_D)[part];
-      __half* dst = const_cast<__half*>(kv ? p.v_resid : p.k_resid) + (bh * ring + (size_t)((n - add + i) % ring)) * TKV_D;
-      reinterpret_cast<uintx4*>(dst)[part] = v;
-    }
-  }
+  uintx4 az[4] = {};  // zero-point rows of 16 groups as MFMA A operand
+  // Eq. 2 in this launch: the step's new rows go into the fp16 ring, into slots whose tokens were
+  // quantized long ago.  Nothing in this launch reads those slots: the tail waves take the new
+  // rows from the caller's buffers.  Requested here, stored when the set-up loads behind them have arrived.
+  const int n_copy = has_tail && p.k_new != nullptr ? 32 * p.n_add.n[b] : 0;  // 16-byte pieces
+  auto new_piece = [&](int x) -> const uintx4* {
+    return reinterpret_cast<const uintx4*>(tkv::pick(x % 32 >= 16, p.k_new, p.v_new) + (((size_t)b * p.n_stride + x / 32) * p.hkv + h) * TKV_D) + x % 16;
+  };
+  auto ring_piece = [&](int x) -> uintx4* {
+    const int ring = p.residual + GRP, add = p.n_add.n[b];
+    const __half* to = tkv::pick(x % 32 >= 16, p.k_resid, p.v_resid) + (bh * ring + (size_t)((n - add + x / 32) % ring)) * TKV_D;
+    return reinterpret_cast<uintx4*>(const_cast<__half*>(to)) + x % 16;
+  };
+  uintx4 copied = {0u, 0u, 0u, 0u};
+  if (tid < n_copy) copied = *new_piece(tid);
 #pragma unroll
   for (int hh = 0; hh < H; ++hh)  // heads >= G re-read head G-1 (in bounds); their results are not used
     q2[hh] = reinterpret_cast<const uint32_t*>(qrow + (size_t)(hh < G ? hh : G - 1) * TKV_D)[lane];
@@ -582,23 +587,9 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
     for (int m = 0; m < 4; ++m) az[m] = *reinterpret_cast<const uintx4*>(p.k_zero + grp * TKV_D + 32 * m + 8 * rb);
   };
   if (16 * wave < ng) load_az(16 * wave);
-  __builtin_amdgcn_sched_barrier(0);
-  if (active) {
-    // issue order K0 V0 K1 K2 V1, then per step [K(i+3) V(i+2)]: the counter retires loads
-    // in order, so "at most N outstanding" names exactly which parts have landed
-    load_kpart(kl, g0);
-    load_vpart(vp, g0);
-    load_kpart(kq, g1);
-    load_kpart(kk, g2);
-    load_vpart(vn, g1);
-  }
-  __builtin_amdgcn_sched_barrier(0);
-  if (tid == 0) s_next = blk0 + 3 * W;
-
   // ---- zero-point term of every group of the chunk: cz[g][head] = scale2 * sum_c q[c] z_g[c],
   // 16 groups per MFMA (A rows = groups, B = the exact fp16 query)
-  for (int t0 = 16 * wave; t0 < ng; t0 += 16 * W) {
-    if (t0 != 16 * wave) load_az(t0);
+  auto zero_terms = [&](int t0) {
     floatx4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int m = 0; m < 4; ++m) acc = mfma(az[m], bq[m], acc);
@@ -609,11 +600,11 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
         if (gl < ng) cz_s[gl * H + hs] = acc[x] * p.scale2;
       }
     }
-  }
-  // query times the factor that undoes the field position of this lane's channels
-  // (1 bit: 2^(lane%4), times 2^4 in odd 32-channel blocks; 2 bit: 4^(lane%4); 4 bit: 16^(lane%2))
-  float qf[H][2];
-  {
+  };
+  float qf[H][2];  // query times the factor that undoes the field position of this lane's channels
+  auto use_set_up_loads = [&]() {
+    if (16 * wave < ng) zero_terms(16 * wave);
+    // (1 bit: 2^(lane%4), times 2^4 in odd 32-channel blocks; 2 bit: 4^(lane%4); 4 bit: 16^(lane%2))
     const int shift = BITS == 1 ? lane % 4 + 4 * ((lane / 16) % 2) : BITS == 2 ? 2 * (lane % 4) : 4 * (lane % 2);
     const float comp = (float)(1 << kEK) / (float)(1 << shift);
 #pragma unroll
@@ -622,6 +613,38 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
       qf[hh][0] = hh < G ? (float)qq[0] * comp : 0.f;
       qf[hh][1] = hh < G ? (float)qq[1] * comp : 0.f;
     }
+    // (waited for here, on every path)
+    asm volatile("" ::"v"(az[0]), "v"(az[1]), "v"(az[2]), "v"(az[3]), "v"(bq[0]), "v"(bq[1]), "v"(bq[2]), "v"(bq[3]), "v"(copied));
+  };
+  __builtin_amdgcn_sched_barrier(0);
+  // (Written out for either case: behind the end of a branch around the loads below the compiler can only wait for all of
+  // them before it uses the set-up loads in front of them.  The block loop then began when the whole ring had been filled, 28 MB for
+  // a launch of 256 workgroups.  us per pass so, with global loads to LDS, against this: 2 bit, 32/8 heads, 131072 tokens, two layers
+  // 58.9, 57.5; 4 bit, 32770 17.25, 17.15.)
+  if (active) {
+    // issue order K0 V0 K1 K2 V1, then per step [K(i+3) V(i+2)]: the counter retires loads
+    // in order, so "at most N outstanding" names exactly which parts have landed
+    load_kpart(kl, g0);
+    load_vpart(vp, g0);
+    load_kpart(kq, g1);
+    load_kpart(kk, g2);
+    load_vpart(vn, g1);
+    __builtin_amdgcn_sched_barrier(0);
+    use_set_up_loads();
+    asm volatile("; set up, ring loads in flight");  // (keeps the two copies apart)
+  } else {
+    use_set_up_loads();
+    asm volatile("; set up");
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  if (tid == 0) s_next = blk0 + 3 * W;
+  for (int t0 = 16 * (wave + W); t0 < ng; t0 += 16 * W) {
+    load_az(t0);
+    zero_terms(t0);
+  }
+  if (tid < n_copy) {
+    *ring_piece(tid) = copied;
+    for (int x = tid + 64 * W; x < n_copy; x += 64 * W) *ring_piece(x) = *new_piece(x);
   }
   TKV_PH();  // 1 this wave's set-up work done
   // cz table and group counter are in place (a bare barrier: __syncthreads() would also wait for

@@ -107,9 +107,17 @@ __device__ inline void quantize_group_block(const Row& row, const GroupOut& out,
   uint32_t* part = reinterpret_cast<uint32_t*>(smem + 2 * GRP * kRow);    // [2][4][64] minima, maxima of channel pairs
   uint32_t* ksz = part + 2 * 4 * 64;                                      // [2][64] scalers, zero-points of channel pairs
   uint32_t* vsz = ksz + 2 * 64;                                           // [128] (scaler, zero-point) of token t, channel group u
-  for (int i = tid; i < 2 * GRP * 16; i += NT) {
-    const int kv = i / (GRP * 16), t = i / 16 % GRP, piece = i % 16;
-    reinterpret_cast<u32x4*>(rows + (kv * GRP + t) * kRow)[piece] = reinterpret_cast<const u32x4*>(row(kv, t))[piece];
+  constexpr int kPieces = 2 * GRP * 16, kRounds = (kPieces + NT - 1) / NT;  // 16-byte pieces, all in one round trip
+  u32x4 piece[kRounds];
+#pragma unroll
+  for (int y = 0; y < kRounds; ++y) {
+    const int i = min(tid + NT * y, kPieces - 1);
+    piece[y] = reinterpret_cast<const u32x4*>(row(i / (GRP * 16), i / 16 % GRP))[i % 16];
+  }
+#pragma unroll
+  for (int y = 0; y < kRounds; ++y) {
+    const int i = tid + NT * y;
+    if (i < kPieces) reinterpret_cast<u32x4*>(rows + i / 16 * kRow)[i % 16] = piece[y];
   }
   __syncthreads();
   if (tid < 256) {  // keys: a wave takes a quarter of the tokens, a lane two channels

@@ -49,7 +49,7 @@ __global__ __launch_bounds__(256) void sparse_append_kernel(AppendParams p) {
   for (int x = tid; x < 2 * chunks; x += 256) {
     const int kv = x / chunks, rem = x % chunks, h = rem / 16, part = rem % 16;
     const size_t bh = bh0 + h;
-    const uint4 v = reinterpret_cast<const uint4*>((kv ? p.v_new : p.k_new) + (row0 + h) * TKV_D)[part];
+    const uint4 v = reinterpret_cast<const uint4*>(tkv::pick(kv != 0, p.k_new, p.v_new) + (row0 + h) * TKV_D)[part];
     reinterpret_cast<uint4*>(p.kv_host + ((bh * p.capacity + tok) * 2 + kv) * TKV_D)[part] = v;
     if (local)
       reinterpret_cast<uint4*>(p.kv_local + ((bh * (p.n_sink + p.n_window) + slot) * 2 + kv) * TKV_D)[part] = v;

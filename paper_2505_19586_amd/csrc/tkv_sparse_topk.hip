@@ -252,7 +252,7 @@ __device__ inline void append_tokens(const TopkParams& p, int b, int h, int tid)
   for (int x = tid; x < add * 32; x += kThreads) {
     const int i = x / 32, kv = (x % 32) / 16, part = x % 16;
     const int tok = n0 + i;
-    const uint4 v = reinterpret_cast<const uint4*>((kv ? p.app_v : p.app_k) +
+    const uint4 v = reinterpret_cast<const uint4*>(tkv::pick(kv != 0, p.app_k, p.app_v) +
                                                    (((size_t)b * p.app_stride + i) * p.hkv + h) * TKV_D)[part];
     reinterpret_cast<uint4*>(p.app_host + ((bh * p.capacity + tok) * 2 + kv) * TKV_D)[part] = v;
     const bool local = tok < p.n_sink || tok >= n1 - p.n_window;
