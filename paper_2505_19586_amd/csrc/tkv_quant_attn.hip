@@ -495,7 +495,7 @@ void quant_attn_f32_kernel(QuantAttnParams p) {
           kh[i] = __builtin_fmaf((float)code[i / 2][i % 2], sc[o][i / 4][i % 4], (float)as_half2(zi)[i % 2]);
         }
         dot8(acc, c, kh);
-        if (!kApart || c % 32 == 24) __builtin_amdgcn_sched_barrier(0);
+        if (c % 32 == 24) __builtin_amdgcn_sched_barrier(0);
       }
       load_k(mine(next));
       float al[H];
