@@ -276,7 +276,7 @@ __device__ inline void codes_of(uint32_t w, int base, half2_t (&pair)[4]) {
 // multiply-adds take as they are, query elements are scalar operands.  Bound by vector instructions: 1.6 + H per element and contraction.
 //
 // 4 bits, 32 / 32 heads, 20479 + 16857 tokens: 44 us per call, 542 on the generic kernel; 32 / 8 heads, 65500
-// tokens: 46 and 256; 1 bit, 41 and 252.  With a byte conversion (4 bits) or an extraction and a conversion (1 bit) per code and
+// tokens: 42 and 256; 1 bit, 39 and 252.  With a byte conversion (4 bits) or an extraction and a conversion (1 bit) per code and
 // fp16 scalers 48, 48 and 46; 1 bit, 32 / 32, 20000 tokens 30.0, now 25.0.  The matrix cores serve the first three in 45, 26 and 25 us, but
 // their operands are fp16: scalers above 1024 overflow, weights below 2^-14 lose bits, and the order of
 // the blocks is decided at run time.
@@ -688,51 +688,85 @@ int32_t launch_f32(const QuantAttnParams& p, bool any_group, hipStream_t s) {
   return TKV_OK;
 }
 
-// Log-sum-exp merge of the chunk partials of one query head; writes fp16.
-// One workgroup per query head, one thread per channel; the per-part maxima and sums
-// are staged in LDS so that the channel loop issues independent loads.
-__global__ __launch_bounds__(TKV_D) void attn_merge_kernel(const float* parts, __half* out, int n_parts) {
+// Log-sum-exp merge of the chunk partials of one query head; writes fp16.  One workgroup per query head; a thread takes one channel of
+// every fourth part.  Bound by latency: the maxima and sums and the first 16 of a thread's parts are requested at once (64 parts in one
+// round trip).  us per call with one thread per channel, four parts requested at a time behind two round trips for the weights, and
+// so: 1 bit, 32/8 heads, 65500 tokens 40.6, 38.7; 4 bit, 32/8, 65500 44.7, 42.3; 5000 14.4, 12.9; 1500 11.6, 11.0; 32/4, 3000 12.9, 11.7.
+constexpr int kMergeClasses = 4;
+template <int kMergeLoads>
+__global__ __launch_bounds__(kMergeClasses * TKV_D) void attn_merge_kernel(const float* parts, __half* out, int n_parts) {
+  constexpr int kOwn = (TKV_MAX_CHUNKS + TKV_D) / TKV_D;  // parts whose weights one of the first TKV_D threads works out
   __shared__ float wgt[TKV_MAX_CHUNKS + 1];
-  __shared__ float red[2];
+  __shared__ float red_m[2], red_l[2];
+  __shared__ float red_o[kMergeClasses][TKV_D];
   const size_t head = blockIdx.x;  // b * Hq + i
-  const int c = threadIdx.x;
+  const int tid = threadIdx.x, c = tid % TKV_D, j = __builtin_amdgcn_readfirstlane(tid / TKV_D);
   const float* base = parts + head * n_parts * TKV_PART_STRIDE;
-  for (int k = c; k < n_parts; k += TKV_D) wgt[k] = base[(size_t)k * TKV_PART_STRIDE];
-  __syncthreads();
-  float M = -INFINITY;
-  for (int k = 0; k < n_parts; ++k) M = fmaxf(M, wgt[k]);
-  __syncthreads();
-  float lsum = 0.f;
-  for (int k = c; k < n_parts; k += TKV_D) {
-    const float mk = wgt[k];
-    const float w = mk == -INFINITY ? 0.f : exp2f(mk - M);
-    wgt[k] = w;
-    lsum += w * base[(size_t)k * TKV_PART_STRIDE + 1];
+  const int n4 = n_parts / kMergeClasses * kMergeClasses;  // the parts past it join the first class
+  float2 ml[kOwn];
+  if (j == 0) {
+#pragma unroll
+    for (int y = 0; y < kOwn; ++y)
+      ml[y] = *reinterpret_cast<const float2*>(base + (size_t)min(c + TKV_D * y, n_parts - 1) * TKV_PART_STRIDE);
   }
-  for (int m = 32; m >= 1; m >>= 1) lsum += __shfl_xor(lsum, m, 64);
-  if (c % 64 == 0) red[c / 64] = lsum;
-  __syncthreads();
-  const float L = red[0] + red[1];
-  float O0 = 0.f, O1 = 0.f, O2 = 0.f, O3 = 0.f;
-  int k = 0;
-  for (; k + 4 <= n_parts; k += 4) {
-    const float* pk = base + (size_t)k * TKV_PART_STRIDE + TKV_PART_O + c;
-    const float v0 = pk[0], v1 = pk[TKV_PART_STRIDE], v2 = pk[2 * TKV_PART_STRIDE], v3 = pk[3 * TKV_PART_STRIDE];
-    O0 = __builtin_fmaf(v0, wgt[k], O0);
-    O1 = __builtin_fmaf(v1, wgt[k + 1], O1);
-    O2 = __builtin_fmaf(v2, wgt[k + 2], O2);
-    O3 = __builtin_fmaf(v3, wgt[k + 3], O3);
+  float v[kMergeLoads];
+  auto request = [&](int k0) {
+#pragma unroll
+    for (int y = 0; y < kMergeLoads; ++y)
+      v[y] = base[(size_t)min(k0 + kMergeClasses * y, n_parts - 1) * TKV_PART_STRIDE + TKV_PART_O + c];
+  };
+  request(j);
+  if (j == 0) {
+    float m = -INFINITY;
+#pragma unroll
+    for (int y = 0; y < kOwn; ++y) m = fmaxf(m, ml[y].x);
+    m = tkv::over_wave(m, tkv::MaxOf{});
+    if (c % 64 == 0) red_m[c / 64] = m;
   }
-  for (; k < n_parts; ++k) O0 = __builtin_fmaf(base[(size_t)k * TKV_PART_STRIDE + TKV_PART_O + c], wgt[k], O0);
-  const float O = (O0 + O1) + (O2 + O3);
-  out[head * TKV_D + c] = __float2half_rn(L > 0.f ? O / L : 0.f);
+  __syncthreads();
+  if (j == 0) {
+    const float M = fmaxf(red_m[0], red_m[1]);
+    float lsum = 0.f;
+#pragma unroll
+    for (int y = 0; y < kOwn; ++y) {
+      const int k = c + TKV_D * y;
+      if (k < n_parts) {
+        const float w = ml[y].x == -INFINITY ? 0.f : exp2f(ml[y].x - M);
+        wgt[k] = w;
+        lsum += w * ml[y].y;
+      }
+    }
+    for (int m = 32; m >= 1; m >>= 1) lsum += __shfl_xor(lsum, m, 64);
+    if (c % 64 == 0) red_l[c / 64] = lsum;
+  }
+  __syncthreads();
+  float O = 0.f;
+  for (int k0 = j;;) {
+#pragma unroll
+    for (int y = 0; y < kMergeLoads; ++y) {
+      const int k = k0 + kMergeClasses * y;
+      if (k < n4) O = __builtin_fmaf(v[y], wgt[k], O);
+    }
+    k0 += kMergeClasses * kMergeLoads;
+    if (k0 >= n4) break;
+    request(k0);
+  }
+  if (j == 0)
+    for (int k = n4; k < n_parts; ++k) O = __builtin_fmaf(base[(size_t)k * TKV_PART_STRIDE + TKV_PART_O + c], wgt[k], O);
+  red_o[j][c] = O;
+  __syncthreads();
+  if (j != 0) return;
+  const float L = red_l[0] + red_l[1], sum = (red_o[0][c] + red_o[1][c]) + (red_o[2][c] + red_o[3][c]);
+  out[head * TKV_D + c] = __float2half_rn(L > 0.f ? sum / L : 0.f);
 }
 
 }  // namespace
 
 namespace tkv {
 int32_t launch_attn_merge(const float* parts, __half* out, int n_heads_total, int n_parts, hipStream_t s) {
-  TKV_LAUNCH(attn_merge_kernel, dim3(n_heads_total), TKV_D, 0, s, parts, out, n_parts);
+  // (few parts: the loads that there are none for would repeat the last one's)
+  if (n_parts <= 4 * kMergeClasses) TKV_LAUNCH(attn_merge_kernel<4>, dim3(n_heads_total), kMergeClasses * TKV_D, 0, s, parts, out, n_parts);
+  else TKV_LAUNCH(attn_merge_kernel<16>, dim3(n_heads_total), kMergeClasses * TKV_D, 0, s, parts, out, n_parts);
   return TKV_OK;
 }
 }  // namespace tkv
