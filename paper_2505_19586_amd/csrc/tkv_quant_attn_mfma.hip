@@ -227,7 +227,7 @@ struct Cfg {
   static constexpr int kDepth = 3;
   static constexpr int kWaveRing = kDepth * (kKPart + kVPart);
   // direct-to-LDS load instructions per part: 1 bit = two 4-byte-per-lane loads of codes, else
-  // 16-byte-per-lane loads; GS = 2 fetches V scalers and zero-points with one instruction
+  // 16-byte-per-lane loads; one load each for scalers and zero-points (GS = 2: V's by half of the lanes each)
   static constexpr int kCodeLoads = BITS == 1 ? 2 : BITS / 2;
   static constexpr int kKLoads = kCodeLoads + 1;
   static constexpr int kVLoads = kCodeLoads + 2;
@@ -516,6 +516,13 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
   const auto k_scale = array_of(p.k_scale + kgrp_base * TKV_D, (uint32_t)(jq >> KSH) * (TKV_D * 2));
   const auto v_scale = array_of(p.v_scale + grp_base * (TKV_D / GS), (uint32_t)jq * kVMetaBytes);
   const auto v_zero = array_of(p.v_zero + grp_base * (TKV_D / GS), (uint32_t)jq * kVMetaBytes);
+  const auto k_zero = array_of(p.k_zero + kgrp_base * TKV_D, (uint32_t)(jq >> KSH) * (TKV_D * 2));
+  // the query rows of the workgroup's heads as MFMA B operand, exact (heads >= G re-read head G-1, in bounds; their results are not used)
+  auto load_query_rows = [&](uintx4 (&to)[4]) {
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+      to[m] = *reinterpret_cast<const uintx4*>(qrow + (size_t)(hs < G ? hs : G - 1) * TKV_D + 32 * m + 8 * rb);
+  };
   auto load_codes = [&](unsigned char* s, auto codes, uint32_t at) {
     if (BITS == 1) {
       buffer_to_lds<4>(codes, s, lane4, at);
@@ -555,15 +562,10 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
   const int g0 = blk0 + wave;
   int g1 = g0 + W, g2 = g0 + 2 * W;
   const bool active = g0 < blk1;
-  // Set-up loads first (query rows, zero-points of this wave's first 16 groups), then the
-  // ring prologue: one memory round trip covers both.
   const int ng = blk1 - blk0;
-  uint32_t q2[H];   // K-prep role: this lane owns channels 2*lane, 2*lane+1
-  uintx4 bq[4];     // exact fp16 query as MFMA B operand (zero-point term)
-  uintx4 az[4] = {};  // zero-point rows of 16 groups as MFMA A operand
   // Eq. 2 in this launch: the step's new rows go into the fp16 ring, into slots whose tokens were
   // quantized long ago.  Nothing in this launch reads those slots: the tail waves take the new
-  // rows from the caller's buffers.  Requested here, stored when the set-up loads behind them have arrived.
+  // rows from the caller's buffers.
   const int n_copy = has_tail && p.k_new != nullptr ? 32 * p.n_add.n[b] : 0;  // 16-byte pieces
   auto new_piece = [&](int x) -> const uintx4* {
     return reinterpret_cast<const uintx4*>(tkv::pick(x % 32 >= 16, p.k_new, p.v_new) + (((size_t)b * p.n_stride + x / 32) * p.hkv + h) * TKV_D) + x % 16;
@@ -573,55 +575,37 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
     const __half* to = tkv::pick(x % 32 >= 16, p.k_resid, p.v_resid) + (bh * ring + (size_t)((n - add + x / 32) % ring)) * TKV_D;
     return reinterpret_cast<uintx4*>(const_cast<__half*>(to)) + x % 16;
   };
-  uintx4 copied = {0u, 0u, 0u, 0u};
-  if (tid < n_copy) copied = *new_piece(tid);
-#pragma unroll
-  for (int hh = 0; hh < H; ++hh)  // heads >= G re-read head G-1 (in bounds); their results are not used
-    q2[hh] = reinterpret_cast<const uint32_t*>(qrow + (size_t)(hh < G ? hh : G - 1) * TKV_D)[lane];
-#pragma unroll
-  for (int m = 0; m < 4; ++m)
-    bq[m] = *reinterpret_cast<const uintx4*>(qrow + (size_t)(hs < G ? hs : G - 1) * TKV_D + 32 * m + 8 * rb);
-  auto load_az = [&](int t0) {
-    const size_t grp = kgrp_base + (min(blk0 + t0 + slot, last) >> KSH);
-#pragma unroll
-    for (int m = 0; m < 4; ++m) az[m] = *reinterpret_cast<const uintx4*>(p.k_zero + grp * TKV_D + 32 * m + 8 * rb);
-  };
-  if (16 * wave < ng) load_az(16 * wave);
-  // ---- zero-point term of every group of the chunk: cz[g][head] = scale2 * sum_c q[c] z_g[c],
-  // 16 groups per MFMA (A rows = groups, B = the exact fp16 query)
-  auto zero_terms = [&](int t0) {
-    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int m = 0; m < 4; ++m) acc = mfma(az[m], bq[m], acc);
-    if (us == 0) {
-#pragma unroll
-      for (int x = 0; x < 4; ++x) {
-        const int gl = t0 + 4 * rb + x;
-        if (gl < ng) cz_s[gl * H + hs] = acc[x] * p.scale2;
-      }
-    }
-  };
-  float qf[H][2];  // query times the factor that undoes the field position of this lane's channels
-  auto use_set_up_loads = [&]() {
-    if (16 * wave < ng) zero_terms(16 * wave);
-    // (1 bit: 2^(lane%4), times 2^4 in odd 32-channel blocks; 2 bit: 4^(lane%4); 4 bit: 16^(lane%2))
-    const int shift = BITS == 1 ? lane % 4 + 4 * ((lane / 16) % 2) : BITS == 2 ? 2 * (lane % 4) : 4 * (lane % 2);
-    const float comp = (float)(1 << kEK) / (float)(1 << shift);
-#pragma unroll
-    for (int hh = 0; hh < H; ++hh) {
-      const half2_t qq = as_half2(q2[hh]);
-      qf[hh][0] = hh < G ? (float)qq[0] * comp : 0.f;
-      qf[hh][1] = hh < G ? (float)qq[1] * comp : 0.f;
-    }
-    // (waited for here, on every path)
-    asm volatile("" ::"v"(az[0]), "v"(az[1]), "v"(az[2]), "v"(az[3]), "v"(bq[0]), "v"(bq[1]), "v"(bq[2]), "v"(bq[3]), "v"(copied));
-  };
-  __builtin_amdgcn_sched_barrier(0);
-  // (Written out for either case: behind the end of a branch around the loads below the compiler can only wait for all of
-  // them before it uses the set-up loads in front of them.  The block loop then began when the whole ring had been filled, 28 MB for
-  // a launch of 256 workgroups.  us per pass so, with global loads to LDS, against this: 2 bit, 32/8 heads, 131072 tokens, two layers
-  // 58.9, 57.5; 4 bit, 32770 17.25, 17.15.)
+  if (tid == 0) s_next = blk0 + 3 * W;
+  float scale2 = p.scale2;
+  asm volatile("" : "+s"(scale2));  // (else it is fetched anew before each of zero_terms' products)
+  // Set-up loads, then the ring prologue behind them: one memory round trip covers both.  Only waves that have blocks load, and of
+  // them only those that work out zero-point terms wait in front of the barrier: wave 0, up to 16 blocks.  No set-up load is in flight
+  // where a path without it joins (hence the tail's own load of the query rows): there the compiler would wait for loads behind
+  // it too, and the block loop would begin when the whole ring is full, 28 MB for a launch of 256 workgroups.  us per call, first with
+  // that, then with the set-up loads in every wave and a wait for them in front of the barrier, then so (a call of 2 bit, 2000
+  // tokens passes the barrier 1.8, 2.5 and 1.5 us after its start; of 2 / 64, 131071 tokens 3.8, 4.2 and 3.3), 32/8 heads: 2 bit, 2000 tokens
+  // 10.9, 11.2, 10.4; 131071 27.2, 26.1, 26.0; 4 bit, 2000 10.4, 10.5, 9.9; 2 / 64, 16 x 300 10.2, 10.6, 10.1; 2000 10.9, 11.2, 10.5;
+  // 131071 26.3, 26.1, 25.6; 1 / 64, 32/4 heads, 98413 21.9, 21.9, 21.4.
+  uint32_t q2[H];  // K-prep role: this lane owns channels 2*lane, 2*lane+1
   if (active) {
+    uintx4 copied;
+    if (tid < n_copy) copied = *new_piece(tid);
+#pragma unroll
+    for (int hh = 0; hh < H; ++hh)
+      q2[hh] = reinterpret_cast<const uint32_t*>(qrow + (size_t)(hh < G ? hh : G - 1) * TKV_D)[lane];
+    const bool zero_point_wave = 16 * wave < ng;  // (a wave without blocks has no groups either)
+    uintx4 bq[4];  // exact fp16 query as MFMA B operand
+    uintx4 az[4];  // zero-point rows of 16 groups as MFMA A operand
+    auto load_az = [&](int t0) {
+      const uint32_t at = (uint32_t)(min(blk0 + t0 + slot, last) >> KSH) * (TKV_D * 2) + 16u * (uint32_t)rb;
+#pragma unroll
+      for (int m = 0; m < 4; ++m) az[m] = __builtin_amdgcn_raw_buffer_load_b128(k_zero, at + 64u * m, 0, 0);
+    };
+    if (zero_point_wave) {
+      load_query_rows(bq);
+      load_az(16 * wave);
+    }
+    __builtin_amdgcn_sched_barrier(0);
     // issue order K0 V0 K1 K2 V1, then per step [K(i+3) V(i+2)]: the counter retires loads
     // in order, so "at most N outstanding" names exactly which parts have landed
     load_kpart(kl, g0);
@@ -630,22 +614,29 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
     load_kpart(kk, g2);
     load_vpart(vn, g1);
     __builtin_amdgcn_sched_barrier(0);
-    use_set_up_loads();
-    asm volatile("; set up, ring loads in flight");  // (keeps the two copies apart)
-  } else {
-    use_set_up_loads();
-    asm volatile("; set up");
+    // ---- zero-point term of every group of the chunk: cz[g][head] = scale2 * sum_c q[c] z_g[c],
+    // 16 groups per MFMA (A rows = groups, B = the exact fp16 query).  Column groups hold the same numbers, and there is room up
+    // to the next multiple of 16 groups: written without a condition.
+    static_assert(C::kMaxGpc % 16 == 0, "room of the last 16 groups");
+    auto zero_terms = [&](int t0) {
+      floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int m = 0; m < 4; ++m) acc = mfma(az[m], bq[m], acc);
+#pragma unroll
+      for (int x = 0; x < 4; ++x) cz_s[(t0 + 4 * rb + x) * H + hs] = acc[x] * scale2;
+    };
+    if (zero_point_wave) {
+      zero_terms(16 * wave);
+      for (int t0 = 16 * (wave + W); t0 < ng; t0 += 16 * W) {
+        load_az(t0);
+        zero_terms(t0);
+      }
+    }
+    if (tid < n_copy) *ring_piece(tid) = copied;
+  } else if (tid < n_copy) {
+    *ring_piece(tid) = *new_piece(tid);
   }
-  __builtin_amdgcn_sched_barrier(0);
-  if (tid == 0) s_next = blk0 + 3 * W;
-  for (int t0 = 16 * (wave + W); t0 < ng; t0 += 16 * W) {
-    load_az(t0);
-    zero_terms(t0);
-  }
-  if (tid < n_copy) {
-    *ring_piece(tid) = copied;
-    for (int x = tid + 64 * W; x < n_copy; x += 64 * W) *ring_piece(x) = *new_piece(x);
-  }
+  for (int x = tid + 64 * W; x < n_copy; x += 64 * W) *ring_piece(x) = *new_piece(x);
   TKV_PH();  // 1 this wave's set-up work done
   // cz table and group counter are in place (a bare barrier: __syncthreads() would also wait for
   // every load in flight)
@@ -671,9 +662,12 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
   for (int i = 0; i < 8; ++i) acc_o[i] = floatx4{0.f, 0.f, 0.f, 0.f};
   floatx4 acc_z = {0.f, 0.f, 0.f, 0.f};
   float m_run = -INFINITY;
-  if (has_tail && wave * 32 < n - nq)
+  if (has_tail && wave * 32 < n - nq) {
+    uintx4 bq[4];
+    load_query_rows(bq);
     tail_pieces<BITS, GS, W, H>(TailRows(p, b, h, bh, nq, n, p.residual + GRP), p.scale2, bq,
                                 reinterpret_cast<float*>(smem) + wave * (C::kBkWave / 4), wave, lane, acc_o, acc_z, m_run);
+  }
   TKV_PH();  // 3 tail done
 
   // codes carry 2^-24, query side 2^kEK, so S = acc * 2^(24-kEK)
@@ -702,6 +696,8 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
     const int j = i / 2;
     off[i] = BITS == 1 ? (float)(kEP - j) : BITS == 2 ? (float)(kEP - 2 * j) : (float)(kEP - 4 * (j % 2));
   }
+
+  float qf[H][2];  // query times the factor that undoes the field position of this lane's channels (set before the first group)
 
   // ---- pipeline stages of one group.  Every stage is split into its LDS reads and its
   // arithmetic, so that a step can issue the reads well ahead of their use (a wave issues in
@@ -887,6 +883,15 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
   if (active) {
     floatx4 acc_a[2], acc_b[2];
     TKV_WAIT_VMCNT(2 * C::kKLoads + C::kVLoads);  // K0, V0 landed
+    // (1 bit: 2^(lane%4), times 2^4 in odd 32-channel blocks; 2 bit: 4^(lane%4); 4 bit: 16^(lane%2))
+    const int shift = BITS == 1 ? lane % 4 + 4 * ((lane / 16) % 2) : BITS == 2 ? 2 * (lane % 4) : 4 * (lane % 2);
+    const float comp = (float)(1 << kEK) / (float)(1 << shift);
+#pragma unroll
+    for (int hh = 0; hh < H; ++hh) {
+      const half2_t qq = as_half2(q2[hh]);
+      qf[hh][0] = hh < G ? (float)qq[0] * comp : 0.f;
+      qf[hh][1] = hh < G ? (float)qq[1] * comp : 0.f;
+    }
     stage_k(read_ks(kl));
     {
       QkIn qi;
