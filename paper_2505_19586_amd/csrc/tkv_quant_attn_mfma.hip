@@ -223,11 +223,11 @@ struct Cfg {
   static constexpr int kKPart = kCode + 256;
   static constexpr int kVPart = kCode + 512;
   static constexpr int oVs = kCode;                 // V scalers inside a V slot
-  static constexpr int oVz = kCode + 256 / GS;      // V zero-points
+  static constexpr int oVz = kCode + 256;           // V zero-points (GS = 2: 128 bytes each, and as many unused)
   static constexpr int kDepth = 3;
   static constexpr int kWaveRing = kDepth * (kKPart + kVPart);
   // direct-to-LDS load instructions per part: 1 bit = two 4-byte-per-lane loads of codes, else
-  // 16-byte-per-lane loads; one load each for scalers and zero-points (GS = 2: V's by half of the lanes each)
+  // 16-byte-per-lane loads; one load each for scalers and zero-points (GS = 2: V's by half of the lanes)
   static constexpr int kCodeLoads = BITS == 1 ? 2 : BITS / 2;
   static constexpr int kKLoads = kCodeLoads + 1;
   static constexpr int kVLoads = kCodeLoads + 2;
@@ -523,6 +523,12 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
     for (int m = 0; m < 4; ++m)
       to[m] = *reinterpret_cast<const uintx4*>(qrow + (size_t)(hs < G ? hs : G - 1) * TKV_D + 32 * m + 8 * rb);
   };
+  // GS = 2: 128 bytes each of V scalers and zero-points.  Lanes 32..63 read at kNone, past the end of any array (2^28 bytes at most,
+  // 131072 blocks), where nothing is fetched; what they write to LDS is not used.  (With a lane mask around either load the compiler
+  // counts them as loads that may not have been issued, and waits for others in their place.  us per call so / now, 2 bit, 32/8 heads,
+  // 98413 tokens 22.6, 22.3; 64/8 27.4, 26.9; 32/8, 131071 25.5, 25.2; 2000 10.5, 10.4.)
+  constexpr uint32_t kNone = 0x80000000u;
+  const uint32_t lane4_meta = GS == 1 || lane < 32 ? lane4 : kNone;
   auto load_codes = [&](unsigned char* s, auto codes, uint32_t at) {
     if (BITS == 1) {
       buffer_to_lds<4>(codes, s, lane4, at);
@@ -542,14 +548,8 @@ __global__ __launch_bounds__(64 * W) void quant_attn_mfma_kernel(MfmaParams p) {
     const uint32_t gi = (uint32_t)min(g, last);
     unsigned char* s = smem + so;
     load_codes(s, v_codes, gi * kCodeBytes);
-    if (GS == 1) {
-      buffer_to_lds<4>(v_scale, s + C::oVs, lane4, gi * kVMetaBytes);
-      buffer_to_lds<4>(v_zero, s + C::oVz, lane4, gi * kVMetaBytes);
-    } else if (lane < 32) {  // 128 bytes each: lanes 0..31 fetch the block's V scalers, lanes 32..63 its zero-points
-      buffer_to_lds<4>(v_scale, s + C::oVs, lane4, gi * kVMetaBytes);
-    } else {
-      buffer_to_lds<4>(v_zero, s + C::oVs, lane4 - 128u, gi * kVMetaBytes);
-    }
+    buffer_to_lds<4>(v_scale, s + C::oVs, lane4_meta, gi * kVMetaBytes);
+    buffer_to_lds<4>(v_zero, s + C::oVz, lane4_meta, gi * kVMetaBytes);
   };
 
   // The first three groups of a wave are fixed (wave, wave + W, wave + 2W), the rest come
