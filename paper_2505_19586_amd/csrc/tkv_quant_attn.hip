@@ -689,12 +689,13 @@ int32_t launch_f32(const QuantAttnParams& p, bool any_group, hipStream_t s) {
 }
 
 // Log-sum-exp merge of the chunk partials of one query head; writes fp16.  One workgroup per query head; a thread takes one channel of
-// every fourth part.  Bound by latency: the maxima and sums and the first 16 of a thread's parts are requested at once (64 parts in one
-// round trip).  us per call with one thread per channel, four parts requested at a time behind two round trips for the weights, and
-// so: 1 bit, 32/8 heads, 65500 tokens 40.6, 38.7; 4 bit, 32/8, 65500 44.7, 42.3; 5000 14.4, 12.9; 1500 11.6, 11.0; 32/4, 3000 12.9, 11.7.
+// kThreadClasses of the four classes of parts (every fourth part each).  Bound by latency: the maxima and sums and the first kMergeLoads parts
+// of each of a thread's classes are requested at once (16 or 64 parts in one round trip).  us per call with one thread per channel, four parts
+// requested at a time behind two round trips for the weights, and with four threads: 1 bit, 32/8 heads, 65500 tokens 40.6, 38.7; 4 bit, 32/8,
+// 65500 44.7, 42.3; 5000 14.4, 12.9.  Up to 16 parts see launch_attn_merge.
 constexpr int kMergeClasses = 4;
-template <int kMergeLoads>
-__global__ __launch_bounds__(kMergeClasses * TKV_D) void attn_merge_kernel(const float* parts, __half* out, int n_parts) {
+template <int kMergeLoads, int kThreadClasses>
+__global__ __launch_bounds__(kMergeClasses / kThreadClasses * TKV_D) void attn_merge_kernel(const float* parts, __half* out, int n_parts) {
   constexpr int kOwn = (TKV_MAX_CHUNKS + TKV_D) / TKV_D;  // parts whose weights one of the first TKV_D threads works out
   __shared__ float wgt[TKV_MAX_CHUNKS + 1];
   __shared__ float red_m[2], red_l[2];
@@ -709,13 +710,15 @@ __global__ __launch_bounds__(kMergeClasses * TKV_D) void attn_merge_kernel(const
     for (int y = 0; y < kOwn; ++y)
       ml[y] = *reinterpret_cast<const float2*>(base + (size_t)min(c + TKV_D * y, n_parts - 1) * TKV_PART_STRIDE);
   }
-  float v[kMergeLoads];
+  float v[kMergeLoads][kThreadClasses];
   auto request = [&](int k0) {
 #pragma unroll
     for (int y = 0; y < kMergeLoads; ++y)
-      v[y] = base[(size_t)min(k0 + kMergeClasses * y, n_parts - 1) * TKV_PART_STRIDE + TKV_PART_O + c];
+#pragma unroll
+      for (int x = 0; x < kThreadClasses; ++x)
+        v[y][x] = base[(size_t)min(k0 + kMergeClasses * y + x, n_parts - 1) * TKV_PART_STRIDE + TKV_PART_O + c];
   };
-  request(j);
+  request(kThreadClasses * j);
   if (j == 0) {
     float m = -INFINITY;
 #pragma unroll
@@ -740,23 +743,30 @@ __global__ __launch_bounds__(kMergeClasses * TKV_D) void attn_merge_kernel(const
     if (c % 64 == 0) red_l[c / 64] = lsum;
   }
   __syncthreads();
-  float O = 0.f;
-  for (int k0 = j;;) {
+  float O[kThreadClasses] = {};
+  for (int k0 = kThreadClasses * j;;) {
 #pragma unroll
     for (int y = 0; y < kMergeLoads; ++y) {
       const int k = k0 + kMergeClasses * y;
-      if (k < n4) O = __builtin_fmaf(v[y], wgt[k], O);
+      if (k < n4) {
+#pragma unroll
+        for (int x = 0; x < kThreadClasses; ++x) O[x] = __builtin_fmaf(v[y][x], wgt[k + x], O[x]);
+      }
     }
     k0 += kMergeClasses * kMergeLoads;
     if (k0 >= n4) break;
     request(k0);
   }
   if (j == 0)
-    for (int k = n4; k < n_parts; ++k) O = __builtin_fmaf(base[(size_t)k * TKV_PART_STRIDE + TKV_PART_O + c], wgt[k], O);
-  red_o[j][c] = O;
-  __syncthreads();
-  if (j != 0) return;
-  const float L = red_l[0] + red_l[1], sum = (red_o[0][c] + red_o[1][c]) + (red_o[2][c] + red_o[3][c]);
+    for (int k = n4; k < n_parts; ++k) O[0] = __builtin_fmaf(base[(size_t)k * TKV_PART_STRIDE + TKV_PART_O + c], wgt[k], O[0]);
+  if constexpr (kThreadClasses < kMergeClasses) {
+#pragma unroll
+    for (int x = 0; x < kThreadClasses; ++x) red_o[kThreadClasses * j + x][c] = O[x];
+    __syncthreads();
+    if (j != 0) return;
+  }
+  const auto class_sum = [&](int x) { return kThreadClasses < kMergeClasses ? red_o[x][c] : O[x]; };
+  const float L = red_l[0] + red_l[1], sum = (class_sum(0) + class_sum(1)) + (class_sum(2) + class_sum(3));
   out[head * TKV_D + c] = __float2half_rn(L > 0.f ? sum / L : 0.f);
 }
 
@@ -764,9 +774,14 @@ __global__ __launch_bounds__(kMergeClasses * TKV_D) void attn_merge_kernel(const
 
 namespace tkv {
 int32_t launch_attn_merge(const float* parts, __half* out, int n_heads_total, int n_parts, hipStream_t s) {
-  // (few parts: the loads that there are none for would repeat the last one's)
-  if (n_parts <= 4 * kMergeClasses) TKV_LAUNCH(attn_merge_kernel<4>, dim3(n_heads_total), kMergeClasses * TKV_D, 0, s, parts, out, n_parts);
-  else TKV_LAUNCH(attn_merge_kernel<16>, dim3(n_heads_total), kMergeClasses * TKV_D, 0, s, parts, out, n_parts);
+  // Up to 16 parts are one thread's loads: a thread per channel, and of 4 parts or fewer no load that would repeat the last one's.
+  // Four threads per channel are 16384 waves for 2048 heads, and behind them the next call's attention falls unevenly on the compute
+  // units.  us per call with four / with one, 32/8 heads: 1 bit, 64 x 100 tokens (2 parts) 19.7, 16.8; 64 x 300 (3) 27.3, 25.1; 50 x 4000 (3; the
+  // attention alone 158, 118) 156, 119; 4 bit, 50 x 4000 (6) 102.8, 100.1; one sequence of 900 to 1900 tokens (7 to 15) the same.
+  const dim3 grid(n_heads_total);
+  if (n_parts <= kMergeClasses) TKV_LAUNCH((attn_merge_kernel<1, kMergeClasses>), grid, TKV_D, 0, s, parts, out, n_parts);
+  else if (n_parts <= 4 * kMergeClasses) TKV_LAUNCH((attn_merge_kernel<4, kMergeClasses>), grid, TKV_D, 0, s, parts, out, n_parts);
+  else TKV_LAUNCH((attn_merge_kernel<16, 1>), grid, kMergeClasses * TKV_D, 0, s, parts, out, n_parts);
   return TKV_OK;
 }
 }  // namespace tkv
