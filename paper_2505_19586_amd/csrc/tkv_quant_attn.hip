@@ -283,6 +283,7 @@ __device__ inline void codes_of(uint32_t w, int base, half2_t (&pair)[4]) {
 // Workgroups that a compute unit holds: 2 waves each, 2 to 4 of them per SIMD with the registers of each variant (its attribute
 // says so, as the least and the most: aiming at a fourth wave the compiler keeps fewer loads in flight; 4 bit, 32/32 heads, 16 x 900
 // tokens 24.7, with the attribute 23.7; 32/4, 98413 tokens 60.4, 57.4).
+constexpr int kF32TailsLast = 9;  // chunks of more blocks than this: tails behind them, else in front
 constexpr int f32_waves(int bits, int heads) { return bits == 4 ? (heads == 4 ? 2 : 3) : heads == 1 ? 4 : 3; }
 inline int f32_resident(int bits, int group) { return 2 * f32_waves(bits, group > 2 ? 4 : group); }
 template <int BITS, int GRP, int H>
@@ -311,7 +312,7 @@ void quant_attn_f32_kernel(QuantAttnParams p) {
   // are short, else last: 4 bit, 32/8 heads, 5000 tokens (4 blocks per chunk, 4 heads) 18.5 us per call, 21.7 with the tails last; 32/32,
   // 16 x 2500 tokens (37 blocks) 53.4 with the tails last, 63.0 first.
   const int units = p.hkv * split, n_heavy = p.batch * units * p.n_chunks, n_tails = (int)gridDim.x - n_heavy;
-  const bool tails_last = p.groups_per_chunk > 9;
+  const bool tails_last = p.groups_per_chunk > kF32TailsLast;
   const int at = (int)blockIdx.x - (tails_last ? 0 : n_tails);  // place among the chunks
   const bool tail = at < 0 || at >= n_heavy;
   const int x = at < 0 ? at + n_tails : at - n_heavy;           // ... and among the tails
@@ -832,18 +833,24 @@ int32_t quant_attn_decode_impl(const tkv_quant_desc* d, const tkv_quant_cache* c
   // call with about 1024 chunks, the tails in between and groups of 5 to 8 not counted twice, against this: 4 bit, 32/32 heads,
   // 2 x 20479 tokens 65.9, 51.4; 16 x 2500 64.1, 52.7; 20000 28.2, 28.2; 32/8, 65500 tokens 57.2, 48.0; 50 x 4000 162.7, 116.5; 32
   // x 900 36.3, 26.0; 64/8, 30000 47.1, 41.0; 1 bit, 32/32, 2 x 20000 69.6, 51.7.
+  // Short chunks have the tails in front of them (kF32TailsLast) and are over soon: what counts there is that no SIMD gets a third wave, so
+  // that four workgroups per compute unit, tails included, are all that counts as resident, however many the registers allow.  us per call
+  // with as many as those allow / so: 4 bit, 16/8 heads, 24 x 900 tokens 19.9, 16.1 (17.4 with two waves per SIMD allowed for two heads);
+  // 32 x 1300 26.2, 22.8; 6 x 6000 25.0, 20.8; 8/8, 32 x 750 18.1, 14.7; 1 bit, 32/8, 24 x 900 26.1, 19.9; 6 x 6000 32.6, 25.7.  Of 270 shapes of
+  // which this changes the plan four are more than 0.8 % slower: 1 bit, 32/8, 48 x 500 27.9, 28.4.
   const int units = d->batch * d->n_kv_heads * ((d->n_q_heads / d->n_kv_heads + 3) / 4);
   int gpc = 4, n_chunks = 1;
   long long least = -1;
   const int resident = 256 * f32_resident(d->bits, d->n_q_heads / d->n_kv_heads);
-  for (int round = 3; round <= 8; ++round) {
-    const int want = round == 3 ? resident / units - 1 : 256 * round / units;
+  const int resident_short = std::min(resident, 4 * 256);
+  for (int round = 2; round <= 8; ++round) {
+    const int want = round == 2 ? resident_short / units - 1 : round == 3 ? resident / units - 1 : 256 * round / units;
     const int target = std::min(std::max(want, 1), TKV_MAX_CHUNKS);
     const int blocks = std::max((max_groups + target - 1) / target, 4);
     const int chunks = std::max((max_groups + blocks - 1) / blocks, 1);
     const long long per_cu = std::max(((long long)units * chunks + 255) / 256, 4ll);
     const long long cost = per_cu * (blocks + 6) + (units + 255) / 256 * 12 +
-                           ((long long)units * (chunks + 1) > resident ? blocks + 18 : 0);
+                           ((long long)units * (chunks + 1) > (blocks > kF32TailsLast ? resident : resident_short) ? blocks + 18 : 0);
     if (least < 0 || cost < least) least = cost, gpc = blocks, n_chunks = chunks;
   }
 
