@@ -153,9 +153,10 @@ __device__ inline float* part_ml(float* head, int n_chunks, int k) { return head
 
 // Fetches the BYTES of a kernel's arguments at its start, all lines in one round trip.  (The compiler loads an argument shortly before
 // its use; every line that is touched for the first time there is a round trip of its own on the way to the first load of data.)
-// us per pass without and with it: sparse decode step, 4095 tokens, 32/8 heads 23.8, 23.1; dynamic channels, 98101 tokens (three launches)
-// 63.9, 63.3; dense preference score, 131072 keys (eight launches) 172, 169; quantized decode, 4 bit, 32770 tokens 17.4, 17.25; 1 bit,
-// 98413 22.0, 21.8; 131072 tokens quantized 126.8, 126.4.  The float32 attention kernel does without: 0.1 slower with it.
+// us per pass without and with it, in turn: sparse decode step, 4095 tokens, 32/8 heads 23.6, 23.1; dynamic channels, 98101 tokens (three
+// launches) 63.9, 63.3; quantized decode, 2 bit, 2000 tokens 10.45, 10.4; 4 bit, 32770 16.9, 16.7; 1 bit, 98413 21.4, 21.25.  No difference: dense
+// preference score of 131072 keys (eight launches), 131072 tokens quantized (where a compute unit's later workgroups find the lines cached;
+// 64 x 300 tokens, 2 bit, 32/32 heads 105.8, 107.4).  The float32 attention kernel does without: 0.1 slower with it.
 template <int BYTES>
 __device__ inline void fetch_arguments() {
   static_assert(BYTES <= 16 * 64, "lines");
@@ -221,8 +222,11 @@ struct SumOf { __device__ float operator()(float a, float b) const { return a + 
 // maxima and sums of its own head (of two heads where 32 KS items are no whole number of waves) and its channels at once and
 // works out the chunks' weights by itself: one round trip, one barrier.  us per call with the pairs fetched by the whole
 // workgroup before everything else and the weights shared through LDS / so: quantized attention, 2 bit, 32/8 heads, 2000
-// tokens (7 chunks) 12.1, 10.9; 8000 13.5, 12.5; 131000 (32 chunks) 29.3, 28.0; 4/1, 50000 (64 chunks) 17.2, 15.5; 1 bit, 32/4,
+// tokens (7 chunks) 12.1, 10.9; 8000 13.5, 12.5; 131000 (32 chunks) 29.3, 28.0; 4/1, 50000 (132 chunks) 17.2, 15.5; 1 bit, 32/4,
 // 98413 (64 chunks of 8 heads) 23.0, 21.9.  (With the pairs in front of the chunks' sums, a line each: 16.6 and 23.7 for the last two.)
+// More than 64 chunks, one sequence of one to three KV heads (4/1 from 25000 tokens on): their pairs come in a second and third
+// round trip, which costs less than the workgroup's rounds did: 2 bit, 4/1, 131071 tokens (256 chunks) 22.5, 19.6; 8/2 (128) 19.7, 17.7; 8/1, 400000
+// (256 chunks of 8 heads) 34.4, 31.8.
 constexpr int merge_lds_floats(int KS, int G, int n_chunks, int nthr) {
   return nthr / 64 * (KS == 3 ? 2 : 1) * ((n_chunks + 63) / 64 * 64) + G * KS * TKV_D + G;
 }
@@ -270,7 +274,7 @@ __device__ inline void merge_chunks(const float* head0, int G, int n_chunks, __h
       const uint32_t v_max = ml[z].x, v_sum = ml[z].y;
       const float m0 = lane < n_chunks ? __uint_as_float(v_max) : -INFINITY;
       float M = m0;
-      for (int k = 64 + lane; k < cw_len; k += 64) {  // (more than 64 chunks: beyond a million tokens)
+      for (int k = 64 + lane; k < cw_len; k += 64) {  // (more than 64 chunks)
         const uint32_t v = pair_of(z, k).x;
         M = fmaxf(M, k < n_chunks ? __uint_as_float(v) : -INFINITY);
       }

@@ -521,7 +521,9 @@ extern "C" int32_t tkv_quantize_append_ragged(const tkv_quant_desc* d, tkv_quant
   // 4.3, 6.3; 2000 (464) 5.7, 6.5; 3000 (712) 7.1, 6.6; 8200 (2016) 15.2, 11.5; 4 bit, 400 4.6, 7.3; 2000 6.1,
   // 7.6; 3000 7.5, 7.7; 6000 (1464) 11.8, 10.7; 1 bit, 400 6.8, 4.2.  Groups of 64: 2 bit, 300 tokens (16 groups) 5.0, 6.1; 2000 (232) 5.5,
   // 6.7; 3000 (352) 7.7, 6.9; 16 x 300 (256, and 128 copying) 9.5, 8.3; 4 bit, 300 5.9, 7.0; 2000 6.5, 7.8; 3000 9.6, 8.0; 16 x 300 11.2,
-  // 10.2; 1 bit, 300 4.6, 4.0; 2000 5.0, 4.6.
+  // 10.2; 1 bit, 300 4.6, 4.0; 2000 5.0, 4.6; onto a tail, the copy a launch of its own: 2 bit, 2048 tokens onto 150 (256) 7.3, 9.1; 2600
+  // (320) 9.6, 9.1; 32 heads, 500 onto 170 (256) 8.6, 9.7; 600 (320) 10.1, 9.8; 4 bit, 2048 8.5, 10.1; 2600 11.3, 10.3; 24 x 100 tokens onto 190
+  // (384, short copies) 16.4, 18.1 on the other side of the line.
   const int few_groups = d->bits == 1 ? 0 : g == 64 ? 256 : d->bits == 2 ? 512 : together ? 768 : 1024;
   const int few_copies = g == 64 && together ? (max_copy + 63) / 64 : 0;
   const bool few = (max_groups + few_copies) * hkv * d->batch <= few_groups;

@@ -281,8 +281,9 @@ __device__ inline void codes_of(uint32_t w, int base, half2_t (&pair)[4]) {
 // their operands are fp16: scalers above 1024 overflow, weights below 2^-14 lose bits, and the order of
 // the blocks is decided at run time.
 // Workgroups that a compute unit holds: 2 waves each, 2 to 4 of them per SIMD with the registers of each variant (its attribute
-// says so, as the least and the most: aiming at a fourth wave the compiler keeps fewer loads in flight; 4 bit, 32/32 heads, 16 x 900
-// tokens 24.7, with the attribute 23.7; 32/4, 98413 tokens 60.4, 57.4).
+// says so, as the least and the most: the chunks are planned for that many.  Without a most (then a fourth wave for 4 bits and one head, a
+// third for four) 16 x 900 tokens of 32/32 heads take 24.5 us, 23.6 with it; 44 x 4000 209, 182; 25 x 8000 of 32/8 121, 115, but 32 x 4000 of
+// 32/32 127, 141, and 64 x 4000 of 32/8 119, 152).
 constexpr int kF32TailsLast = 9;  // chunks of more blocks than this: tails behind them, else in front
 constexpr int f32_waves(int bits, int heads) { return bits == 4 ? (heads == 4 ? 2 : 3) : heads == 1 ? 4 : 3; }
 inline int f32_resident(int bits, int group) { return 2 * f32_waves(bits, group > 2 ? 4 : group); }
@@ -293,9 +294,10 @@ void quant_attn_f32_kernel(QuantAttnParams p) {
   constexpr int NU = TKV_D / GRP;        // channel groups of a value row
   constexpr int NWORDS = TKV_D * BITS;   // words of a packed block
   constexpr int BPG = GRP / TKV_BLK;     // blocks per key group
-  // With 4 heads the loads of all pieces, hoisted above one another, would not fit the registers: they
-  // are kept piece by piece.  With fewer heads that only costs (16 / 8 heads, 4 x 30000 tokens: 66 us with
-  // the pieces kept apart, 56 without).
+  // With 4 heads an octet's scalers and zero-points are fetched where they are used and the pieces of the values kept apart: all of them
+  // hoisted above one another do not fit the registers.  With one head that costs, with two it makes no difference.  (The pieces of the keys,
+  // 32 channels each, are apart for any number of heads.)  us per call without / with it: 4 bit, 32/8 heads, 65500 tokens 45.1, 42.4; 32 x 900 26.1,
+  // 24.7; 16/8, 4 x 30000 44.1, 43.7; 1 bit, 32/32, 16 x 2500 40.5, 41.7.
   constexpr bool kApart = H == 4;
   constexpr int KW = BITS == 4 ? 4 : 1;  // words per lane and 8-channel (8-token) class
   // per wave, half: scalers times 2^code_exp in float32, zero-points in fp16

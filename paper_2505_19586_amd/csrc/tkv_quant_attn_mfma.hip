@@ -243,7 +243,6 @@ struct Cfg {
   // chunk classes and loads in flight of the cross-chunk merge: one thread per item, 64 chunks in one round
   static constexpr int kMergeClasses = H == 4 ? 4 : W == 12 ? 3 : 2, kMergeLoads = H == 4 ? 16 : W == 12 ? 22 : 32;
   static_assert(tkv::merge_lds_floats(kMergeClasses, H, TKV_MAX_CHUNKS, kThreads) * 4 <= W * kWaveRing, "merge scratch must fit in the ring");
-  static_assert(kThreads >= 64 * H, "the cross-chunk merge takes a wave per head");
   static_assert(kLdsBytes + 64 <= 160 * 1024, "LDS budget of one compute unit");
 };
 
