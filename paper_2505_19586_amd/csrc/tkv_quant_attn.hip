@@ -839,7 +839,7 @@ int32_t quant_attn_decode_impl(const tkv_quant_desc* d, const tkv_quant_cache* c
   // that four workgroups per compute unit, tails included, are all that counts as resident, however many the registers allow.  us per call
   // with as many as those allow / so: 4 bit, 16/8 heads, 24 x 900 tokens 19.9, 16.1 (17.4 with two waves per SIMD allowed for two heads);
   // 32 x 1300 26.2, 22.8; 6 x 6000 25.0, 20.8; 8/8, 32 x 750 18.1, 14.7; 1 bit, 32/8, 24 x 900 26.1, 19.9; 6 x 6000 32.6, 25.7.  Of 270 shapes of
-  // which this changes the plan four are more than 0.8 % slower: 1 bit, 32/8, 48 x 500 27.9, 28.4.
+  // which this changes the plan three are more than 0.8 % slower, all with four heads at 1 bit: 32/8, 48 x 500 27.9, 28.4.
   const int units = d->batch * d->n_kv_heads * ((d->n_q_heads / d->n_kv_heads + 3) / 4);
   int gpc = 4, n_chunks = 1;
   long long least = -1;
